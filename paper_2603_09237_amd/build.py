@@ -15,7 +15,8 @@ ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 OBJ = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libmorlax.so")
-SOURCES = ["morlax_api.hip", "kernels_scan_loss.hip", "kernels_hyper.hip", "kernels_eval.hip", "kernels_mlp.hip"]
+SOURCES = ["morlax_api.hip", "kernels_scan_loss.hip", "kernels_hyper.hip", "kernels_eval.hip", "kernels_mlp.hip",
+           "fused_fwd_bf16_act.hip", "fused_fwd_bf16_save.hip", "fused_fwd_f32_act.hip", "fused_fwd_f32_save.hip"]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-I" + os.path.join(ROOT, "include"),
          "-I" + CSRC, "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
@@ -36,7 +37,7 @@ def _compile(src: str) -> str:
 
 def build(verbose: bool = True) -> str:
     os.makedirs(OBJ, exist_ok=True)
-    with ThreadPoolExecutor(max_workers=min(5, len(SOURCES))) as ex:
+    with ThreadPoolExecutor(max_workers=min(8, len(SOURCES))) as ex:
         objs = list(ex.map(_compile, SOURCES))
     cmd = [HIPCC, "--offload-arch=gfx950", "-shared", "-fPIC", "-o", LIB, *objs]
     r = subprocess.run(cmd, capture_output=True, text=True)

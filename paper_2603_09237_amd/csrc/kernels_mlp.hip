@@ -12,39 +12,18 @@
 // axis in memory (W in the dX product, both operands of the dW product) are transposed on the way
 // into LDS.  The skinny output layer (<= 16 columns) uses 16x16 MFMA tiles straight from global
 // memory in the forward pass and plain vector code in the backward pass.
-#include <type_traits>
+#include "fused_fwd.h"
 
-#include "morlax_internal.h"
-#include "numeric.h"
+void launch_mlp_fwd_bf16_act(const FwdArgs& a, int rt, int n_tiles, hipStream_t s);
+void launch_mlp_fwd_bf16_save(const FwdArgs& a, int rt, int n_tiles, hipStream_t s);
+void launch_mlp_fwd_f32_act(const FwdArgs& a, int rt, int n_tiles, hipStream_t s);
+void launch_mlp_fwd_f32_save(const FwdArgs& a, int rt, int n_tiles, hipStream_t s);
 
 #define BM 128
 #define BN 128
 #define GEMM_NCH 4         // 16-byte chunks of the contraction axis staged per step and operand row
-#define OUT_PITCH 16       // floats per row of the saved head output
 
 enum { SRC_KCONTIG = 0, SRC_KSTRIDED = 1, SRC_X_KCONTIG = 2, SRC_X_KSTRIDED = 3 };
-
-struct RowMap {  // compact row m of preference p -> row of a time-major tensor
-    int32_t t0, j0, j_cnt, N, n_g;
-    __device__ inline int64_t row(int p, int m) const {
-        return (int64_t)(t0 + m / j_cnt) * N + (int64_t)p * n_g + j0 + m % j_cnt;
-    }
-};
-
-template <typename T> struct Elems { static constexpr int VE = 16 / sizeof(T); };
-
-__device__ inline uint32_t pack2(bf16_t a, bf16_t b) {
-    return (uint32_t)__builtin_bit_cast(uint16_t, a) | ((uint32_t)__builtin_bit_cast(uint16_t, b) << 16);
-}
-
-template <typename T> __device__ inline uint4 pack_chunk(const float* v);
-template <> __device__ inline uint4 pack_chunk<float>(const float* v) {
-    return make_uint4(__float_as_uint(v[0]), __float_as_uint(v[1]), __float_as_uint(v[2]), __float_as_uint(v[3]));
-}
-template <> __device__ inline uint4 pack_chunk<bf16_t>(const float* v) {
-    return make_uint4(pack2((bf16_t)v[0], (bf16_t)v[1]), pack2((bf16_t)v[2], (bf16_t)v[3]),
-                      pack2((bf16_t)v[4], (bf16_t)v[5]), pack2((bf16_t)v[6], (bf16_t)v[7]));
-}
 
 // One GEMM operand: a [rows x kdim] matrix of which a workgroup stages 128 rows x NCH 16-byte chunks of
 // the contraction axis per step.  FAST = every access is a full, aligned vector (the launcher checks
@@ -228,107 +207,6 @@ struct Operand {
     }
 };
 
-template <typename T> struct Mma32;
-template <> struct Mma32<bf16_t> {
-    static __device__ inline void run(const uint4& a, const uint4& b, float16_t& c) {
-        c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8_t, a), __builtin_bit_cast(bf16x8_t, b), c,
-                                                    0, 0, 0);
-    }
-};
-template <> struct Mma32<float> {
-    static __device__ inline void run(const uint4& a, const uint4& b, float16_t& c) {
-        c = __builtin_amdgcn_mfma_f32_32x32x2f32(__uint_as_float(a.x), __uint_as_float(b.x), c, 0, 0, 0);
-        c = __builtin_amdgcn_mfma_f32_32x32x2f32(__uint_as_float(a.y), __uint_as_float(b.y), c, 0, 0, 0);
-        c = __builtin_amdgcn_mfma_f32_32x32x2f32(__uint_as_float(a.z), __uint_as_float(b.z), c, 0, 0, 0);
-        c = __builtin_amdgcn_mfma_f32_32x32x2f32(__uint_as_float(a.w), __uint_as_float(b.w), c, 0, 0, 0);
-    }
-};
-
-template <typename T> struct Mma16;
-template <> struct Mma16<bf16_t> {
-    static __device__ inline void run(const uint4& a, const uint4& b, float4_t& c) {
-        c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, a), __builtin_bit_cast(bf16x8_t, b), c,
-                                                    0, 0, 0);
-    }
-};
-template <> struct Mma16<float> {
-    static __device__ inline void run(const uint4& a, const uint4& b, float4_t& c) {
-        c = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(a.x), __uint_as_float(b.x), c, 0, 0, 0);
-        c = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(a.y), __uint_as_float(b.y), c, 0, 0, 0);
-        c = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(a.z), __uint_as_float(b.z), c, 0, 0, 0);
-        c = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(a.w), __uint_as_float(b.w), c, 0, 0, 0);
-    }
-};
-
-// out = head(h W_L(p)^T + b_L(p)); actor: optional sampling a = mu + sigma eps and its log-density.
-// A wave owns 16 rows; lane (row = lane % 16, chunk = lane / 16) feeds 16x16 MFMA tiles from global.
-// h = act(z) and g = act'(z).  SiLU uses the hardware exp2 / reciprocal approximations (about 1 ulp
-// each): s = 1 / (1 + e^-z), h = z s, g = s (1 + z - h).  tanh keeps the library routine.
-template <int ACT>
-__device__ inline void act_pair(float z, float& h, float& g) {
-    if (ACT == 0) {
-        h = tanhf(z);
-        g = 1.f - h * h;
-    } else {
-        const float e = __expf(-z);
-        const float s = __builtin_amdgcn_rcpf(1.f + e);
-        h = z * s;
-        g = s * (1.f + z - h);
-    }
-}
-
-// eight consecutive elements of type T / of the saved-derivative type: packing and 16-byte accesses
-struct Pack8 { uint4 lo, hi; };  // bf16 / fixed point use lo only; fp32 uses both
-__device__ inline Pack8 pack8(const float v[8], const float*) {
-    Pack8 r;
-    r.lo = make_uint4(__float_as_uint(v[0]), __float_as_uint(v[1]), __float_as_uint(v[2]), __float_as_uint(v[3]));
-    r.hi = make_uint4(__float_as_uint(v[4]), __float_as_uint(v[5]), __float_as_uint(v[6]), __float_as_uint(v[7]));
-    return r;
-}
-__device__ inline Pack8 pack8(const float v[8], const bf16_t*) {
-    Pack8 r;
-    r.lo = pack_chunk<bf16_t>(v);
-    r.hi = make_uint4(0, 0, 0, 0);
-    return r;
-}
-__device__ inline Pack8 pack8(const float v[8], const gfix16_t*) {
-    // round(v / step + 1/8 / step); values are in (-0.125, 1.125) so the conversion cannot overflow
-    uint32_t q[8];
-#pragma unroll
-    for (int i = 0; i < 8; ++i) q[i] = (uint32_t)(v[i] * (1.0f / GFIX_STEP) + (0.125f / GFIX_STEP + 0.5f));
-    Pack8 r;
-    r.lo = make_uint4(q[0] | (q[1] << 16), q[2] | (q[3] << 16), q[4] | (q[5] << 16), q[6] | (q[7] << 16));
-    r.hi = make_uint4(0, 0, 0, 0);
-    return r;
-}
-__device__ inline void put8(float* dst, const Pack8& pk) {
-    reinterpret_cast<uint4*>(dst)[0] = pk.lo;
-    reinterpret_cast<uint4*>(dst)[1] = pk.hi;
-}
-__device__ inline void put8(bf16_t* dst, const Pack8& pk) { *reinterpret_cast<uint4*>(dst) = pk.lo; }
-__device__ inline void put8(gfix16_t* dst, const Pack8& pk) { *reinterpret_cast<uint4*>(dst) = pk.lo; }
-__device__ inline void get8(const float* src, float v[8]) {
-    const float4 a = reinterpret_cast<const float4*>(src)[0], b = reinterpret_cast<const float4*>(src)[1];
-    v[0] = a.x; v[1] = a.y; v[2] = a.z; v[3] = a.w; v[4] = b.x; v[5] = b.y; v[6] = b.z; v[7] = b.w;
-}
-__device__ inline void unpack8(const uint4& u, float v[8]) {  // eight fixed-point derivatives
-    const uint32_t w[4] = {u.x, u.y, u.z, u.w};
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        v[2 * i] = (float)(w[i] & 0xffffu) * GFIX_STEP - 0.125f;
-        v[2 * i + 1] = (float)(w[i] >> 16) * GFIX_STEP - 0.125f;
-    }
-}
-__device__ inline void get8(const gfix16_t* src, float v[8]) {
-    const uint4 u = *reinterpret_cast<const uint4*>(src);
-    const uint32_t w[4] = {u.x, u.y, u.z, u.w};
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        v[2 * i] = (float)(w[i] & 0xffffu) * GFIX_STEP - 0.125f;
-        v[2 * i + 1] = (float)(w[i] >> 16) * GFIX_STEP - 0.125f;
-    }
-}
-
 // ---- epilogues.  A lane owns, for each of its 8 "octets", row r and the eight consecutive columns
 // c .. c+7 (c a multiple of 8).  compute() turns the accumulators into results (left in v[], used for
 // the column sums) and packs what will be stored; flush() issues the stores.  The kernel calls
@@ -352,7 +230,7 @@ struct EpiFwd {  // h = act(z + b) and, when SAVE, act'(z); compact [M][ld] stor
     __device__ inline void compute_biased(float v[8], Out& o) const {  // v already holds z + b
         float g[8];
 #pragma unroll
-        for (int i = 0; i < 8; ++i) act_pair<ACT>(v[i], v[i], g[i]);
+        for (int i = 0; i < 8; ++i) act_pair<T, ACT>(v[i], v[i], g[i]);
         o.h = pack8(v, (const T*)nullptr);
         if (SAVE) o.g = pack8(g, (const typename GradT<T>::type*)nullptr);
     }
@@ -451,13 +329,6 @@ template <typename T> __device__ inline void shift_epi(EpiDx<T>& e, int p, int64
     e.dZ += (int64_t)p * s0;
 }
 __device__ inline void shift_epi(EpiDw& e, int p, int64_t s0, int64_t, int64_t) { e.dW += (int64_t)p * s0; }
-
-// Logical tile id so that consecutive ids run on the same XCD (workgroups are dealt round-robin to
-// the 8 XCDs by hardware id): the tiles of one preference then share that XCD's L2 copy of W(p).
-__device__ inline int xcd_remap(int bid, int nb) {
-    const int q = nb / 8, rem = nb % 8, x = bid % 8, pos = bid / 8;
-    return x * q + (x < rem ? x : rem) + pos;
-}
 
 // One step of the pairwise fold of per-lane slot arrays: lanes whose bit H of lr is set keep the upper H
 // slots, the others the lower H, and each adds what its partner (lr ^ H) held for the kept slots.
@@ -1250,8 +1121,6 @@ struct FusedFwdArgs {
     float* logp;
 };
 
-__device__ inline int swap_bits23(int i) { return (i & 0x13) | ((i & 4) << 1) | ((i & 8) >> 1); }
-
 // Fragment order of a [W][K] bf16 matrix (K a multiple of 64): the 16-byte pieces of W in the order in
 // which the fused forward requests them, so that each of its load instructions reads 1 KB of consecutive
 // addresses (eight whole cache lines) instead of 32 bytes from each of 32 rows.  Wave v of the forward owns
@@ -1297,13 +1166,6 @@ __global__ __launch_bounds__(256) void k_theta_fragment_order(FragOrderArgs a) {
         q = make_uint4(w[0], w[1], w[2], w[3]);
     }
     *reinterpret_cast<uint4*>(D + (int64_t)v * (K >> 5) * 4096 + u * 4096 + j * 2048 + e * 1024 + ln * 16) = q;
-}
-
-// a value the compiler can no longer trace back to its source: address arithmetic derived from it stays
-// where it is written instead of being hoisted out of the layer loop into registers held across the products
-__device__ inline int opaque(int v) {
-    asm volatile("" : "+v"(v));
-    return v;
 }
 
 template <int ACT, bool SAVE, int WD>
@@ -1442,7 +1304,7 @@ __global__ __launch_bounds__(WD, 2) void k_mlp_fused_fwd(FusedFwdArgs a) {
                         const int j = o >> 1, h = o & 1;
                         float v[8], g[8];
 #pragma unroll
-                        for (int u = 0; u < 8; ++u) act_pair<ACT>(acc[i][j][8 * h + u], v[u], g[u]);
+                        for (int u = 0; u < 8; ++u) act_pair<bf16_t, ACT>(acc[i][j][8 * h + u], v[u], g[u]);
                         const int cc = 8 * wave + 4 * j + 2 * h + olg;
                         hq[o] = pack_chunk<bf16_t>(v);
                         *reinterpret_cast<uint4*>(hrow + i * (32 * RB) + ((cc ^ ox) * 16)) = hq[o];
@@ -1693,6 +1555,8 @@ static void run_gemm(const morlax_ctx* c, int kind, GemmArgs<T, KA, KB, Epi, FAS
 }
 
 // ---- output layer ------------------------------------------------------------------------------
+// out = head(h W_L(p)^T + b_L(p)); actor: optional sampling a = mu + sigma eps and its log-density.
+// A wave owns 16 rows; lane (row = lane % 16, chunk = lane / 16) feeds 16x16 MFMA tiles from global.
 template <typename T>
 __global__ __launch_bounds__(256) void k_head_fwd(const T* __restrict__ Hin, const T* __restrict__ theta_mat,
                                                  const float* __restrict__ theta_vec, int64_t mat_len,
@@ -2069,7 +1933,7 @@ __global__ __launch_bounds__(256) void k_first_fwd_narrow(const float* __restric
             if (r < FN_ROWS && m < M) {
                 float g[8];
 #pragma unroll
-                for (int u = 0; u < 8; ++u) act_pair<ACT>(acc[t][u], acc[t][u], g[u]);
+                for (int u = 0; u < 8; ++u) act_pair<T, ACT>(acc[t][u], acc[t][u], g[u]);
                 const int64_t at = ((int64_t)p * M + m) * W + 8 * chunk;
                 put8(H + at, pack8(acc[t], (const T*)nullptr));
                 if (SAVE) put8(G + at, pack8(g, (const typename GradT<T>::type*)nullptr));
@@ -2397,6 +2261,96 @@ static void launch_fused_fwd(const morlax_ctx* c, const FusedFwdArgs& a, hipStre
     else launch_fused_fwd_w<ACT, SAVE, 512>(c, a, s);
 }
 
+// What the one-launch forward serves: widths its waves cover, and matrices followed by enough of theta for the whole
+// super-steps it requests (see load_w): a hidden row is overrun by less than the rest to a super-step, the first layer's
+// by less than a whole one.
+static bool mlp_fwd_ok(const morlax_ctx* c, const NetDev& nd) {
+    const int W = c->d.width, KS = c->d.wdtype == 1 ? 64 : 32, L = c->d.n_hidden;
+    if (W > 512) return false;
+    const int head = nd.out_dim * W;
+    return L == 1 ? head >= KS - 1 : head >= (W + KS - 1) / KS * KS - W;
+}
+
+static void fill_fwd_net(const morlax_ctx* c, int net, const void* theta_mat, const float* theta_vec, const RowSel& rs,
+                         float* out, float* saved_out, const float* eps, float* act, float* logp, char* H, char* G,
+                         char* x0, FwdNet& n) {
+    const NetDev& nd = c->net[net];
+    const LayerDev& Lo = nd.layer[c->d.n_hidden];
+    n.theta_mat = theta_mat; n.theta_vec = theta_vec;
+    n.mat_len = nd.mat_len; n.vec_len = nd.vec_len;
+    n.head_mat_off = Lo.mat_off; n.head_vec_off = Lo.vec_off; n.logsig_off = Lo.vec_off + Lo.d_out;
+    n.out_dim = nd.out_dim;
+    n.tanh_cols = (net == MORLAX_ACTOR && c->d.mean_tanh) ? c->d.act_dim : 0;
+    n.adim = c->d.act_dim;
+    n.sig_state = (net == MORLAX_ACTOR && c->d.sigma_state) ? 1 : 0;
+    n.M = rs.M; n.rm = make_rowmap(c, rs);
+    n.out = out; n.saved_out = saved_out; n.eps = eps; n.act = act; n.logp = logp;
+    n.H = H; n.G = G; n.x0 = x0;
+}
+
+// Row tiles of 16 per workgroup of the one-launch forward, `rows` rows per preference in all networks of the call
+// together; 0: not this kernel (tall selections of width 512 or 256 have one that multiplies four times the rows per
+// fetched weight, other tall ones the layer-by-layer GEMMs).  The lines are measured ones (saving variant, three hidden
+// layers, preferences x rows; us).
+static int fwd_row_tiles(const morlax_ctx* c, const NetDev& nd, const void* theta_mat, int64_t rows) {
+    const int W = c->d.width, L = c->d.n_hidden, O = c->d.obs_dim, P = c->d.P, nw = fwd_waves(W);
+    const bool bf = c->d.wdtype == 1;
+    if (!mlp_fwd_ok(c, nd)) return 0;
+    auto fits = [&](int r) { return fwd_lds_bytes(bf ? 2 : 4, O, W, L, r) <= 160 * 1024; };
+    auto tiles = [&](int r) { return (int64_t)P * ((rows + 16 * r - 1) / (16 * r)); };
+    if (!fits(bf ? 2 : 1)) return 0;
+    if (bf) {
+        // W 512: 64 x 512 107 tall, 137 here; 16 x 1024 (128 tall tiles) 72 and 59.  W 256: 64 x 1024 71 and 87, 64 x 512
+        // (256 tall tiles) 52 and 42
+        if ((W == 512 && tiles(8) >= 192) || (W == 256 && tiles(8) >= 384))
+            if (fused_fwd_ok(c, nd, theta_mat)) return 0;
+        if (nw == 8 && !fused_fwd_ok(c, nd, theta_mat) && tiles(4) >= 512) return 0;
+        if (nw == 6 && tiles(4) >= 512) return 0;  // W 384: 64 x 700 141 and 145, 64 x 2048 327 and 408, 16 x 700 54 and 46
+        // tiles of 64 rows once 32 would leave more than two rounds of workgroups: W 512 16 x 1024 59 against 63, 64 x 128
+        // 59 against 38; W 144 64 x 700 55 against 63, 16 x 700 28 against 25; W 48 and 128 (2, 4 tiles at a time on a CU) never
+        return nw >= 3 && tiles(2) >= (nw == 3 ? 1024 : 512) && fits(4) ? 4 : 2;
+    }
+    // fp32: W 512 64 x 700 563 GEMMs, 601 here, 16 x 700 equal; W 384 16 x 2048 285 and 297, 64 x 128 101 and 78
+    if ((nw == 8 && tiles(2) >= 512) || (nw == 6 && tiles(2) >= 768)) return 0;
+    // 16 rows until they would leave more than two rounds of workgroups (of 8 waves per CU): W 256 64 x 128 (512 tiles) 41
+    // against 40 of 32 rows, 16 x 700 56 against 61; W 128 64 x 700 69 against 83, 16 x 2048 61 against 43; W 32 64 x 2048 68
+    // against 72
+    return nw > 1 && tiles(1) >= (nw == 2 ? 4096 : 1024) && fits(2) ? 2 : 1;
+}
+
+// one or two networks in one launch
+static void run_mlp_fwd(const morlax_ctx* c, FwdArgs& a, int n_nets, int rt, bool save, hipStream_t s) {
+    const int W = c->d.width, L = c->d.n_hidden, O = c->d.obs_dim, P = c->d.P;
+    a.L = L; a.O = O; a.W = W; a.act = c->d.act;
+    a.perm = fused_fwd_ok(c, c->net[0], a.net[0].theta_mat) ? 1 : 0;
+    a.narrow = !a.perm && !use_x0(c) && first_fwd_narrow_ok(c) ? 1 : 0;
+    const bool bf = c->d.wdtype == 1;
+    double flops = 0.0;
+    for (int i = 0; i < n_nets; ++i) flops += 2.0 * W * ((double)O + (double)(L - 1) * W) * a.net[i].M * P;
+    int n_tiles = 0;
+    auto tiles = [&](int r) {
+        n_tiles = 0;
+        for (int i = 0; i < n_nets; ++i) {
+            a.net[i].tile0 = n_tiles;
+            a.net[i].tiles_m = (a.net[i].M + 16 * r - 1) / (16 * r);
+            n_tiles += a.net[i].tiles_m * P;
+        }
+        if (n_nets == 1) a.net[1].tile0 = 0x7fffffff;
+        return n_tiles;
+    };
+    tiles(rt);
+    GemmProf::Rec* r = prof_take(c, 5, flops);
+    if (r) (void)hipEventRecord(r->a, s);
+    if (bf) {
+        if (save) launch_mlp_fwd_bf16_save(a, rt, n_tiles, s);
+        else launch_mlp_fwd_bf16_act(a, rt, n_tiles, s);
+    } else {
+        if (save) launch_mlp_fwd_f32_save(a, rt, n_tiles, s);
+        else launch_mlp_fwd_f32_act(a, rt, n_tiles, s);
+    }
+    if (r) (void)hipEventRecord(r->b, s);
+}
+
 template <typename T>
 static void policy_fwd_t(const morlax_ctx* c, int net, const T* theta_mat, const float* theta_vec, const float* x,
                          const RowSel& rs, float* out, const float* eps, float* act, float* logp, void* saved,
@@ -2469,6 +2423,18 @@ static void policy_fwd_t(const morlax_ctx* c, int net, const T* theta_mat, const
             run_gemm(c, 1, g, P, s);
         }
     };
+    const int rt = fwd_row_tiles(c, nd, theta_mat, M);
+    if (rt > 0) {
+        FwdArgs a;
+        char* x0 = (sv && use_x0(c)) ? reinterpret_cast<char*>(sv) + (int64_t)2 * L * ae * sizeof(T) +
+                                           align_up((int64_t)P * M * OUT_PITCH * 4, 256)
+                                     : nullptr;
+        fill_fwd_net(c, net, theta_mat, theta_vec, rs, out, saved_out, eps, act, logp, reinterpret_cast<char*>(sv),
+                     reinterpret_cast<char*>(sv ? sv + ae : nullptr), x0, a.net[0]);
+        a.x = x; a.Mp = M; a.ldh = W; a.ldx = O; a.lstride = 2 * ae * (int64_t)sizeof(T);
+        run_mlp_fwd(c, a, 1, rt, sv != nullptr, s);
+        return;
+    }
     bool fused = false;
     if constexpr (std::is_same<T, bf16_t>::value) {
         if (fused_fwd_ok(c, nd, theta_mat)) {

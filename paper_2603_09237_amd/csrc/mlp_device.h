@@ -1,0 +1,156 @@
+// Device helpers shared by the target-network kernels: row map, packing, MFMA wrappers, activations.
+#pragma once
+
+#include <type_traits>
+
+#include "morlax_internal.h"
+#include "numeric.h"
+
+#define OUT_PITCH 16       // floats per row of the saved head output
+
+struct RowMap {  // compact row m of preference p -> row of a time-major tensor
+    int32_t t0, j0, j_cnt, N, n_g;
+    __device__ inline int64_t row(int p, int m) const {
+        return (int64_t)(t0 + m / j_cnt) * N + (int64_t)p * n_g + j0 + m % j_cnt;
+    }
+};
+
+template <typename T> struct Elems { static constexpr int VE = 16 / sizeof(T); };
+
+__device__ inline uint32_t pack2(bf16_t a, bf16_t b) {
+    return (uint32_t)__builtin_bit_cast(uint16_t, a) | ((uint32_t)__builtin_bit_cast(uint16_t, b) << 16);
+}
+
+template <typename T> __device__ inline uint4 pack_chunk(const float* v);  // 16 bytes of GEMM inputs
+template <> __device__ inline uint4 pack_chunk<float>(const float* v) {
+    return make_uint4(__float_as_uint(v[0]), __float_as_uint(v[1]), __float_as_uint(v[2]), __float_as_uint(v[3]));
+}
+template <> __device__ inline uint4 pack_chunk<bf16_t>(const float* v) {
+    return make_uint4(pack2((bf16_t)v[0], (bf16_t)v[1]), pack2((bf16_t)v[2], (bf16_t)v[3]),
+                      pack2((bf16_t)v[4], (bf16_t)v[5]), pack2((bf16_t)v[6], (bf16_t)v[7]));
+}
+
+template <typename T> struct Mma32;
+template <> struct Mma32<bf16_t> {
+    static __device__ inline void run(const uint4& a, const uint4& b, float16_t& c) {
+        c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8_t, a), __builtin_bit_cast(bf16x8_t, b), c,
+                                                    0, 0, 0);
+    }
+};
+template <> struct Mma32<float> {
+    static __device__ inline void run(const uint4& a, const uint4& b, float16_t& c) {
+        c = __builtin_amdgcn_mfma_f32_32x32x2f32(__uint_as_float(a.x), __uint_as_float(b.x), c, 0, 0, 0);
+        c = __builtin_amdgcn_mfma_f32_32x32x2f32(__uint_as_float(a.y), __uint_as_float(b.y), c, 0, 0, 0);
+        c = __builtin_amdgcn_mfma_f32_32x32x2f32(__uint_as_float(a.z), __uint_as_float(b.z), c, 0, 0, 0);
+        c = __builtin_amdgcn_mfma_f32_32x32x2f32(__uint_as_float(a.w), __uint_as_float(b.w), c, 0, 0, 0);
+    }
+};
+
+__device__ inline float chunk_f32(const uint4& u, int e) {  // e a compile-time constant after unrolling
+    return __uint_as_float(e == 0 ? u.x : e == 1 ? u.y : e == 2 ? u.z : u.w);
+}
+
+template <typename T> struct Mma16;
+template <> struct Mma16<bf16_t> {
+    static __device__ inline void run(const uint4& a, const uint4& b, float4_t& c) {
+        c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, a), __builtin_bit_cast(bf16x8_t, b), c,
+                                                    0, 0, 0);
+    }
+};
+template <> struct Mma16<float> {
+    static __device__ inline void run(const uint4& a, const uint4& b, float4_t& c) {
+        c = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(a.x), __uint_as_float(b.x), c, 0, 0, 0);
+        c = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(a.y), __uint_as_float(b.y), c, 0, 0, 0);
+        c = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(a.z), __uint_as_float(b.z), c, 0, 0, 0);
+        c = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(a.w), __uint_as_float(b.w), c, 0, 0, 0);
+    }
+};
+
+// h = act(z) and g = act'(z).  SiLU uses the hardware exp2 / reciprocal approximations (about 1 ulp
+// each): s = 1 / (1 + e^-z), h = z s, g = s (1 + z - h).  bf16 networks take the library's tanh.
+// tanh without a branch (the library routine's two sides diverge inside nearly every wave; its code was most of a tanh
+// network's epilogue): below 0.625 the odd polynomial x + x z P(z), z = x^2, P a relative minimax fit made for this file
+// (4.4e-9), above it 1 - 2 / (1 + e^2|x|).  At most 2 ulp from the exact value, measured against float64 on a dense grid.
+__device__ inline float tanh_f32(float x) {
+    const float a = __builtin_fabsf(x), z = x * x;
+    float p = -0.005705018527805805f;
+    p = __builtin_fmaf(p, z, 0.020639119669795036f);
+    p = __builtin_fmaf(p, z, -0.053739726543426514f);
+    p = __builtin_fmaf(p, z, 0.13331443071365356f);
+    p = __builtin_fmaf(p, z, -0.3333328068256378f);
+    const float lo = __builtin_fmaf(p * z, x, x);
+    const float e = __builtin_amdgcn_exp2f(a * 2.8853900817779268f);
+    const float hi = __builtin_copysignf(__builtin_fmaf(-2.f, __builtin_amdgcn_rcpf(1.f + e), 1.f), x);
+    return a < 0.625f ? lo : hi;
+}
+template <typename T, int ACT>
+__device__ inline void act_pair(float z, float& h, float& g) {
+    if (ACT == 0) {
+        h = sizeof(T) == 2 ? tanhf(z) : tanh_f32(z);
+        g = 1.f - h * h;
+    } else {
+        const float e = __expf(-z);
+        const float s = __builtin_amdgcn_rcpf(1.f + e);
+        h = z * s;
+        g = s * (1.f + z - h);
+    }
+}
+
+// eight consecutive elements of type T / of the saved-derivative type: packing and 16-byte accesses
+struct Pack8 { uint4 lo, hi; };  // bf16 / fixed point use lo only; fp32 uses both
+__device__ inline Pack8 pack8(const float v[8], const float*) {
+    Pack8 r;
+    r.lo = make_uint4(__float_as_uint(v[0]), __float_as_uint(v[1]), __float_as_uint(v[2]), __float_as_uint(v[3]));
+    r.hi = make_uint4(__float_as_uint(v[4]), __float_as_uint(v[5]), __float_as_uint(v[6]), __float_as_uint(v[7]));
+    return r;
+}
+__device__ inline Pack8 pack8(const float v[8], const bf16_t*) {
+    Pack8 r;
+    r.lo = pack_chunk<bf16_t>(v);
+    r.hi = make_uint4(0, 0, 0, 0);
+    return r;
+}
+__device__ inline Pack8 pack8(const float v[8], const gfix16_t*) {
+    // round(v / step + 1/8 / step); values are in (-0.125, 1.125) so the conversion cannot overflow
+    uint32_t q[8];
+#pragma unroll
+    for (int i = 0; i < 8; ++i) q[i] = (uint32_t)(v[i] * (1.0f / GFIX_STEP) + (0.125f / GFIX_STEP + 0.5f));
+    Pack8 r;
+    r.lo = make_uint4(q[0] | (q[1] << 16), q[2] | (q[3] << 16), q[4] | (q[5] << 16), q[6] | (q[7] << 16));
+    r.hi = make_uint4(0, 0, 0, 0);
+    return r;
+}
+__device__ inline void put8(float* dst, const Pack8& pk) {
+    reinterpret_cast<uint4*>(dst)[0] = pk.lo;
+    reinterpret_cast<uint4*>(dst)[1] = pk.hi;
+}
+__device__ inline void put8(bf16_t* dst, const Pack8& pk) { *reinterpret_cast<uint4*>(dst) = pk.lo; }
+__device__ inline void put8(gfix16_t* dst, const Pack8& pk) { *reinterpret_cast<uint4*>(dst) = pk.lo; }
+__device__ inline void get8(const float* src, float v[8]) {
+    const float4 a = reinterpret_cast<const float4*>(src)[0], b = reinterpret_cast<const float4*>(src)[1];
+    v[0] = a.x; v[1] = a.y; v[2] = a.z; v[3] = a.w; v[4] = b.x; v[5] = b.y; v[6] = b.z; v[7] = b.w;
+}
+__device__ inline void unpack8(const uint4& u, float v[8]) {  // eight fixed-point derivatives
+    const uint32_t w[4] = {u.x, u.y, u.z, u.w};
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        v[2 * i] = (float)(w[i] & 0xffffu) * GFIX_STEP - 0.125f;
+        v[2 * i + 1] = (float)(w[i] >> 16) * GFIX_STEP - 0.125f;
+    }
+}
+__device__ inline void get8(const gfix16_t* src, float v[8]) {
+    const uint4 u = *reinterpret_cast<const uint4*>(src);
+    const uint32_t w[4] = {u.x, u.y, u.z, u.w};
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        v[2 * i] = (float)(w[i] & 0xffffu) * GFIX_STEP - 0.125f;
+        v[2 * i + 1] = (float)(w[i] >> 16) * GFIX_STEP - 0.125f;
+    }
+}
+
+// Logical tile id so that consecutive ids run on the same XCD (workgroups are dealt round-robin to
+// the 8 XCDs by hardware id): the tiles of one preference then share that XCD's L2 copy of W(p).
+__device__ inline int xcd_remap(int bid, int nb) {
+    const int q = nb / 8, rem = nb % 8, x = bid % 8, pos = bid / 8;
+    return x * q + (x < rem ? x : rem) + pos;
+}
