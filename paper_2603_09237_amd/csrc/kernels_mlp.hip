@@ -23,7 +23,7 @@ void launch_mlp_fwd_f32_save(const FwdArgs& a, int rt, int n_tiles, hipStream_t 
 #define BN 128
 #define GEMM_NCH 4         // 16-byte chunks of the contraction axis staged per step and operand row
 
-enum { SRC_KCONTIG = 0, SRC_KSTRIDED = 1, SRC_X_KCONTIG = 2, SRC_X_KSTRIDED = 3 };
+enum { SRC_KCONTIG = 0, SRC_KSTRIDED = 1, SRC_X_KCONTIG = 2 };
 
 // One GEMM operand: a [rows x kdim] matrix of which a workgroup stages 128 rows x NCH 16-byte chunks of
 // the contraction axis per step.  FAST = every access is a full, aligned vector (the launcher checks
@@ -51,8 +51,7 @@ struct Operand {
         if (r >= rows || k >= kdim) return 0.f;
         if (KIND == SRC_KCONTIG) return to_f(reinterpret_cast<const T*>(base)[(int64_t)r * ld + k]);
         if (KIND == SRC_KSTRIDED) return to_f(reinterpret_cast<const T*>(base)[(int64_t)k * ld + r]);
-        if (KIND == SRC_X_KCONTIG) return reinterpret_cast<const float*>(base)[rm.row(p, r) * ld + k];
-        return reinterpret_cast<const float*>(base)[rm.row(p, k) * ld + r];
+        return reinterpret_cast<const float*>(base)[rm.row(p, r) * ld + k];
     }
 
     // thread -> (tile row, chunk) of its i-th chunk
@@ -76,17 +75,15 @@ struct Operand {
             int r = r0 + trow(i);
             const int lim = PAIR ? rows - 2 : rows - 1;
             r = r < lim ? r : lim;
-            if (KIND == SRC_KCONTIG) voff[i] = (uint32_t)((r * (int)ld + tchunk(i) * VE) * (int)sizeof(T));
+            if (KIND == SRC_KCONTIG) voff[i] = (uint32_t)(r * (int)ld + tchunk(i) * VE) * (uint32_t)sizeof(T);
             else if (KIND == SRC_X_KCONTIG) voff[i] = (uint32_t)((rm.row(p, r) * ld + tchunk(i) * VE) * 4);
-            else if (KIND == SRC_KSTRIDED) voff[i] = (uint32_t)((tchunk(i) * VE * (int)ld + r) * (int)sizeof(T));
-            else voff[i] = (uint32_t)(r * 4);
+            else voff[i] = (uint32_t)((tchunk(i) * VE * (int)ld + r) * (int)sizeof(T));
         }
     }
 
     // Raw staging registers per thread: the loads of step k+1 are issued before the products of step k
     // and nothing touches the loaded values until store(), so the load latency overlaps the MFMAs.
-    static constexpr bool XSRC = (KIND == SRC_X_KCONTIG || KIND == SRC_X_KSTRIDED);
-    static constexpr int RPC = (XSRC && sizeof(T) == 2) ? 2 : 1;  // uint4 registers per chunk (fp32 source of bf16)
+    static constexpr int RPC = (KIND == SRC_X_KCONTIG && sizeof(T) == 2) ? 2 : 1;  // uint4 registers per chunk (fp32 source of bf16)
     static constexpr int NRAW = FAST ? CPT * RPC : CPT;
 
     // Issue the loads of contraction range [k0, k0 + NCH * VE).  TAIL = the range may cross kdim: indices
@@ -115,7 +112,7 @@ struct Operand {
 #pragma unroll
                 for (int q = 0; q < RPC; ++q) raw[i * RPC + q] = reinterpret_cast<const uint4*>(src)[q];
             }
-        } else if (KIND == SRC_KSTRIDED) {
+        } else {
             const int64_t rstep = ld * (int64_t)sizeof(T);  // bytes between consecutive k
             const char* bk = b + (int64_t)k0 * rstep;
 #pragma unroll
@@ -132,20 +129,6 @@ struct Operand {
                 }
                 raw[i] = make_uint4(d[0], d[1], d[2], d[3]);
                 if (PAIR) raw[i + 1] = make_uint4(d[4], d[5], d[6], d[7]);
-            }
-        } else {
-            // x, contraction over rows of the selection: VE consecutive selected rows share one time step
-            // (the launcher checks j_cnt % VE == 0), so one row lookup serves the chunk
-#pragma unroll
-            for (int i = 0; i < CPT; ++i) {
-                const int k = k0 + tchunk(i) * VE;
-                const int64_t rb = rm.row(p, k < kdim ? k : 0);
-                uint32_t d[8];
-#pragma unroll
-                for (int e = 0; e < VE; ++e)
-                    d[e] = *reinterpret_cast<const uint32_t*>(b + (rb + e) * ld * 4 + voff[i]);
-                raw[i * RPC] = make_uint4(d[0], d[1], d[2], d[3]);
-                if (RPC == 2) raw[i * RPC + 1] = make_uint4(d[4], d[5], d[6], d[7]);
             }
         }
     }
@@ -190,7 +173,7 @@ struct Operand {
                                    k + 3 < kdim ? u.w : 0u);
                 *reinterpret_cast<uint4*>(tile + trow(i) * PITCH + tchunk(i) * 16) = u;
             }
-        } else {  // x sources: fp32 -> T, whole chunks in or out of the contraction range
+        } else {  // x source: fp32 -> T, whole chunks in or out of the contraction range
 #pragma unroll
             for (int i = 0; i < CPT; ++i) {
                 const bool ok = !TAIL || (k0 + tchunk(i) * VE < kdim);
@@ -453,6 +436,24 @@ struct GemmArgs {
     int64_t a_pstride, b_pstride;  // per-preference strides (elements of the operand's storage type)
     int64_t e0_pstride, e1_pstride, e2_pstride;
     int tiles_m, tiles_n;
+    int crows = 0, ccols = 0;  // extent of the product (0: rows of a, rows of b)
+    // dW with few preferences: the contraction cut into `ranges` pieces of `range` indices (a multiple of 64, the last
+    // one shorter), each a group of its own: group p * ranges + s multiplies range s of preference p
+    int ranges = 1, range = 0;
+
+    struct Group { int p, k0, kdim; };  // preference, first contraction index, contraction length
+    __device__ inline Group group(int id) const {
+        if (KA != SRC_KSTRIDED || KB != SRC_KSTRIDED || ranges == 1) return {id, 0, a.kdim};
+        const int pp = id / ranges, k0 = (id - pp * ranges) * range;
+        return {pp, k0, a.kdim - k0 < range ? a.kdim - k0 : range};
+    }
+    // base of the operands for a group (compact kinds; k0 > 0 only where the contraction axis is the slow one)
+    __device__ inline const T* a_base(const Group& q) const {
+        return reinterpret_cast<const T*>(a.base) + (int64_t)q.p * a_pstride + (int64_t)q.k0 * a.ld;
+    }
+    __device__ inline const T* b_base(const Group& q) const {
+        return reinterpret_cast<const T*>(b.base) + (int64_t)q.p * b_pstride + (int64_t)q.k0 * b.ld;
+    }
 };
 
 // C[rows_a x rows_b] = A[rows_a x K] * B[rows_b x K]^T for every preference.
@@ -470,11 +471,11 @@ __global__ __launch_bounds__(256) void k_grouped_gemm(GemmArgs<T, KA, KB, Epi, F
 
     Operand<T, KA, FAST, NCH> A = g.a;
     Operand<T, KB, FAST, NCH> B = g.b;
+    const auto grp = g.group(p);
     A.p = p; B.p = p;
-    if (KA == SRC_KCONTIG || KA == SRC_KSTRIDED)
-        A.base = reinterpret_cast<const T*>(A.base) + (int64_t)p * g.a_pstride;
-    if (KB == SRC_KCONTIG || KB == SRC_KSTRIDED)
-        B.base = reinterpret_cast<const T*>(B.base) + (int64_t)p * g.b_pstride;
+    if (KA == SRC_KCONTIG || KA == SRC_KSTRIDED) A.base = g.a_base(grp);
+    if (KB == SRC_KCONTIG || KB == SRC_KSTRIDED) B.base = g.b_base(grp);
+    A.kdim = B.kdim = grp.kdim;
     Epi epi = g.epi;
     shift_epi(epi, p, g.e0_pstride, g.e1_pstride, g.e2_pstride);
 
@@ -549,7 +550,7 @@ __global__ __launch_bounds__(256) void k_grouped_gemm(GemmArgs<T, KA, KB, Epi, F
         }
         __syncthreads();
     }
-    gemm_epilogue(epi, acc, &lds[0][0][0], p, tm, g.tiles_m, r0, c0, A.rows, B.rows);
+    gemm_epilogue(epi, acc, &lds[0][0][0], p, tm, g.tiles_m, r0, c0, g.crows, g.ccols);
 }
 
 // ---- bf16 grouped GEMM with direct-to-LDS loads ------------------------------------------------
@@ -651,8 +652,9 @@ __global__ __launch_bounds__(256) void k_gemm_dma(GemmArgs<bf16_t, KA, KB, Epi, 
     const int wm = (wave >> 1) * 64, wn = (wave & 1) * 64;
     DmaOperand<KA> A;
     DmaOperand<KB> B;
-    A.init(reinterpret_cast<const bf16_t*>(g.a.base) + (int64_t)p * g.a_pstride, (int)g.a.ld, g.a.rows, r0, wm, false);
-    B.init(reinterpret_cast<const bf16_t*>(g.b.base) + (int64_t)p * g.b_pstride, (int)g.b.ld, g.b.rows, c0, wn, true);
+    const auto grp = g.group(p);
+    A.init(g.a_base(grp), (int)g.a.ld, g.a.rows, r0, wm, false);
+    B.init(g.b_base(grp), (int)g.b.ld, g.b.rows, c0, wn, true);
 
     float16_t acc[2][2];
 #pragma unroll
@@ -662,7 +664,7 @@ __global__ __launch_bounds__(256) void k_gemm_dma(GemmArgs<bf16_t, KA, KB, Epi, 
 #pragma unroll
             for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.f;
 
-    const int nk = g.a.kdim / 32;
+    const int nk = grp.kdim / 32;
     const uint32_t lbase = (uint32_t)(size_t)dlds;
 #pragma unroll
     for (int st = 0; st < DMA_NST - 1; ++st)
@@ -698,7 +700,7 @@ __global__ __launch_bounds__(256) void k_gemm_dma(GemmArgs<bf16_t, KA, KB, Epi, 
         }
     }
     __syncthreads();
-    gemm_epilogue(epi, acc, dlds, p, tm, g.tiles_m, r0, c0, g.a.rows, g.b.rows);
+    gemm_epilogue(epi, acc, dlds, p, tm, g.tiles_m, r0, c0, g.crows, g.ccols);
 }
 
 // ---- persistent bf16 grouped GEMM, 256 x TN tiles -----------------------------------------------
@@ -952,7 +954,7 @@ __global__ __launch_bounds__(2 * TN, 2) void k_gemm_pers(GemmArgs<bf16_t, KA, KB
     const int wave = threadIdx.x >> 6;
     const int wm = (wave / (TN / 64)) * 128, wn = (wave % (TN / 64)) * 64;
     const int per_p = g.tiles_m * g.tiles_n;
-    const int nk = g.a.kdim / 32;
+    int nk = 0;  // contraction steps of the current tile
     const uint32_t lbase = (uint32_t)(size_t)dlds;
     DmaTile<KA, PG_TM, 4, S::kWaves> A;
     DmaTile<KB, TN, 2, S::kWaves> B;
@@ -978,8 +980,10 @@ __global__ __launch_bounds__(2 * TN, 2) void k_gemm_pers(GemmArgs<bf16_t, KA, KB
                      __builtin_amdgcn_readfirstlane(lbase + S::kLds + (uint32_t)(bslot * (4 * TN) + wave * 256)));
             }
         }
-        A.set_tile(reinterpret_cast<const bf16_t*>(g.a.base) + (int64_t)p * g.a_pstride, (int)g.a.ld, g.a.rows, tm * PG_TM);
-        B.set_tile(reinterpret_cast<const bf16_t*>(g.b.base) + (int64_t)p * g.b_pstride, (int)g.b.ld, g.b.rows, tn * TN);
+        const auto grp = g.group(p);
+        nk = grp.kdim / 32;
+        A.set_tile(g.a_base(grp), (int)g.a.ld, g.a.rows, tm * PG_TM);
+        B.set_tile(g.b_base(grp), (int)g.b.ld, g.b.rows, tn * TN);
 #pragma unroll
         for (int st = 0; st < PG_NST - 1; ++st)
             if (st < nk) {
@@ -1063,7 +1067,7 @@ __global__ __launch_bounds__(2 * TN, 2) void k_gemm_pers(GemmArgs<bf16_t, KA, KB
         }
         tile_epilogue<Epi, 4, TN>(epi, acc, dlds + (PG_NST - 1) * S::kStage, lds_bias,
                                   reinterpret_cast<float*>(dlds + S::kLds), first, pc, tmc, g.tiles_m, tmc * PG_TM, tnc * TN,
-                              g.a.rows, g.b.rows, wm, wn);
+                                  g.crows, g.ccols, wm, wn);
         if (!more) break;
     }
 }
@@ -1097,7 +1101,7 @@ __global__ __launch_bounds__(2 * TN, 2) void k_gemm_pers(GemmArgs<bf16_t, KA, KB
 
 struct FusedFwdArgs {
     const float* x;           // observations, time-major rows of O values
-    bf16_t* x0;               // saving: receives the gathered observations, compact [P][M][O] bf16
+    bf16_t* x0;               // saving, optional: receives the gathered observations, compact [P][Mp][ldx] bf16
     const bf16_t* theta_mat;  // [P][mat_len]: the output layer's matrix is read from here
     const bf16_t* theta_frag; // [P][mat_len]: the first and the hidden layers' matrices in fragment order
     const float* theta_vec;   // [P][vec_len]
@@ -1109,6 +1113,7 @@ struct FusedFwdArgs {
     gfix16_t* G;  // saving: act'(z) of layer l at G + l * lstride
     int64_t lstride;
     int32_t L, O, M, tiles_m, n_tiles;
+    int32_t Mp, ldx;  // saving: rows per preference of H, G and x0 (copies of row M - 1 beyond M), row length of x0
     // output layer (applied to the tile's last hidden activations while they are still in LDS)
     int64_t head_mat_off, head_vec_off, logsig_off;
     int32_t out_dim, tanh_cols;  // leading output columns that are squashed by tanh (the actor's means)
@@ -1183,6 +1188,7 @@ __global__ __launch_bounds__(WD, 2) void k_mlp_fused_fwd(FusedFwdArgs a) {
         const int tile = xcd_remap(vt, a.n_tiles);
         const int p = tile / a.tiles_m, m0 = (tile % a.tiles_m) * FF_ROWS;
         const int rows = a.M - m0 < FF_ROWS ? a.M - m0 : FF_ROWS;
+        const int srows = SAVE ? a.Mp - m0 : 0;  // rows to save
         const int wn = wave * 64;
 
         const bf16_t* Wp = a.theta_frag + (int64_t)p * a.frag_len;
@@ -1211,8 +1217,8 @@ __global__ __launch_bounds__(WD, 2) void k_mlp_fused_fwd(FusedFwdArgs a) {
         load_w(wfa, wp[0], wp[1], 0);
 
         {  // the tile's observations, gathered from the time-major tensor and rounded to bf16; rows past the end
-           // repeat the last row (their results are never stored).  The saving variant keeps the compact copy
-           // that the first layer's dW product reads.
+           // repeat the last row (saved up to Mp, no output).  The saving variant keeps the compact copy that the first
+           // layer's dW product reads.
             const int cpr = a.Opad >> 3;
             const bool whole = (a.O & 7) == 0;  // rows of whole 8-value pieces (16-byte aligned: the launcher checks x)
             for (int id = threadIdx.x; id < FF_ROWS * cpr; id += WD) {
@@ -1227,8 +1233,8 @@ __global__ __launch_bounds__(WD, 2) void k_mlp_fused_fwd(FusedFwdArgs a) {
                 }
                 const uint4 q = pack_chunk<bf16_t>(v);
                 *reinterpret_cast<uint4*>(dlds + r * RB + ((c ^ (r & 15)) * 16)) = q;
-                if (SAVE && a.x0 && r < rows && 8 * c < a.O)
-                    *reinterpret_cast<uint4*>(a.x0 + ((int64_t)p * a.M + m0 + r) * a.O + 8 * c) = q;
+                if (SAVE && a.x0 && r < srows && 8 * c < a.ldx)
+                    *reinterpret_cast<uint4*>(a.x0 + ((int64_t)p * a.Mp + m0 + r) * a.ldx + 8 * c) = q;
             }
         }
         // fragment addresses: row 32 i + lr, chunk (8 s + 4 lg + jj) ^ (lr & 15)
@@ -1294,8 +1300,8 @@ __global__ __launch_bounds__(WD, 2) void k_mlp_fused_fwd(FusedFwdArgs a) {
                 const int ol = opaque(lane), olr = ol & 31, olg = ol >> 5, ox = ol & 15;
                 unsigned char* hrow = dlds + olr * RB;
                 unsigned char* patch = dlds + TILE_BYTES + wave * 4096;
-                gfix16_t* Gl = SAVE ? a.G + (int64_t)l * a.lstride + ((int64_t)p * a.M + m0) * WD + wn : nullptr;
-                bf16_t* Hl = SAVE ? a.H + (int64_t)l * a.lstride + ((int64_t)p * a.M + m0) * WD + wn : nullptr;
+                gfix16_t* Gl = SAVE ? a.G + (int64_t)l * a.lstride + ((int64_t)p * a.Mp + m0) * WD + wn : nullptr;
+                bf16_t* Hl = SAVE ? a.H + (int64_t)l * a.lstride + ((int64_t)p * a.Mp + m0) * WD + wn : nullptr;
 #pragma unroll
                 for (int i = 0; i < 4; ++i) {
                     uint4 gq[4], hq[4];
@@ -1329,7 +1335,7 @@ __global__ __launch_bounds__(WD, 2) void k_mlp_fused_fwd(FusedFwdArgs a) {
                                 const int prow = it * 8 + (ol >> 3), pc = ol & 7;
                                 const uint4 u = *reinterpret_cast<const uint4*>(patch + prow * 128 + ((pc ^ (prow & 7)) * 16));
                                 const int gr = 32 * i + prow;
-                                if (gr < rows) *reinterpret_cast<uint4*>(dst + ((int64_t)gr * WD + pc * 8) * 2) = u;
+                                if (gr < srows) *reinterpret_cast<uint4*>(dst + ((int64_t)gr * WD + pc * 8) * 2) = u;
                             }
                             __builtin_amdgcn_wave_barrier();
                         }
@@ -1498,10 +1504,10 @@ static bool launch_dma(GemmArgs<T, KA, KB, Epi, FAST, NCH>& g, int P, int nb, hi
         // large problems: persistent kernel, 256 x 256 tiles (one workgroup of eight waves per CU) when the
         // output is at least that wide and there is a tile for every CU, else 256 x 128 tiles (two workgroups
         // of four waves per CU) as soon as those fill the resident workgroups
-        const int ptm = (g.a.rows + PG_TM - 1) / PG_TM;
+        const int ptm = (g.crows + PG_TM - 1) / PG_TM;
         auto launch_pers = [&](auto tn_tag, int slots) {
             constexpr int TN = decltype(tn_tag)::value;
-            const int ptn = (g.b.rows + TN - 1) / TN, pnt = ptm * ptn * P;
+            const int ptn = (g.ccols + TN - 1) / TN, pnt = ptm * ptn * P;
             static bool pattr_set = false;
             constexpr int plds = PgShape<TN>::kLds + 8 * TN;
             if (!pattr_set) {
@@ -1514,16 +1520,16 @@ static bool launch_dma(GemmArgs<T, KA, KB, Epi, FAST, NCH>& g, int P, int nb, hi
             const int grid = pnt < slots ? pnt : slots;
             k_gemm_pers<KA, KB, Epi, TN><<<grid, 2 * TN, plds, s>>>(g, pnt);
         };
-        if (g.a.rows >= 64) {
+        if (g.crows >= 64) {
             const int slots = resident_slots();
             // (the wide shape as soon as there is a tile per CU: a third fewer operand bytes per product through the
             // vector cache, whose requests in flight are what the products wait for; dW at W = 512 with two tiles per
             // workgroup: 8.3 -> 7.9 ms per step of workload 5, with one tile per workgroup at workload 4: 0.945 -> 0.915)
-            if (g.b.rows >= 256 && ptm * ((g.b.rows + 255) / 256) * P >= slots / 2) {
+            if (g.ccols >= 256 && ptm * ((g.ccols + 255) / 256) * P >= slots / 2) {
                 launch_pers(std::integral_constant<int, 256>{}, slots / 2);
                 return true;
             }
-            if (ptm * ((g.b.rows + 127) / 128) * P >= slots) {
+            if (ptm * ((g.ccols + 127) / 128) * P >= slots) {
                 launch_pers(std::integral_constant<int, 128>{}, slots);
                 return true;
             }
@@ -1545,10 +1551,12 @@ static bool launch_dma(GemmArgs<T, KA, KB, Epi, FAST, NCH>& g, int P, int nb, hi
 
 template <typename T, int KA, int KB, class Epi, bool FAST, int NCH>
 static void run_gemm(const morlax_ctx* c, int kind, GemmArgs<T, KA, KB, Epi, FAST, NCH>& g, int P, hipStream_t s) {
-    g.tiles_m = (g.a.rows + BM - 1) / BM;
-    g.tiles_n = (g.b.rows + BN - 1) / BN;
+    if (g.crows == 0) g.crows = g.a.rows;
+    if (g.ccols == 0) g.ccols = g.b.rows;
+    g.tiles_m = (g.crows + BM - 1) / BM;
+    g.tiles_n = (g.ccols + BN - 1) / BN;
     const int nb = g.tiles_m * g.tiles_n * P;
-    GemmProf::Rec* r = prof_take(c, kind, 2.0 * g.a.rows * (double)g.b.rows * g.a.kdim * P);
+    GemmProf::Rec* r = prof_take(c, kind, 2.0 * g.crows * (double)g.ccols * g.a.kdim * (P / g.ranges));
     if (r) (void)hipEventRecord(r->a, s);
     if (!launch_dma(g, P, nb, s)) k_grouped_gemm<T, KA, KB, Epi, FAST, NCH><<<nb, 256, 0, s>>>(g);
     if (r) (void)hipEventRecord(r->b, s);
@@ -1561,7 +1569,7 @@ template <typename T>
 __global__ __launch_bounds__(256) void k_head_fwd(const T* __restrict__ Hin, const T* __restrict__ theta_mat,
                                                  const float* __restrict__ theta_vec, int64_t mat_len,
                                                  int64_t vec_len, int64_t mat_off, int64_t vec_off, int W,
-                                                 int out_dim, int M, RowMap rm, int tanh_cols,
+                                                 int out_dim, int M, int Mp, RowMap rm, int tanh_cols,
                                                  float* __restrict__ out, float* __restrict__ saved_out,
                                                  const float* __restrict__ eps, float* __restrict__ act,
                                                  float* __restrict__ logp, int64_t logsig_off, int adim,
@@ -1572,7 +1580,7 @@ __global__ __launch_bounds__(256) void k_head_fwd(const T* __restrict__ Hin, con
     const int m0 = (blockIdx.x * 4 + wave) * 16;
     if (m0 >= M) return;
     const int lr = lane & 15, lg = lane >> 4;
-    const T* hrow = Hin + ((int64_t)p * M + (m0 + lr)) * W;
+    const T* hrow = Hin + ((int64_t)p * Mp + (m0 + lr)) * W;
     const T* wrow = theta_mat + (int64_t)p * mat_len + mat_off + (int64_t)lr * W;
     const bool a_ok = (m0 + lr) < M, b_ok = lr < out_dim;
     // eight contraction steps per batch: their loads are issued together, and two accumulators alternate so
@@ -1683,7 +1691,7 @@ __global__ __launch_bounds__(256) void k_head_bwd_dz(const float* __restrict__ d
                                                     int64_t mat_off,
                                                     const typename GradT<T>::type* __restrict__ G,
                                                     T* __restrict__ dZ, float* __restrict__ part,
-                                                    int W, int out_dim, int M) {
+                                                    int W, int out_dim, int M, int Mp) {
     __shared__ float sdz[64][MORLAX_MAX_OUT];
     __shared__ float red[16][128];
     const int p = blockIdx.z, m0 = blockIdx.y * 64, i0 = blockIdx.x * 128;
@@ -1719,8 +1727,8 @@ __global__ __launch_bounds__(256) void k_head_bwd_dz(const float* __restrict__ d
 #pragma unroll
     for (int a = 0; a < 4; ++a) {
         const int m = m0 + tr + a;
-        if (m >= M || !live) continue;
-        const int64_t o = ((int64_t)p * M + m) * W + ti;
+        if (m >= Mp || !live) continue;  // (rows M .. Mp: their dz is zero, and so is dZ)
+        const int64_t o = ((int64_t)p * Mp + m) * W + ti;
         float v[8];
 #pragma unroll
         for (int b = 0; b < 8; ++b) {
@@ -1760,7 +1768,7 @@ __device__ inline short4_t lds_tr4(const E* word) {
 #define HB_SPLIT 4
 template <typename T>
 __global__ __launch_bounds__(256) void k_head_bwd_dw(const float* __restrict__ dzh, const T* __restrict__ Hin,
-                                                    float* __restrict__ pw, int W, int M) {
+                                                    float* __restrict__ pw, int W, int M, int Mp) {
     constexpr int VE = Elems<T>::VE;
     constexpr int HP = 128 + VE;                           // h tile pitch in elements (16 bytes of padding)
     constexpr int CPR = 128 / VE;                          // 16-byte pieces per tile row
@@ -1786,7 +1794,7 @@ __global__ __launch_bounds__(256) void k_head_bwd_dw(const float* __restrict__ d
             const int idx = threadIdx.x + 256 * q, mm = idx / CPR, cc = (idx % CPR) * VE;
             uint4 u = make_uint4(0, 0, 0, 0);
             if (m0 + mm < m_hi && i0 + cc < W)
-                u = *reinterpret_cast<const uint4*>(Hin + ((int64_t)p * M + m0 + mm) * W + i0 + cc);
+                u = *reinterpret_cast<const uint4*>(Hin + ((int64_t)p * Mp + m0 + mm) * W + i0 + cc);
             nxt[q] = u;
         }
     };
@@ -1848,9 +1856,9 @@ __global__ __launch_bounds__(256) void k_head_bwd_dw(const float* __restrict__ d
 }
 
 // ---- dW of a W x W layer with few preferences: contraction split into ranges ---------------------------------
-// dW_l(p) has (W/128)^2 tiles per preference and the whole selection as its contraction; with few preferences that
-// is a few dozen workgroups walking thousands of rows each.  The selection is cut into S equal ranges that run as
-// P S groups of the same grouped GEMM into partial matrices, and the ranges are added in order.
+// dW_l(p) has (W/128)^2 tiles per preference (the first layer fewer still) and the whole selection as its contraction;
+// with few preferences that is a few dozen workgroups walking thousands of rows each.  The selection is cut into ranges
+// that run as groups of the same grouped GEMM into partial matrices, and the ranges are added in order.
 #ifndef DW_SPLIT_TARGET
 #define DW_SPLIT_TARGET 512
 #endif
@@ -1881,7 +1889,7 @@ template <typename T, int ACT, bool SAVE>
 __global__ __launch_bounds__(256) void k_first_fwd_narrow(const float* __restrict__ x, const T* __restrict__ theta_mat,
                                                          const float* __restrict__ theta_vec, int64_t mat_len,
                                                          int64_t vec_len, int64_t mat_off, int64_t vec_off, int O, int W,
-                                                         int M, RowMap rm, T* __restrict__ H,
+                                                         int M, int Mp, RowMap rm, T* __restrict__ H,
                                                          typename GradT<T>::type* __restrict__ G) {
     extern __shared__ __align__(16) float fn_lds[];
     const int WP = W + 4;  // pitch of a row of W0^T: keeps 16-byte alignment, shifts the banks from row to row
@@ -1930,11 +1938,11 @@ __global__ __launch_bounds__(256) void k_first_fwd_narrow(const float* __restric
 #pragma unroll
         for (int t = 0; t < TURNS; ++t) {
             const int r = r0 + slot + t * RPT, m = m0 + r;
-            if (r < FN_ROWS && m < M) {
+            if (r < FN_ROWS && m < Mp) {
                 float g[8];
 #pragma unroll
                 for (int u = 0; u < 8; ++u) act_pair<T, ACT>(acc[t][u], acc[t][u], g[u]);
-                const int64_t at = ((int64_t)p * M + m) * W + 8 * chunk;
+                const int64_t at = ((int64_t)p * Mp + m) * W + 8 * chunk;
                 put8(H + at, pack8(acc[t], (const T*)nullptr));
                 if (SAVE) put8(G + at, pack8(g, (const typename GradT<T>::type*)nullptr));
             }
@@ -1968,7 +1976,7 @@ __global__ __launch_bounds__(256) void k_gather_x_pad(const float* __restrict__ 
 
 template <typename T, int JB>
 __global__ __launch_bounds__(256) void k_first_bwd_dw(const float* __restrict__ xz, const T* __restrict__ dZ,
-                                                     float* __restrict__ pw, int W, int M, int n_split) {
+                                                     float* __restrict__ pw, int W, int M, int Mp, int n_split) {
     constexpr int VE = Elems<T>::VE;
     constexpr int HP = 128 + VE;
     constexpr int CPR = 128 / VE;
@@ -1997,7 +2005,7 @@ __global__ __launch_bounds__(256) void k_first_bwd_dw(const float* __restrict__ 
             const int idx = threadIdx.x + 256 * q, mm = idx / CPR, cc = (idx % CPR) * VE;
             uint4 u = make_uint4(0, 0, 0, 0);
             if (m0 + mm < m_hi && i0 + cc < W)
-                u = *reinterpret_cast<const uint4*>(dZ + ((int64_t)p * M + m0 + mm) * W + i0 + cc);
+                u = *reinterpret_cast<const uint4*>(dZ + ((int64_t)p * Mp + m0 + mm) * W + i0 + cc);
             nxt[q] = u;
         }
     };
@@ -2125,50 +2133,66 @@ __global__ void k_copy_dlogsig(const float* __restrict__ dlogsig, float* __restr
 }
 
 // Rows of the fp32 observation tensor picked by the row map, rounded to the GEMM input type, as compact
-// [P][M][O] rows (O a multiple of 8): the first layer's GEMMs then run on the direct-to-LDS kernels.
+// [P][Mp][ldx] rows (ldx a multiple of 8): zeros beyond O, copies of row M - 1 beyond M.
 template <typename T>
-__global__ __launch_bounds__(256) void k_gather_x(const float* __restrict__ x, T* __restrict__ xc, int O, int M,
-                                                 RowMap rm) {
+__global__ __launch_bounds__(256) void k_gather_x(const float* __restrict__ x, T* __restrict__ xc, int O, int ldx, int M,
+                                                 int Mp, RowMap rm) {
     const int p = blockIdx.y;
     const int64_t idx = (int64_t)blockIdx.x * 256 + threadIdx.x;  // one 8-element piece
-    const int per_row = O / 8;
-    if (idx >= (int64_t)M * per_row) return;
+    const int per_row = ldx / 8;
+    if (idx >= (int64_t)Mp * per_row) return;
     const int m = (int)(idx / per_row), c = (int)(idx % per_row) * 8;
-    const float* src = x + rm.row(p, m) * O + c;
+    const float* src = x + rm.row(p, m < M ? m : M - 1) * O + c;
     float v[8];
-    get8(src, v);
-    store8(xc + ((int64_t)p * M + m) * O + c, v);
+    if ((O & 7) == 0) {
+        get8(src, v);
+    } else {
+#pragma unroll
+        for (int e = 0; e < 8; ++e) v[e] = c + e < O ? src[e] : 0.f;
+    }
+    store8(xc + ((int64_t)p * Mp + m) * ldx + c, v);
 }
 
 // ---- host side ---------------------------------------------------------------------------------
 static int64_t esize(const morlax_ctx* c) { return c->d.wdtype == 1 ? 2 : 4; }
+// Rows per preference of the compact buffers (h, act', dZ, observations): whole contraction steps of the dW products.
+// Rows M .. Mp hold copies of row M - 1 where the forward pass writes and zeros in dZ.  (With Mp = M, a selection that was
+// no multiple of 32 rows took the register-staged GEMM with a masked tail: 41 us against 18 us per launch at 24
+// preferences x 1250 rows x 256 x 256 in bf16, both unsplit; where the first layer's operand was read through the row map
+// element by element, 334 us.)
+static int pad_rows(const RowSel& rs) { return (rs.M + 31) / 32 * 32; }
 static int64_t act_elems(const morlax_ctx* c, const RowSel& rs) {
-    return align_up((int64_t)c->d.P * rs.M * c->d.width, 64);
+    return align_up((int64_t)c->d.P * pad_rows(rs) * c->d.width, 64);
 }
 
+static int x0_ld(const morlax_ctx* c) { return (c->d.obs_dim + 7) / 8 * 8; }
 static int64_t x0_elems(const morlax_ctx* c, const RowSel& rs) {
-    return align_up((int64_t)c->d.P * rs.M * c->d.obs_dim, 64);
+    return align_up((int64_t)c->d.P * pad_rows(rs) * x0_ld(c), 64);
 }
-// compact first-layer input: bf16 networks whose observation width suits the direct-to-LDS GEMMs
+// layer-by-layer forward from the compact first-layer input: bf16 networks whose observation width suits the
+// direct-to-LDS GEMMs
 static bool use_x0(const morlax_ctx* c) { return c->d.wdtype == 1 && c->d.obs_dim % 32 == 0; }
+// the first layer's dW as a streaming split-K kernel: narrow observations and too few GEMM tiles to fill the chip; any
+// other first layer's dW is a grouped GEMM on the compact observations the forward pass saved
+static bool first_skinny(const morlax_ctx* c) {
+    return c->d.obs_dim <= 32 && ((c->d.width + 127) / 128) * c->d.P < 256;
+}
 // saved: per hidden layer h and act', then the head's output rows, then (when used) the gathered observations
+static int64_t saved_x0_off(const morlax_ctx* c, const RowSel& rs) {
+    return 2 * (int64_t)c->d.n_hidden * act_elems(c, rs) * esize(c) + align_up((int64_t)c->d.P * rs.M * OUT_PITCH * 4, 256);
+}
 int64_t mlp_saved_bytes(const morlax_ctx* c, int net, const RowSel& rs) {
     (void)net;
-    return 2 * (int64_t)c->d.n_hidden * act_elems(c, rs) * esize(c) +
-           align_up((int64_t)c->d.P * rs.M * OUT_PITCH * 4, 256) + (use_x0(c) ? x0_elems(c, rs) * esize(c) : 0);
+    return saved_x0_off(c, rs) + (first_skinny(c) ? 0 : x0_elems(c, rs) * esize(c));
 }
 // fp32 scratch behind the two activation buffers: [0, head_lo): partial column sums of dZ, or the output
 // layer's dW partials followed by its bias partials; [head_lo, ..): the compact dz rows of the output layer
 // (still read while the column sums of the layer below are written).
 static int64_t head_pw_elems(const morlax_ctx* c) { return (int64_t)c->d.P * HB_SPLIT * MORLAX_MAX_OUT * c->d.width; }
 static int64_t head_lo_elems(const morlax_ctx* c, const RowSel& rs) {
-    const int64_t colsum = (int64_t)c->d.P * ((rs.M + 63) / 64) * c->d.width;
+    const int64_t colsum = (int64_t)c->d.P * ((pad_rows(rs) + 63) / 64) * c->d.width;
     const int64_t head = head_pw_elems(c) + (int64_t)c->d.P * ((rs.M + 255) / 256) * MORLAX_MAX_OUT;
     return align_up(colsum > head ? colsum : head, 64);
-}
-// the first layer's dW as a streaming split-K kernel: narrow observations and too few GEMM tiles to fill the chip
-static bool first_skinny(const morlax_ctx* c) {
-    return c->d.obs_dim <= 32 && ((c->d.width + 127) / 128) * c->d.P < 256;
 }
 static int first_split(const morlax_ctx* c, const RowSel& rs) {
     const int tiles = ((c->d.width + 127) / 128) * c->d.P;
@@ -2183,20 +2207,30 @@ static int64_t first_skinny_elems(const morlax_ctx* c, const RowSel& rs) {  // p
     const int OP = c->d.obs_dim <= 16 ? 16 : 32;
     return align_up((int64_t)c->d.P * rs.M * OP, 64) + align_up((int64_t)c->d.P * first_split(c, rs) * OP * c->d.width, 64);
 }
-// ranges the contraction of a hidden layer's dW is cut into (1 = the plain grouped GEMM)
-static int dw_split(const morlax_ctx* c, const RowSel& rs) {
-    const int t = (c->d.width + 127) / 128, tiles = t * t * c->d.P;
+// Ranges the contraction of a layer's dW is cut into (1 = the plain grouped GEMM), until there are DW_SPLIT_TARGET
+// workgroups (1024 measured slower: twice the partials).  fp32: ranges of 256 rows and more, of 64 while the workgroups
+// reach less than a quarter of the CUs (4 preferences x 256 rows x 64 x 64: 22.7 us unsplit, 12 us with the merge).
+// bf16, whose steps are eight times shorter: only into equal whole ranges (23 preferences x 1120 rows x 512 x 512 in two
+// ranges cost 4 % of the update step), and the first layer, whose few columns make few tiles, into ranges of 2048 rows
+// and more.  Such a selection's bf16 gradients thereby do not depend on the split, whose last bits Adam would carry on
+// through the rounding of theta.  The room for the partials is sized for the most ranges any smaller selection takes.
+static int dw_split(const morlax_ctx* c, int M, int layer, bool room) {
+    const bool bf = c->d.wdtype == 1;
+    const int d_in = layer == 0 ? c->d.obs_dim : c->d.width;
+    const int64_t tiles = (int64_t)((c->d.width + 127) / 128) * ((d_in + 127) / 128) * c->d.P;
     int S = 1;
-    while (S < 16 && tiles * S < DW_SPLIT_TARGET && rs.M % (2 * S * 64) == 0 && rs.M / (2 * S) >= 256) S *= 2;
+    while (S < 16 && tiles * S < DW_SPLIT_TARGET) {
+        const int rows = bf ? (layer == 0 ? 2048 : 256) : (tiles * S < 64 ? 64 : 256);
+        if (M / (2 * S) < rows || (bf && layer > 0 && !room && M % (2 * S * 64))) break;
+        S *= 2;
+    }
     return S;
 }
-// room for the partial matrices: sized by the most ranges any selection of at most this many rows can be cut
-// into, so that the workspace of a selection also serves every smaller one
+static int dw_range(const RowSel& rs, int S) { return (int)align_up((pad_rows(rs) + S - 1) / S, 64); }
 static int64_t dw_split_elems(const morlax_ctx* c, const RowSel& rs) {
-    const int t = (c->d.width + 127) / 128, tiles = t * t * c->d.P;
-    int S = 1;
-    while (S < 16 && tiles * S < DW_SPLIT_TARGET && rs.M / (2 * S) >= 256) S *= 2;
-    return S > 1 ? align_up((int64_t)c->d.P * S * c->d.width * c->d.width, 64) : 0;
+    const int W = c->d.width, O = c->d.obs_dim, Sh = dw_split(c, rs.M, 1, true), S0 = dw_split(c, rs.M, 0, true);
+    const int64_t h = Sh > 1 ? (int64_t)Sh * W * W : 0, f = S0 > 1 ? (int64_t)S0 * W * O : 0;
+    return align_up((int64_t)c->d.P * (h > f ? h : f), 64);
 }
 static int64_t part_elems(const morlax_ctx* c, const RowSel& rs) {
     return head_lo_elems(c, rs) + align_up((int64_t)c->d.P * rs.M * MORLAX_MAX_OUT, 64) + first_skinny_elems(c, rs) +
@@ -2332,7 +2366,7 @@ static void run_mlp_fwd(const morlax_ctx* c, FwdArgs& a, int n_nets, int rt, boo
         n_tiles = 0;
         for (int i = 0; i < n_nets; ++i) {
             a.net[i].tile0 = n_tiles;
-            a.net[i].tiles_m = (a.net[i].M + 16 * r - 1) / (16 * r);
+            a.net[i].tiles_m = ((save ? a.Mp : a.net[i].M) + 16 * r - 1) / (16 * r);
             n_tiles += a.net[i].tiles_m * P;
         }
         if (n_nets == 1) a.net[1].tile0 = 0x7fffffff;
@@ -2357,9 +2391,11 @@ static void policy_fwd_t(const morlax_ctx* c, int net, const T* theta_mat, const
                          void* ws, hipStream_t s) {
     const NetDev& nd = c->net[net];
     const int P = c->d.P, W = c->d.width, M = rs.M, L = c->d.n_hidden, O = c->d.obs_dim;
+    const int Mp = pad_rows(rs);
     const int64_t ae = act_elems(c, rs);
     const RowMap rm = make_rowmap(c, rs);
     T* sv = reinterpret_cast<T*>(saved);
+    T* sv_x0 = (sv && !first_skinny(c)) ? reinterpret_cast<T*>(reinterpret_cast<char*>(sv) + saved_x0_off(c, rs)) : nullptr;
     T* wsT = reinterpret_cast<T*>(ws);
     auto Hbuf = [&](int l) { return sv ? sv + (int64_t)(2 * l) * ae : wsT + (int64_t)(l & 1) * ae; };
     typedef typename GradT<T>::type GT;
@@ -2376,18 +2412,19 @@ static void policy_fwd_t(const morlax_ctx* c, int net, const T* theta_mat, const
         ep.G = Gbuf(l);
         ep.ld = W;
         ep.part = nullptr;
+        T* x0 = sv_x0;
+        if (l == 0 && !x0 && use_x0(c)) x0 = reinterpret_cast<T*>(reinterpret_cast<float*>(wsT + 2 * ae) + part_elems(c, rs));
+        if (l == 0 && x0) {
+            const int64_t pieces = (int64_t)Mp * (x0_ld(c) / 8);
+            k_gather_x<T><<<dim3((unsigned)((pieces + 255) / 256), P), 256, 0, s>>>(x, x0, O, x0_ld(c), M, Mp, rm);
+        }
         if (l == 0 && use_x0(c)) {
             if constexpr (std::is_same<T, bf16_t>::value) {
-                T* x0 = sv ? reinterpret_cast<T*>(reinterpret_cast<char*>(sv) + (int64_t)2 * L * ae * sizeof(T) +
-                                                  align_up((int64_t)P * M * OUT_PITCH * 4, 256))
-                           : reinterpret_cast<T*>(reinterpret_cast<float*>(wsT + 2 * ae) + part_elems(c, rs));
-                const int64_t pieces = (int64_t)M * (O / 8);
-                k_gather_x<T><<<dim3((unsigned)((pieces + 255) / 256), P), 256, 0, s>>>(x, x0, O, M, rm);
                 GemmArgs<T, SRC_KCONTIG, SRC_KCONTIG, EpiFwd<T, ACT, SAVE>, true, GEMM_NCH> g;
-                g.a.base = x0; g.a.ld = O; g.a.rows = M; g.a.kdim = O; g.a.rm = rm;
+                g.a.base = x0; g.a.ld = O; g.a.rows = Mp; g.a.kdim = O; g.a.rm = rm;
                 g.b.base = theta_mat + Ld.mat_off; g.b.ld = O; g.b.rows = W; g.b.kdim = O; g.b.rm = rm;
-                g.a_pstride = (int64_t)M * O; g.b_pstride = nd.mat_len;
-                g.epi = ep; g.e0_pstride = nd.vec_len; g.e1_pstride = (int64_t)M * W; g.e2_pstride = 0;
+                g.a_pstride = (int64_t)Mp * O; g.b_pstride = nd.mat_len;
+                g.epi = ep; g.e0_pstride = nd.vec_len; g.e1_pstride = (int64_t)Mp * W; g.e2_pstride = 0;
                 run_gemm(c, 0, g, P, s);
             }
         } else if (l == 0 && first_fwd_narrow_ok(c)) {
@@ -2400,8 +2437,8 @@ static void policy_fwd_t(const morlax_ctx* c, int net, const T* theta_mat, const
             }
             GemmProf::Rec* r = prof_take(c, 0, 2.0 * M * (double)W * O * P);
             if (r) (void)hipEventRecord(r->a, s);
-            k_first_fwd_narrow<T, ACT, SAVE><<<dim3((M + FN_ROWS - 1) / FN_ROWS, P), 256, lds, s>>>(
-                x, theta_mat, theta_vec, nd.mat_len, nd.vec_len, Ld.mat_off, Ld.vec_off, O, W, M, rm, Hbuf(0), Gbuf(0));
+            k_first_fwd_narrow<T, ACT, SAVE><<<dim3((Mp + FN_ROWS - 1) / FN_ROWS, P), 256, lds, s>>>(
+                x, theta_mat, theta_vec, nd.mat_len, nd.vec_len, Ld.mat_off, Ld.vec_off, O, W, M, Mp, rm, Hbuf(0), Gbuf(0));
             if (r) (void)hipEventRecord(r->b, s);
         } else if (l == 0) {
             auto launch = [&](auto fast) {
@@ -2410,28 +2447,26 @@ static void policy_fwd_t(const morlax_ctx* c, int net, const T* theta_mat, const
                 g.a.base = x; g.a.ld = O; g.a.rows = M; g.a.kdim = O; g.a.rm = rm;
                 g.b.base = theta_mat + Ld.mat_off; g.b.ld = O; g.b.rows = W; g.b.kdim = O; g.b.rm = rm;
                 g.a_pstride = 0; g.b_pstride = nd.mat_len;
-                g.epi = ep; g.e0_pstride = nd.vec_len; g.e1_pstride = (int64_t)M * W; g.e2_pstride = 0;
+                g.epi = ep; g.e0_pstride = nd.vec_len; g.e1_pstride = (int64_t)Mp * W; g.e2_pstride = 0;
+                g.crows = Mp;
                 run_gemm(c, 0, g, P, s);
             };
             if (O % VE == 0) launch(std::true_type{}); else launch(std::false_type{});
         } else {
             GemmArgs<T, SRC_KCONTIG, SRC_KCONTIG, EpiFwd<T, ACT, SAVE>, true, GEMM_NCH> g;
-            g.a.base = Hbuf(l - 1); g.a.ld = W; g.a.rows = M; g.a.kdim = W; g.a.rm = rm;
+            g.a.base = Hbuf(l - 1); g.a.ld = W; g.a.rows = Mp; g.a.kdim = W; g.a.rm = rm;
             g.b.base = theta_mat + Ld.mat_off; g.b.ld = W; g.b.rows = W; g.b.kdim = W; g.b.rm = rm;
-            g.a_pstride = (int64_t)M * W; g.b_pstride = nd.mat_len;
-            g.epi = ep; g.e0_pstride = nd.vec_len; g.e1_pstride = (int64_t)M * W; g.e2_pstride = 0;
+            g.a_pstride = (int64_t)Mp * W; g.b_pstride = nd.mat_len;
+            g.epi = ep; g.e0_pstride = nd.vec_len; g.e1_pstride = (int64_t)Mp * W; g.e2_pstride = 0;
             run_gemm(c, 1, g, P, s);
         }
     };
     const int rt = fwd_row_tiles(c, nd, theta_mat, M);
     if (rt > 0) {
         FwdArgs a;
-        char* x0 = (sv && use_x0(c)) ? reinterpret_cast<char*>(sv) + (int64_t)2 * L * ae * sizeof(T) +
-                                           align_up((int64_t)P * M * OUT_PITCH * 4, 256)
-                                     : nullptr;
         fill_fwd_net(c, net, theta_mat, theta_vec, rs, out, saved_out, eps, act, logp, reinterpret_cast<char*>(sv),
-                     reinterpret_cast<char*>(sv ? sv + ae : nullptr), x0, a.net[0]);
-        a.x = x; a.Mp = M; a.ldh = W; a.ldx = O; a.lstride = 2 * ae * (int64_t)sizeof(T);
+                     reinterpret_cast<char*>(sv ? sv + ae : nullptr), reinterpret_cast<char*>(sv_x0), a.net[0]);
+        a.x = x; a.Mp = Mp; a.ldh = W; a.ldx = x0_ld(c); a.lstride = 2 * ae * (int64_t)sizeof(T);
         run_mlp_fwd(c, a, 1, rt, sv != nullptr, s);
         return;
     }
@@ -2440,9 +2475,7 @@ static void policy_fwd_t(const morlax_ctx* c, int net, const T* theta_mat, const
         if (fused_fwd_ok(c, nd, theta_mat)) {
             FusedFwdArgs a;
             a.x = x;
-            a.x0 = (sv && use_x0(c)) ? reinterpret_cast<T*>(reinterpret_cast<char*>(sv) + (int64_t)2 * L * ae * sizeof(T) +
-                                                            align_up((int64_t)P * M * OUT_PITCH * 4, 256))
-                                     : nullptr;
+            a.x0 = sv_x0; a.ldx = x0_ld(c); a.Mp = Mp;
             a.theta_mat = theta_mat; a.theta_vec = theta_vec;
             a.Opad = (O + 63) & ~63;
             a.frag_len = fused_frag_len(c, net);
@@ -2469,7 +2502,7 @@ static void policy_fwd_t(const morlax_ctx* c, int net, const T* theta_mat, const
             a.G = sv ? reinterpret_cast<gfix16_t*>(sv + ae) : nullptr;
             a.lstride = 2 * ae;
             a.L = L; a.O = O; a.M = M;
-            a.tiles_m = (M + FF_ROWS - 1) / FF_ROWS;
+            a.tiles_m = (M + FF_ROWS - 1) / FF_ROWS;  // (128: covers Mp as well)
             a.n_tiles = a.tiles_m * P;
             const LayerDev& Lo = nd.layer[L];
             a.head_mat_off = Lo.mat_off; a.head_vec_off = Lo.vec_off; a.logsig_off = Lo.vec_off + Lo.d_out;
@@ -2501,7 +2534,7 @@ static void policy_fwd_t(const morlax_ctx* c, int net, const T* theta_mat, const
     const int tanh_cols = (net == MORLAX_ACTOR && c->d.mean_tanh) ? c->d.act_dim : 0;
     const dim3 grid((M + 63) / 64, P);
     k_head_fwd<T><<<grid, 256, 0, s>>>(Hbuf(L - 1), theta_mat, theta_vec, nd.mat_len, nd.vec_len, Lh.mat_off,
-                                       Lh.vec_off, W, nd.out_dim, M, rm, tanh_cols, out, saved_out, eps, act, logp,
+                                       Lh.vec_off, W, nd.out_dim, M, Mp, rm, tanh_cols, out, saved_out, eps, act, logp,
                                        Lh.vec_off + Lh.d_out, c->d.act_dim,
                                        (net == MORLAX_ACTOR && c->d.sigma_state) ? 1 : 0);
 }
@@ -2513,6 +2546,7 @@ static void policy_bwd_t(const morlax_ctx* c, int net, const T* theta_mat, const
     (void)theta_vec;
     const NetDev& nd = c->net[net];
     const int P = c->d.P, W = c->d.width, M = rs.M, L = c->d.n_hidden, O = c->d.obs_dim;
+    const int Mp = pad_rows(rs);
     const int64_t ae = act_elems(c, rs);
     const RowMap rm = make_rowmap(c, rs);
     const T* sv = reinterpret_cast<const T*>(saved);
@@ -2522,10 +2556,9 @@ static void policy_bwd_t(const morlax_ctx* c, int net, const T* theta_mat, const
     auto Gbuf = [&](int l) { return reinterpret_cast<const GT*>(sv + (int64_t)(2 * l + 1) * ae); };
     auto dZbuf = [&](int l) { return wsT + (int64_t)(l & 1) * ae; };
     float* part = reinterpret_cast<float*>(wsT + 2 * ae);
-    int n_part = (M + 63) / 64;  // row blocks of whichever kernel produced the current dZ
+    int n_part = (Mp + 63) / 64;  // row blocks of whichever kernel produced the current dZ
     const float* saved_out = reinterpret_cast<const float*>(sv + (int64_t)2 * L * ae);
     const int tanh_cols = (net == MORLAX_ACTOR && c->d.mean_tanh) ? c->d.act_dim : 0;
-    constexpr int VE = Elems<T>::VE;
     const LayerDev& Lh = nd.layer[L];
     // output layer
     {
@@ -2534,46 +2567,48 @@ static void policy_bwd_t(const morlax_ctx* c, int net, const T* theta_mat, const
         float* pb = part + head_pw_elems(c);
         float* dzh = part + head_lo_elems(c, rs);
         k_head_dzh<T><<<dim3(n_chunk_b, P), 256, 0, s>>>(dout, saved_out, dzh, pb, nd.out_dim, M, rm, tanh_cols);
-        k_head_bwd_dw<T><<<dim3((W + 127) / 128, HB_SPLIT, P), 256, 0, s>>>(dzh, Hbuf(L - 1), pw, W, M);
+        k_head_bwd_dw<T><<<dim3((W + 127) / 128, HB_SPLIT, P), 256, 0, s>>>(dzh, Hbuf(L - 1), pw, W, M, Mp);
         k_head_bwd_dw_final<<<dim3((nd.out_dim * W + 255) / 256, P), 256, 0, s>>>(
             pw, pb, HB_SPLIT, n_chunk_b, dtheta_mat, dtheta_vec, nd.mat_len, nd.vec_len, Lh.mat_off, Lh.vec_off, W,
             nd.out_dim);
-        k_head_bwd_dz<T><<<dim3((W + 127) / 128, (M + 63) / 64, P), 256, 0, s>>>(
-            dzh, theta_mat, nd.mat_len, Lh.mat_off, Gbuf(L - 1), dZbuf(L - 1), part, W, nd.out_dim, M);
+        k_head_bwd_dz<T><<<dim3((W + 127) / 128, (Mp + 63) / 64, P), 256, 0, s>>>(
+            dzh, theta_mat, nd.mat_len, Lh.mat_off, Gbuf(L - 1), dZbuf(L - 1), part, W, nd.out_dim, M, Mp);
     }
     for (int l = L - 1; l >= 0; --l) {
         const LayerDev& Ld = nd.layer[l];
         k_colsum_final<<<dim3((W + 31) / 32, P), 256, 0, s>>>(part, n_part, dtheta_vec, nd.vec_len, Ld.vec_off, W);
-        EpiDw ew;
-        ew.dW = dtheta_mat + Ld.mat_off;
-        ew.ld = Ld.d_in;
-        if (l > 0) {
+        // dW_l = dZ_l^T in: `in` the layer's compact input, [P][Mp][ld]
+        auto weight_grad = [&](int kind, const T* in, int ld) {
             GemmArgs<T, SRC_KSTRIDED, SRC_KSTRIDED, EpiDw, true, GEMM_NCH> g;
-            g.a.base = dZbuf(l); g.a.ld = W; g.a.rows = W; g.a.kdim = M; g.a.rm = rm;
-            g.b.base = Hbuf(l - 1); g.b.ld = W; g.b.rows = W; g.b.kdim = M; g.b.rm = rm;
-            g.a_pstride = (int64_t)M * W; g.b_pstride = (int64_t)M * W;
-            g.epi = ew; g.e0_pstride = nd.mat_len; g.e1_pstride = 0; g.e2_pstride = 0;
-            const int S = dw_split(c, rs);
-            if (S > 1) {
-                float* pws = part + head_lo_elems(c, rs) + align_up((int64_t)P * M * MORLAX_MAX_OUT, 64) +
-                             first_skinny_elems(c, rs);
-                const int64_t WW = (int64_t)W * W;
-                g.a.kdim = g.b.kdim = M / S;
-                g.a_pstride = g.b_pstride = (int64_t)(M / S) * W;
-                g.epi.dW = pws; g.epi.ld = W; g.e0_pstride = WW;
-                run_gemm(c, 3, g, P * S, s);
-                k_dw_split_final<<<dim3((unsigned)((WW / 4 + 255) / 256), P), 256, 0, s>>>(pws, S, WW, dtheta_mat, nd.mat_len,
-                                                                                        Ld.mat_off);
-                prof_extend(c, s);
-            } else {
-                run_gemm(c, 3, g, P, s);
+            g.a.base = dZbuf(l); g.a.ld = W; g.a.rows = W; g.a.kdim = Mp; g.a.rm = rm;
+            g.b.base = in; g.b.ld = ld; g.b.rows = ld; g.b.kdim = Mp; g.b.rm = rm;
+            g.a_pstride = (int64_t)Mp * W; g.b_pstride = (int64_t)Mp * ld;
+            g.ccols = Ld.d_in;
+            g.epi.dW = dtheta_mat + Ld.mat_off; g.epi.ld = Ld.d_in; g.epi.part = nullptr;
+            g.e0_pstride = nd.mat_len; g.e1_pstride = 0; g.e2_pstride = 0;
+            const int S = dw_split(c, M, l, false);
+            if (S == 1) {
+                run_gemm(c, kind, g, P, s);
+                return;
             }
+            float* pws = part + head_lo_elems(c, rs) + align_up((int64_t)P * M * MORLAX_MAX_OUT, 64) + first_skinny_elems(c, rs);
+            const int64_t n = (int64_t)W * Ld.d_in;
+            g.range = dw_range(rs, S);
+            g.ranges = (Mp + g.range - 1) / g.range;
+            g.epi.dW = pws; g.e0_pstride = n;
+            run_gemm(c, kind, g, P * g.ranges, s);
+            k_dw_split_final<<<dim3((unsigned)((n / 4 + 255) / 256), P), 256, 0, s>>>(pws, g.ranges, n, dtheta_mat, nd.mat_len,
+                                                                                    Ld.mat_off);
+            prof_extend(c, s);
+        };
+        if (l > 0) {
+            weight_grad(3, Hbuf(l - 1), W);
             GemmArgs<T, SRC_KCONTIG, SRC_KSTRIDED, EpiDx<T>, true, GEMM_NCH> h;
-            h.a.base = dZbuf(l); h.a.ld = W; h.a.rows = M; h.a.kdim = W; h.a.rm = rm;
+            h.a.base = dZbuf(l); h.a.ld = W; h.a.rows = Mp; h.a.kdim = W; h.a.rm = rm;
             h.b.base = theta_mat + Ld.mat_off; h.b.ld = W; h.b.rows = W; h.b.kdim = W; h.b.rm = rm;
-            h.a_pstride = (int64_t)M * W; h.b_pstride = nd.mat_len;
+            h.a_pstride = (int64_t)Mp * W; h.b_pstride = nd.mat_len;
             h.epi.G = Gbuf(l - 1); h.epi.dZ = dZbuf(l - 1); h.epi.ld = W; h.epi.part = part;
-            h.e0_pstride = (int64_t)M * W; h.e1_pstride = 0; h.e2_pstride = 0;
+            h.e0_pstride = (int64_t)Mp * W; h.e1_pstride = 0; h.e2_pstride = 0;
             run_gemm(c, 2, h, P, s);
             n_part = h.tiles_m;  // row tiles of the kernel that ran (128 or 256 rows)
         } else if (first_skinny(c)) {
@@ -2585,36 +2620,14 @@ static void policy_bwd_t(const morlax_ctx* c, int net, const T* theta_mat, const
             if (r) (void)hipEventRecord(r->a, s);
             k_gather_x_pad<T><<<dim3((unsigned)((n + 255) / 256), P), 256, 0, s>>>(x, xz, O, OP, M, rm);
             const dim3 grid((W + 127) / 128, ns, P);
-            if (OP == 16) k_first_bwd_dw<T, 1><<<grid, 256, 0, s>>>(xz, dZbuf(0), pw1, W, M, ns);
-            else k_first_bwd_dw<T, 2><<<grid, 256, 0, s>>>(xz, dZbuf(0), pw1, W, M, ns);
+            if (OP == 16) k_first_bwd_dw<T, 1><<<grid, 256, 0, s>>>(xz, dZbuf(0), pw1, W, M, Mp, ns);
+            else k_first_bwd_dw<T, 2><<<grid, 256, 0, s>>>(xz, dZbuf(0), pw1, W, M, Mp, ns);
             k_first_dw_final<<<dim3((W * O + 255) / 256, P), 256, 0, s>>>(pw1, ns, OP, dtheta_mat, nd.mat_len, Ld.mat_off, W, O);
             if (r) (void)hipEventRecord(r->b, s);
-        } else if (use_x0(c)) {
-            if constexpr (std::is_same<T, bf16_t>::value) {
-                // the rows gathered by the forward pass
-                const T* x0 = reinterpret_cast<const T*>(reinterpret_cast<const char*>(sv) + (int64_t)2 * L * ae * sizeof(T) +
-                                                         align_up((int64_t)P * M * OUT_PITCH * 4, 256));
-                GemmArgs<T, SRC_KSTRIDED, SRC_KSTRIDED, EpiDw, true, GEMM_NCH> g;
-                g.a.base = dZbuf(0); g.a.ld = W; g.a.rows = W; g.a.kdim = M; g.a.rm = rm;
-                g.b.base = x0; g.b.ld = O; g.b.rows = O; g.b.kdim = M; g.b.rm = rm;
-                g.a_pstride = (int64_t)M * W; g.b_pstride = (int64_t)M * O;
-                g.epi = ew; g.e0_pstride = nd.mat_len; g.e1_pstride = 0; g.e2_pstride = 0;
-                run_gemm(c, 4, g, P, s);
-            }
         } else {
-            auto launch = [&](auto fast) {
-                constexpr bool F = decltype(fast)::value;
-                GemmArgs<T, SRC_KSTRIDED, SRC_X_KSTRIDED, EpiDw, F, GEMM_NCH> g;
-                g.a.base = dZbuf(0); g.a.ld = W; g.a.rows = W; g.a.kdim = M; g.a.rm = rm;
-                g.b.base = x; g.b.ld = O; g.b.rows = O; g.b.kdim = M; g.b.rm = rm;
-                g.a_pstride = (int64_t)M * W; g.b_pstride = 0;
-                g.epi = ew; g.e0_pstride = nd.mat_len; g.e1_pstride = 0; g.e2_pstride = 0;
-                run_gemm(c, 4, g, P, s);
-            };
-            if (rs.j_cnt % VE == 0) launch(std::true_type{}); else launch(std::false_type{});
+            weight_grad(4, reinterpret_cast<const T*>(reinterpret_cast<const char*>(sv) + saved_x0_off(c, rs)), x0_ld(c));
         }
     }
-    (void)VE;
     if (net == MORLAX_ACTOR && !c->d.sigma_state) {  // (a state-dependent log sigma is part of dout)
         const int n = P * c->d.act_dim;
         k_copy_dlogsig<<<(n + 255) / 256, 256, 0, s>>>(dlogsig, dtheta_vec, nd.vec_len, Lh.vec_off + Lh.d_out, P,
