@@ -276,16 +276,41 @@ void launch_hypernet_fwd(const morlax_ctx* c, int net, const float* hparams, con
 // ------------------------------------------------------------------------------------------------
 // Backward.
 
-// dW0_l = sum_p dW_l(p): four consecutive elements per thread, p ascending.
+// Offset inside hparams of every row of the stacked affine matrix (built once per call).
+__device__ inline void mrow_entry(const AffineTable& at, int32_t* __restrict__ mrow, int F, int q) {
+    if (q >= at.q_total) return;
+    const int s = find_seg(at, q);
+    mrow[q] = (int32_t)(at.hp_m[s] + (int64_t)(q - at.q0[s]) * F);
+}
+__global__ __launch_bounds__(256) void k_hyper_mrow(AffineTable at, int32_t* __restrict__ mrow, int F) {
+    mrow_entry(at, mrow, F, blockIdx.x * 256 + threadIdx.x);
+}
+
+// dW0_l = sum_p dW_l(p): four consecutive elements per thread, p ascending.  The blocks behind the first n_base make
+// the row offsets of the stacked affine matrix, which would otherwise take a launch of 5 us on the dependent chain.
 __global__ __launch_bounds__(256) void k_hyper_dbase(NetDev nd, const float* __restrict__ dmat,
-                                                    float* __restrict__ dhp, int P) {
+                                                    float* __restrict__ dhp, int P, int n_base, AffineTable at,
+                                                    int32_t* __restrict__ mrow, int F) {
+    if ((int)blockIdx.x >= n_base) {
+        mrow_entry(at, mrow, F, ((int)blockIdx.x - n_base) * 256 + threadIdx.x);
+        return;
+    }
     const int64_t e = ((int64_t)blockIdx.x * 256 + threadIdx.x) * 4;
     if (e >= nd.mat_len) return;
     int l = 0;
     while (l + 1 < nd.n_layers && e >= nd.layer[l + 1].mat_off) ++l;
     float4 a = make_float4(0.f, 0.f, 0.f, 0.f);
-    for (int p = 0; p < P; ++p) {
-        const float4 v = *reinterpret_cast<const float4*>(dmat + (int64_t)p * nd.mat_len + e);
+    const float* src = dmat + e;
+    int p = 0;
+    for (; p + 8 <= P; p += 8) {  // eight preferences' loads in flight together
+        float4 v[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) v[u] = *reinterpret_cast<const float4*>(src + (int64_t)(p + u) * nd.mat_len);
+#pragma unroll
+        for (int u = 0; u < 8; ++u) { a.x += v[u].x; a.y += v[u].y; a.z += v[u].z; a.w += v[u].w; }
+    }
+    for (; p < P; ++p) {
+        const float4 v = *reinterpret_cast<const float4*>(src + (int64_t)p * nd.mat_len);
         a.x += v.x; a.y += v.y; a.z += v.z; a.w += v.w;
     }
     float* d = dhp + nd.layer[l].hp_w0 + (e - nd.layer[l].mat_off);
@@ -508,14 +533,6 @@ __global__ __launch_bounds__(256) void k_hyper_dM(AffineTable at, const float* _
         if (j < F) mr[j] = acc[j];
 }
 
-// Offset inside hparams of every row of the stacked affine matrix (built once per call).
-__global__ __launch_bounds__(256) void k_hyper_mrow(AffineTable at, int32_t* __restrict__ mrow, int F) {
-    const int q = blockIdx.x * 256 + threadIdx.x;
-    if (q >= at.q_total) return;
-    const int s = find_seg(at, q);
-    mrow[q] = (int32_t)(at.hp_m[s] + (int64_t)(q - at.q0[s]) * F);
-}
-
 // df partials on fp32 MFMA: part[chunk, p, j] = sum over the chunk's qw stacked rows q of g[p, q] M[q, j].
 // One wave per chunk; lane (ln, kg) feeds rows p = 16 pt + ln of g and columns j = 16 jt + ln of M for the
 // contraction indices q0 + 4 kg + e, e = 0..3 (one MFMA per e).
@@ -707,115 +724,106 @@ __global__ __launch_bounds__(256) void k_hyper_dM_df(AffineTable at, const float
             }
 }
 
-// df[p, j] = sum_chunk part; dz2 = df * (1 - f^2).  64 outputs per block; the four thread groups take the
-// chunks c = g, g + 4, ... and are merged in group order.
-__global__ __launch_bounds__(256) void k_hyper_df_final(const float* __restrict__ part, int n_chunk,
-                                                       const float* __restrict__ f, float* __restrict__ dz2,
-                                                       int PF) {
+// Trunk backward, stage 1: df[p, j] = sum_chunk part; dz2 = df * (1 - f^2); dz1 = (dz2 Wh2) * (1 - h1^2).  A block
+// takes the 64 / F preferences that fit into 64 outputs, so that dz1 follows out of LDS in the launch that made dz2;
+// the four thread groups take the chunks c = g, g + 4, ... and are merged in group order.  Bound by latency (a few
+// hundred KB): what counts is launches and dependent round trips.
+__global__ __launch_bounds__(256) void k_hyper_trunk_bwd_a(const float* __restrict__ hp, const float* __restrict__ part,
+                                                          int n_chunk, const float* __restrict__ f,
+                                                          const float* __restrict__ h1, float* __restrict__ dz2,
+                                                          float* __restrict__ dz1, int P, int F, int64_t o_wh2) {
     __shared__ float red[4][64];
+    __shared__ float z2[64];
+    __shared__ float wh2[MORLAX_MAX_F * MORLAX_MAX_F];
     const int o = threadIdx.x & 63, g = threadIdx.x >> 6;
-    const int i = blockIdx.x * 64 + o;
+    const int PF = P * F, per = (64 / F) * F;
+    const int i = blockIdx.x * per + o;
+    const bool live = o < per && i < PF;
+    for (int e = threadIdx.x; e < F * F; e += 256) wh2[e] = hp[o_wh2 + e];
     float a = 0.f;
-    if (i < PF) {
+    if (live) {
         int c = g;
-        for (; c + 28 < n_chunk; c += 32) {  // eight chunks of this group per batch, loads in flight together
-            float v[8];
+        for (; c + 60 < n_chunk; c += 64) {  // sixteen chunks of this group per batch, loads in flight together
+            float v[16];
 #pragma unroll
-            for (int u = 0; u < 8; ++u) v[u] = part[(int64_t)(c + 4 * u) * PF + i];
+            for (int u = 0; u < 16; ++u) v[u] = part[(int64_t)(c + 4 * u) * PF + i];
 #pragma unroll
-            for (int u = 0; u < 8; ++u) a += v[u];
+            for (int u = 0; u < 16; ++u) a += v[u];
+        }
+        for (; c + 12 < n_chunk; c += 16) {
+            float v[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) v[u] = part[(int64_t)(c + 4 * u) * PF + i];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) a += v[u];
         }
         for (; c < n_chunk; c += 4) a += part[(int64_t)c * PF + i];
     }
     red[g][o] = a;
     __syncthreads();
-    if (g == 0 && i < PF) {
+    if (g == 0 && live) {
         const float fv = f[i];
-        dz2[i] = (red[0][o] + red[1][o] + red[2][o] + red[3][o]) * (1.f - fv * fv);
+        const float z = (red[0][o] + red[1][o] + red[2][o] + red[3][o]) * (1.f - fv * fv);
+        z2[o] = z;
+        dz2[i] = z;
+    }
+    __syncthreads();
+    if (g == 0 && live) {
+        const float* z = z2 + (o / F) * F;
+        const int k = o % F;
+        float b = 0.f;
+        for (int j = 0; j < F; ++j) b += z[j] * wh2[j * F + k];
+        const float h = h1[i];
+        dz1[i] = b * (1.f - h * h);
     }
 }
 
-// Trunk backward, stage 1: dWh2, dbh2 (sums over p ascending) and dz1 = (dz2 Wh2) * (1 - h1^2).
-// One thread per output element.
-__global__ __launch_bounds__(256) void k_hyper_trunk_bwd_a(const float* __restrict__ hp, const float* __restrict__ h1,
-                                                          const float* __restrict__ dz2, float* __restrict__ dz1,
-                                                          float* __restrict__ dhp, int P, int F, int64_t o_wh2,
-                                                          int64_t o_bh2) {
-    int idx = blockIdx.x * 256 + threadIdx.x;
-    if (idx < F * F) {
-        const int j = idx / F, i = idx % F;
-        float a = 0.f;
-        int p = 0;
-        for (; p + 8 <= P; p += 8) {
-            float x[8], y[8];
+// acc + the sum over p = p0 .. ascending of x[p * sx] * y[p * sy] (y null: of x alone), N preferences' loads in flight
+// together; p0 moves behind the last whole batch
+template <int N>
+__device__ inline float trunk_dot_batches(float acc, int& p0, const float* __restrict__ x, int sx,
+                                          const float* __restrict__ y, int sy, int P) {
+    for (; p0 + N <= P; p0 += N) {
+        float u[N], v[N];
 #pragma unroll
-            for (int u = 0; u < 8; ++u) { x[u] = dz2[(p + u) * F + j]; y[u] = h1[(p + u) * F + i]; }
-#pragma unroll
-            for (int u = 0; u < 8; ++u) a += x[u] * y[u];
+        for (int q = 0; q < N; ++q) {
+            u[q] = x[(p0 + q) * sx];
+            v[q] = y ? y[(p0 + q) * sy] : 1.f;
         }
-        for (; p < P; ++p) a += dz2[p * F + j] * h1[p * F + i];
-        dhp[o_wh2 + idx] = a;
+#pragma unroll
+        for (int q = 0; q < N; ++q) acc += u[q] * v[q];
+    }
+    return acc;
+}
+__device__ inline float trunk_dot(const float* x, int sx, const float* y, int sy, int P) {
+    int p = 0;
+    float a = trunk_dot_batches<32>(0.f, p, x, sx, y, sy, P);
+    a = trunk_dot_batches<8>(a, p, x, sx, y, sy, P);
+    return trunk_dot_batches<1>(a, p, x, sx, y, sy, P);
+}
+
+// Stage 2: dWh2, dbh2, dWh1, dbh1, one thread per output element.
+__global__ __launch_bounds__(64) void k_hyper_trunk_bwd_b(const float* __restrict__ w, const float* __restrict__ h1,
+                                                         const float* __restrict__ dz2, const float* __restrict__ dz1,
+                                                         float* __restrict__ dhp, int P, int K, int F, int64_t o_wh1,
+                                                         int64_t o_bh1, int64_t o_wh2, int64_t o_bh2) {
+    int idx = blockIdx.x * 64 + threadIdx.x;
+    if (idx < F * F) {
+        dhp[o_wh2 + idx] = trunk_dot(dz2 + idx / F, F, h1 + idx % F, F, P);
         return;
     }
     idx -= F * F;
-    if (idx < F) {
-        float a = 0.f;
-        int p = 0;
-        for (; p + 8 <= P; p += 8) {
-            float x[8];
-#pragma unroll
-            for (int u = 0; u < 8; ++u) x[u] = dz2[(p + u) * F + idx];
-#pragma unroll
-            for (int u = 0; u < 8; ++u) a += x[u];
-        }
-        for (; p < P; ++p) a += dz2[p * F + idx];
-        dhp[o_bh2 + idx] = a;
-        return;
-    }
-    idx -= F;
-    if (idx < P * F) {
-        const int p = idx / F, i = idx % F;
-        float a = 0.f;
-        for (int j = 0; j < F; ++j) a += dz2[p * F + j] * hp[o_wh2 + (int64_t)j * F + i];
-        const float h = h1[idx];
-        dz1[idx] = a * (1.f - h * h);
-    }
-}
-
-// Stage 2: dWh1, dbh1 (sums over p ascending).
-__global__ __launch_bounds__(256) void k_hyper_trunk_bwd_b(const float* __restrict__ w, const float* __restrict__ dz1,
-                                                          float* __restrict__ dhp, int P, int K, int F, int64_t o_wh1,
-                                                          int64_t o_bh1) {
-    int idx = blockIdx.x * 256 + threadIdx.x;
     if (idx < F * K) {
-        const int i = idx / K, k = idx % K;
-        float a = 0.f;
-        int p = 0;
-        for (; p + 8 <= P; p += 8) {
-            float x[8], y[8];
-#pragma unroll
-            for (int u = 0; u < 8; ++u) { x[u] = dz1[(p + u) * F + i]; y[u] = w[(p + u) * K + k]; }
-#pragma unroll
-            for (int u = 0; u < 8; ++u) a += x[u] * y[u];
-        }
-        for (; p < P; ++p) a += dz1[p * F + i] * w[p * K + k];
-        dhp[o_wh1 + idx] = a;
+        dhp[o_wh1 + idx] = trunk_dot(dz1 + idx / K, F, w + idx % K, K, P);
         return;
     }
     idx -= F * K;
     if (idx < F) {
-        float a = 0.f;
-        int p = 0;
-        for (; p + 8 <= P; p += 8) {
-            float x[8];
-#pragma unroll
-            for (int u = 0; u < 8; ++u) x[u] = dz1[(p + u) * F + idx];
-#pragma unroll
-            for (int u = 0; u < 8; ++u) a += x[u];
-        }
-        for (; p < P; ++p) a += dz1[p * F + idx];
-        dhp[o_bh1 + idx] = a;
+        dhp[o_bh2 + idx] = trunk_dot(dz2 + idx, F, nullptr, 0, P);
+        return;
     }
+    idx -= F;
+    if (idx < F) dhp[o_bh1 + idx] = trunk_dot(dz1 + idx, F, nullptr, 0, P);
 }
 
 void launch_hypernet_bwd(const morlax_ctx* c, int net, const float* hparams, const float* w,
@@ -836,7 +844,8 @@ void launch_hypernet_bwd(const morlax_ctx* c, int net, const float* hparams, con
     } else {
         // recompute f and the factors; the theta_vec rows of the affine map land in a scratch nobody reads
         if (!kept) run_trunk_and_affine(c, net, hparams, w, L, nullptr, L.vecs, s);
-        k_hyper_dbase<<<(int)((nd.mat_len / 4 + 255) / 256), 256, 0, s>>>(nd, dtheta_mat, dhparams, P);
+        const int n_base = (int)((nd.mat_len / 4 + 255) / 256);
+        k_hyper_dbase<<<n_base + (at.q_total + 255) / 256, 256, 0, s>>>(nd, dtheta_mat, dhparams, P, n_base, at, L.mrow, F);
     }
     if (r > 0) {
         DabWork wk;
@@ -856,7 +865,7 @@ void launch_hypernet_bwd(const morlax_ctx* c, int net, const float* hparams, con
         if (split)
             k_hyper_dA_merge<<<dim3((int)((nd.fac_len + 255) / 256), P), 256, 0, s>>>(nd, L.da_part, L.dfac, r, P);
     }
-    k_hyper_mrow<<<(at.q_total + 255) / 256, 256, 0, s>>>(at, L.mrow, F);
+    if (affine) k_hyper_mrow<<<(at.q_total + 255) / 256, 256, 0, s>>>(at, L.mrow, F);
     int n_chunk;
     if (P <= 128) {
         // one pass over the gradient of the stacked rows; at least four tiles per workgroup, about a thousand
@@ -883,8 +892,9 @@ void launch_hypernet_bwd(const morlax_ctx* c, int net, const float* hparams, con
             k_hyper_df_part<4><<<(n_chunk + 3) / 4, 256, 0, s>>>(hparams, L.mrow, dlead, dtheta_vec, L.df_part, P, F,
                                                                 nd.fac_len, nd.vec_len, at.q_total, n_chunk, qw);
     }
-    k_hyper_df_final<<<(P * F + 63) / 64, 256, 0, s>>>(L.df_part, n_chunk, L.f, L.dz2, P * F);
-    k_hyper_trunk_bwd_a<<<(F * F + F + P * F + 255) / 256, 256, 0, s>>>(hparams, L.h1, L.dz2, L.dz1, dhparams, P, F,
-                                                                       nd.hp_wh2, nd.hp_bh2);
-    k_hyper_trunk_bwd_b<<<(F * K + F + 255) / 256, 256, 0, s>>>(w, L.dz1, dhparams, P, K, F, nd.hp_wh1, nd.hp_bh1);
+    const int ppb = 64 / F;  // preferences per block (F <= 64)
+    k_hyper_trunk_bwd_a<<<(P + ppb - 1) / ppb, 256, 0, s>>>(hparams, L.df_part, n_chunk, L.f, L.h1, L.dz2, L.dz1, P, F,
+                                                           nd.hp_wh2);
+    k_hyper_trunk_bwd_b<<<(F * F + F * K + 2 * F + 63) / 64, 64, 0, s>>>(w, L.h1, L.dz2, L.dz1, dhparams, P, K, F,
+                                                                        nd.hp_wh1, nd.hp_bh1, nd.hp_wh2, nd.hp_bh2);
 }
