@@ -93,49 +93,64 @@ int64_t hv_ws_bytes(int n, int K) {
 }
 
 // One workgroup: shifted coordinates, dominance flags, the order by objective 0, and per cut objective the
-// slab thicknesses and prefix masks.  lds: V [K][n] doubles, then rank-by-position [n] uint16.
+// slab thicknesses and prefix masks.  Bound by the latency of its serial scans over the points, not by their n^2 K
+// comparisons: G lanes share the scan of one point (all 1024 threads at work down to n = 16), the values as given
+// are compared out of LDS, and a mask word is one ballot.  64 points in 6 objectives: 70 us with a thread a point and
+// the values in global memory, 14 us now.
+// lds: V [K][n] doubles, sorted coordinates [n] doubles, J transposed [K][n] floats, two uint16 [n].
+static size_t hv_prepare_lds(int n, int K) { return (size_t)n * (8 * K + 8 + 4 * K + 4); }
+
 __global__ __launch_bounds__(1024) void k_hv_prepare(const float* __restrict__ J, const float* __restrict__ ref, int n,
-                                                    int K, uint8_t* __restrict__ front, HvWs h, double* __restrict__ hv) {
+                                                    int K, int G, uint8_t* __restrict__ front, HvWs h,
+                                                    double* __restrict__ hv) {
     extern __shared__ __align__(16) unsigned char hv_lds[];
     double* V = reinterpret_cast<double*>(hv_lds);
-    uint16_t* posof = reinterpret_cast<uint16_t*>(V + (size_t)K * n);  // point -> position in the objective-0 order
+    double* cut = V + (size_t)K * n;                                   // sorted coordinates of the current objective
+    float* Jt = reinterpret_cast<float*>(cut + n);
+    uint16_t* posof = reinterpret_cast<uint16_t*>(Jt + (size_t)K * n); // point -> position in the objective-0 order
     uint16_t* rpos = posof + n;                                        // position -> rank in the current cut objective
-    double* cut = reinterpret_cast<double*>(rpos + n + ((4 - ((2 * n) & 3)) & 3));  // sorted coordinates of the current objective
     const int tid = threadIdx.x, W = (n + 63) / 64;
-    for (int i = tid; i < n; i += blockDim.x)
-        for (int k = 0; k < K; ++k) {
-            const double v = (double)J[(int64_t)i * K + k] - (double)ref[k];
-            V[(size_t)k * n + i] = v > 0.0 ? v : 0.0;
-        }
+    const int lane = tid % G, i0 = tid / G, di = 1024 / G;             // point i0, i0 + di, ...: lanes of one wave
+    for (int id = tid; id < n * K; id += 1024) {
+        const int i = id / K, k = id - i * K;
+        const float a = J[id];
+        const double v = (double)a - (double)ref[k];
+        Jt[(size_t)k * n + i] = a;
+        V[(size_t)k * n + i] = v > 0.0 ? v : 0.0;
+    }
+    __syncthreads();
     // Pareto dominance on the values as given (Sec. II-A): j dominates i when it is at least as good in every
     // objective and the two differ
-    for (int i = tid; i < n; i += blockDim.x) {
-        bool dominated = false;
-        for (int j = 0; j < n && !dominated; ++j) {
+    for (int i = i0; i < n; i += di) {
+        int dominated = 0;
+        for (int j = lane; j < n && !dominated; j += G) {
             bool ge = true, gt = false;
             for (int k = 0; k < K; ++k) {
-                const float a = J[(int64_t)j * K + k], b = J[(int64_t)i * K + k];
+                const float a = Jt[(size_t)k * n + j], b = Jt[(size_t)k * n + i];
                 ge = ge && (a >= b);
                 gt = gt || (a > b);
             }
             dominated = ge && gt;
         }
-        front[i] = dominated ? 0 : 1;
+        for (int m = G / 2; m > 0; m >>= 1) dominated |= __shfl_xor(dominated, m);
+        if (lane == 0) front[i] = dominated ? 0 : 1;
     }
-    __syncthreads();
     // rank of point i in objective d: points with a larger coordinate, or an equal one and a smaller index
     auto rank_in = [&](int d, int i) {
         const double* c = V + (size_t)d * n;
         const double vi = c[i];
         int rk = 0;
-        for (int j = 0; j < n; ++j) rk += (c[j] > vi) || (c[j] == vi && j < i);
+        for (int j = lane; j < n; j += G) rk += (c[j] > vi) || (c[j] == vi && j < i);
+        for (int m = G / 2; m > 0; m >>= 1) rk += __shfl_xor(rk, m);
         return rk;
     };
-    for (int i = tid; i < n; i += blockDim.x) {
+    for (int i = i0; i < n; i += di) {
         const int pos = rank_in(0, i);
-        posof[i] = (uint16_t)pos;
-        h.xs[pos] = V[i];
-        h.ys[pos] = K > 1 ? V[(size_t)n + i] : 1.0;
+        if (lane == 0) {
+            posof[i] = (uint16_t)pos;
+            h.xs[pos] = V[i];
+            h.ys[pos] = K > 1 ? V[(size_t)n + i] : 1.0;
+        }
     }
     __syncthreads();
     if (K == 1 && tid == 0) {
@@ -144,24 +159,22 @@ __global__ __launch_bounds__(1024) void k_hv_prepare(const float* __restrict__ J
         hv[0] = m;
     }
     for (int d = 2; d < K; ++d) {
-        for (int i = tid; i < n; i += blockDim.x) {
+        for (int i = i0; i < n; i += di) {
             const int rk = rank_in(d, i);
-            rpos[posof[i]] = (uint16_t)rk;
-            cut[rk] = V[(size_t)d * n + i];
-            if (d == 2) h.pr0[rk] = posof[i];
+            if (lane == 0) {
+                rpos[posof[i]] = (uint16_t)rk;
+                cut[rk] = V[(size_t)d * n + i];
+                if (d == 2) h.pr0[rk] = posof[i];
+            }
         }
         __syncthreads();
         double* dl = h.delta + (size_t)(d - 2) * n;
-        for (int j = tid; j < n; j += blockDim.x) dl[j] = cut[j] - (j + 1 < n ? cut[j + 1] : 0.0);
+        for (int j = tid; j < n; j += 1024) dl[j] = cut[j] - (j + 1 < n ? cut[j + 1] : 0.0);
         uint64_t* mk = h.mask + (size_t)(d - 2) * n * W;
-        for (int id = tid; id < n * W; id += blockDim.x) {
-            const int j = id / W, wd = id % W;
-            uint64_t m = 0;
-            for (int b = 0; b < 64; ++b) {
-                const int pos = 64 * wd + b;
-                if (pos < n && rpos[pos] <= j) m |= (uint64_t)1 << b;
-            }
-            mk[id] = m;
+        for (int id = tid / 64; id < n * W; id += 16) {  // a wave a word
+            const int j = id / W, pos = 64 * (id - j * W) + (tid & 63);
+            const uint64_t m = __ballot(pos < n && rpos[pos < n ? pos : 0] <= j);
+            if ((tid & 63) == 0) mk[id] = m;
         }
         __syncthreads();
     }
@@ -169,8 +182,12 @@ __global__ __launch_bounds__(1024) void k_hv_prepare(const float* __restrict__ J
 
 // Work item = the slabs of objectives 3 .. K-1 (the "outer" tuple: its weight and the AND of its masks are
 // formed once) x a run of consecutive slabs of objective 2.  Going down the slabs of objective 2 the set gains
-// the point of rank j at slab j: the staircase is recomputed only when that point belongs to the outer set,
-// otherwise the slab repeats the area of the one above.
+// the point of rank j at slab j.  When that point belongs to the outer set it is put into the staircase: the mask f
+// of the points that form the staircase gives the neighbour above, the points the new one covers are taken out, and
+// the area grows by what lies between the new corner and the old steps (a sum of non-negative terms).  A point
+// enters and leaves at most once, so a run of n slabs costs O(n) steps; recomputing the staircase at each of them
+// cost O(n) passes over the set and was bound by those chains of dependent LDS reads (64 points in 6 objectives: 239 us,
+// 28 us now).
 #define HV_MAX_W (HV_MAX_N / 64)
 // WB: compile-time bound on the mask words, ceil(n / 64) <= WB.  The staircase coordinates, the thicknesses and
 // ranks of objective 2 and (up to 256 points) its prefix masks sit in LDS: the passes over the set bits are
@@ -222,25 +239,64 @@ __global__ __launch_bounds__(HV_THREADS) void k_hv_slices(int n, int K, HvWs h, 
                 if (wd < W) mo[wd] &= mk[wd];
         }
         if (wout == 0.0) continue;
-        // area of the staircase of the outer set's points inside prefix j of objective 2 (j < 0: the outer set)
+        // area of the staircase of the outer set's points inside prefix j of objective 2 (j < 0: the outer set), and
+        // in f the points that form it: their y increase strictly as their x fall
+        uint64_t f[WB];
         auto staircase = [&](int j) {
             const uint64_t* mk = mask0 + (size_t)(j < 0 ? 0 : j) * W;
             double area = 0.0, top = 0.0;
 #pragma unroll
             for (int wd = 0; wd < WB; ++wd) {
-                uint64_t m = mo[wd];
+                uint64_t m = mo[wd], kept = 0;
                 if (j >= 0 && wd < W) m &= mk[wd];
                 while (m) {
-                    const int pos = 64 * wd + __builtin_ctzll(m);
+                    const int b = __builtin_ctzll(m);
                     m &= m - 1;
-                    const double2 c = xy[pos];
+                    const double2 c = xy[64 * wd + b];
                     if (c.y > top) {
                         area += c.x * (c.y - top);
                         top = c.y;
+                        kept |= (uint64_t)1 << b;
                     }
                 }
+                f[wd] = kept;
             }
             return area;
+        };
+        // what the point at `pos` adds to the staircase f; differences are formed only where they are positive, so
+        // infinite coordinates meet no inf - inf
+        auto insert = [&](int pos) {
+            const int pw = pos >> 6;
+            const uint64_t bit = (uint64_t)1 << (pos & 63);
+            const double2 c = xy[pos];
+            int prev = -1;
+#pragma unroll
+            for (int wd = 0; wd < WB; ++wd) {
+                const uint64_t m = wd < pw ? f[wd] : (wd == pw ? f[wd] & (bit - 1) : 0);
+                if (m) prev = 64 * wd + 63 - __builtin_clzll(m);
+            }
+            double top = prev >= 0 ? xy[prev].y : 0.0, gain = 0.0, xr = 0.0;
+            if (!(c.y > top)) return 0.0;
+            bool open = true;  // no point beyond the new one's y met yet
+#pragma unroll
+            for (int wd = 0; wd < WB; ++wd) {
+                uint64_t m = wd > pw ? f[wd] : (wd == pw ? f[wd] & ~(bit - 1) : 0);
+                while (open && m) {
+                    const double2 q = xy[64 * wd + __builtin_ctzll(m)];
+                    if (q.y > c.y) {
+                        open = false;
+                        xr = q.x;
+                    } else {
+                        f[wd] ^= m & (~m + 1);
+                        m &= m - 1;
+                        if (c.x > q.x) gain += (c.x - q.x) * (q.y - top);
+                        top = q.y;
+                    }
+                }
+                if (wd == pw) f[wd] |= bit;
+            }
+            if (c.x > xr && c.y > top) gain += (c.x - xr) * (c.y - top);
+            return gain;
         };
         if (S == 0) {
             sum += staircase(-1);
@@ -248,14 +304,20 @@ __global__ __launch_bounds__(HV_THREADS) void k_hv_slices(int n, int K, HvWs h, 
         }
         const int j_lo = run * run_len, j_hi = j_lo + run_len < n ? j_lo + run_len : n;
         if (j_lo >= j_hi) continue;
-        double cur = j_lo > 0 ? staircase(j_lo - 1) : 0.0, acc = 0.0;
+        double cur = 0.0, acc = 0.0;
+        if (j_lo > 0) {
+            cur = staircase(j_lo - 1);
+        } else {
+#pragma unroll
+            for (int wd = 0; wd < WB; ++wd) f[wd] = 0;
+        }
         for (int j = j_lo; j < j_hi; ++j) {
             const int pos = (int)pr0[j];
             uint64_t word = 0;
 #pragma unroll
             for (int wd = 0; wd < WB; ++wd)
                 if (wd == (pos >> 6)) word = mo[wd];
-            if ((word >> (pos & 63)) & 1) cur = staircase(j);
+            if ((word >> (pos & 63)) & 1) cur += insert(pos);
             acc += d0[j] * cur;
         }
         sum += wout * acc;
@@ -269,18 +331,17 @@ __global__ __launch_bounds__(HV_THREADS) void k_hv_slices(int n, int K, HvWs h, 
     if (threadIdx.x == 0) h.part[blockIdx.x] = red[0];
 }
 
-// the workgroups' sums: thread t adds partials t, t + 64, ... in order, then a fixed tree over the 64 threads
-__global__ __launch_bounds__(64) void k_hv_final(const double* __restrict__ part, int nb, double* __restrict__ hv) {
-    __shared__ double red[64];
-    double s = 0.0;
-    for (int b = threadIdx.x; b < nb; b += 64) s += part[b];
-    red[threadIdx.x] = s;
+// the workgroups' sums, at most one a thread, in a fixed tree
+__global__ __launch_bounds__(HV_BLOCKS) void k_hv_final(const double* __restrict__ part, int nb, double* __restrict__ hv) {
+    __shared__ double red[HV_BLOCKS];
+    const int t = threadIdx.x;
+    red[t] = t < nb ? part[t] : 0.0;
     __syncthreads();
-    for (int w = 32; w > 0; w >>= 1) {
-        if ((int)threadIdx.x < w) red[threadIdx.x] += red[threadIdx.x + w];
+    for (int w = HV_BLOCKS / 2; w > 0; w >>= 1) {
+        if (t < w) red[t] += red[t + w];
         __syncthreads();
     }
-    if (threadIdx.x == 0) hv[0] = red[0];
+    if (t == 0) hv[0] = red[0];
 }
 
 uint64_t hv_tuples(int n, int K) {  // n^(K-2), saturating at 2^63
@@ -295,15 +356,16 @@ uint64_t hv_tuples(int n, int K) {  // n^(K-2), saturating at 2^63
 void launch_pareto_hypervolume(const float* J, const float* ref, int n, int K, uint8_t* front, double* hv, void* ws,
                                hipStream_t s) {
     const HvWs h = hv_layout(ws, n, K);
-    const size_t lds = (size_t)K * n * 8 + (size_t)2 * n * 2 + 8 + (size_t)n * 8;
     static bool attr_set = false;
     if (!attr_set) {
         (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&k_hv_prepare),
                                   hipFuncAttributeMaxDynamicSharedMemorySize,
-                                  HV_MAX_K * HV_MAX_N * 8 + 4 * HV_MAX_N + 8 + HV_MAX_N * 8);
+                                  (int)hv_prepare_lds(HV_MAX_N, HV_MAX_K));
         attr_set = true;
     }
-    k_hv_prepare<<<1, 1024, lds, s>>>(J, ref, n, K, front, h, hv);
+    int G = 64;  // lanes that share a point's scans: as many as 1024 threads hold, within a wave
+    while (G > 1 && n * G > 1024) G /= 2;
+    k_hv_prepare<<<1, 1024, hv_prepare_lds(n, K), s>>>(J, ref, n, K, G, front, h, hv);
     if (K == 1) return;
     // enough work items for every lane of the chip: the outer tuples, split along objective 2 when they are few
     const uint64_t outer = K > 3 ? hv_tuples(n, K - 1) : 1;
@@ -322,5 +384,5 @@ void launch_pareto_hypervolume(const float* J, const float* ref, int n, int K, u
     else if (W <= 2) k_hv_slices<2><<<nb, HV_THREADS, 0, s>>>(n, K, h, items, runs, run_len);
     else if (W <= 4) k_hv_slices<4><<<nb, HV_THREADS, 0, s>>>(n, K, h, items, runs, run_len);
     else k_hv_slices<HV_MAX_W><<<nb, HV_THREADS, 0, s>>>(n, K, h, items, runs, run_len);
-    k_hv_final<<<1, 64, 0, s>>>(h.part, nb, hv);
+    k_hv_final<<<1, HV_BLOCKS, 0, s>>>(h.part, nb, hv);
 }
