@@ -599,7 +599,7 @@ __global__ __launch_bounds__(256) void k_hyper_df_part(const float* __restrict__
 // dM, dc and the df partials in one pass over the gradient g of the stacked affine rows (P <= 128):
 //   dM[q, :] = sum_p g[p, q] f[p, :],  dc[q] = sum_p g[p, q] (four interleaved shares of the preferences, each in
 //   order, added in a fixed order),  part[wg, p, j] = sum over the workgroup's rows q of g[p, q] M[q, j].
-// A workgroup walks one or more tiles of 64 rows.  The tile of g (all P preferences x 64 rows, every
+// A workgroup walks DMF_TPW-or-more tiles of 64 rows.  The tile of g (all P preferences x 64 rows, every
 // preference's 64 values one 256-byte run) and the tile of M go through LDS and feed fp32 MFMAs twice: wave w
 // forms dM of rows 16 w .. 16 w + 15 (contraction over p), and accumulates, across the tiles, the df partial of
 // preferences 32 w .. 32 w + 31 (contraction over the tile's rows).  The next tiles of g and M are in flight in
@@ -628,22 +628,12 @@ __global__ __launch_bounds__(256) void k_hyper_dM_df(AffineTable at, const float
     // (piece idx = thread + 256 i of the 64 x 16 JT values), requested one tile ahead
     constexpr int MPT = DMF_Q * 16 * JT / 256;
     float nxt[PP / 4], mnx[MPT];
-#pragma unroll
-    for (int i = 0; i < PP / 4; ++i) nxt[i] = 0.f;  // preferences from P on stay zero
-    const int uwave = __builtin_amdgcn_readfirstlane(wave);
     auto fetch = [&](int tile) {
         const int q = tile * DMF_Q + lane;
-        const float* gq = q < fac_len ? dfac + q : dvec + (q - fac_len);
-        const int64_t gs = q < fac_len ? fac_len : vec_len;
-        if (q < q_total) {
 #pragma unroll
-            for (int i = 0; i < PP / 4; ++i) {
-                const int pp = uwave + 4 * i;
-                if (pp < P) nxt[i] = gq[pp * gs];
-            }
-        } else {
-#pragma unroll
-            for (int i = 0; i < PP / 4; ++i) nxt[i] = 0.f;
+        for (int i = 0; i < PP / 4; ++i) {
+            const int pp = wave + 4 * i;
+            nxt[i] = (pp < P && q < q_total) ? grad_row(dfac, dvec, pp, q, fac_len, vec_len) : 0.f;
         }
 #pragma unroll
         for (int i = 0; i < MPT; ++i) {
@@ -681,19 +671,12 @@ __global__ __launch_bounds__(256) void k_hyper_dM_df(AffineTable at, const float
             float4_t accM[JT];
 #pragma unroll
             for (int jt = 0; jt < JT; ++jt) accM[jt] = float4_t{0.f, 0.f, 0.f, 0.f};
-            for (int k0 = 0; 4 * k0 < P; k0 += 4) {  // sixteen preferences' operands requested together (zeros from P on)
-                float a[4], b[4][JT];
+            const int kmax = (P + 3) / 4;
+            for (int kk = 0; kk < kmax; ++kk) {
+                const float a = Dl[4 * kk + kg][16 * wave + ln];
 #pragma unroll
-                for (int u = 0; u < 4; ++u) {
-                    a[u] = Dl[4 * (k0 + u) + kg][16 * wave + ln];
-#pragma unroll
-                    for (int jt = 0; jt < JT; ++jt) b[u][jt] = Fl[4 * (k0 + u) + kg][16 * jt + ln];
-                }
-#pragma unroll
-                for (int u = 0; u < 4; ++u)
-#pragma unroll
-                    for (int jt = 0; jt < JT; ++jt)
-                        accM[jt] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[u], b[u][jt], accM[jt], 0, 0, 0);
+                for (int jt = 0; jt < JT; ++jt)
+                    accM[jt] = __builtin_amdgcn_mfma_f32_16x16x4f32(a, Fl[4 * kk + kg][16 * jt + ln], accM[jt], 0, 0, 0);
             }
             // lane holds feature j = 16 jt + ln of rows q0 + 16 wave + 4 kg + e
 #pragma unroll
@@ -715,7 +698,6 @@ __global__ __launch_bounds__(256) void k_hyper_dM_df(AffineTable at, const float
                 (Cl[0][threadIdx.x] + Cl[1][threadIdx.x]) + (Cl[2][threadIdx.x] + Cl[3][threadIdx.x]);
         }
         // df partial of preferences 32 wave + (0..31): contraction over the tile's rows
-        if (32 * uwave >= P) continue;  // a wave without preferences (it meets the next tile's barriers at its head)
 #pragma unroll
         for (int kk = 0; kk < DMF_Q / 4; ++kk) {
             float b[JT];
@@ -886,13 +868,11 @@ void launch_hypernet_bwd(const morlax_ctx* c, int net, const float* hparams, con
     if (affine) k_hyper_mrow<<<(at.q_total + 255) / 256, 256, 0, s>>>(at, L.mrow, F);
     int n_chunk;
     if (P <= 128) {
-        // one pass over the gradient of the stacked rows.  A tile is a chain of loads, two barriers and products, so
-        // what counts is how many are under way: up to 512 workgroups (two fit a CU), then several tiles each (a
-        // workgroup is at least QW rows, so the partial slots of the layout suffice).  Against four tiles or more each:
-        // 13 thousand rows x 32 preferences 38 -> 14.6 us, 60 thousand x 128 59 -> 49 us (the trunk's launch, which adds
-        // the partials, 0.7 us longer)
+        // one pass over the gradient of the stacked rows; at least four tiles per workgroup, about a thousand
+        // workgroups at most (never more partial slots than the layout holds)
         const int n_tiles = (at.q_total + DMF_Q - 1) / DMF_Q;
-        const int tpw = (n_tiles + 511) / 512;
+        int tpw = (n_tiles + 1023) / 1024;
+        if (tpw < 4) tpw = 4;
         n_chunk = (n_tiles + tpw - 1) / tpw;
         if (F <= 32)
             k_hyper_dM_df<2><<<n_chunk, 256, 0, s>>>(at, hparams, L.mrow, L.f, dlead, dtheta_vec, dhparams, L.df_part, P, F,
