@@ -1,8 +1,7 @@
-"""Gradient of the stacked hypernet rows at the edges of its preference groups and row tiles, against the oracle with the
+"""Gradient of the stacked hypernet rows at the edges of its preference groups, against the oracle with the
 bounds of the parity tests.
 
-Preferences around multiples of 16 (operands requested together) and 32 (a wave's share of df, waves without any), and row
-counts that give a workgroup one tile of 64, several, and a last one that is not full."""
+Preferences around multiples of 16 and 32 (a wave's share of df, waves without any), with a last row tile that is not full."""
 import pytest
 
 import test_gpu_parity as parity
@@ -11,8 +10,7 @@ from test_gpu_parity import RAGGED, _float32_default, binding, torch  # noqa: F4
 
 pytestmark = pytest.mark.gpu
 
-CASES = [scaled(RAGGED, name=f"P{p}", P=p, N=2 * p) for p in (1, 2, 15, 16, 17, 32, 33, 64, 65, 97, 127, 128)]
-CASES += [scaled(RAGGED, name=f"affine-{w}-P{p}", P=p, N=2 * p, rank=-1, width=w, n_hidden=3) for w, p in ((144, 5), (208, 3))]
+CASES = [scaled(RAGGED, name=f"P{p}", P=p, N=2 * p) for p in (2, 15, 16, 17, 32, 33, 64, 65, 97, 127, 128)]
 
 
 @pytest.mark.parametrize("cfg", CASES, ids=lambda c: c.name)
