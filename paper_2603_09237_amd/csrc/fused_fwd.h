@@ -22,6 +22,7 @@
 // asked for.  fp32 products are 16x16x4, whose smaller tiles reach more CUs.
 #pragma once
 
+#include "fwd_shape.h"
 #include "mlp_device.h"
 
 struct FwdNet {  // what differs between the two network families of a call
@@ -61,11 +62,6 @@ struct __attribute__((packed, aligned(4))) FloatRun4 { float4 q; };
 constexpr int fwd_depth(int es, int nw, int rt) {
     if (es == 4) return 2;
     return nw % 2 == 0 ? 2 : nw == 3 && rt <= 2 ? 3 : 1;
-}
-constexpr int fwd_waves(int w) { return w <= 256 ? (w + 63) / 64 : w <= 384 ? 6 : 8; }
-inline int fwd_lds_bytes(int es, int O, int W, int L, int rt) {
-    const int nw = fwd_waves(W), pitch = (64 * nw * es + 255) / 256 * 256, pitch0 = (O * es + 255) / 256 * 256;
-    return 16 * rt * (pitch0 > pitch ? pitch0 : pitch) + nw * 8192 + L * 64 * nw * 4;
 }
 
 // a value the compiler can no longer trace back to its source: address arithmetic derived from it stays
@@ -126,9 +122,9 @@ __global__ __launch_bounds__(64 * NW, 2) void k_mlp_fwd(FwdArgs a) {
 
     // W in LDS: 64 feature rows of eight 16-byte chunks, chunk c of row R at position c ^ ((R >> 1) & 7), so that the
     // fragment reads of 16 lanes (16 rows, one chunk) cover all banks.  Request b of lane l is position l & 7 of row
-    // 8 b + (l >> 3).  Features beyond W repeat the last row (zeroed in the epilogue).  A super-step may run past the
-    // end of a row into the next one, or into the matrix behind (the launcher checks that there is enough of it): the
-    // activations it meets there are zero.
+    // 8 b + (l >> 3).  Features beyond W repeat the last row (zeroed in the epilogue).  The super-steps run past the
+    // end of a row into the next ones, or into the matrix behind (fwd_reads_inside: the launcher checks that there is
+    // enough of it): the activations it meets there are zero.
     auto load_w = [&](u32x4_t (&w)[8], const char* base, int ld) __attribute__((always_inline)) {
         const int ol = opaque(lane);  // (formed here: addresses held across the products would cost them registers)
         const int q0 = ((ol & 7) ^ ((ol >> 4) & 3)) * 16;  // chunk of even b; odd b: the other half of the line

@@ -2295,16 +2295,6 @@ static void launch_fused_fwd(const morlax_ctx* c, const FusedFwdArgs& a, hipStre
     else launch_fused_fwd_w<ACT, SAVE, 512>(c, a, s);
 }
 
-// What the one-launch forward serves: widths its waves cover, and matrices followed by enough of theta for the whole
-// super-steps it requests (see load_w): a hidden row is overrun by less than the rest to a super-step, the first layer's
-// by less than a whole one.
-static bool mlp_fwd_ok(const morlax_ctx* c, const NetDev& nd) {
-    const int W = c->d.width, KS = c->d.wdtype == 1 ? 64 : 32, L = c->d.n_hidden;
-    if (W > 512) return false;
-    const int head = nd.out_dim * W;
-    return L == 1 ? head >= KS - 1 : head >= (W + KS - 1) / KS * KS - W;
-}
-
 static void fill_fwd_net(const morlax_ctx* c, int net, const void* theta_mat, const float* theta_vec, const RowSel& rs,
                          float* out, float* saved_out, const float* eps, float* act, float* logp, char* H, char* G,
                          char* x0, FwdNet& n) {
@@ -2329,7 +2319,7 @@ static void fill_fwd_net(const morlax_ctx* c, int net, const void* theta_mat, co
 static int fwd_row_tiles(const morlax_ctx* c, const NetDev& nd, const void* theta_mat, int64_t rows) {
     const int W = c->d.width, L = c->d.n_hidden, O = c->d.obs_dim, P = c->d.P, nw = fwd_waves(W);
     const bool bf = c->d.wdtype == 1;
-    if (!mlp_fwd_ok(c, nd)) return 0;
+    if (!fwd_reads_inside((int)esize(c), W, L, nd.out_dim)) return 0;
     auto fits = [&](int r) { return fwd_lds_bytes(bf ? 2 : 4, O, W, L, r) <= 160 * 1024; };
     auto tiles = [&](int r) { return (int64_t)P * ((rows + 16 * r - 1) / (16 * r)); };
     if (!fits(bf ? 2 : 1)) return 0;

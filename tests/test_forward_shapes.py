@@ -1,0 +1,74 @@
+"""The one-launch forward requests weights in whole 128-byte pieces; which networks it may serve is a rule on their shape
+(csrc/fwd_shape.h).  Here every request of a preference is walked on the host, lane by lane, for every width, output width
+and element type: what the rule accepts must end inside that preference's matrices."""
+import os
+import shutil
+import subprocess
+
+import pytest
+
+CSRC = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))), "paper_2603_09237_amd", "csrc")
+
+# The walk repeats the kernel's request pattern: wave w, request b of lane l = chunk (l & 7) ^ ((l >> 4) & 3) (odd b: the
+# other half of the line) of feature 64 w + 8 b + (l >> 3), features beyond W reading the last row; a bf16 first layer of at
+# most 32 columns is read as 32 consecutive elements a row instead, where another kernel did so before.
+PROGRAM = r"""
+#include <cstdio>
+#include "fwd_shape.h"
+static long last_of_matrix(int es, int W, int ld, int steps, long off) {
+    const int VE = 16 / es, KS = 8 * VE;
+    long last = 0;
+    for (int w = 0; w < fwd_waves(W); ++w)
+        for (int s = 0; s < steps; ++s)
+            for (int b = 0; b < 8; ++b)
+                for (int l = 0; l < 64; ++l) {
+                    const int f = 64 * w + 8 * b + (l >> 3);
+                    const int chunk = ((l & 7) ^ ((l >> 4) & 3)) ^ (4 * (b & 1));
+                    const long e = off + (long)(f < W ? f : W - 1) * ld + s * KS + chunk * VE + VE - 1;
+                    if (e > last) last = e;
+                }
+    return last;
+}
+int main() {
+    const int Os[] = {1, 2, 3, 8, 11, 19, 31, 32, 33, 45, 63, 64, 65, 100, 127, 513, 1024};
+    long n = 0, wrong = 0, refused = 0, refused_wide = 0;
+    for (int es = 2; es <= 4; es += 2)
+        for (int W = 16; W <= 2048; W += 16)
+            for (int L = 1; L <= 8; L += L < 3 ? 1 : 5)
+                for (int O : Os) {
+                    const int KS = 128 / es;
+                    long last = 0;
+                    if (W <= kFwdMaxWidth) {
+                        last = last_of_matrix(es, W, O, (O + KS - 1) / KS, 0);
+                        if (es == 2 && O <= 32 && (long)(W - 1) * O + 31 > last) last = (long)(W - 1) * O + 31;
+                        for (int l = 1; l < L; ++l) {
+                            const long e = last_of_matrix(es, W, W, 64 * fwd_waves(W) / KS, (long)W * O + (long)(l - 1) * W * W);
+                            if (e > last) last = e;
+                        }
+                    }
+                    for (int out = 1; out <= 16; ++out) {
+                        const long mat_len = (long)W * O + (long)(L - 1) * W * W + (long)out * W;
+                        const bool ok = fwd_reads_inside(es, W, L, out);
+                        ++n;
+                        if (W > kFwdMaxWidth) refused_wide += ok ? 0 : 1, wrong += ok ? 1 : 0;
+                        else if (!ok) ++refused;
+                        else if (last >= mat_len && wrong++ < 10)
+                            printf("reads element %ld of %ld: %d bytes, W %d, O %d, %d hidden, output %d\n", last, mat_len, es, W, O, L, out);
+                    }
+                }
+    printf("shapes %ld wrong %ld refused %ld\n", n, wrong, refused);
+    return wrong ? 1 : 0;
+}
+"""
+
+
+@pytest.mark.skipif(shutil.which("g++") is None, reason="needs a host compiler")
+def test_accepted_networks_are_read_inside_their_matrices(tmp_path):
+    src, exe = tmp_path / "walk.cpp", tmp_path / "walk"
+    src.write_text(PROGRAM)
+    subprocess.run(["g++", "-O2", "-std=c++17", "-I" + CSRC, str(src), "-o", str(exe)], check=True)
+    r = subprocess.run([str(exe)], capture_output=True, text=True)
+    assert r.returncode == 0, r.stdout
+    # only narrow networks of few outputs are refused: the requests of all others find enough of the output layer
+    refused = int(r.stdout.split("refused")[1])
+    assert 0 < refused < 400, r.stdout
