@@ -78,7 +78,7 @@ enum { kActTanh = 0, kActSiluFused = 1, kActSiluPlain = 2 };
 template <typename T, int MODE>
 __device__ inline void fwd_act(float z, float& h, float& g) {
     if (MODE == kActTanh) {
-        act_pair<T, 0>(z, h, g);
+        act_pair<0>(z, h, g);
     } else {
         const float s = __builtin_amdgcn_rcpf(1.f + __expf(-z)), z1 = 1.f + z;
         h = z * s;
