@@ -92,8 +92,12 @@ __device__ inline void fwd_act(float z, float& h, float& g) {
     }
 }
 
-template <typename T, bool SAVE, int NW, int RT>
-__global__ __launch_bounds__(64 * NW, 2) void k_mlp_fwd(FwdArgs a) {
+// WHOLE: the waves' features are the network's, W = 64 NW (as a condition at run time: 31.6 against 29.1 us for
+// one step of 64 preferences x 64 rows of width 256, the two kinds of requests waiting for each other's registers).
+// fp32 tiles of one and two row blocks stay within the 168 registers of three waves a SIMD: with 169 the update step of 10
+// preferences x 3700 rows of width 160 took 1.48 ms, 1.42 now.
+template <typename T, bool SAVE, int NW, int RT, bool WHOLE>
+__global__ __launch_bounds__(64 * NW, sizeof(T) == 4 && RT <= 2 ? 3 : 2) void k_mlp_fwd(FwdArgs a) {
     constexpr int ES = sizeof(T), VE = 16 / ES;
     constexpr bool B32 = ES == 2;    // 32x32 products
     constexpr int KS = 8 * VE;       // contraction indices of a super-step: a 128-byte line of every W row
@@ -110,7 +114,7 @@ __global__ __launch_bounds__(64 * NW, 2) void k_mlp_fwd(FwdArgs a) {
     const FwdNet& net = a.net[gid >= a.net[1].tile0 ? 1 : 0];
     const int tile = gid - net.tile0;
     const int p = tile / net.tiles_m, m0 = (tile % net.tiles_m) * ROWS;
-    const int O = a.O, W = a.W, L = a.L;
+    const int O = a.O, W = WHOLE ? WP : a.W, L = a.L;
     const bool perm = B32 && a.perm;
     const char* Wp = reinterpret_cast<const char*>(net.theta_mat) + (int64_t)p * net.mat_len * ES;
     const float* bp = net.theta_vec + (int64_t)p * net.vec_len;
@@ -122,22 +126,30 @@ __global__ __launch_bounds__(64 * NW, 2) void k_mlp_fwd(FwdArgs a) {
 
     // W in LDS: 64 feature rows of eight 16-byte chunks, chunk c of row R at position c ^ ((R >> 1) & 7), so that the
     // fragment reads of 16 lanes (16 rows, one chunk) cover all banks.  Request b of lane l is position l & 7 of row
-    // 8 b + (l >> 3).  Features beyond W repeat the last row (zeroed in the epilogue).  The super-steps run past the
-    // end of a row into the next ones, or into the matrix behind (fwd_reads_inside: the launcher checks that there is
-    // enough of it): the activations it meets there are zero.
-    auto load_w = [&](u32x4_t (&w)[8], const char* base, int ld) __attribute__((always_inline)) {
+    // 8 b + (l >> 3).  Features beyond W repeat the last row (zeroed in the epilogue).  `left`: elements from here to the
+    // end of a hidden row (a multiple of VE), chunks beyond which are zeros.
+    auto load_w = [&](u32x4_t (&w)[8], const char* base, int ld, int left) __attribute__((always_inline)) {
         const int ol = opaque(lane);  // (formed here: addresses held across the products would cost them registers)
         const int q0 = ((ol & 7) ^ ((ol >> 4) & 3)) * 16;  // chunk of even b; odd b: the other half of the line
-        if (W == WP) {
+        if constexpr (WHOLE) {
             const uint32_t row = (uint32_t)((64 * wave + (ol >> 3)) * ld) * ES;
 #pragma unroll
             for (int b = 0; b < 8; ++b)
                 w[b] = *reinterpret_cast<const chunk2_t*>(base + (int64_t)(8 * b * ld) * ES + (row + (uint32_t)(q0 ^ (64 * (b & 1)))));
         } else {
 #pragma unroll
-            for (int b = 0; b < 8; ++b) {
-                const int f = 64 * wave + 8 * b + (ol >> 3);
-                w[b] = *reinterpret_cast<const chunk2_t*>(base + ((uint32_t)((f < W ? f : W - 1) * ld) * ES + (uint32_t)(q0 ^ (64 * (b & 1)))));
+            for (int h = 0; h < 2; ++h) {  // even b, odd b
+                const int q = q0 ^ (64 * h);
+                if (q < left * ES) {
+#pragma unroll
+                    for (int b = h; b < 8; b += 2) {
+                        const int f = 64 * wave + 8 * b + (ol >> 3);
+                        w[b] = *reinterpret_cast<const chunk2_t*>(base + ((uint32_t)((f < W ? f : W - 1) * ld) * ES + (uint32_t)q));
+                    }
+                } else {
+#pragma unroll
+                    for (int b = h; b < 8; b += 2) w[b] = u32x4_t{0, 0, 0, 0};
+                }
             }
         }
     };
@@ -153,14 +165,33 @@ __global__ __launch_bounds__(64 * NW, 2) void k_mlp_fwd(FwdArgs a) {
 #pragma unroll
         for (int b = 0; b < 4; ++b) w0[b] = *reinterpret_cast<const chunk2_t*>(row + 16 * b);
     } else {
-        load_w(w0, Wp, O);
+        load_w(w0, Wp, O, KS);
+    }
+    // The first layer's last super-step runs past the end of the rows into the next ones, or into the matrix behind
+    // (fwd_reads_inside: the launcher checks that there is enough of it).  The observations it meets there are zero, but an
+    // infinite or undefined weight of another row would make a NaN of them, so those elements are zeroed: `kept` of register
+    // e of request b are not.  bf16: by masks formed here, while the requests are on their way (behind them: 32.5 against
+    // 29.1 us for one step of 64 preferences x 64 rows of width 256); in fp32 the masks' registers would spill.
+    auto kept = [&](int l, int b, int e) __attribute__((always_inline)) {
+        return O - (n0 - 1) * KS - (((l & 7) ^ ((l >> 4) & 3) ^ (4 * (b & 1))) * VE + e * (4 / ES));
+    };
+    u32x4_t keep[2];
+    if constexpr (B32) {
+#pragma unroll
+        for (int h = 0; h < 2; ++h)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const int n = kept(lane, h, e);
+                keep[h][e] = n > 1 ? 0xffffffffu : n > 0 ? 0xffffu : 0u;
+                asm volatile("" : "+v"(keep[h][e]));
+            }
     }
     // requests of the hidden layers; past the last layer the cursor repeats a valid one, so that every super-step has
     // the same number of loads in flight
     u32x4_t wf[D][8];
     int cl = 1, cs = 0;
     auto fetch = [&](u32x4_t (&w)[8]) __attribute__((always_inline)) {
-        load_w(w, Wp + ((int64_t)W * O + (int64_t)(cl - 1) * W * W) * ES + cs * 128, W);
+        load_w(w, Wp + ((int64_t)W * O + (int64_t)(cl - 1) * W * W) * ES + cs * 128, W, W - cs * KS);
         if (++cs == S1) {
             cs = 0;
             cl = cl + 1 < L ? cl + 1 : cl;
@@ -311,7 +342,7 @@ __global__ __launch_bounds__(64 * NW, 2) void k_mlp_fwd(FwdArgs a) {
                 }
 #pragma unroll
                 for (int u = 0; u < VE; ++u) fwd_act<T, MODE>(v[u], v[u], g[u]);
-                if (W != WP && f >= W) {
+                if (!WHOLE && f >= W) {
 #pragma unroll
                     for (int u = 0; u < VE; ++u) v[u] = g[u] = 0.f;
                 }
@@ -319,7 +350,7 @@ __global__ __launch_bounds__(64 * NW, 2) void k_mlp_fwd(FwdArgs a) {
                 gq[q] = pack8(g, (const typename GradT<T>::type*)nullptr).lo;
                 *reinterpret_cast<uint4*>(dlds + row * PITCH + (((f / VE) ^ (er & 15)) * 16)) = hq[q];
                 if (SAVE && !B32) {  // four lanes' pieces of a row are 64 contiguous bytes
-                    if (row < mlim && (W == WP || f < a.ldh)) {
+                    if (row < mlim && (WHOLE || f < a.ldh)) {
                         const uint32_t o = (uint32_t)(row * a.ldh + f) * ES;
                         *reinterpret_cast<uint4*>(Gl + o) = gq[q];
                         *reinterpret_cast<uint4*>(Hl + o) = hq[q];
@@ -338,7 +369,7 @@ __global__ __launch_bounds__(64 * NW, 2) void k_mlp_fwd(FwdArgs a) {
                     for (int it = 0; it < 4; ++it) {
                         const int prow = it * 8 + (el >> 3), pc = el & 7, f = 64 * wave + pc * 8;
                         const uint4 u = *reinterpret_cast<const uint4*>(wst + prow * 128 + ((pc ^ (prow & 7)) * 16));
-                        if (32 * i + prow < mlim && (W == WP || f < a.ldh))
+                        if (32 * i + prow < mlim && (WHOLE || f < a.ldh))
                             *reinterpret_cast<uint4*>(dst + (uint32_t)((32 * i + prow) * a.ldh + f) * ES) = u;
                     }
                     __builtin_amdgcn_wave_barrier();
@@ -378,8 +409,20 @@ __global__ __launch_bounds__(64 * NW, 2) void k_mlp_fwd(FwdArgs a) {
         }
     } else {
         for (int s = 0; s < n0; ++s) {
+            if (s + 1 == n0) {
+                const int ol = opaque(lane);
+#pragma unroll
+                for (int b = 0; b < 8; ++b) {
+                    if constexpr (B32) {
+                        w0[b] &= keep[b & 1];
+                    } else {
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) w0[b][e] = kept(ol, b, e) > 0 ? w0[b][e] : 0u;
+                    }
+                }
+            }
             products(w0, s, pitch0);
-            if (s + 1 < n0) load_w(w0, Wp + (s + 1) * 128, O);
+            if (s + 1 < n0) load_w(w0, Wp + (s + 1) * 128, O, KS);
         }
     }
     if (RT > 2) fill();
@@ -417,7 +460,12 @@ __global__ __launch_bounds__(64 * NW, 2) void k_mlp_fwd(FwdArgs a) {
             for (int u = 0; u < NB; ++u) {
                 const int ch = 4 * (b0 + u) + kg;
                 fa[u] = *reinterpret_cast<const uint4*>(hrow + ((ch ^ ln) * 16));
-                fb[u] = *reinterpret_cast<const uint4*>(wr + (ch * VE < W ? ch : 0) * 16);  // h is zero beyond W
+                fb[u] = *reinterpret_cast<const uint4*>(wr + (ch * VE < W ? ch : 0) * 16);
+            }
+            if constexpr (!WHOLE) {  // zero beyond W, as h is
+#pragma unroll
+                for (int u = 0; u < NB; ++u)
+                    if ((4 * (b0 + u) + kg) * VE >= W) fb[u] = make_uint4(0, 0, 0, 0);
             }
 #pragma unroll
             for (int u = 0; u < NB; u += 2) {
@@ -465,16 +513,21 @@ __global__ __launch_bounds__(64 * NW, 2) void k_mlp_fwd(FwdArgs a) {
 }
 
 // ---- host side: one launch function per (type, SAVE), each instantiated in a translation unit of its own ----------
-template <typename T, bool SAVE, int NW, int RT>
-static void fwd_launch(const FwdArgs& a, int n_tiles, hipStream_t s) {
+template <typename T, bool SAVE, int NW, int RT, bool WHOLE>
+static void fwd_launch_w(const FwdArgs& a, int n_tiles, hipStream_t s) {
     const int lds = fwd_lds_bytes(sizeof(T), a.O, a.W, a.L, RT);
     static bool attr_set = false;
     if (!attr_set) {
-        (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&k_mlp_fwd<T, SAVE, NW, RT>),
+        (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&k_mlp_fwd<T, SAVE, NW, RT, WHOLE>),
                                   hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
         attr_set = true;
     }
-    k_mlp_fwd<T, SAVE, NW, RT><<<n_tiles, 64 * NW, lds, s>>>(a);
+    k_mlp_fwd<T, SAVE, NW, RT, WHOLE><<<n_tiles, 64 * NW, lds, s>>>(a);
+}
+template <typename T, bool SAVE, int NW, int RT>
+static void fwd_launch(const FwdArgs& a, int n_tiles, hipStream_t s) {
+    if (a.W == 64 * NW) fwd_launch_w<T, SAVE, NW, RT, true>(a, n_tiles, s);
+    else fwd_launch_w<T, SAVE, NW, RT, false>(a, n_tiles, s);
 }
 template <typename T, bool SAVE, int NW>
 static void fwd_launch_rt(const FwdArgs& a, int rt, int n_tiles, hipStream_t s) {

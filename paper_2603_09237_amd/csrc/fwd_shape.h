@@ -12,12 +12,9 @@ inline int fwd_lds_bytes(int es, int O, int W, int L, int rt) {
     return 16 * rt * (pitch0 > pitch ? pitch0 : pitch) + nw * 8192 + L * 64 * nw * 4;
 }
 
-// Requests come as whole super-steps (128 bytes of each row), and those of a hidden layer always cover the 64 features of
-// every wave, so the last row of the last matrix is followed by elements of the output layer: by less than a super-step
-// when that matrix is the first layer's, else by 64 NW - W.  Served are the networks whose output layer has that many;
-// the others keep the layer-by-layer kernels.  (Rounding W up to a super-step is not enough: fp32 at width 16 requests two.)
+// Hidden rows are requested up to their end.  The first layer's come as whole super-steps (128 bytes of each row) whatever
+// O is, so its last row is followed by less than a super-step of the matrix behind: a hidden layer's always has that much,
+// with one hidden layer the output layer's must.  The others keep the layer-by-layer kernels.
 inline bool fwd_reads_inside(int es, int W, int L, int out_dim) {
-    if (W > kFwdMaxWidth) return false;
-    const int head = out_dim * W;
-    return head >= (L == 1 ? 128 / es - 1 : 64 * fwd_waves(W) - W);
+    return W <= kFwdMaxWidth && (L > 1 || out_dim * W >= 128 / es - 1);
 }

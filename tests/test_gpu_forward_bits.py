@@ -1,5 +1,5 @@
-"""What the one-launch forward promises beyond the oracle's tolerances: fp32 hidden layers take the library's tanh.
-Inputs are made on the device and everything here is compared bit for bit."""
+"""What the one-launch forward promises beyond the oracle's tolerances: fp32 hidden layers take the library's tanh, weights
+of one row never reach the feature of another.  Inputs are made on the device."""
 import pytest
 
 from paper_2603_09237_amd.configs import CONFIGS, scaled
@@ -81,3 +81,49 @@ def test_fp32_hidden_layers_take_the_librarys_tanh(W, torch, binding):  # noqa: 
           flush=True)
     n_diff = int((got != ref).sum())
     assert n_diff == 0, n_diff
+
+
+def plain_forward(cfg, net, tm, tv, x, torch):
+    """The network in float64 with the matrices as they stand, [T, N, outputs]."""
+    h = x.double().view(cfg.T, cfg.P, cfg.n_g, -1).permute(1, 0, 2, 3).reshape(cfg.P, cfg.T * cfg.n_g, -1).cpu()
+    tm, tv, voff = tm.double().cpu(), tv.double().cpu(), 0
+    for l, (do, di, off) in enumerate(layers(cfg, net)):
+        z = torch.stack([h[p] @ tm[p, off:off + do * di].view(do, di).t() for p in range(cfg.P)]) + tv[:, None, voff:voff + do]
+        voff += do
+        last = l == cfg.n_hidden
+        h = torch.tanh(z) if not last or (net == ACTOR and cfg.mean_tanh) else z
+    return h.view(cfg.P, cfg.T, cfg.n_g, -1).permute(1, 0, 2, 3).reshape(cfg.T, cfg.N, -1)
+
+
+@pytest.mark.parametrize("wd,W,O,L", [(0, 80, 11, 3), (0, 64, 45, 2), (0, 160, 33, 1), (1, 80, 45, 3), (1, 256, 45, 2),
+                                      (1, 160, 40, 1), (1, 384, 72, 2)])
+def test_infinite_and_undefined_weights_stay_in_their_row(wd, W, O, L, torch, binding):  # noqa: F811
+    """An infinite weight saturates its own tanh feature, a NaN row of the output layer spoils its own output: the
+    neighbouring rows, which a request for whole pieces of a row also reads, must not show it."""
+    cfg = scaled(BASE, name=f"inf-{wd}-W{W}-O{O}-L{L}", wdtype=wd, width=W, obs_dim=O, act=0, n_hidden=L, P=2, N=2 * 21, T=1)
+    ctx = binding.Context.from_config(cfg)
+    g = torch.Generator(device="cuda").manual_seed(3)
+    x = torch.randn(1, cfg.N, O, device="cuda", generator=g)
+    for net in (ACTOR, CRITIC):
+        tm, tv = make_theta(cfg, ctx, net, torch, 5 + net)
+        for l, (do, di, off) in enumerate(layers(cfg, net)[:-1]):
+            tm[1, off + 7 * di + 1] = float("inf")
+            tm[1, off + (do - 1) * di] = float("-inf")
+        off = layers(cfg, net)[-1][2]
+        tm[:, off:off + W] = float("nan")
+        tm[:, off + 2 * W + 3] = float("inf")
+        ref = plain_forward(cfg, net, tm, tv, x, torch)
+        assert ref[..., 0].isnan().all() and not ref[..., 1:].isnan().any() and ref[..., 1].isfinite().all()
+        for saving in (False, True):
+            got = forward(cfg, ctx, net, tm, tv, x, (0, 1, 0, cfg.n_g), torch.zeros(1, cfg.N, 5, device="cuda"), torch, saving)[0]
+            got = got.double().cpu().view(ref.shape)
+            say = f" {cfg.name} net={net} saving={saving}: NaN {int(got.isnan().sum())} of {int(ref.isnan().sum())}"
+            print("[gpu-bits] " + say, flush=True)
+            same = bool((got.isnan() == ref.isnan()).all()) and bool((got.isinf() == ref.isinf()).all())
+            assert same, say
+            ok = ref.isfinite()
+            # (the bounds of the parity tests: fp32 1e-5 + 1e-4 |ref|; bf16 relative RMS error 1e-2)
+            if wd == 0:
+                assert bool(((got - ref).abs() <= 1e-5 + 1e-4 * ref.abs())[ok].all())
+            else:
+                assert float((got - ref)[ok].square().mean().sqrt()) < 1e-2 * float(ref[ok].square().mean().sqrt())

@@ -32,8 +32,8 @@ CASES += [case(1, 512, 90, 37, 11), case(1, 256, 180, 37, 11), case(0, 512, 70, 
 CASES += [case(wd, 32, 3, 20, 2, obs_dim=121) for wd in (0, 1)] + [case(wd, 96, 3, 20, 2, obs_dim=513, n_hidden=2) for wd in (0, 1)]
 CASES += [case(wd, 48, 3, 20, 2, n_hidden=1, obs_dim=45) for wd in (0, 1)] + [case(1, 16, 3, 20, 2, K=1, n_hidden=2)]
 CASES += [case(wd, 144, 5, 30, 2, act=0, sigma_state=1) for wd in (0, 1)]
-# the narrowest network, output layers of 1, 2 and 3 columns: the first two leave too little behind the last matrix for whole
-# requests (test_forward_shapes.py) and go layer by layer
+# the narrowest network, output layers of 1, 2 and 3 columns: behind its last matrix comes less than a whole request
+# (test_forward_shapes.py walks them)
 CASES += [case(wd, 16, 3, 33, 2, K=o, act_dim=o, n_hidden=2, obs_dim=8) for wd in (0, 1) for o in (1, 2, 3)]
 
 
