@@ -1,5 +1,6 @@
 """What the one-launch forward promises beyond the oracle's tolerances: fp32 hidden layers take the library's tanh, weights
-of one row never reach the feature of another.  Inputs are made on the device."""
+of one row never reach the feature of another, and in bf16 a result does not depend on how many rows are asked for.
+Inputs are made on the device."""
 import pytest
 
 from paper_2603_09237_amd.configs import CONFIGS, scaled
@@ -127,3 +128,31 @@ def test_infinite_and_undefined_weights_stay_in_their_row(wd, W, O, L, torch, bi
                 assert bool(((got - ref).abs() <= 1e-5 + 1e-4 * ref.abs())[ok].all())
             else:
                 assert float((got - ref)[ok].square().mean().sqrt()) < 1e-2 * float(ref[ok].square().mean().sqrt())
+
+
+# (width, observation widths, time steps of 131 rows that go to the kernel for tall selections): width 512 and 256 to the
+# one that reads the matrices in fragment order, 384 and 448 to the tiled GEMMs behind the three first-layer forms (O <= 32
+# by multiply-adds, O a multiple of 32 and of 8 and odd O on tiles), 160 and 208 to the same kernel with taller tiles
+BIT_CASES = [(512, (11, 45, 64, 100), 4), (256, (11, 45, 64, 256), 6), (384, (11, 31, 32, 40, 45, 96), 4),
+             (448, (19, 45, 64), 4), (160, (11, 45), 4), (208, (31, 64), 4)]
+
+
+@pytest.mark.parametrize("act", (0, 1))
+@pytest.mark.parametrize("W,O,T", [(W, O, T) for W, Os, T in BIT_CASES for O in Os])
+def test_bf16_results_do_not_depend_on_the_rows_asked_for(W, O, T, act, torch, binding):  # noqa: F811
+    """One time step of 40 rows (32-row tiles), two of 128 (64-row tiles) and the whole selection: outputs, samples,
+    log-densities, saved activations and derivative codes of the rows they share."""
+    cfg = scaled(BASE, name=f"bits-W{W}-O{O}-a{act}", width=W, obs_dim=O, act=act, P=64, N=64 * 131, T=T)
+    ctx = binding.Context.from_config(cfg)
+    g = torch.Generator(device="cuda").manual_seed(W + O)
+    x = torch.randn(cfg.T, cfg.N, O, device="cuda", generator=g)
+    eps = torch.randn(cfg.T, cfg.N, cfg.act_dim, device="cuda", generator=g)
+    for net in (ACTOR, CRITIC):
+        tm, tv = make_theta(cfg, ctx, net, torch, 5 + net)
+        for saving in (False, True):
+            tall = forward(cfg, ctx, net, tm, tv, x, (0, T, 0, 131), eps, torch, saving)
+            assert all(bool(t.float().isfinite().all()) for t in tall)
+            for t0, tc, j0, jc in ((1, 1, 3, 40), (0, 2, 3, 128)):
+                part = forward(cfg, ctx, net, tm, tv, x, (t0, tc, j0, jc), eps, torch, saving)
+                diff = [int((a != b[t0:t0 + tc, :, j0:j0 + jc]).sum()) for a, b in zip(part, tall)]
+                assert not any(diff), (net, saving, tc, diff, [a.numel() for a in part])
