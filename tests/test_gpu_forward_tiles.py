@@ -42,3 +42,13 @@ def test_forward_and_backward_at_tile_edges(cfg, torch, binding):  # noqa: F811
     parity.test_policy_fwd_matches_oracle(cfg, None, torch, binding)
     if cfg.n_g * cfg.T >= 60 and cfg.P <= 5:
         parity.test_policy_bwd_matches_oracle(cfg, None, torch, binding)
+
+
+# what the saving forwards of many preferences leave for the backward pass, on three of the preferences: 64-row tiles of four,
+# six and eight waves (185 rows), and the layer-by-layer forward on the persistent GEMM with a cut row tile and, at 528, a cut
+# column tile (384: 407 rows, beyond the one-launch forward; 528: too wide for it)
+@pytest.mark.parametrize("cfg", [case(1, 256, 90, 37, 5), case(1, 384, 90, 37, 5), case(1, 448, 90, 37, 5), case(1, 512, 90, 37, 5),
+                                 case(1, 384, 90, 37, 11), case(1, 528, 90, 37, 5)], ids=lambda c: c.name)
+def test_backward_on_what_wide_forwards_save(cfg, torch, binding, monkeypatch):  # noqa: F811
+    monkeypatch.setattr(parity, "sample_prefs", lambda c: [0, c.P // 3 + 1, c.P - 1])
+    parity.test_policy_bwd_matches_oracle(cfg, None, torch, binding)

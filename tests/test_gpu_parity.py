@@ -52,8 +52,8 @@ def binding():
 RAGGED = scaled(CONFIGS[1], name="ragged-K3-P3-N69-T7", K=3, P=3, N=69, T=7, obs_dim=11, act_dim=3, n_hidden=2,
                 width=48, act=1, rank=3, hyper_width=20)
 RAGGED_BF16 = scaled(RAGGED, name="ragged-bf16", wdtype=1, N=3 * 150, T=5, width=144)
-# enough tiles for the persistent GEMM kernel, with a cut last row tile (2016 rows per preference) and a cut
-# last column tile (width 160), and an observation width that takes the gathered first-layer path
+# enough tiles for the persistent GEMM kernel in dX (the forward is the one-launch one, in 64-row tiles), with a cut last row
+# tile (2016 rows per preference) and a cut last column tile (width 160), and an observation width of whole 32-index steps
 RAGGED_PERS = scaled(RAGGED, name="ragged-persistent-bf16", wdtype=1, P=32, N=32 * 126, T=16, width=160, obs_dim=32,
                      rank=4)
 # the fused forward of all hidden layers (bf16, width 512, observation width a multiple of 64): three row
