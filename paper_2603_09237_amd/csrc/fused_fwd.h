@@ -1,5 +1,5 @@
 // Fused target-network forward (paper Sec. III-C, rollout and update phases): observations -> every hidden layer ->
-// output layer with tanh, sampling and log-density, in one launch for one or both networks.
+// output layer with tanh, sampling and log-density, in one launch.
 //
 // A workgroup of NW waves carries ROWS = 16 RT rows of one preference through every layer.  The activations of the
 // tile live in LDS (16-byte chunks XOR-swizzled by the row) and are rewritten in place layer after layer; HBM sees the
@@ -25,14 +25,14 @@
 #include "fwd_shape.h"
 #include "mlp_device.h"
 
-struct FwdNet {  // what differs between the two network families of a call
+struct FwdNet {  // the network family of a call
     const void* theta_mat;   // [P][mat_len]: W_0 [W][O], W_1 .. [W][W] back to back, then the output layer
     const float* theta_vec;  // [P][vec_len]: W biases a layer, then the output layer's
     int64_t mat_len, vec_len;
     int64_t head_mat_off, head_vec_off, logsig_off;
     int32_t out_dim, tanh_cols;  // leading output columns that are squashed by tanh (the actor's means)
     int32_t adim, sig_state;     // action width; 1: log sigma = output columns [adim, 2 adim) of the same row
-    int32_t M, tiles_m, tile0;   // rows per preference, row tiles per preference, first tile id
+    int32_t M, tiles_m;          // rows per preference, row tiles per preference
     RowMap rm;
     float* out;        // time-major [.., N, out_dim]
     float* saved_out;  // saving: compact [P][M][OUT_PITCH]
@@ -46,7 +46,7 @@ struct FwdNet {  // what differs between the two network families of a call
 
 struct FwdArgs {
     const float* x;  // observations, time-major rows of O values
-    FwdNet net[2];   // the second one starts at tile net[1].tile0 (beyond the grid when there is one network)
+    FwdNet net;
     int32_t L, O, W, act;
     int32_t perm, narrow;  // bf16: contraction order, first layer by multiply-adds (see above)
     int32_t Mp, ldh, ldx;  // saving: rows per preference and row lengths of the compact buffers
@@ -110,9 +110,8 @@ __global__ __launch_bounds__(64 * NW, sizeof(T) == 4 && RT <= 2 ? 3 : 2) void k_
     extern __shared__ __align__(16) unsigned char dlds[];
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int gid = xcd_remap(blockIdx.x, gridDim.x);
-    const FwdNet& net = a.net[gid >= a.net[1].tile0 ? 1 : 0];
-    const int tile = gid - net.tile0;
+    const int tile = xcd_remap(blockIdx.x, gridDim.x);
+    const FwdNet& net = a.net;
     const int p = tile / net.tiles_m, m0 = (tile % net.tiles_m) * ROWS;
     const int O = a.O, W = WHOLE ? WP : a.W, L = a.L;
     const bool perm = B32 && a.perm;

@@ -2312,10 +2312,9 @@ static void fill_fwd_net(const morlax_ctx* c, int net, const void* theta_mat, co
     n.H = H; n.G = G; n.x0 = x0;
 }
 
-// Row tiles of 16 per workgroup of the one-launch forward, `rows` rows per preference in all networks of the call
-// together; 0: not this kernel (tall selections of width 512 or 256 have one that multiplies four times the rows per
-// fetched weight, other tall ones the layer-by-layer GEMMs).  The lines are measured ones (saving variant, three hidden
-// layers, preferences x rows; us).
+// Row tiles of 16 per workgroup of the one-launch forward, `rows` rows per preference; 0: not this kernel (tall selections
+// of width 512 or 256 have one that multiplies four times the rows per fetched weight, other tall ones the layer-by-layer
+// GEMMs).  The lines are measured ones (saving variant, three hidden layers, preferences x rows; us).
 static int fwd_row_tiles(const morlax_ctx* c, const NetDev& nd, const void* theta_mat, int64_t rows) {
     const int W = c->d.width, L = c->d.n_hidden, O = c->d.obs_dim, P = c->d.P, nw = fwd_waves(W);
     const bool bf = c->d.wdtype == 1;
@@ -2342,30 +2341,16 @@ static int fwd_row_tiles(const morlax_ctx* c, const NetDev& nd, const void* thet
     return nw > 1 && tiles(1) >= (nw == 2 ? 4096 : 1024) && fits(2) ? 2 : 1;
 }
 
-// one or two networks in one launch
-static void run_mlp_fwd(const morlax_ctx* c, FwdArgs& a, int n_nets, int rt, bool save, hipStream_t s) {
+static void run_mlp_fwd(const morlax_ctx* c, const NetDev& nd, FwdArgs& a, int rt, bool save, hipStream_t s) {
     const int W = c->d.width, L = c->d.n_hidden, O = c->d.obs_dim, P = c->d.P;
     a.L = L; a.O = O; a.W = W; a.act = c->d.act;
-    a.perm = fused_fwd_ok(c, c->net[0], a.net[0].theta_mat) ? 1 : 0;
+    a.perm = fused_fwd_ok(c, nd, a.net.theta_mat) ? 1 : 0;
     a.narrow = !a.perm && !use_x0(c) && first_fwd_narrow_ok(c) ? 1 : 0;
-    const bool bf = c->d.wdtype == 1;
-    double flops = 0.0;
-    for (int i = 0; i < n_nets; ++i) flops += 2.0 * W * ((double)O + (double)(L - 1) * W) * a.net[i].M * P;
-    int n_tiles = 0;
-    auto tiles = [&](int r) {
-        n_tiles = 0;
-        for (int i = 0; i < n_nets; ++i) {
-            a.net[i].tile0 = n_tiles;
-            a.net[i].tiles_m = ((save ? a.Mp : a.net[i].M) + 16 * r - 1) / (16 * r);
-            n_tiles += a.net[i].tiles_m * P;
-        }
-        if (n_nets == 1) a.net[1].tile0 = 0x7fffffff;
-        return n_tiles;
-    };
-    tiles(rt);
-    GemmProf::Rec* r = prof_take(c, 5, flops);
+    a.net.tiles_m = ((save ? a.Mp : a.net.M) + 16 * rt - 1) / (16 * rt);
+    const int n_tiles = a.net.tiles_m * P;
+    GemmProf::Rec* r = prof_take(c, 5, 2.0 * W * ((double)O + (double)(L - 1) * W) * a.net.M * P);
     if (r) (void)hipEventRecord(r->a, s);
-    if (bf) {
+    if (c->d.wdtype == 1) {
         if (save) launch_mlp_fwd_bf16_save(a, rt, n_tiles, s);
         else launch_mlp_fwd_bf16_act(a, rt, n_tiles, s);
     } else {
@@ -2455,9 +2440,9 @@ static void policy_fwd_t(const morlax_ctx* c, int net, const T* theta_mat, const
     if (rt > 0) {
         FwdArgs a;
         fill_fwd_net(c, net, theta_mat, theta_vec, rs, out, saved_out, eps, act, logp, reinterpret_cast<char*>(sv),
-                     reinterpret_cast<char*>(sv ? sv + ae : nullptr), reinterpret_cast<char*>(sv_x0), a.net[0]);
+                     reinterpret_cast<char*>(sv ? sv + ae : nullptr), reinterpret_cast<char*>(sv_x0), a.net);
         a.x = x; a.Mp = Mp; a.ldh = W; a.ldx = x0_ld(c); a.lstride = 2 * ae * (int64_t)sizeof(T);
-        run_mlp_fwd(c, a, 1, rt, sv != nullptr, s);
+        run_mlp_fwd(c, nd, a, rt, sv != nullptr, s);
         return;
     }
     bool fused = false;
