@@ -22,6 +22,8 @@
 // asked for.  fp32 products are 16x16x4, whose smaller tiles reach more CUs.
 #pragma once
 
+#include <atomic>
+
 #include "fwd_shape.h"
 #include "mlp_device.h"
 
@@ -515,11 +517,14 @@ __global__ __launch_bounds__(64 * NW, sizeof(T) == 4 && RT <= 2 ? 3 : 2) void k_
 template <typename T, bool SAVE, int NW, int RT, bool WHOLE>
 static void fwd_launch_w(const FwdArgs& a, int n_tiles, hipStream_t s) {
     const int lds = fwd_lds_bytes(sizeof(T), a.O, a.W, a.L, RT);
-    static bool attr_set = false;
-    if (!attr_set) {
+    static std::atomic<uint64_t> allowed{0};  // devices on which the kernel may take more LDS than the default (a bit each)
+    int dev = 0;
+    (void)hipGetDevice(&dev);
+    const uint64_t bit = (uint64_t)1 << (dev & 63);
+    if (!(allowed.load(std::memory_order_relaxed) & bit)) {
         (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&k_mlp_fwd<T, SAVE, NW, RT, WHOLE>),
                                   hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
-        attr_set = true;
+        allowed.fetch_or(bit, std::memory_order_relaxed);
     }
     k_mlp_fwd<T, SAVE, NW, RT, WHOLE><<<n_tiles, 64 * NW, lds, s>>>(a);
 }
