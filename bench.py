@@ -30,7 +30,7 @@ KERNEL_OF_KIND = {
     "dx_hidden": "grouped GEMM <SRC_KCONTIG, SRC_KSTRIDED, EpiDx> dX, W x W layers",
     "dw_hidden": "grouped GEMM <SRC_KSTRIDED, SRC_KSTRIDED, EpiDw> dW, W x W layers (with the merge of a split contraction)",
     "dw_first": "dW, first layer: grouped GEMM, or k_gather_x_pad + k_first_bwd_dw + k_first_dw_final for narrow observations",
-    "fwd_fused": "k_mlp_fused_fwd: first layer and all W x W layers of a 128-row tile in one launch (rollout + update)",
+    "fwd_fused": "k_mlp_fused_fwd / k_mlp_fwd: all layers of a row tile in one launch (rollout + update)",
 }
 
 

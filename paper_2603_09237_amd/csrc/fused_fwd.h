@@ -10,11 +10,13 @@
 // between a request and its use.
 //
 // Why through LDS: an MFMA operand wants consecutive lanes on consecutive rows, and the vector cache looks addresses up
-// four lanes at a time -- fetched that way from a row-major matrix that is four lookups per 64 bytes.  Measured, one CU
-// then takes W at 11 bytes per clock, and a tile of three 512 x 512 layers takes 50 us whatever its height; with eight
-// lanes to a line it takes half of that.  (Copying the matrices into fragment order first, as the kernel for tall
-// selections does, is a launch that moves every weight twice: 74 us at 128 preferences of width 512, against 42 us for
-// reading them.)
+// four lanes at a time -- fetched that way from a row-major matrix that is four lookups per 64 bytes.  A loop that only
+// requests three 512 x 512 matrices, one workgroup of eight waves a CU and 16 KB a wave in flight, takes 46 us that way (16
+// bytes per clock and CU) and 19 us with eight lanes to a line, while the caches serve the weights (32 workgroups on 16
+// networks; 256 on 8: 47 and 20 us).  With every CU on weights of its own the way from memory bounds both: 59 and 63 us; the
+// largest policies are there (a step of 128 preferences x 128 rows of 4 x 512: 70.6 us a network, 10.6 bytes per clock and
+// CU, 3.0 TB/s).  (Copying the matrices into fragment order first, as the kernel for tall selections does, is a launch of 87
+// us at that size.)
 //
 // bf16 products are 32x32x16 in the contraction order of the kernels that serve taller selections of the same network
 // (k_mlp_fused_fwd: `perm`, chunks jj and 4 + jj of a line together, bias first; the tiled GEMMs: ascending, bias last;
@@ -95,7 +97,7 @@ __device__ inline void fwd_act(float z, float& h, float& g) {
 }
 
 // WHOLE: the waves' features are the network's, W = 64 NW (as a condition at run time: 31.6 against 29.1 us for
-// one step of 64 preferences x 64 rows of width 256, the two kinds of requests waiting for each other's registers).
+// one step of 32 preferences x 256 rows of width 256, the two kinds of requests waiting for each other's registers).
 // fp32 tiles of one and two row blocks stay within the 168 registers of three waves a SIMD: with 169 the update step of 10
 // preferences x 3700 rows of width 160 took 1.48 ms, 1.42 now.
 template <typename T, bool SAVE, int NW, int RT, bool WHOLE>
@@ -172,7 +174,7 @@ __global__ __launch_bounds__(64 * NW, sizeof(T) == 4 && RT <= 2 ? 3 : 2) void k_
     // (fwd_reads_inside: the launcher checks that there is enough of it).  The observations it meets there are zero, but an
     // infinite or undefined weight of another row would make a NaN of them, so those elements are zeroed: `kept` of register
     // e of request b are not.  bf16: by masks formed here, while the requests are on their way (behind them: 32.5 against
-    // 29.1 us for one step of 64 preferences x 64 rows of width 256); in fp32 the masks' registers would spill.
+    // 29.1 us for one step of 32 preferences x 256 rows of width 256); in fp32 the masks' registers would spill.
     auto kept = [&](int l, int b, int e) __attribute__((always_inline)) {
         return O - (n0 - 1) * KS - (((l & 7) ^ ((l >> 4) & 3) ^ (4 * (b & 1))) * VE + e * (4 / ES));
     };

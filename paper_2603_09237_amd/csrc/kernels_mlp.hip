@@ -2156,10 +2156,11 @@ __global__ __launch_bounds__(256) void k_gather_x(const float* __restrict__ x, T
 // ---- host side ---------------------------------------------------------------------------------
 static int64_t esize(const morlax_ctx* c) { return c->d.wdtype == 1 ? 2 : 4; }
 // Rows per preference of the compact buffers (h, act', dZ, observations): whole contraction steps of the dW products.
-// Rows M .. Mp hold copies of row M - 1 where the forward pass writes and zeros in dZ.  (With Mp = M, a selection that was
-// no multiple of 32 rows took the register-staged GEMM with a masked tail: 41 us against 18 us per launch at 24
-// preferences x 1250 rows x 256 x 256 in bf16, both unsplit; where the first layer's operand was read through the row map
-// element by element, 334 us.)
+// Rows M .. Mp are zero in dZ and what h, act' and the observations hold there is finite where row M - 1 and the biases are
+// (copies of row M - 1; behind the tiled first layer of an odd observation width, the activation of the bias alone), so
+// they add nothing.  (With Mp = M, a selection that was no multiple of 32 rows took the register-staged GEMM with a masked
+// tail: 41 us against 18 us per launch at 24 preferences x 1250 rows x 256 x 256 in bf16, both unsplit; where the first
+// layer's operand was read through the row map element by element, 334 us.)
 static int pad_rows(const RowSel& rs) { return (rs.M + 31) / 32 * 32; }
 static int64_t act_elems(const morlax_ctx* c, const RowSel& rs) {
     return align_up((int64_t)c->d.P * pad_rows(rs) * c->d.width, 64);
@@ -2210,10 +2211,11 @@ static int64_t first_skinny_elems(const morlax_ctx* c, const RowSel& rs) {  // p
 // Ranges the contraction of a layer's dW is cut into (1 = the plain grouped GEMM), until there are DW_SPLIT_TARGET
 // workgroups (1024 measured slower: twice the partials).  fp32: ranges of 256 rows and more, of 64 while the workgroups
 // reach less than a quarter of the CUs (4 preferences x 256 rows x 64 x 64: 22.7 us unsplit, 12 us with the merge).
-// bf16, whose steps are eight times shorter: only into equal whole ranges (23 preferences x 1120 rows x 512 x 512 in two
-// ranges cost 4 % of the update step), and the first layer, whose few columns make few tiles, into ranges of 2048 rows
-// and more.  Such a selection's bf16 gradients thereby do not depend on the split, whose last bits Adam would carry on
-// through the rounding of theta.  The room for the partials is sized for the most ranges any smaller selection takes.
+// bf16: hidden layers only into equal ranges of whole 64-row steps, 256 rows and more; the first layer, whose few columns
+// make few tiles, into ranges of 2048 rows and more, uneven ones too.  Uneven ranges of a bf16 hidden layer were timed at
+// one shape only, which has more tiles than the chip has CUs (23 preferences x 1120 rows x 512 x 512 in two: 4 % of the
+// update step lost); where few tiles leave the chip idle nothing was measured, and such a selection runs unsplit.  The room
+// for the partials is sized for the most ranges any smaller selection takes.
 static int dw_split(const morlax_ctx* c, int M, int layer, bool room) {
     const bool bf = c->d.wdtype == 1;
     const int d_in = layer == 0 ? c->d.obs_dim : c->d.width;
