@@ -1,6 +1,6 @@
 """The one-launch forward requests the first layer's weights in whole 128-byte pieces; which networks it may serve is a rule
-on their shape (csrc/fwd_shape.h).  Here every request of a preference is walked on the host, lane by lane, for every width, output width
-and element type: what the rule accepts must end inside that preference's matrices."""
+on their shape (csrc/fwd_shape.h).  Here every request of a preference is walked on the host, lane by lane, for every width,
+output width and element type: what the rule accepts must end inside that preference's matrices."""
 import os
 import shutil
 import subprocess
