@@ -1082,8 +1082,8 @@ __global__ __launch_bounds__(2 * TN, 2) void k_gemm_pers(GemmArgs<bf16_t, KA, KB
 // an activation.
 // Wave w owns output features [64 w, 64 w + 64) of every layer for all 128 rows: its slice of W_l(p) is
 // used by no other wave, so the W fragments go from global memory (they sit in L2: 64 tiles share one
-// W(p)) straight into registers, requested half a super-step ("unit": 16 products, 32 contraction indices
-// per lane group) ahead of their use.  The kernel reads them from a copy of the matrices in fragment order
+// W(p)) straight into registers, half a super-step at a time ("unit": 16 products, 32 contraction indices
+// per lane group).  The kernel reads them from a copy of the matrices in fragment order
 // (k_theta_fragment_order, made by the same call): every load instruction then covers 1 KB of consecutive
 // addresses.  Read from the row-major matrices the same stream takes 32 bytes from each of 32 rows per
 // instruction, and the workgroups of a CU, 64 KB of such lines in flight against its vector cache, fetch
@@ -1193,28 +1193,27 @@ __global__ __launch_bounds__(WD, 2) void k_mlp_fused_fwd(FusedFwdArgs a) {
 
         const bf16_t* Wp = a.theta_frag + (int64_t)p * a.frag_len;
         const float* bp = a.theta_vec + (int64_t)p * a.vec_len;
-        auto w_rows = [&](int l, const char* (&w)[2]) {  // the lane's place in the wave's stream of W_l(p), per feature half
+        // the wave's stream of W_l(p) in fragment order: a uniform base and the lane's 16 bytes
+        auto w_stream = [&](int l) {
             const int K = l == 0 ? a.Opad : WD;
-#pragma unroll
-            for (int j = 0; j < 2; ++j)
-                w[j] = reinterpret_cast<const char*>(Wp + a.frag_off[l]) + (int64_t)wave * (K >> 5) * 4096 + j * 2048 +
-                       lane * 16;
+            return reinterpret_cast<const char*>(Wp + a.frag_off[l]) + (int64_t)wave * (K >> 5) * 4096;
         };
         // unit u of a layer = 32 contraction indices per lane group, 4 KB of the wave's stream (fragment order)
-        auto load_w = [&](uint4 (&wf)[2][2], const char* w0, const char* w1, int u) {
-            const int off = u * 4096;
-            wf[0][0] = *reinterpret_cast<const uint4*>(w0 + off);
-            wf[0][1] = *reinterpret_cast<const uint4*>(w0 + off + 1024);
-            wf[1][0] = *reinterpret_cast<const uint4*>(w1 + off);
-            wf[1][1] = *reinterpret_cast<const uint4*>(w1 + off + 1024);
+        auto load_w = [&](u32x4_t (&wf)[2][2], const char* w, int u) __attribute__((always_inline)) {
+            const uint32_t lo = (uint32_t)lane * 16u;
+#pragma unroll
+            for (int j = 0; j < 2; ++j)
+#pragma unroll
+                for (int e = 0; e < 2; ++e) wf[j][e] = *reinterpret_cast<const u32x4_t*>(w + u * 4096 + (j * 2048 + e * 1024) + lo);
         };
-        // W fragments: two buffers, a unit's request one unit ahead of its use (a longer distance with four
-        // buffers measured slower: the registers it takes spill in the epilogue)
-        const char* wp[2];
-        uint4 wfa[2][2], wfb[2][2];
+        // W fragments: a ring of four buffers.  In the hidden layers a unit is requested three units ahead of its use: the
+        // stores of the saving variant raise the latency of a W request from 140 to 750 cycles on average, a unit's
+        // products take 1000.  Only a layer's first unit is requested ahead of the epilogue in front of it, whose registers
+        // the other buffers are.  (128 preferences x 2048 rows of 4 x 512, with the fragment-order copy: 856 -> 835 us.)
+        u32x4_t wfa[2][2], wfb[2][2], wfc[2][2], wfd[2][2];
         float16_t acc[4][2];
-        w_rows(0, wp);
-        load_w(wfa, wp[0], wp[1], 0);
+        const char* wp = w_stream(0);
+        load_w(wfa, wp, 0);
 
         {  // the tile's observations, gathered from the time-major tensor and rounded to bf16; rows past the end
            // repeat the last row (saved up to Mp, no output).  The saving variant keeps the compact copy that the first
@@ -1246,7 +1245,7 @@ __global__ __launch_bounds__(WD, 2) void k_mlp_fused_fwd(FusedFwdArgs a) {
         const int sflip = x >> 3;
 
         // one unit: 16 products; HALF = u & 1 picks the chunks 2 HALF, 2 HALF + 1 of the super-step
-        auto unit = [&](const uint4 (&wf)[2][2], int u, auto half_tag) {
+        auto unit = [&](const u32x4_t (&wf)[2][2], int u, auto half_tag) __attribute__((always_inline)) {
             constexpr int HALF = decltype(half_tag)::value;
             const unsigned char* as = arow + ((u >> 1) ^ sflip) * 128;
             uint4 fa[2][4];
@@ -1259,15 +1258,16 @@ __global__ __launch_bounds__(WD, 2) void k_mlp_fused_fwd(FusedFwdArgs a) {
 #pragma unroll
                 for (int i = 0; i < 4; ++i)
 #pragma unroll
-                    for (int j = 0; j < 2; ++j) Mma32<bf16_t>::run(wf[j][jj], fa[jj][i], acc[i][j]);
+                    for (int j = 0; j < 2; ++j) Mma32<bf16_t>::run(__builtin_bit_cast(uint4, wf[j][jj]), fa[jj][i], acc[i][j]);
         };
         // lane n of `bias` holds b_l[wn + n]; every accumulator of a lane's octet o starts from its feature's bias
-        auto init_acc = [&](float bias) {
+        auto init_acc = [&](float bias) __attribute__((always_inline)) {
+            const int at = (opaque(lane) >> 5) * 32;  // (formed here: addresses held across the epilogue would spill)
 #pragma unroll
             for (int o = 0; o < 4; ++o)
 #pragma unroll
                 for (int u = 0; u < 8; ++u) {
-                    const float b = __shfl(bias, 16 * o + 8 * lg + u, 64);
+                    const float b = __int_as_float(__builtin_amdgcn_ds_bpermute(at + 4 * (16 * o + u), __float_as_int(bias)));
 #pragma unroll
                     for (int i = 0; i < 4; ++i) acc[i][o >> 1][8 * (o & 1) + u] = b;
                 }
@@ -1276,24 +1276,15 @@ __global__ __launch_bounds__(WD, 2) void k_mlp_fused_fwd(FusedFwdArgs a) {
 
         init_acc(load_bias(0));
         __syncthreads();
-        for (int l = 0; l < a.L; ++l) {
-            const bool more = l + 1 < a.L;
-            // the last request of a layer fetches the first unit of the next one (of this one again after the last
-            // layer: a harmless, valid load), so that every pass through the loop has the same loads in flight
-            const char* wq[2];
-            w_rows(more ? l + 1 : l, wq);
-            const int nU = l == 0 ? a.Opad >> 5 : WD / 32;
-            for (int u = 0; u < nU; u += 2) {
-                load_w(wfb, wp[0], wp[1], u + 1);
-                __builtin_amdgcn_sched_barrier(0);  // the requests stay ahead of the products they overlap with
-                unit(wfa, u, std::integral_constant<int, 0>{});
-                const bool last = u + 2 == nU;
-                load_w(wfa, last ? wq[0] : wp[0], last ? wq[1] : wp[1], last ? 0 : u + 2);
-                __builtin_amdgcn_sched_barrier(0);
-                unit(wfb, u + 1, std::integral_constant<int, 1>{});
-            }
-            wp[0] = wq[0];
-            wp[1] = wq[1];
+        constexpr std::integral_constant<int, 0> even{};
+        constexpr std::integral_constant<int, 1> odd{};
+        auto step = [&](u32x4_t (&next)[2][2], const char* w, int un, const u32x4_t (&wf)[2][2], int u, auto half) __attribute__((always_inline)) {
+            load_w(next, w, un);
+            __builtin_amdgcn_sched_barrier(0);  // the requests stay ahead of the products they overlap with
+            unit(wf, u, half);
+            __builtin_amdgcn_sched_barrier(0);
+        };
+        auto finish = [&](int l, bool more) __attribute__((always_inline)) {
             __syncthreads();  // every wave has read the layer's input for the last time
             const float bnext = load_bias(more ? l + 1 : l);
             {
@@ -1335,6 +1326,8 @@ __global__ __launch_bounds__(WD, 2) void k_mlp_fused_fwd(FusedFwdArgs a) {
                                 const int prow = it * 8 + (ol >> 3), pc = ol & 7;
                                 const uint4 u = *reinterpret_cast<const uint4*>(patch + prow * 128 + ((pc ^ (prow & 7)) * 16));
                                 const int gr = 32 * i + prow;
+                                // (a guard per store although whole row blocks are saved or not: the blocks it makes keep
+                                // the compiler from mixing row blocks, which spills)
                                 if (gr < srows) *reinterpret_cast<uint4*>(dst + ((int64_t)gr * WD + pc * 8) * 2) = u;
                             }
                             __builtin_amdgcn_wave_barrier();
@@ -1342,52 +1335,90 @@ __global__ __launch_bounds__(WD, 2) void k_mlp_fused_fwd(FusedFwdArgs a) {
                     }
                 }
             }
-            __syncthreads();  // the layer's output is complete in LDS
-            if (more) init_acc(bnext);
+            if (more) {
+                __syncthreads();  // the layer's output is complete in LDS
+                init_acc(bnext);
+            }
+        };
+        const char* wq = w_stream(a.L > 1 ? 1 : 0);
+        const int nU = a.Opad >> 5;
+        for (int u = 0; u < nU; u += 2) {
+            const bool last = u + 2 == nU;
+            step(wfb, wp, u + 1, wfa, u, even);
+            step(wfa, last ? wq : wp, last ? 0 : u + 2, wfb, u + 1, odd);
+        }
+        finish(0, a.L > 1);
+        for (int l = 1; l < a.L; ++l) {
+            const bool more = l + 1 < a.L;
+            wp = wq;
+            wq = w_stream(more ? l + 1 : l);
+            constexpr int NU = WD / 32;
+            load_w(wfb, wp, 1);
+            load_w(wfc, wp, 2);
+            for (int u = 0; u < NU - 4; u += 4) {
+                step(wfd, wp, u + 3, wfa, u, even);
+                step(wfa, wp, u + 4, wfb, u + 1, odd);
+                step(wfb, wp, u + 5, wfc, u + 2, even);
+                step(wfc, wp, u + 6, wfd, u + 3, odd);
+            }
+            step(wfd, wp, NU - 1, wfa, NU - 4, even);
+            step(wfa, wq, 0, wfb, NU - 3, odd);
+            unit(wfc, NU - 2, even);
+            __builtin_amdgcn_sched_barrier(0);
+            unit(wfd, NU - 1, odd);
+            finish(l, more);
         }
 
         // output layer: wave w takes rows 16 w .. 16 w + 15 of the tile with 16x16x32 products; lane (hl, hg)
         // supplies row hl / output hl at contraction chunk 4 u + hg and receives output hl of rows 4 hg + e
-        // (width 256: four waves, two passes of 64 rows)
+        // (width 256: four waves, two passes of 64 rows).  Its weights, biases and noise are requested ahead of the barrier
+        // that completes the last hidden layer: behind it they were three round trips to memory one after the other.
+        const int hl = lane & 15, hg = lane >> 4;
+        const bool b_ok = hl < a.out_dim;
+        const bool a_ok = hl < a.adim;  // lanes that hold an action mean
+        u32x4_t fb[WD / 32];
+        {
+            const bf16_t* wrow = a.theta_mat + (int64_t)p * a.mat_len + a.head_mat_off + (int64_t)(b_ok ? hl : 0) * WD;
+#pragma unroll
+            for (int u = 0; u < WD / 32; ++u) fb[u] = *reinterpret_cast<const u32x4_t*>(wrow + 8 * (4 * u + hg));
+        }
+        const float hbias = bp[a.head_vec_off + (b_ok ? hl : 0)];
+        float ls_p = 0.f;
+        if (a.eps && a_ok && !a.sig_state) ls_p = bp[a.logsig_off + hl];
+        float noise[8 / NW][4];
+        int64_t orow[8 / NW][4];
+#pragma unroll
+        for (int pass = 0; pass < 8 / NW; ++pass)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const int tr = 16 * (wave + NW * pass) + 4 * hg + e;
+                orow[pass][e] = a.rm.row(p, m0 + (tr < rows ? tr : 0));
+                noise[pass][e] = 0.f;
+                if (a.eps && a_ok && tr < rows) noise[pass][e] = a.eps[orow[pass][e] * a.adim + hl];
+            }
+        __syncthreads();  // the last hidden layer's output is complete in LDS
 #pragma unroll
         for (int pass = 0; pass < 8 / NW; ++pass) {
-            const int hl = lane & 15, hg = lane >> 4;
             const int wv = wave + NW * pass;
             const int r = 16 * wv + hl;
             const unsigned char* hrow = dlds + r * RB;
-            const bf16_t* wrow = a.theta_mat + (int64_t)p * a.mat_len + a.head_mat_off + (int64_t)hl * WD;
-            const bool b_ok = hl < a.out_dim;
             float4_t c = {0.f, 0.f, 0.f, 0.f}, c2 = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-            for (int half = 0; half < WD / 256; ++half) {
-                uint4 fa[8], fb[8];
-#pragma unroll
-                for (int u = 0; u < 8; ++u) {
-                    const int ch = 32 * half + 4 * u + hg;
-                    fa[u] = *reinterpret_cast<const uint4*>(hrow + ((ch ^ (r & 15)) * 16));
-                    fb[u] = make_uint4(0, 0, 0, 0);
-                    if (b_ok) fb[u] = *reinterpret_cast<const uint4*>(wrow + 8 * ch);
-                }
-#pragma unroll
-                for (int u = 0; u < 8; u += 2) {
-                    Mma16<bf16_t>::run(fa[u], fb[u], c);
-                    Mma16<bf16_t>::run(fa[u + 1], fb[u + 1], c2);
-                }
+            for (int u = 0; u < WD / 32; u += 2) {
+                const uint4 f0 = *reinterpret_cast<const uint4*>(hrow + (((4 * u + hg) ^ (r & 15)) * 16));
+                const uint4 f1 = *reinterpret_cast<const uint4*>(hrow + (((4 * u + 4 + hg) ^ (r & 15)) * 16));
+                Mma16<bf16_t>::run(f0, __builtin_bit_cast(uint4, fb[u]), c);
+                Mma16<bf16_t>::run(f1, __builtin_bit_cast(uint4, fb[u + 1]), c2);
             }
 #pragma unroll
             for (int e = 0; e < 4; ++e) c[e] += c2[e];
-            const float bias = b_ok ? bp[a.head_vec_off + hl] : 0.f;
-            const bool a_ok = hl < a.adim;  // lanes that hold an action mean
-            float ls_p = 0.f;
-            if (a.eps && a_ok && !a.sig_state) ls_p = bp[a.logsig_off + hl];
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
                 const int tr = 16 * wv + 4 * hg + e, m = m0 + tr;
                 const bool ok = (tr < rows) && b_ok;
-                const float z = c[e] + bias;
+                const float z = c[e] + hbias;
                 const float o = (hl < a.tanh_cols) ? tanhf(z) : z;
-                int64_t row = 0;
-                if (tr < rows) row = a.rm.row(p, m);
+                const int64_t row = orow[pass][e];
                 float term = 0.f;
                 // a state-dependent log sigma sits adim columns to the right, in the same group of 16 lanes
                 const float ls_s = __shfl(o, (lane & 48) | ((hl + a.adim) & 15), 64);
@@ -1396,7 +1427,7 @@ __global__ __launch_bounds__(WD, 2) void k_mlp_fused_fwd(FusedFwdArgs a) {
                     if (SAVE) a.saved_out[((int64_t)p * a.M + m) * OUT_PITCH + hl] = o;
                     if (a.eps && a_ok) {
                         const float ls = a.sig_state ? ls_s : ls_p;
-                        const float ep = a.eps[row * a.adim + hl];
+                        const float ep = noise[pass][e];
                         a.act[row * a.adim + hl] = o + expf(ls) * ep;
                         term = -0.5f * ep * ep - ls;
                     }
@@ -1410,7 +1441,7 @@ __global__ __launch_bounds__(WD, 2) void k_mlp_fused_fwd(FusedFwdArgs a) {
                 }
             }
         }
-        __syncthreads();  // the tile's last readers are done before the next tile is gathered
+        __syncthreads();  // the tile's last readers are done before the next tile is written
     }
 }
 
