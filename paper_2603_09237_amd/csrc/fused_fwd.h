@@ -77,10 +77,11 @@ __device__ inline int opaque(int v) {
 __device__ inline int swap_bits23(int i) { return (i & 0x13) | ((i & 4) << 1) | ((i & 8) >> 1); }
 
 // activation and derivative, rounded as the kernels that serve taller selections round them
-template <typename T, int ACT>
+enum { kActTanh = 0, kActSiluFused = 1, kActSiluPlain = 2 };
+template <typename T, int MODE>
 __device__ inline void fwd_act(float z, float& h, float& g) {
-    if (ACT == 0 || sizeof(T) == 2) {
-        act_pair<T, ACT>(z, h, g);
+    if (MODE == kActTanh || sizeof(T) == 2) {
+        act_pair<T, MODE == kActTanh ? 0 : 1, MODE == kActSiluFused>(z, h, g);
     } else {
 #pragma clang fp contract(off)
         const float s = __builtin_amdgcn_rcpf(1.f + __expf(-z)), z1 = 1.f + z;
@@ -89,6 +90,7 @@ __device__ inline void fwd_act(float z, float& h, float& g) {
         g = s * d;
     }
 }
+
 // WHOLE: the waves' features are the network's, W = 64 NW (as a condition at run time: 31.6 against 29.1 us for
 // one step of 32 preferences x 256 rows of width 256, the two kinds of requests waiting for each other's registers).
 // fp32 tiles of one and two row blocks stay within the 168 registers of three waves a SIMD: with 169 the update step of 10
@@ -315,7 +317,7 @@ __global__ __launch_bounds__(64 * NW, sizeof(T) == 4 && RT <= 2 ? 3 : 2) void k_
         }
     };
     auto epilogue = [&](int l, bool add_bias, auto act_tag) __attribute__((always_inline)) {
-        constexpr int ACT = decltype(act_tag)::value;
+        constexpr int MODE = decltype(act_tag)::value;
         const int mlim = SAVE ? a.Mp - m0 : 0;
         const int el = opaque(lane), er = B32 ? (el & 31) : (el & 15), eg = B32 ? el >> 5 : el >> 4;
         const int64_t at = (int64_t)l * a.lstride + ((int64_t)p * a.Mp + m0) * a.ldh * ES;
@@ -337,7 +339,7 @@ __global__ __launch_bounds__(64 * NW, sizeof(T) == 4 && RT <= 2 ? 3 : 2) void k_
                     for (int u = 0; u < VE; ++u) v[u] += sbias[l * WP + f + u];
                 }
 #pragma unroll
-                for (int u = 0; u < VE; ++u) fwd_act<T, ACT>(v[u], v[u], g[u]);
+                for (int u = 0; u < VE; ++u) fwd_act<T, MODE>(v[u], v[u], g[u]);
                 if (!WHOLE && f >= W) {
 #pragma unroll
                     for (int u = 0; u < VE; ++u) v[u] = g[u] = 0.f;
@@ -375,8 +377,9 @@ __global__ __launch_bounds__(64 * NW, sizeof(T) == 4 && RT <= 2 ? 3 : 2) void k_
     };
     auto finish_layer = [&](int l, bool add_bias) __attribute__((always_inline)) {
         __syncthreads();  // every wave has read the layer's input for the last time
-        if (a.act == 0) epilogue(l, add_bias, std::integral_constant<int, 0>{});
-        else epilogue(l, add_bias, std::integral_constant<int, 1>{});
+        if (a.act == 0) epilogue(l, add_bias, std::integral_constant<int, kActTanh>{});
+        else if (B32 && (perm || (narrow && l == 0))) epilogue(l, add_bias, std::integral_constant<int, kActSiluFused>{});
+        else epilogue(l, add_bias, std::integral_constant<int, kActSiluPlain>{});
     };
     const bool bias_last = B32 && !perm;
     __syncthreads();  // the observations and the biases are complete in LDS

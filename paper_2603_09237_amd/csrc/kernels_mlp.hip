@@ -213,7 +213,7 @@ struct EpiFwd {  // h = act(z + b) and, when SAVE, act'(z); compact [M][ld] stor
     __device__ inline void compute_biased(float v[8], Out& o) const {  // v already holds z + b
         float g[8];
 #pragma unroll
-        for (int i = 0; i < 8; ++i) act_pair<T, ACT>(v[i], v[i], g[i]);
+        for (int i = 0; i < 8; ++i) act_pair<T, ACT, false>(v[i], v[i], g[i]);
         o.h = pack8(v, (const T*)nullptr);
         if (SAVE) o.g = pack8(g, (const typename GradT<T>::type*)nullptr);
     }
@@ -1301,7 +1301,7 @@ __global__ __launch_bounds__(WD, 2) void k_mlp_fused_fwd(FusedFwdArgs a) {
                         const int j = o >> 1, h = o & 1;
                         float v[8], g[8];
 #pragma unroll
-                        for (int u = 0; u < 8; ++u) act_pair<bf16_t, ACT>(acc[i][j][8 * h + u], v[u], g[u]);
+                        for (int u = 0; u < 8; ++u) act_pair<bf16_t, ACT, true>(acc[i][j][8 * h + u], v[u], g[u]);
                         const int cc = 8 * wave + 4 * j + 2 * h + olg;
                         hq[o] = pack_chunk<bf16_t>(v);
                         *reinterpret_cast<uint4*>(hrow + i * (32 * RB) + ((cc ^ ox) * 16)) = hq[o];
@@ -1972,7 +1972,7 @@ __global__ __launch_bounds__(256) void k_first_fwd_narrow(const float* __restric
             if (r < FN_ROWS && m < Mp) {
                 float g[8];
 #pragma unroll
-                for (int u = 0; u < 8; ++u) act_pair<T, ACT>(acc[t][u], acc[t][u], g[u]);
+                for (int u = 0; u < 8; ++u) act_pair<T, ACT, true>(acc[t][u], acc[t][u], g[u]);
                 const int64_t at = ((int64_t)p * Mp + m) * W + 8 * chunk;
                 put8(H + at, pack8(acc[t], (const T*)nullptr));
                 if (SAVE) put8(G + at, pack8(g, (const typename GradT<T>::type*)nullptr));

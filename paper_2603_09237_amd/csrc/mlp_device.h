@@ -69,12 +69,11 @@ template <> struct Mma16<float> {
 };
 
 // h = act(z) and g = act'(z) of a network with GEMM inputs of type T.  SiLU uses the hardware exp2 / reciprocal
-// approximations (about 1 ulp each): s = 1 / (1 + e^-z), h = z s, g = s (1 + z - h).  In bf16 networks g is written as
-// s + z s - h s, two fused multiply-adds: no multiplication is left that the compiler could fuse in one kernel and not in
-// another, and an epilogue on the vector ALU saves an instruction per value.  (With the paired conversions below: 7 plain and
-// 2 transcendental instructions a value instead of 10.5 and 2; rollout forward of 64 preferences x 4224 rows of 4 x 512,
-// with what belongs to the evaluation sweep around it: 737 -> 713 us.)  tanh is the library's routine.
-template <typename T, int ACT>
+// approximations (about 1 ulp each): s = 1 / (1 + e^-z), h = z s, g = s (1 + z - h).  In bf16 networks every kernel that
+// may serve a layer rounds g alike: FUSED with h = z s inside a fused multiply-add, else without.  (Another rounding of g
+// moves the gradients by 4e-5, which six Adam steps, whose normalised step turns the sign of a gradient near zero into a
+// whole step, turned into 0.12.)  tanh is the library's routine.
+template <typename T, int ACT, bool FUSED>
 __device__ inline void act_pair(float z, float& h, float& g) {
     if (ACT == 0) {
         h = tanhf(z);
@@ -83,7 +82,15 @@ __device__ inline void act_pair(float z, float& h, float& g) {
         const float e = __expf(-z);
         const float s = __builtin_amdgcn_rcpf(1.f + e);
         h = z * s;
-        g = sizeof(T) == 2 ? __builtin_fmaf(-h, s, __builtin_fmaf(z, s, s)) : s * (1.f + z - h);
+        if (sizeof(T) == 4) {
+            g = s * (1.f + z - h);
+        } else if (FUSED) {
+            g = s * __builtin_fmaf(-z, s, 1.f + z);
+        } else {
+#pragma clang fp contract(off)
+            const float z1 = 1.f + z, d = z1 - h;
+            g = s * d;
+        }
     }
 }
 
@@ -102,15 +109,12 @@ __device__ inline Pack8 pack8(const float v[8], const bf16_t*) {
     return r;
 }
 __device__ inline Pack8 pack8(const float v[8], const gfix16_t*) {
-    // round((v + 1/8) / step) of values in (-0.125, 1.125): the unsigned-normalised conversion (round(65535 x) of two
-    // values in one instruction) of the scaled value
-    constexpr float a = (float)(1.0 / (65535.0 * GFIX_STEP)), b = (float)(0.125 / (65535.0 * GFIX_STEP));
-    uint32_t q[4];
+    // round(v / step + 1/8 / step); values are in (-0.125, 1.125) so the conversion cannot overflow
+    uint32_t q[8];
 #pragma unroll
-    for (int i = 0; i < 4; ++i)
-        q[i] = __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_pknorm_u16(__builtin_fmaf(v[2 * i], a, b), __builtin_fmaf(v[2 * i + 1], a, b)));
+    for (int i = 0; i < 8; ++i) q[i] = (uint32_t)(v[i] * (1.0f / GFIX_STEP) + (0.125f / GFIX_STEP + 0.5f));
     Pack8 r;
-    r.lo = make_uint4(q[0], q[1], q[2], q[3]);
+    r.lo = make_uint4(q[0] | (q[1] << 16), q[2] | (q[3] << 16), q[4] | (q[5] << 16), q[6] | (q[7] << 16));
     r.hi = make_uint4(0, 0, 0, 0);
     return r;
 }
