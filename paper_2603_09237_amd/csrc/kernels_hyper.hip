@@ -5,23 +5,22 @@
 #include "morlax_internal.h"
 #include "numeric.h"
 
-#define QW 64  // stacked-affine rows per wave of the df partial kernel (at least)
+#include <type_traits>
+
 #define DAB_COLS 128  // columns of dW one block of the fused dA/dB kernel walks
 #define DAB_NCT (DAB_COLS / 64)
 #define DAB_MAX_CS (2048 / DAB_COLS)  // column runs of the widest layer
 
 struct HyperWs {
     float *h1, *f, *fac, *dfac, *df_part, *df, *dz2, *dz1, *vecs, *da_part;
-    int32_t* mrow;  // [q_total] offset of row q of the stacked affine matrix inside hparams
+    int32_t *mrow, *crow;  // [q_total] offsets inside hparams of row q of the stacked affine matrix and of its constant
     int n_chunk, n_cs;
 };
 
-// stacked-affine rows per wave of the df partial kernel: QW, more when there are very many rows (strictly
-// affine hypernetwork), so that the partials stay a few thousand chunks
-static int df_chunk_rows(int64_t q_total) {
-    int qw = QW;
-    while ((q_total + qw - 1) / qw > 4096) qw *= 2;
-    return qw;
+// 64-row tiles of the stacked affine map per chunk of the df partials
+static int df_chunk_tiles(int64_t q_total) {
+    const int64_t t = ((q_total + 63) / 64 + 1023) / 1024;
+    return t < 4 ? 4 : (int)t;
 }
 
 static HyperWs hyper_ws_layout(const morlax_ctx* c, void* ws, int64_t* total) {
@@ -43,17 +42,15 @@ static HyperWs hyper_ws_layout(const morlax_ctx* c, void* ws, int64_t* total) {
     }
     L.fac = take(P * fac);
     L.dfac = take(P * fac);
-    {  // chunks of the df partials: each network with its own rows per chunk
-        L.n_chunk = 0;
-        for (int n = 0; n < 2; ++n) {
-            const int64_t qn = c->aff[n].q_total;
-            const int qw = df_chunk_rows(qn);
-            const int nc = (int)((qn + qw - 1) / qw);
-            L.n_chunk = nc > L.n_chunk ? nc : L.n_chunk;
-        }
+    L.n_chunk = 0;  // chunks of the df partials
+    for (int n = 0; n < 2; ++n) {
+        const int64_t nt = (c->aff[n].q_total + 63) / 64, per = df_chunk_tiles(c->aff[n].q_total);
+        const int nc = (int)((nt + per - 1) / per);
+        L.n_chunk = nc > L.n_chunk ? nc : L.n_chunk;
     }
     L.df_part = take((int64_t)L.n_chunk * P * F);
     L.mrow = reinterpret_cast<int32_t*>(take(q));
+    L.crow = reinterpret_cast<int32_t*>(take(q));
     {
         int wmax = c->d.width > c->d.obs_dim ? c->d.width : c->d.obs_dim;
         L.n_cs = (wmax + DAB_COLS - 1) / DAB_COLS;
@@ -97,63 +94,122 @@ __device__ inline int find_seg(const AffineTable& at, int q) {
     return s;
 }
 
-// Stacked affine map: row q for every preference.  Thread per row with its M row in registers; f[p, :]
-// is read through wave-uniform addresses (scalar loads), so the inner product costs no LDS traffic.
-template <typename TF>  // type of the leading rows' destination: float factors, or theta_mat (strictly affine form)
+// offsets inside hparams of row q of the stacked affine matrix and of its constant
+__device__ inline void row_offsets(const AffineTable& at, int F, int q, int32_t& m, int32_t& c) {
+    const int s = find_seg(at, q), loc = q - at.q0[s];
+    m = (int32_t)at.hp_m[s] + loc * F;
+    c = (int32_t)at.hp_c[s] + loc;
+}
+
+struct __attribute__((packed, aligned(4))) Run4 { float v[4]; };  // four consecutive floats at any 4-byte boundary
+
+__device__ inline void put_run4(float* d, const float (&v)[4]) {
+    Run4 r;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) r.v[j] = v[j];
+    *reinterpret_cast<Run4*>(d) = r;
+}
+__device__ inline void put_run4(bf16_t* d, const float (&v)[4]) {
+    typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
+    typedef bf16x4 bf16x4_any __attribute__((aligned(2)));
+    bf16x4 r;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) r[j] = (bf16_t)v[j];
+    *reinterpret_cast<bf16x4_any*>(d) = r;
+}
+
+// Stacked affine map out[p, q] = c[q] + sum_j M[q, j] f[p, j] on fp32 MFMA: a workgroup takes 64 rows q, wave w of it the
+// preferences 16 (w + 4 i) .. + 15.  The 64 rows of M go through LDS (pitch 4 KS + 1: the fragment reads of 16 lanes, four
+// rows apart, and of the four lane groups, neighbouring columns, are free of bank conflicts); lane ln of an accumulator
+// j holds row 4 ln + j, so that its four accumulators are four consecutive outputs of a preference and a store
+// instruction writes 256-byte runs.  Products are added to c in ascending j, four to an instruction, as the sequence of
+// fused multiply-adds of a thread per row would: the same bits.  That form (a thread's row of M from 32 loads a
+// 128-byte line apart, f through scalar loads whose latency nothing covered) took 45.9 us for 69 thousand rows x 128
+// preferences, of which the 36 MB of results are 7; here 22.2.  14.3 us at 15 thousand x 24, here 5.1.
+template <typename TF, int KS>  // TF: type of the leading rows' destination (float factors, or theta_mat: strictly affine form)
 __global__ __launch_bounds__(256) void k_hyper_affine(AffineTable at, const float* __restrict__ hp,
                                                      const float* __restrict__ f, TF* __restrict__ fac,
                                                      float* __restrict__ theta_vec, int P, int F,
                                                      int64_t fac_len, int64_t vec_len) {
-    const int q = blockIdx.x * 256 + threadIdx.x;
-    if (q >= at.q_total) return;
-    float m[MORLAX_MAX_F];
-    const int s = find_seg(at, q);
-    const int64_t loc = q - at.q0[s];
-    const float c = hp[at.hp_c[s] + loc];
-    const float* mr = hp + at.hp_m[s] + loc * F;
+    constexpr int K4 = 4 * KS;
+    __shared__ float sm[64][K4 + 1];
+    __shared__ float sc[64];
+    __shared__ int32_t so[64];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, ln = lane & 15, kg = lane >> 4;
+    const int q0 = blockIdx.x * 64, q4 = q0 + 4 * ln;
+    if (threadIdx.x < 64) {  // (rows past the end repeat the last one; they are not stored)
+        int32_t m, c;
+        row_offsets(at, F, q0 + lane < at.q_total ? q0 + lane : at.q_total - 1, m, c);
+        so[lane] = m;
+        sc[lane] = hp[c];
+    }
+    float a[KS];
+    auto load_f = [&](int p0) {
+        const float* fp = f + (int64_t)(p0 + ln < P ? p0 + ln : P - 1) * F;
 #pragma unroll
-    for (int j = 0; j < MORLAX_MAX_F; ++j) m[j] = (j < F) ? mr[j] : 0.f;
-    const bool lead = q < fac_len;
-    TF* dst_f = fac + q;
-    float* dst_v = theta_vec + (q - fac_len);
-    auto put = [&](int p, float a) {
-        if (lead) dst_f[(int64_t)p * fac_len] = cvt<TF>(a);
-        else dst_v[(int64_t)p * vec_len] = a;
+        for (int k = 0; k < KS; ++k) a[k] = fp[4 * k + kg < F ? 4 * k + kg : 0];
+#pragma unroll
+        for (int k = 0; k < KS; ++k) a[k] = 4 * k + kg < F ? a[k] : 0.f;
     };
-    // blockIdx.y takes a run of preferences (one run: more did not pay, the per-thread row of M is reloaded)
-    const int per = (P + gridDim.y - 1) / gridDim.y;
-    const int p_lo = blockIdx.y * per, p_hi = (p_lo + per < P) ? (p_lo + per) : P;
-    if (F == 32) {
-        // four preferences per batch: their feature rows (wave-uniform loads) are requested together
-        int p = p_lo;
-        for (; p + 4 <= p_hi; p += 4) {
-            float a[4] = {c, c, c, c};
+    if (16 * wave < P) load_f(16 * wave);
+    __syncthreads();
+    {
+        float v[K4 / 4];
 #pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                const float* fp = f + (int64_t)(p + u) * 32;
-#pragma unroll
-                for (int j = 0; j < 32; ++j) a[u] += m[j] * fp[j];
-            }
-#pragma unroll
-            for (int u = 0; u < 4; ++u) put(p + u, a[u]);
+        for (int i = 0; i < K4 / 4; ++i) {
+            const int idx = threadIdx.x + 256 * i, k = idx % K4;
+            v[i] = hp[so[idx / K4] + (k < F ? k : 0)];
         }
-        for (; p < p_hi; ++p) {
-            const float* fp = f + (int64_t)p * 32;
-            float a = c;
 #pragma unroll
-            for (int j = 0; j < 32; ++j) a += m[j] * fp[j];
-            put(p, a);
-        }
-    } else {
-        for (int p = p_lo; p < p_hi; ++p) {
-            const float* fp = f + (int64_t)p * F;
-            float a = c;
-#pragma unroll
-            for (int j = 0; j < MORLAX_MAX_F; ++j)
-                if (j < F) a += m[j] * fp[j];
-            put(p, a);
+        for (int i = 0; i < K4 / 4; ++i) {
+            const int idx = threadIdx.x + 256 * i, k = idx % K4;
+            sm[idx / K4][k] = k < F ? v[i] : 0.f;
         }
     }
+    __syncthreads();
+    float b[4][KS];
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+#pragma unroll
+        for (int k = 0; k < KS; ++k) b[j][k] = sm[4 * ln + j][4 * k + kg];
+    const bool lead = q4 + 3 < fac_len, vec = q4 >= fac_len && q4 + 3 < at.q_total;
+    for (int p0 = 16 * wave; p0 < P; p0 += 64) {
+        float4_t acc[4];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const float c = sc[4 * ln + j];
+            acc[j] = float4_t{c, c, c, c};
+        }
+#pragma unroll
+        for (int k = 0; k < KS; ++k)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) acc[j] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[k], b[j][k], acc[j], 0, 0, 0);
+        if (p0 + 64 < P) load_f(p0 + 64);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const int64_t p = p0 + 4 * kg + e;
+            if (p >= P) continue;
+            const float v[4] = {acc[0][e], acc[1][e], acc[2][e], acc[3][e]};
+            if (lead) {
+                put_run4(fac + p * fac_len + q4, v);
+            } else if (vec) {
+                put_run4(theta_vec + p * vec_len + (q4 - fac_len), v);
+            } else {  // the run crosses the end of the leading rows, or of the table
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    if (q4 + j < fac_len) fac[p * fac_len + q4 + j] = cvt<TF>(v[j]);
+                    else if (q4 + j < at.q_total) theta_vec[p * vec_len + (q4 + j - fac_len)] = v[j];
+                }
+            }
+        }
+    }
+}
+template <typename TF>
+static void launch_affine(const AffineTable& at, const float* hp, const float* f, TF* fac, float* theta_vec, int P, int F,
+                          int64_t fac_len, int64_t vec_len, hipStream_t s) {
+    const int nb = (at.q_total + 63) / 64;
+    if (F <= 32) k_hyper_affine<TF, 8><<<nb, 256, 0, s>>>(at, hp, f, fac, theta_vec, P, F, fac_len, vec_len);
+    else k_hyper_affine<TF, 16><<<nb, 256, 0, s>>>(at, hp, f, fac, theta_vec, P, F, fac_len, vec_len);
 }
 
 // W_l(p) = W0_l + A_l(p) B_l(p).  A block makes a 64 (d_out) x 128 (d_in) tile of one layer of one
@@ -230,8 +286,7 @@ static void run_trunk_and_affine(const morlax_ctx* c, int net, const float* hp, 
     const int P = c->d.P, F = c->d.hyper_width;
     k_hyper_trunk<<<P, 64, 0, s>>>(hp, w, L.h1, L.f, c->d.K, F, nd.hp_wh1, nd.hp_bh1, nd.hp_wh2, nd.hp_bh2);
     float* tv = theta_vec_or_null ? theta_vec_or_null : vec_scratch;
-    k_hyper_affine<float><<<dim3((at.q_total + 255) / 256, 1), 256, 0, s>>>(at, hp, L.f, L.fac, tv, P, F, nd.fac_len,
-                                                                            nd.vec_len);
+    launch_affine<float>(at, hp, L.f, L.fac, tv, P, F, nd.fac_len, nd.vec_len, s);
 }
 
 static MatTiles mat_tiles(const NetDev& nd) {
@@ -255,13 +310,10 @@ void launch_hypernet_fwd(const morlax_ctx* c, int net, const float* hparams, con
         const AffineTable& at = c->aff[net];
         const int P = c->d.P, F = c->d.hyper_width;
         k_hyper_trunk<<<P, 64, 0, s>>>(hparams, w, L.h1, L.f, c->d.K, F, nd.hp_wh1, nd.hp_bh1, nd.hp_wh2, nd.hp_bh2);
-        const dim3 grid((at.q_total + 255) / 256, 1);
         if (c->d.wdtype == 1)
-            k_hyper_affine<bf16_t><<<grid, 256, 0, s>>>(at, hparams, L.f, (bf16_t*)theta_mat, theta_vec, P, F, nd.fac_len,
-                                                        nd.vec_len);
+            launch_affine<bf16_t>(at, hparams, L.f, (bf16_t*)theta_mat, theta_vec, P, F, nd.fac_len, nd.vec_len, s);
         else
-            k_hyper_affine<float><<<grid, 256, 0, s>>>(at, hparams, L.f, (float*)theta_mat, theta_vec, P, F, nd.fac_len,
-                                                       nd.vec_len);
+            launch_affine<float>(at, hparams, L.f, (float*)theta_mat, theta_vec, P, F, nd.fac_len, nd.vec_len, s);
         return;
     }
     run_trunk_and_affine(c, net, hparams, w, L, theta_vec, nullptr, s);
@@ -276,23 +328,21 @@ void launch_hypernet_fwd(const morlax_ctx* c, int net, const float* hparams, con
 // ------------------------------------------------------------------------------------------------
 // Backward.
 
-// Offset inside hparams of every row of the stacked affine matrix (built once per call).
-__device__ inline void mrow_entry(const AffineTable& at, int32_t* __restrict__ mrow, int F, int q) {
-    if (q >= at.q_total) return;
-    const int s = find_seg(at, q);
-    mrow[q] = (int32_t)(at.hp_m[s] + (int64_t)(q - at.q0[s]) * F);
+// Offsets inside hparams of every row of the stacked affine matrix and of its constant (built once per call).
+__device__ inline void mrow_entry(const AffineTable& at, int32_t* __restrict__ mrow, int32_t* __restrict__ crow, int F, int q) {
+    if (q < at.q_total) row_offsets(at, F, q, mrow[q], crow[q]);
 }
-__global__ __launch_bounds__(256) void k_hyper_mrow(AffineTable at, int32_t* __restrict__ mrow, int F) {
-    mrow_entry(at, mrow, F, blockIdx.x * 256 + threadIdx.x);
+__global__ __launch_bounds__(256) void k_hyper_mrow(AffineTable at, int32_t* __restrict__ mrow, int32_t* __restrict__ crow, int F) {
+    mrow_entry(at, mrow, crow, F, blockIdx.x * 256 + threadIdx.x);
 }
 
 // dW0_l = sum_p dW_l(p): four consecutive elements per thread, p ascending.  The blocks behind the first n_base make
 // the row offsets of the stacked affine matrix, which would otherwise take a launch of 5 us on the dependent chain.
 __global__ __launch_bounds__(256) void k_hyper_dbase(NetDev nd, const float* __restrict__ dmat,
                                                     float* __restrict__ dhp, int P, int n_base, AffineTable at,
-                                                    int32_t* __restrict__ mrow, int F) {
+                                                    int32_t* __restrict__ mrow, int32_t* __restrict__ crow, int F) {
     if ((int)blockIdx.x >= n_base) {
-        mrow_entry(at, mrow, F, ((int)blockIdx.x - n_base) * 256 + threadIdx.x);
+        mrow_entry(at, mrow, crow, F, ((int)blockIdx.x - n_base) * 256 + threadIdx.x);
         return;
     }
     const int64_t e = ((int64_t)blockIdx.x * 256 + threadIdx.x) * 4;
@@ -478,250 +528,169 @@ __device__ inline float grad_row(const float* __restrict__ dfac, const float* __
     return (q < fac_len) ? dfac[p * fac_len + q] : dvec[p * vec_len + (q - fac_len)];
 }
 
-// dM[q, :] = sum_p g[p, q] f[p, :],  dc[q] = sum_p g[p, q]  (g: gradient of the stacked affine rows).
-// Thread per row, p ascending, f[p, :] through wave-uniform (scalar) loads.
-__global__ __launch_bounds__(256) void k_hyper_dM(AffineTable at, const float* __restrict__ f,
-                                                 const float* __restrict__ dfac, const float* __restrict__ dvec,
-                                                 float* __restrict__ dhp, int P, int F, int64_t fac_len,
-                                                 int64_t vec_len) {
-    const int q = blockIdx.x * 256 + threadIdx.x;
-    if (q >= at.q_total) return;
-    float acc[MORLAX_MAX_F];
-#pragma unroll
-    for (int j = 0; j < MORLAX_MAX_F; ++j) acc[j] = 0.f;
-    float dc = 0.f;
-    const float* src = (q < fac_len) ? (dfac + q) : (dvec + (q - fac_len));
-    const int64_t stride = (q < fac_len) ? fac_len : vec_len;
-    if (F == 32) {
-        // eight preferences per batch: their (strided, independent) loads are in flight together
-        int p = 0;
-        for (; p + 8 <= P; p += 8) {
-            float g[8];
-#pragma unroll
-            for (int u = 0; u < 8; ++u) g[u] = src[(int64_t)(p + u) * stride];
-#pragma unroll
-            for (int u = 0; u < 8; ++u) {
-                const float* fp = f + (int64_t)(p + u) * 32;
-                dc += g[u];
-#pragma unroll
-                for (int j = 0; j < 32; ++j) acc[j] += g[u] * fp[j];
-            }
-        }
-        for (; p < P; ++p) {
-            const float g = src[(int64_t)p * stride];
-            const float* fp = f + (int64_t)p * 32;
-            dc += g;
-#pragma unroll
-            for (int j = 0; j < 32; ++j) acc[j] += g * fp[j];
-        }
-    } else {
-        for (int p = 0; p < P; ++p) {
-            const float g = src[(int64_t)p * stride];
-            const float* fp = f + (int64_t)p * F;
-            dc += g;
-#pragma unroll
-            for (int j = 0; j < MORLAX_MAX_F; ++j)
-                if (j < F) acc[j] += g * fp[j];
-        }
-    }
-    const int s = find_seg(at, q);
-    const int64_t loc = q - at.q0[s];
-    dhp[at.hp_c[s] + loc] = dc;
-    float* mr = dhp + at.hp_m[s] + loc * F;
-#pragma unroll
-    for (int j = 0; j < MORLAX_MAX_F; ++j)
-        if (j < F) mr[j] = acc[j];
-}
-
-// df partials on fp32 MFMA: part[chunk, p, j] = sum over the chunk's qw stacked rows q of g[p, q] M[q, j].
-// One wave per chunk; lane (ln, kg) feeds rows p = 16 pt + ln of g and columns j = 16 jt + ln of M for the
-// contraction indices q0 + 4 kg + e, e = 0..3 (one MFMA per e).
-template <int JT>
-__global__ __launch_bounds__(256) void k_hyper_df_part(const float* __restrict__ hp, const int32_t* __restrict__ mrow,
-                                                      const float* __restrict__ dfac,
-                                                      const float* __restrict__ dvec, float* __restrict__ part,
-                                                      int P, int F, int64_t fac_len, int64_t vec_len, int q_total,
-                                                      int n_chunk, int qw) {
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, ln = lane & 15, kg = lane >> 4;
-    const int chunk = blockIdx.x * 4 + wave;
-    if (chunk >= n_chunk) return;
-    const int qa = chunk * qw;
-    const int qb = (qa + qw < q_total) ? (qa + qw) : q_total;
-    for (int p0 = 0; p0 < P; p0 += 128) {
-        float4_t acc[8][JT];
-#pragma unroll
-        for (int pt = 0; pt < 8; ++pt)
-#pragma unroll
-            for (int jt = 0; jt < JT; ++jt) acc[pt][jt] = float4_t{0.f, 0.f, 0.f, 0.f};
-        for (int q0 = qa; q0 < qb; q0 += 16) {
-            float b[JT][4];
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                const int q = q0 + 4 * kg + e;
-                const int off = (q < qb) ? mrow[q] : 0;
-#pragma unroll
-                for (int jt = 0; jt < JT; ++jt) {
-                    const int j = 16 * jt + ln;
-                    b[jt][e] = (q < qb && j < F) ? hp[off + j] : 0.f;
-                }
-            }
-#pragma unroll
-            for (int pt = 0; pt < 8; ++pt) {
-                const int pp = p0 + 16 * pt + ln;
-                if (p0 + 16 * pt < P) {  // uniform
-                    float a[4];
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) {
-                        const int q = q0 + 4 * kg + e;
-                        a[e] = (pp < P && q < qb) ? grad_row(dfac, dvec, pp, q, fac_len, vec_len) : 0.f;
-                    }
-#pragma unroll
-                    for (int e = 0; e < 4; ++e)
-#pragma unroll
-                        for (int jt = 0; jt < JT; ++jt)
-                            acc[pt][jt] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[e], b[jt][e], acc[pt][jt], 0, 0, 0);
-                }
-            }
-        }
-        // lane holds column j = 16 jt + ln of rows p = p0 + 16 pt + 4 kg + e
-#pragma unroll
-        for (int pt = 0; pt < 8; ++pt)
-#pragma unroll
-            for (int jt = 0; jt < JT; ++jt)
-#pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                    const int pp = p0 + 16 * pt + 4 * kg + e, j = 16 * jt + ln;
-                    if (pp < P && j < F) part[((int64_t)chunk * P + pp) * F + j] = acc[pt][jt][e];
-                }
-    }
-}
-
-// dM, dc and the df partials in one pass over the gradient g of the stacked affine rows (P <= 128):
+// From the gradient g of the stacked affine rows (fp32 MFMA, fixed orders):
 //   dM[q, :] = sum_p g[p, q] f[p, :],  dc[q] = sum_p g[p, q] (four interleaved shares of the preferences, each in
-//   order, added in a fixed order),  part[wg, p, j] = sum over the workgroup's rows q of g[p, q] M[q, j].
-// A workgroup walks DMF_TPW-or-more tiles of 64 rows.  The tile of g (all P preferences x 64 rows, every
-// preference's 64 values one 256-byte run) and the tile of M go through LDS and feed fp32 MFMAs twice: wave w
-// forms dM of rows 16 w .. 16 w + 15 (contraction over p), and accumulates, across the tiles, the df partial of
-// preferences 32 w .. 32 w + 31 (contraction over the tile's rows).  The next tiles of g and M are in flight in
-// registers meanwhile.  LDS pitches: g 68 floats (the df read, lane -> preference, is conflict free; the dM read
-// shares banks four ways), f and M 16 JT + 16 (conflict free).
+//   order, added in a fixed order),  part[chunk, p, j] = sum over the chunk's rows q of g[p, q] M[q, j].
+// A chunk is tpw tiles of 64 rows.  Its workgroups have two roles, and being neighbours they find g in the caches
+// the other has filled:
+//   dM: a wave takes one tile and all preferences, operands straight from memory: lane ln reads four consecutive rows
+//       of a preference, so that a request covers 256-byte runs; no LDS, no barrier, nothing carried between tiles.
+//   df: a workgroup takes 64 preferences (16 a wave) and walks the chunk's tiles in order; the tile of g (a preference's
+//       64 values one 256-byte run) and of M go through LDS, the next ones are in flight in registers meanwhile.
+//       LDS pitches: g 68 floats, M 16 JT + 16 (reads free of conflicts).
+// Both in one role (a workgroup walked four tiles, each a chain of LDS exchanges and products of one accumulator) took
+// 59 us for 69 thousand rows x 128 preferences, 35 us for 15 thousand x 24 and 23 us for 2600 x 4; now 39, 11.4, 10.7.
 #define DMF_Q 64
+#define DMF_P 64  // preferences of a df workgroup
 template <int JT>
-__global__ __launch_bounds__(256) void k_hyper_dM_df(AffineTable at, const float* __restrict__ hp,
-                                                    const int32_t* __restrict__ mrow, const float* __restrict__ f,
+__global__ __launch_bounds__(256) void k_hyper_dM_df(const float* __restrict__ hp, const int32_t* __restrict__ mrow,
+                                                    const int32_t* __restrict__ crow, const float* __restrict__ f,
                                                     const float* __restrict__ dfac, const float* __restrict__ dvec,
                                                     float* __restrict__ dhp, float* __restrict__ part, int P, int F,
-                                                    int64_t fac_len, int64_t vec_len, int q_total, int n_tiles, int tpw) {
-    constexpr int PD = 68, PJ = 16 * JT + 16, PP = 128;
-    __shared__ float Dl[PP][PD];
-    __shared__ float Fl[PP][PJ];
+                                                    int64_t fac_len, int64_t vec_len, int q_total, int n_tiles, int tpw,
+                                                    int n_df, int n_dm) {
+    constexpr int PD = 68, PJ = 16 * JT + 16;
+    __shared__ float Dl[DMF_P][PD];
     __shared__ float Ml[DMF_Q][PJ];
-    __shared__ float Cl[4][DMF_Q];
+    __shared__ int32_t Rl[2][DMF_Q];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, ln = lane & 15, kg = lane >> 4;
-    const int t_lo = blockIdx.x * tpw, t_hi = (t_lo + tpw < n_tiles) ? (t_lo + tpw) : n_tiles;
-    // f, zero-padded to 128 preferences and 16 JT features
-    for (int idx = threadIdx.x; idx < PP * 16 * JT; idx += 256) {
-        const int pp = idx / (16 * JT), j = idx % (16 * JT);
-        Fl[pp][j] = (pp < P && j < F) ? f[(int64_t)pp * F + j] : 0.f;
+    const int chunk = blockIdx.x / (n_df + n_dm), role = blockIdx.x % (n_df + n_dm);
+    const int t_lo = chunk * tpw, t_hi = (t_lo + tpw < n_tiles) ? (t_lo + tpw) : n_tiles;
+    if (role >= n_df) {  // dM and dc of one tile a wave (no barrier: the waves are on their own)
+        const int tile = t_lo + 4 * (role - n_df) + wave;
+        if (tile >= t_hi) return;
+        const int q0 = tile * DMF_Q, q4 = q0 + 4 * ln;
+        float4_t acc[4][JT];
+        float dc[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int mt = 0; mt < 4; ++mt)
+#pragma unroll
+            for (int jt = 0; jt < JT; ++jt) acc[mt][jt] = float4_t{0.f, 0.f, 0.f, 0.f};
+        // whole: the tile's rows are all leading rows, or all theta_vec rows; the others are read one by one
+        auto walk = [&](auto whole) {
+            constexpr bool WHOLE = decltype(whole)::value;
+            const float* src = q0 < fac_len ? dfac + q4 : dvec + (q4 - fac_len);
+            const int64_t stride = q0 < fac_len ? fac_len : vec_len;
+            constexpr int U = 4;  // contraction steps whose operands are requested together
+            for (int k0 = 0; 4 * k0 < P; k0 += U) {
+                Run4 g[U];
+                float b[U][JT];
+#pragma unroll
+                for (int u = 0; u < U; ++u) {
+                    const int p = 4 * (k0 + u) + kg, pc = p < P ? p : P - 1;
+                    if constexpr (WHOLE) {
+                        g[u] = *reinterpret_cast<const Run4*>(src + pc * stride);
+                    } else {
+#pragma unroll
+                        for (int mt = 0; mt < 4; ++mt)
+                            g[u].v[mt] = q4 + mt < q_total ? grad_row(dfac, dvec, pc, q4 + mt, fac_len, vec_len) : 0.f;
+                    }
+#pragma unroll
+                    for (int jt = 0; jt < JT; ++jt) b[u][jt] = f[(int64_t)pc * F + (16 * jt + ln < F ? 16 * jt + ln : 0)];
+                }
+#pragma unroll
+                for (int u = 0; u < U; ++u) {
+                    const bool ok = 4 * (k0 + u) + kg < P;
+#pragma unroll
+                    for (int jt = 0; jt < JT; ++jt) b[u][jt] = ok && 16 * jt + ln < F ? b[u][jt] : 0.f;
+#pragma unroll
+                    for (int mt = 0; mt < 4; ++mt) {
+                        const float v = ok ? g[u].v[mt] : 0.f;
+                        dc[mt] += v;
+#pragma unroll
+                        for (int jt = 0; jt < JT; ++jt)
+                            acc[mt][jt] = __builtin_amdgcn_mfma_f32_16x16x4f32(v, b[u][jt], acc[mt][jt], 0, 0, 0);
+                    }
+                }
+            }
+        };
+        if (q0 + DMF_Q <= fac_len || (q0 >= fac_len && q0 + DMF_Q <= q_total)) walk(std::true_type{});
+        else walk(std::false_type{});
+        // lane holds feature j = 16 jt + ln of rows q0 + 4 (4 kg + e) + mt
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+#pragma unroll
+            for (int mt = 0; mt < 4; ++mt) {
+                const int q = q0 + 16 * kg + 4 * e + mt;
+                if (q < q_total) {
+                    float* mr = dhp + mrow[q];
+#pragma unroll
+                    for (int jt = 0; jt < JT; ++jt)
+                        if (16 * jt + ln < F) mr[16 * jt + ln] = acc[mt][jt][e];
+                }
+            }
+        // dc: lane group kg holds share kg of rows q4 .. q4 + 3
+        float mine = 0.f;
+#pragma unroll
+        for (int mt = 0; mt < 4; ++mt) {
+            dc[mt] += __shfl_xor(dc[mt], 16, 64);
+            dc[mt] += __shfl_xor(dc[mt], 32, 64);
+            if (kg == mt) mine = dc[mt];
+        }
+        if (q4 + kg < q_total) dhp[crow[q4 + kg]] = mine;
+        return;
     }
-    // a thread's share of a tile of g (row qq = lane of preferences wave, wave + 4, ...) and of the tile of M
-    // (piece idx = thread + 256 i of the 64 x 16 JT values), requested one tile ahead
+    // df partial of preferences p0 .. p0 + 15 (this wave's)
+    const int pb = role * DMF_P, p0 = pb + 16 * wave;
     constexpr int MPT = DMF_Q * 16 * JT / 256;
-    float nxt[PP / 4], mnx[MPT];
+    float nxt[DMF_P / 4], mnx[MPT];
+    auto row_of = [&](int tile) {  // (threads 0 .. 63) offset of a row of M
+        const int q = tile * DMF_Q + (int)threadIdx.x;
+        return tile < t_hi && threadIdx.x < DMF_Q && q < q_total ? mrow[q] : 0;
+    };
     auto fetch = [&](int tile) {
         const int q = tile * DMF_Q + lane;
 #pragma unroll
-        for (int i = 0; i < PP / 4; ++i) {
-            const int pp = wave + 4 * i;
+        for (int i = 0; i < DMF_P / 4; ++i) {
+            const int pp = pb + wave + 4 * i;
             nxt[i] = (pp < P && q < q_total) ? grad_row(dfac, dvec, pp, q, fac_len, vec_len) : 0.f;
         }
 #pragma unroll
         for (int i = 0; i < MPT; ++i) {
-            const int idx = threadIdx.x + 256 * i, qq = idx / (16 * JT), j = idx % (16 * JT), qm = tile * DMF_Q + qq;
-            mnx[i] = (qm < q_total && j < F) ? hp[mrow[qm] + j] : 0.f;
+            const int idx = threadIdx.x + 256 * i, qq = idx / (16 * JT), j = idx % (16 * JT);
+            mnx[i] = (tile * DMF_Q + qq < q_total && j < F) ? hp[Rl[tile & 1][qq] + j] : 0.f;
         }
     };
-    float4_t accF[2][JT];
+    float4_t accF[JT];
 #pragma unroll
-    for (int u = 0; u < 2; ++u)
-#pragma unroll
-        for (int jt = 0; jt < JT; ++jt) accF[u][jt] = float4_t{0.f, 0.f, 0.f, 0.f};
-    if (t_lo < t_hi) fetch(t_lo);
+    for (int jt = 0; jt < JT; ++jt) accF[jt] = float4_t{0.f, 0.f, 0.f, 0.f};
+    if (threadIdx.x < DMF_Q) Rl[t_lo & 1][threadIdx.x] = row_of(t_lo);
+    int32_t rnext = row_of(t_lo + 1);
+    __syncthreads();
+    fetch(t_lo);
     for (int tile = t_lo; tile < t_hi; ++tile) {
-        const int q0 = tile * DMF_Q;
-        __syncthreads();  // the previous tile's readers are done (first pass: orders nothing that matters)
-        {
-            float c = 0.f;  // this wave's share of dc: its preferences in order
+        __syncthreads();  // the previous tile's readers are done
 #pragma unroll
-            for (int i = 0; i < PP / 4; ++i) {
-                Dl[wave + 4 * i][lane] = nxt[i];
-                c += nxt[i];
-            }
-            Cl[wave][lane] = c;
-        }
+        for (int i = 0; i < DMF_P / 4; ++i) Dl[wave + 4 * i][lane] = nxt[i];
 #pragma unroll
         for (int i = 0; i < MPT; ++i) {
             const int idx = threadIdx.x + 256 * i;
             Ml[idx / (16 * JT)][idx % (16 * JT)] = mnx[i];
         }
-        if (tile + 1 < t_hi) fetch(tile + 1);
+        if (threadIdx.x < DMF_Q) Rl[(tile + 1) & 1][threadIdx.x] = rnext;
         __syncthreads();
-        // dM of rows q0 + 16 wave + (0..15): contraction over the preferences
-        {
-            float4_t accM[JT];
+        if (tile + 1 < t_hi) {
+            fetch(tile + 1);
+            rnext = row_of(tile + 2);
+        }
+        if (p0 < P) {
 #pragma unroll
-            for (int jt = 0; jt < JT; ++jt) accM[jt] = float4_t{0.f, 0.f, 0.f, 0.f};
-            const int kmax = (P + 3) / 4;
-            for (int kk = 0; kk < kmax; ++kk) {
-                const float a = Dl[4 * kk + kg][16 * wave + ln];
+            for (int kk = 0; kk < DMF_Q / 4; ++kk) {
+                const float a = Dl[16 * wave + ln][4 * kk + kg];
 #pragma unroll
                 for (int jt = 0; jt < JT; ++jt)
-                    accM[jt] = __builtin_amdgcn_mfma_f32_16x16x4f32(a, Fl[4 * kk + kg][16 * jt + ln], accM[jt], 0, 0, 0);
-            }
-            // lane holds feature j = 16 jt + ln of rows q0 + 16 wave + 4 kg + e
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                const int q = q0 + 16 * wave + 4 * kg + e;
-                if (q < q_total) {
-                    float* mr = dhp + mrow[q];
-#pragma unroll
-                    for (int jt = 0; jt < JT; ++jt)
-                        if (16 * jt + ln < F) mr[16 * jt + ln] = accM[jt][e];
-                }
-            }
-        }
-        // dc: the four waves' shares, in wave order
-        if (threadIdx.x < DMF_Q && q0 + (int)threadIdx.x < q_total) {
-            const int q = q0 + threadIdx.x;
-            const int sg = find_seg(at, q);
-            dhp[at.hp_c[sg] + (q - at.q0[sg])] =
-                (Cl[0][threadIdx.x] + Cl[1][threadIdx.x]) + (Cl[2][threadIdx.x] + Cl[3][threadIdx.x]);
-        }
-        // df partial of preferences 32 wave + (0..31): contraction over the tile's rows
-#pragma unroll
-        for (int kk = 0; kk < DMF_Q / 4; ++kk) {
-            float b[JT];
-#pragma unroll
-            for (int jt = 0; jt < JT; ++jt) b[jt] = Ml[4 * kk + kg][16 * jt + ln];
-#pragma unroll
-            for (int u = 0; u < 2; ++u) {
-                const float a = Dl[32 * wave + 16 * u + ln][4 * kk + kg];
-#pragma unroll
-                for (int jt = 0; jt < JT; ++jt)
-                    accF[u][jt] = __builtin_amdgcn_mfma_f32_16x16x4f32(a, b[jt], accF[u][jt], 0, 0, 0);
+                    accF[jt] = __builtin_amdgcn_mfma_f32_16x16x4f32(a, Ml[4 * kk + kg][16 * jt + ln], accF[jt], 0, 0, 0);
             }
         }
     }
-    // lane holds feature j = 16 jt + ln of preferences 32 wave + 16 u + 4 kg + e
+    // lane holds feature j = 16 jt + ln of preferences p0 + 4 kg + e
 #pragma unroll
-    for (int u = 0; u < 2; ++u)
+    for (int jt = 0; jt < JT; ++jt)
 #pragma unroll
-        for (int jt = 0; jt < JT; ++jt)
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                const int pp = 32 * wave + 16 * u + 4 * kg + e, j = 16 * jt + ln;
-                if (pp < P && j < F) part[((int64_t)blockIdx.x * P + pp) * F + j] = accF[u][jt][e];
-            }
+        for (int e = 0; e < 4; ++e) {
+            const int pp = p0 + 4 * kg + e, j = 16 * jt + ln;
+            if (pp < P && j < F) part[((int64_t)chunk * P + pp) * F + j] = accF[jt][e];
+        }
 }
 
 // Trunk backward, stage 1: df[p, j] = sum_chunk part; dz2 = df * (1 - f^2); dz1 = (dz2 Wh2) * (1 - h1^2).  A block
@@ -845,7 +814,7 @@ void launch_hypernet_bwd(const morlax_ctx* c, int net, const float* hparams, con
         // recompute f and the factors; the theta_vec rows of the affine map land in a scratch nobody reads
         if (!kept) run_trunk_and_affine(c, net, hparams, w, L, nullptr, L.vecs, s);
         const int n_base = (int)((nd.mat_len / 4 + 255) / 256);
-        k_hyper_dbase<<<n_base + (at.q_total + 255) / 256, 256, 0, s>>>(nd, dtheta_mat, dhparams, P, n_base, at, L.mrow, F);
+        k_hyper_dbase<<<n_base + (at.q_total + 255) / 256, 256, 0, s>>>(nd, dtheta_mat, dhparams, P, n_base, at, L.mrow, L.crow, F);
     }
     if (r > 0) {
         DabWork wk;
@@ -865,33 +834,16 @@ void launch_hypernet_bwd(const morlax_ctx* c, int net, const float* hparams, con
         if (split)
             k_hyper_dA_merge<<<dim3((int)((nd.fac_len + 255) / 256), P), 256, 0, s>>>(nd, L.da_part, L.dfac, r, P);
     }
-    if (affine) k_hyper_mrow<<<(at.q_total + 255) / 256, 256, 0, s>>>(at, L.mrow, F);
-    int n_chunk;
-    if (P <= 128) {
-        // one pass over the gradient of the stacked rows; at least four tiles per workgroup, about a thousand
-        // workgroups at most (never more partial slots than the layout holds)
-        const int n_tiles = (at.q_total + DMF_Q - 1) / DMF_Q;
-        int tpw = (n_tiles + 1023) / 1024;
-        if (tpw < 4) tpw = 4;
-        n_chunk = (n_tiles + tpw - 1) / tpw;
-        if (F <= 32)
-            k_hyper_dM_df<2><<<n_chunk, 256, 0, s>>>(at, hparams, L.mrow, L.f, dlead, dtheta_vec, dhparams, L.df_part, P, F,
-                                                     nd.fac_len, nd.vec_len, at.q_total, n_tiles, tpw);
-        else
-            k_hyper_dM_df<4><<<n_chunk, 256, 0, s>>>(at, hparams, L.mrow, L.f, dlead, dtheta_vec, dhparams, L.df_part, P, F,
-                                                     nd.fac_len, nd.vec_len, at.q_total, n_tiles, tpw);
-    } else {
-        k_hyper_dM<<<(at.q_total + 255) / 256, 256, 0, s>>>(at, L.f, dlead, dtheta_vec, dhparams, P, F, nd.fac_len,
-                                                           nd.vec_len);
-        const int qw = df_chunk_rows(at.q_total);
-        n_chunk = (at.q_total + qw - 1) / qw;
-        if (F <= 32)
-            k_hyper_df_part<2><<<(n_chunk + 3) / 4, 256, 0, s>>>(hparams, L.mrow, dlead, dtheta_vec, L.df_part, P, F,
-                                                                nd.fac_len, nd.vec_len, at.q_total, n_chunk, qw);
-        else
-            k_hyper_df_part<4><<<(n_chunk + 3) / 4, 256, 0, s>>>(hparams, L.mrow, dlead, dtheta_vec, L.df_part, P, F,
-                                                                nd.fac_len, nd.vec_len, at.q_total, n_chunk, qw);
-    }
+    if (affine) k_hyper_mrow<<<(at.q_total + 255) / 256, 256, 0, s>>>(at, L.mrow, L.crow, F);
+    // at least four tiles per chunk, about a thousand chunks at most
+    const int n_tiles = (at.q_total + DMF_Q - 1) / DMF_Q, tpw = df_chunk_tiles(at.q_total);
+    const int n_chunk = (n_tiles + tpw - 1) / tpw, n_df = (P + DMF_P - 1) / DMF_P, n_dm = (tpw + 3) / 4;
+    auto dM_df = [&](auto kernel) {
+        kernel<<<n_chunk * (n_df + n_dm), 256, 0, s>>>(hparams, L.mrow, L.crow, L.f, dlead, dtheta_vec, dhparams, L.df_part, P,
+                                                       F, nd.fac_len, nd.vec_len, at.q_total, n_tiles, tpw, n_df, n_dm);
+    };
+    if (F <= 32) dM_df(k_hyper_dM_df<2>);
+    else dM_df(k_hyper_dM_df<4>);
     const int ppb = 64 / F;  // preferences per block (F <= 64)
     k_hyper_trunk_bwd_a<<<(P + ppb - 1) / ppb, 256, 0, s>>>(hparams, L.df_part, n_chunk, L.f, L.h1, L.dz2, L.dz1, P, F,
                                                            nd.hp_wh2);

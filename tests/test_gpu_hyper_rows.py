@@ -16,3 +16,19 @@ CASES = [scaled(RAGGED, name=f"P{p}", P=p, N=2 * p) for p in (2, 15, 16, 17, 32,
 @pytest.mark.parametrize("cfg", CASES, ids=lambda c: c.name)
 def test_stacked_row_gradients_at_group_and_tile_edges(cfg, torch, binding):  # noqa: F811
     parity.test_hypernet_bwd_matches_oracle(cfg, torch, binding)
+
+
+# feature widths at the edges of the contraction steps, factor and output widths that leave runs of four rows across
+# segment ends and row ends at odd offsets, more than 64 preferences beside them, and enough rows (strictly affine, more
+# than 4096 tiles of 64) for chunks of more than four tiles
+ROW_CASES = [scaled(RAGGED, name=f"F{F}-r{r}-A{A}-O{O}-W{W}-P{P}", hyper_width=F, rank=r, act_dim=A, obs_dim=O, width=W, P=P, N=2 * P)
+             for F, r, A, O, W, P in ((1, 3, 3, 5, 16, 3), (7, 1, 1, 7, 48, 5), (31, 5, 3, 9, 32, 66), (32, 4, 2, 8, 32, 70),
+                                      (33, 3, 5, 11, 16, 4), (64, 7, 3, 13, 80, 129), (32, -1, 3, 5, 48, 6), (33, -1, 5, 7, 16, 67))]
+ROW_CASES += [scaled(RAGGED, name=f"many-rows-bf16-{b}", hyper_width=3, rank=-1, obs_dim=61, width=272, n_hidden=5, P=3, N=6, wdtype=b)
+              for b in (0, 1)]
+
+
+@pytest.mark.parametrize("cfg", ROW_CASES, ids=lambda c: c.name)
+def test_stacked_rows_and_their_gradients_at_odd_sizes(cfg, torch, binding):  # noqa: F811
+    parity.test_hypernet_fwd_matches_oracle(cfg, torch, binding)
+    parity.test_hypernet_bwd_matches_oracle(cfg, torch, binding)

@@ -347,7 +347,7 @@ def test_hypernet_fwd_matches_oracle(cfg, torch, binding):
             assert same > 0.999, same
 
 
-# (more than 128 preferences: the backward's two-pass dM / df kernels instead of the fused one)
+# (130 preferences: more than two groups of 64 in the gradient of the stacked rows)
 @pytest.mark.parametrize("cfg", all_cfgs() + [RAGGED, scaled(RAGGED, name="rank0", rank=0),
                                              scaled(RAGGED, name="ragged-P130", P=130, N=260),
                                              scaled(RAGGED, name="ragged-P130-affine", P=130, N=260, rank=-1)] + AFFINE_CASES,
