@@ -1499,12 +1499,6 @@ static GemmProf::Rec* prof_take(const morlax_ctx* c, int kind, double flops) {
     return r;
 }
 
-// the launches since the last record's end belong to it too (a merge after a split GEMM)
-static void prof_extend(const morlax_ctx* c, hipStream_t s) {
-    GemmProf* pr = c->prof;
-    if (pr && pr->on && pr->used > 0) (void)hipEventRecord(pr->recs[pr->used - 1].b, s);
-}
-
 // The direct-to-LDS kernel serves bf16 GEMMs of compact operands whose contraction length is a multiple
 // of 32 and whose addresses are 16-byte aligned; everything else runs k_grouped_gemm.
 template <int KIND>
@@ -1671,114 +1665,27 @@ __global__ __launch_bounds__(256) void k_head_fwd(const T* __restrict__ Hin, con
     }
 }
 
-// dz_L = dout * (1 - mu^2) for the tanh head (else dout), gathered once per call into compact rows
-// dzh[p][m][0..15] (unrounded, zero beyond out_dim) for the two kernels below; the bias gradient
-// db_L(p)[j] = sum_m dz_L[m, j] leaves as per-block partials pb[p][block][j] (256 rows per block, summed in a
-// fixed order).
-template <typename T>
-__global__ __launch_bounds__(256) void k_head_dzh(const float* __restrict__ dout, const float* __restrict__ saved_out,
-                                                 float* __restrict__ dzh, float* __restrict__ pb, int out_dim, int M,
-                                                 RowMap rm, int tanh_cols) {
-    __shared__ float red[4][MORLAX_MAX_OUT];
-    const int p = blockIdx.y, m = blockIdx.x * 256 + threadIdx.x;
-    float d[MORLAX_MAX_OUT];
+// ---- backward of the output layer, one launch -----------------------------------------------------------------
+// dz_L = dout * (1 - mu^2) for the tanh head (else dout): four columns of row m of preference p, zero beyond out_dim
+struct HeadDz {
+    const float *dout, *saved_out;  // time-major [.., out_dim]; compact [P][M][OUT_PITCH]
+    int32_t out_dim, tanh_cols, M;
+    RowMap rm;
+    struct Raw { float d[4], mu[4]; };
+    __device__ inline void request(int p, int m, int q, Raw& r) const {
+        const float* src = dout + rm.row(p, m) * out_dim;
+        const float4 mu = *reinterpret_cast<const float4*>(saved_out + ((int64_t)p * M + m) * OUT_PITCH + 4 * q);
+        r.mu[0] = mu.x; r.mu[1] = mu.y; r.mu[2] = mu.z; r.mu[3] = mu.w;
 #pragma unroll
-    for (int j = 0; j < MORLAX_MAX_OUT; ++j) d[j] = 0.f;
-    if (m < M) {
-        const int64_t row = rm.row(p, m);
-#pragma unroll
-        for (int j = 0; j < MORLAX_MAX_OUT; ++j) {
-            if (j < out_dim) {
-                d[j] = dout[row * out_dim + j];
-                if (j < tanh_cols) {
-                    const float mu = saved_out[((int64_t)p * M + m) * OUT_PITCH + j];
-                    d[j] *= (1.f - mu * mu);
-                }
-            }
-        }
-        float4* dst = reinterpret_cast<float4*>(dzh + ((int64_t)p * M + m) * MORLAX_MAX_OUT);
-#pragma unroll
-        for (int q = 0; q < MORLAX_MAX_OUT / 4; ++q) dst[q] = make_float4(d[4 * q], d[4 * q + 1], d[4 * q + 2], d[4 * q + 3]);
+        for (int e = 0; e < 4; ++e) r.d[e] = src[4 * q + e < out_dim ? 4 * q + e : 0];
     }
-    // bias partials: butterfly inside each wave, then the four waves in order
-#pragma unroll
-    for (int j = 0; j < MORLAX_MAX_OUT; ++j) {
-        float v = d[j];
-#pragma unroll
-        for (int o = 32; o > 0; o >>= 1) v += __shfl_down(v, o, 64);
-        if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6][j] = v;
+    __device__ inline float value(const Raw& r, int q, int e, bool ok) const {
+        const int j = 4 * q + e;
+        float d = ok && j < out_dim ? r.d[e] : 0.f;
+        if (j < tanh_cols) d *= (1.f - r.mu[e] * r.mu[e]);
+        return ok ? d : 0.f;
     }
-    __syncthreads();
-    if (threadIdx.x < MORLAX_MAX_OUT)
-        pb[((int64_t)p * gridDim.x + blockIdx.x) * MORLAX_MAX_OUT + threadIdx.x] =
-            (red[0][threadIdx.x] + red[1][threadIdx.x]) + (red[2][threadIdx.x] + red[3][threadIdx.x]);
-}
-
-// dZ_{L-1}[m, i] = (sum_j dz_L[m, j] W_L(p)[j, i]) * act'(z_{L-1})[m, i].  Block: 64 rows x 128 columns of
-// one preference; thread: 4 rows x 8 columns.
-template <typename T>
-__global__ __launch_bounds__(256) void k_head_bwd_dz(const float* __restrict__ dzh,
-                                                    const T* __restrict__ theta_mat, int64_t mat_len,
-                                                    int64_t mat_off,
-                                                    const typename GradT<T>::type* __restrict__ G,
-                                                    T* __restrict__ dZ, float* __restrict__ part,
-                                                    int W, int out_dim, int M, int Mp) {
-    __shared__ float sdz[64][MORLAX_MAX_OUT];
-    __shared__ float red[16][128];
-    const int p = blockIdx.z, m0 = blockIdx.y * 64, i0 = blockIdx.x * 128;
-    for (int idx = threadIdx.x; idx < 64 * MORLAX_MAX_OUT; idx += 256) {
-        const int mm = idx / MORLAX_MAX_OUT, j = idx % MORLAX_MAX_OUT;
-        float d = 0.f;
-        if (m0 + mm < M) d = to_f(cvt<T>(dzh[((int64_t)p * M + m0 + mm) * MORLAX_MAX_OUT + j]));  // GEMM input rounding
-        sdz[mm][j] = d;
-    }
-    __syncthreads();
-    const int tr = (threadIdx.x / 16) * 4, ti = i0 + (threadIdx.x % 16) * 8;
-    const bool live = ti < W;
-    float acc[4][8];
-#pragma unroll
-    for (int a = 0; a < 4; ++a)
-#pragma unroll
-        for (int b = 0; b < 8; ++b) acc[a][b] = 0.f;
-    const T* wl = theta_mat + (int64_t)p * mat_len + mat_off;
-    for (int j = 0; j < out_dim && live; ++j) {
-        float wv[8];
-#pragma unroll
-        for (int b = 0; b < 8; ++b) wv[b] = to_f(wl[(int64_t)j * W + ti + b]);
-#pragma unroll
-        for (int a = 0; a < 4; ++a) {
-            const float d = sdz[tr + a][j];
-#pragma unroll
-            for (int b = 0; b < 8; ++b) acc[a][b] += d * wv[b];
-        }
-    }
-    float cs[8];
-#pragma unroll
-    for (int b = 0; b < 8; ++b) cs[b] = 0.f;
-#pragma unroll
-    for (int a = 0; a < 4; ++a) {
-        const int m = m0 + tr + a;
-        if (m >= Mp || !live) continue;  // (rows M .. Mp: their dz is zero, and so is dZ)
-        const int64_t o = ((int64_t)p * Mp + m) * W + ti;
-        float v[8];
-#pragma unroll
-        for (int b = 0; b < 8; ++b) {
-            v[b] = acc[a][b] * to_f(G[o + b]);
-            cs[b] += v[b];
-        }
-        store8(dZ + o, v);
-    }
-    // partial column sums of the unrounded dZ over this block's 64 rows (row groups in fixed order)
-#pragma unroll
-    for (int b = 0; b < 8; ++b) red[threadIdx.x / 16][(threadIdx.x % 16) * 8 + b] = cs[b];
-    __syncthreads();
-    if (threadIdx.x < 128 && i0 + threadIdx.x < W) {
-        float v = 0.f;
-#pragma unroll
-        for (int q = 0; q < 16; ++q) v += red[q][threadIdx.x];
-        part[((int64_t)p * gridDim.y + blockIdx.y) * W + i0 + threadIdx.x] = v;
-    }
-}
+};
 
 // Transposing 8-byte LDS read: the 16 lanes of a group address the 64-bit words of a 4 x 16 block of 16-bit values
 // -- lane 4 e + c the word of contraction index e that holds columns 4 c .. 4 c + 3 -- and lane b of the group
@@ -1789,29 +1696,136 @@ __device__ inline short4_t lds_tr4(const E* word) {
     return __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s4*)(word));
 }
 
-// dW_L(p)[j, i] = sum_m dz_L[m, j] h_{L-1}[m, i] in two stages.  Stage 1: a block takes one of HB_SPLIT row
-// ranges of one preference and 128 columns, and walks its rows 128 at a time: the dz rows (rounded to the
-// GEMM input type) and the h tile sit in LDS, the next h tile is already on its way in registers; wave w
-// multiplies dz^T [16 x 128] by h [128 x columns 32 w .. 32 w + 31]: bf16 networks with 16x16x16 bf16 MFMAs (dz^T
-// staged with the contraction contiguous, h read through transposing LDS reads), fp32 ones with 16x16x4 MFMAs.  Partials go to pw[p][range][j][i]; stage 2
-// (k_head_bwd_dw_final) adds the ranges, and the bias partials of k_head_dzh, in order.
+// Two roles, both bound by the streams they read (h; act'(z) and the stores of dZ):
+//   dW  dW_L(p)[j, i] = sum_m dz_L[m, j] h_{L-1}[m, i]: a workgroup takes one of HB_SPLIT row ranges of one preference and
+//       128 columns, and walks its rows 128 at a time: the dz rows (rounded to the GEMM input type) and the h tile sit in
+//       LDS, the next ones are already on their way in registers; wave w multiplies dz^T [16 x 128] by h [128 x columns
+//       32 w .. 32 w + 31]: bf16 networks with 16x16x16 bf16 MFMAs (dz^T staged with the contraction contiguous, h read
+//       through transposing LDS reads), fp32 ones with 16x16x4 MFMAs.  Partials go to pw[p][range][j][i].
+//   dZ  dZ_{L-1}[m, i] = (sum_j dz_L[m, j] W_L(p)[j, i]) * act'(z_{L-1})[m, i]: 64 rows x 128 columns a workgroup, 4 x 8 a
+//       thread, with the column sums of the unrounded dZ over the 64 rows (the bias gradient of the layer below) and, the
+//       first column's workgroups, of dz_L (that of the output layer).
+// k_bwd_final adds the partials.  (As launches of their own behind one that wrote dz_L as compact rows: 20 + 78 + 109 us
+// for 128 preferences x 2048 rows of width 512, here 185; 7.2 + 8.7 + 12.9 for 24 x 1250 of 256, here 17.4.)
 #define HB_ROWS 128
 #define HB_SPLIT 4
 template <typename T>
-__global__ __launch_bounds__(256) void k_head_bwd_dw(const float* __restrict__ dzh, const T* __restrict__ Hin,
-                                                    float* __restrict__ pw, int W, int M, int Mp) {
+struct HeadBwdLds {
+    static constexpr int HP = 128 + Elems<T>::VE;          // h tile pitch in elements (16 bytes of padding)
+    static constexpr bool kBf = std::is_same<T, bf16_t>::value;
+    float sdr[kBf ? 1 : HB_ROWS][MORLAX_MAX_OUT];          // fp32: dz rows as they lie
+    bf16_t sdT[kBf ? MORLAX_MAX_OUT : 1][HB_ROWS + 8];     // bf16: dz^T, contraction contiguous
+    T sh[HB_ROWS][HP];
+};
+struct HeadBwdLdsDz {
+    float sdz[64][MORLAX_MAX_OUT], sdu[64][MORLAX_MAX_OUT + 1], red[16][128];
+};
+template <typename T>
+__global__ __launch_bounds__(256, sizeof(T) == 2 ? 4 : 2) void k_head_bwd(HeadDz hz, const T* __restrict__ Hin, const T* __restrict__ theta_mat,
+                                                 int64_t mat_len, int64_t mat_off,
+                                                 const typename GradT<T>::type* __restrict__ G, T* __restrict__ dZ,
+                                                 float* __restrict__ pw, float* __restrict__ pb, float* __restrict__ part,
+                                                 int W, int Mp) {
+    constexpr size_t kLds = sizeof(HeadBwdLds<T>) > sizeof(HeadBwdLdsDz) ? sizeof(HeadBwdLds<T>) : sizeof(HeadBwdLdsDz);
+    __shared__ __align__(16) unsigned char lds[kLds];
     constexpr int VE = Elems<T>::VE;
-    constexpr int HP = 128 + VE;                           // h tile pitch in elements (16 bytes of padding)
+    const int p = blockIdx.y, ncol = (W + 127) / 128, M = hz.M;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const bool dw_role = (int)blockIdx.x < ncol * HB_SPLIT;
+    const int item = dw_role ? blockIdx.x : blockIdx.x - ncol * HB_SPLIT;
+    const int i0 = item % ncol * 128;
+    if (!dw_role) {
+        HeadBwdLdsDz& L = *reinterpret_cast<HeadBwdLdsDz*>(lds);
+        const int mb = item / ncol, m0 = mb * 64, n_mb = (Mp + 63) / 64;
+        const int tr = (threadIdx.x / 16) * 4, ti = i0 + (threadIdx.x % 16) * 8;
+        const bool live = ti < W;
+        Pack8 gq[4];
+#pragma unroll
+        for (int a = 0; a < 4; ++a) {
+            const int m = m0 + tr + a < Mp ? m0 + tr + a : Mp - 1;
+            const uint4* src = reinterpret_cast<const uint4*>(G + ((int64_t)p * Mp + m) * W + (live ? ti : 0));
+            gq[a].lo = src[0];
+            if (sizeof(T) == 4) gq[a].hi = src[1];
+        }
+        {
+            const int mm = threadIdx.x / 4, q = threadIdx.x % 4, m = m0 + mm;
+            HeadDz::Raw r;
+            hz.request(p, m < M ? m : M - 1, q, r);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const float d = hz.value(r, q, e, m < M);
+                L.sdu[mm][4 * q + e] = d;
+                L.sdz[mm][4 * q + e] = to_f(cvt<T>(d));  // GEMM input rounding
+            }
+        }
+        __syncthreads();
+        float acc[4][8];
+#pragma unroll
+        for (int a = 0; a < 4; ++a)
+#pragma unroll
+            for (int b = 0; b < 8; ++b) acc[a][b] = 0.f;
+        const T* wl = theta_mat + (int64_t)p * mat_len + mat_off;
+        for (int j = 0; j < hz.out_dim && live; ++j) {
+            float wv[8];
+#pragma unroll
+            for (int b = 0; b < 8; ++b) wv[b] = to_f(wl[(int64_t)j * W + ti + b]);
+#pragma unroll
+            for (int a = 0; a < 4; ++a) {
+                const float d = L.sdz[tr + a][j];
+#pragma unroll
+                for (int b = 0; b < 8; ++b) acc[a][b] += d * wv[b];
+            }
+        }
+        float cs[8];
+#pragma unroll
+        for (int b = 0; b < 8; ++b) cs[b] = 0.f;
+#pragma unroll
+        for (int a = 0; a < 4; ++a) {
+            const int m = m0 + tr + a;
+            if (m >= Mp || !live) continue;  // (rows M .. Mp: their dz is zero, and so is dZ)
+            float v[8], g[8];
+            if constexpr (sizeof(T) == 2) {
+                unpack8(gq[a].lo, g);
+            } else {
+                const uint32_t w[8] = {gq[a].lo.x, gq[a].lo.y, gq[a].lo.z, gq[a].lo.w, gq[a].hi.x, gq[a].hi.y, gq[a].hi.z, gq[a].hi.w};
+#pragma unroll
+                for (int b = 0; b < 8; ++b) g[b] = __uint_as_float(w[b]);
+            }
+#pragma unroll
+            for (int b = 0; b < 8; ++b) {
+                v[b] = acc[a][b] * g[b];
+                cs[b] += v[b];
+            }
+            store8(dZ + ((int64_t)p * Mp + m) * W + ti, v);
+        }
+        // partial column sums of the unrounded dZ over this block's 64 rows (row groups in fixed order)
+#pragma unroll
+        for (int b = 0; b < 8; ++b) L.red[threadIdx.x / 16][(threadIdx.x % 16) * 8 + b] = cs[b];
+        __syncthreads();
+        if (threadIdx.x < 128 && i0 + threadIdx.x < W) {
+            float v = 0.f;
+#pragma unroll
+            for (int q = 0; q < 16; ++q) v += L.red[q][threadIdx.x];
+            part[((int64_t)p * n_mb + mb) * W + i0 + threadIdx.x] = v;
+        }
+        if (i0 == 0) {  // sums of dz_L over the 64 rows: a wave's butterfly, columns wave, wave + 4, ..
+#pragma unroll
+            for (int k = 0; k < MORLAX_MAX_OUT / 4; ++k) {
+                float v = L.sdu[lane][wave + 4 * k];
+#pragma unroll
+                for (int o = 32; o > 0; o >>= 1) v += __shfl_down(v, o, 64);
+                if (lane == 0) pb[((int64_t)p * n_mb + mb) * MORLAX_MAX_OUT + wave + 4 * k] = v;
+            }
+        }
+        return;
+    }
+    HeadBwdLds<T>& L = *reinterpret_cast<HeadBwdLds<T>*>(lds);
     constexpr int CPR = 128 / VE;                          // 16-byte pieces per tile row
     constexpr int NPT = HB_ROWS * CPR / 256;               // pieces per thread
-    constexpr bool kBf = std::is_same<T, bf16_t>::value;
-    __shared__ __align__(16) float sdr[kBf ? 1 : HB_ROWS][MORLAX_MAX_OUT];        // fp32: dz rows as they lie
-    __shared__ __align__(16) bf16_t sdT[kBf ? MORLAX_MAX_OUT : 1][HB_ROWS + 8];  // bf16: dz^T, contraction contiguous
-    __shared__ __align__(16) T sh[HB_ROWS][HP];
-    const int p = blockIdx.z, rs = blockIdx.y, i0 = blockIdx.x * 128;
+    constexpr bool kBf = HeadBwdLds<T>::kBf;
+    const int rs = item / ncol;
     const int per = ((M + HB_SPLIT - 1) / HB_SPLIT + HB_ROWS - 1) / HB_ROWS * HB_ROWS;  // rows per range
     const int m_lo = rs * per, m_hi = (m_lo + per < M) ? (m_lo + per) : M;
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int ln = lane & 15, kg = lane >> 4;
     float4_t acc[2][2];
 #pragma unroll
@@ -1819,7 +1833,13 @@ __global__ __launch_bounds__(256) void k_head_bwd_dw(const float* __restrict__ d
 #pragma unroll
         for (int q = 0; q < 2; ++q) acc[c][q] = float4_t{0.f, 0.f, 0.f, 0.f};
     uint4 nxt[NPT];
+    HeadDz::Raw dnx[2];
     auto fetch = [&](int m0) {
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+            const int idx = threadIdx.x + 256 * i, m = m0 + idx / 4;
+            hz.request(p, m < m_hi ? m : m_hi - 1, idx % 4, dnx[i]);
+        }
 #pragma unroll
         for (int q = 0; q < NPT; ++q) {
             const int idx = threadIdx.x + 256 * q, mm = idx / CPR, cc = (idx % CPR) * VE;
@@ -1833,21 +1853,19 @@ __global__ __launch_bounds__(256) void k_head_bwd_dw(const float* __restrict__ d
     for (int m0 = m_lo; m0 < m_hi; m0 += HB_ROWS) {
         __syncthreads();  // the previous tile has been multiplied
 #pragma unroll
+        for (int i = 0; i < 2; ++i) {
+            const int idx = threadIdx.x + 256 * i, mm = idx / 4, q = idx % 4;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const T d = cvt<T>(hz.value(dnx[i], q, e, m0 + mm < m_hi));
+                if constexpr (kBf) L.sdT[4 * q + e][mm] = d;
+                else L.sdr[mm][4 * q + e] = to_f(d);
+            }
+        }
+#pragma unroll
         for (int q = 0; q < NPT; ++q) {
             const int idx = threadIdx.x + 256 * q;
-            *reinterpret_cast<uint4*>(&sh[idx / CPR][(idx % CPR) * VE]) = nxt[q];
-        }
-        for (int idx = threadIdx.x; idx < HB_ROWS * (MORLAX_MAX_OUT / 4); idx += 256) {
-            const int mm = idx / (MORLAX_MAX_OUT / 4), q = idx % (MORLAX_MAX_OUT / 4);
-            float4 d = make_float4(0.f, 0.f, 0.f, 0.f);
-            if (m0 + mm < m_hi) d = *reinterpret_cast<const float4*>(dzh + ((int64_t)p * M + m0 + mm) * MORLAX_MAX_OUT + 4 * q);
-            if constexpr (kBf) {
-                sdT[4 * q][mm] = cvt<T>(d.x); sdT[4 * q + 1][mm] = cvt<T>(d.y);
-                sdT[4 * q + 2][mm] = cvt<T>(d.z); sdT[4 * q + 3][mm] = cvt<T>(d.w);
-            } else {
-                sdr[mm][4 * q] = to_f(cvt<T>(d.x)); sdr[mm][4 * q + 1] = to_f(cvt<T>(d.y));
-                sdr[mm][4 * q + 2] = to_f(cvt<T>(d.z)); sdr[mm][4 * q + 3] = to_f(cvt<T>(d.w));
-            }
+            *reinterpret_cast<uint4*>(&L.sh[idx / CPR][(idx % CPR) * VE]) = nxt[q];
         }
         if (m0 + HB_ROWS < m_hi) fetch(m0 + HB_ROWS);
         __syncthreads();
@@ -1855,20 +1873,20 @@ __global__ __launch_bounds__(256) void k_head_bwd_dw(const float* __restrict__ d
             // both operands are bf16 values: 16x16x16 bf16 MFMAs, eight times the fp32 rate for the same sums
 #pragma unroll
             for (int ks = 0; ks < HB_ROWS / 16; ++ks) {
-                const short4_t a = *reinterpret_cast<const short4_t*>(&sdT[ln][16 * ks + 4 * kg]);  // dz^T[j = ln][4 m]
+                const short4_t a = *reinterpret_cast<const short4_t*>(&L.sdT[ln][16 * ks + 4 * kg]);  // dz^T[j = ln][4 m]
 #pragma unroll
                 for (int c = 0; c < 2; ++c)
                     acc[c][ks & 1] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(
-                        a, lds_tr4(&sh[16 * ks + 4 * kg + (ln >> 2)][32 * wave + 16 * c + 4 * (ln & 3)]), acc[c][ks & 1], 0, 0, 0);
+                        a, lds_tr4(&L.sh[16 * ks + 4 * kg + (ln >> 2)][32 * wave + 16 * c + 4 * (ln & 3)]), acc[c][ks & 1], 0, 0, 0);
             }
         } else {
 #pragma unroll
             for (int kk = 0; kk < HB_ROWS / 4; ++kk) {
                 const int m = 4 * kk + kg;
-                const float a = sdr[m][ln];                              // dz^T[j = ln][m]
+                const float a = L.sdr[m][ln];                              // dz^T[j = ln][m]
 #pragma unroll
                 for (int c = 0; c < 2; ++c) {
-                    const float b = to_f(sh[m][32 * wave + 16 * c + ln]);  // h[m][column]
+                    const float b = to_f(L.sh[m][32 * wave + 16 * c + ln]);  // h[m][column]
                     acc[c][kk & 1] = __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, acc[c][kk & 1], 0, 0, 0);
                 }
             }
@@ -1889,24 +1907,10 @@ __global__ __launch_bounds__(256) void k_head_bwd_dw(const float* __restrict__ d
 // ---- dW of a W x W layer with few preferences: contraction split into ranges ---------------------------------
 // dW_l(p) has (W/128)^2 tiles per preference (the first layer fewer still) and the whole selection as its contraction;
 // with few preferences that is a few dozen workgroups walking thousands of rows each.  The selection is cut into ranges
-// that run as groups of the same grouped GEMM into partial matrices, and the ranges are added in order.
+// that run as groups of the same grouped GEMM into partial matrices, and k_bwd_final adds the ranges in order.
 #ifndef DW_SPLIT_TARGET
 #define DW_SPLIT_TARGET 512
 #endif
-__global__ __launch_bounds__(256) void k_dw_split_final(const float* __restrict__ pw, int S, int64_t WW,
-                                                       float* __restrict__ dtheta_mat, int64_t mat_len, int64_t mat_off) {
-    const int p = blockIdx.y;
-    const int64_t i4 = ((int64_t)blockIdx.x * 256 + threadIdx.x) * 4;
-    if (i4 >= WW) return;
-    float4 v = *reinterpret_cast<const float4*>(pw + (int64_t)p * S * WW + i4);
-    for (int c = 1; c < S; ++c) {
-        const float4 u = *reinterpret_cast<const float4*>(pw + ((int64_t)p * S + c) * WW + i4);
-        v.x += u.x; v.y += u.y; v.z += u.z; v.w += u.w;
-    }
-    // W is a multiple of 16, so every matrix starts on a 16-byte boundary of the row
-    *reinterpret_cast<float4*>(dtheta_mat + (int64_t)p * mat_len + mat_off + i4) = v;
-}
-
 // ---- forward of the first layer with a narrow observation (O <= 32) ---------------------------------------
 // h = act(x W0(p)^T + b0(p)) is, per output, an inner product of O terms: too short to fill GEMM tiles (the tiled
 // kernel pads the contraction to 32 and loads the odd-width rows element by element) and bound by the stores of h
@@ -1992,31 +1996,26 @@ static bool first_fwd_narrow_ok(const morlax_ctx* c) {
 // ---- first layer with a narrow observation (O <= 32) and few preferences ----------------------------------
 // dW_0(p)[o, i] = sum_m dZ_0[m, o] x[m, i] has W x O outputs and the whole selection as its contraction: as a tiled
 // GEMM it is two or three tiles per preference walking thousands of rows each (workload 2: 32 workgroups on 256 CUs).
-// It is the output layer's dW with the roles exchanged, so it takes the same streaming form: the observation rows
-// are gathered once into compact fp32 rows padded to 16 JB columns, a block takes one of n_split row ranges of one
-// preference and 128 columns of dZ_0, and the ranges are added in order by k_first_dw_final.
-template <typename T>
-__global__ __launch_bounds__(256) void k_gather_x_pad(const float* __restrict__ x, float* __restrict__ xz, int O, int OP,
-                                                     int M, RowMap rm) {
-    const int p = blockIdx.y;
-    const int64_t idx = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (idx >= (int64_t)M * OP) return;
-    const int m = (int)(idx / OP), c = (int)(idx % OP);
-    xz[((int64_t)p * M + m) * OP + c] = c < O ? x[rm.row(p, m) * O + c] : 0.f;
-}
-
+// It is the output layer's dW with the roles exchanged, so it takes the same streaming form: a block takes one of n_split
+// row ranges of one preference and 128 columns of dZ_0, gathers the observation rows through the row map (the offsets of
+// the next tile's rows in LDS, the rows' values one after the other: consecutive threads read consecutive floats of an
+// environment's run) into 16 JB columns, zero beyond O, and k_bwd_final adds the ranges in order.  (The rows gathered by a
+// launch of their own first: 14.2 + 29.2 us for 32 preferences x 8192 rows x 11 x 256, here 31.1.)
 template <typename T, int JB>
-__global__ __launch_bounds__(256) void k_first_bwd_dw(const float* __restrict__ xz, const T* __restrict__ dZ,
-                                                     float* __restrict__ pw, int W, int M, int Mp, int n_split) {
+__global__ __launch_bounds__(256) void k_first_bwd_dw(const float* __restrict__ x, const T* __restrict__ dZ,
+                                                     float* __restrict__ pw, int O, int W, int M, int Mp, int n_split,
+                                                     RowMap rm) {
     constexpr int VE = Elems<T>::VE;
     constexpr int HP = 128 + VE;
     constexpr int CPR = 128 / VE;
     constexpr int NPT = HB_ROWS * CPR / 256;
     constexpr int OP = 16 * JB;
+    constexpr int NX = HB_ROWS * OP / 256;  // observation values per thread, at most
     constexpr bool kBf = std::is_same<T, bf16_t>::value;
     __shared__ __align__(16) float sdr[kBf ? 1 : HB_ROWS][OP];        // fp32: observation rows as they lie
     __shared__ __align__(16) bf16_t sdT[kBf ? OP : 1][HB_ROWS + 8];  // bf16: x^T, contraction contiguous
     __shared__ __align__(16) T sh[HB_ROWS][HP];
+    __shared__ uint32_t sro[2][HB_ROWS];  // first element of a tile row's observation
     const int p = blockIdx.z, rs = blockIdx.y, i0 = blockIdx.x * 128;
     const int per = ((M + n_split - 1) / n_split + HB_ROWS - 1) / HB_ROWS * HB_ROWS;  // rows per range
     const int m_lo = rs * per, m_hi = (m_lo + per < M) ? (m_lo + per) : M;
@@ -2030,7 +2029,25 @@ __global__ __launch_bounds__(256) void k_first_bwd_dw(const float* __restrict__ 
 #pragma unroll
             for (int q = 0; q < 2; ++q) acc[jb][c][q] = float4_t{0.f, 0.f, 0.f, 0.f};
     uint4 nxt[NPT];
-    auto fetch = [&](int m0) {
+    float xn[NX];
+    const int mm0 = threadIdx.x / O, c0 = threadIdx.x % O, dm = 256 / O, dc = 256 % O;  // value i + 1 of a thread: 256 further
+    auto each_x = [&](auto fn) {
+        int mm = mm0, c = c0;
+#pragma unroll
+        for (int i = 0; i < NX; ++i) {
+            if (mm < HB_ROWS) fn(i, mm, c);
+            mm += dm; c += dc;
+            if (c >= O) { c -= O; ++mm; }
+        }
+    };
+    auto offsets = [&](int m0, int slot) {
+        if (threadIdx.x < HB_ROWS) {
+            const int m = m0 + (int)threadIdx.x;
+            sro[slot][threadIdx.x] = (uint32_t)(rm.row(p, m < m_hi ? m : m_hi - 1) * O);
+        }
+    };
+    auto fetch = [&](int m0, int slot) {
+        each_x([&](int i, int mm, int c) { xn[i] = x[sro[slot][mm] + c]; });
 #pragma unroll
         for (int q = 0; q < NPT; ++q) {
             const int idx = threadIdx.x + 256 * q, mm = idx / CPR, cc = (idx % CPR) * VE;
@@ -2040,28 +2057,31 @@ __global__ __launch_bounds__(256) void k_first_bwd_dw(const float* __restrict__ 
             nxt[q] = u;
         }
     };
-    if (m_lo < m_hi) fetch(m_lo);
-    for (int m0 = m_lo; m0 < m_hi; m0 += HB_ROWS) {
+    for (int idx = threadIdx.x; idx < HB_ROWS * (OP - O); idx += 256) {  // columns beyond O
+        const int mm = idx % HB_ROWS, c = O + idx / HB_ROWS;
+        if constexpr (kBf) sdT[c][mm] = (bf16_t)0.f;
+        else sdr[mm][c] = 0.f;
+    }
+    if (m_lo < m_hi) {
+        offsets(m_lo, 0);
+        __syncthreads();
+        fetch(m_lo, 0);
+    }
+    for (int m0 = m_lo, slot = 0; m0 < m_hi; m0 += HB_ROWS, slot ^= 1) {
         __syncthreads();  // the previous tile has been multiplied
 #pragma unroll
         for (int q = 0; q < NPT; ++q) {
             const int idx = threadIdx.x + 256 * q;
             *reinterpret_cast<uint4*>(&sh[idx / CPR][(idx % CPR) * VE]) = nxt[q];
         }
-        for (int idx = threadIdx.x; idx < HB_ROWS * (OP / 4); idx += 256) {
-            const int mm = idx / (OP / 4), q = idx % (OP / 4);
-            float4 d = make_float4(0.f, 0.f, 0.f, 0.f);
-            if (m0 + mm < m_hi) d = *reinterpret_cast<const float4*>(xz + ((int64_t)p * M + m0 + mm) * OP + 4 * q);
-            if constexpr (kBf) {  // GEMM input rounding
-                sdT[4 * q][mm] = cvt<T>(d.x); sdT[4 * q + 1][mm] = cvt<T>(d.y);
-                sdT[4 * q + 2][mm] = cvt<T>(d.z); sdT[4 * q + 3][mm] = cvt<T>(d.w);
-            } else {
-                sdr[mm][4 * q] = to_f(cvt<T>(d.x)); sdr[mm][4 * q + 1] = to_f(cvt<T>(d.y));
-                sdr[mm][4 * q + 2] = to_f(cvt<T>(d.z)); sdr[mm][4 * q + 3] = to_f(cvt<T>(d.w));
-            }
-        }
-        if (m0 + HB_ROWS < m_hi) fetch(m0 + HB_ROWS);
+        each_x([&](int i, int mm, int c) {
+            const T v = cvt<T>(m0 + mm < m_hi ? xn[i] : 0.f);  // GEMM input rounding
+            if constexpr (kBf) sdT[c][mm] = v;
+            else sdr[mm][c] = to_f(v);
+        });
+        if (m0 + HB_ROWS < m_hi) offsets(m0 + HB_ROWS, slot ^ 1);
         __syncthreads();
+        if (m0 + HB_ROWS < m_hi) fetch(m0 + HB_ROWS, slot ^ 1);
         if constexpr (kBf) {
 #pragma unroll
             for (int ks = 0; ks < HB_ROWS / 16; ++ks) {
@@ -2102,65 +2122,95 @@ __global__ __launch_bounds__(256) void k_first_bwd_dw(const float* __restrict__ 
         }
 }
 
-// dW_0(p)[o, i] = the ranges' partials [i][o] added in order
-__global__ __launch_bounds__(256) void k_first_dw_final(const float* __restrict__ pw, int n_split, int OP,
-                                                       float* __restrict__ dtheta_mat, int64_t mat_len, int64_t mat_off,
-                                                       int W, int O) {
-    const int p = blockIdx.y, idx = blockIdx.x * 256 + threadIdx.x;
-    if (idx >= W * O) return;
-    const int o = idx / O, i = idx % O;
-    float v = 0.f;
-    for (int c = 0; c < n_split; ++c) v += pw[(((int64_t)p * n_split + c) * OP + i) * W + o];
-    dtheta_mat[(int64_t)p * mat_len + mat_off + idx] = v;
-}
-
-__global__ __launch_bounds__(256) void k_head_bwd_dw_final(const float* __restrict__ pw, const float* __restrict__ pb,
-                                                          int n_chunk_w, int n_chunk_b, float* __restrict__ dtheta_mat,
-                                                          float* __restrict__ dtheta_vec, int64_t mat_len,
-                                                          int64_t vec_len, int64_t mat_off, int64_t vec_off, int W,
-                                                          int out_dim) {
-    const int p = blockIdx.y, idx = blockIdx.x * 256 + threadIdx.x;
-    if (idx < out_dim * W) {
-        const int j = idx / W, i = idx % W;
-        float v = 0.f;
-        for (int c = 0; c < n_chunk_w; ++c) v += pw[(((int64_t)p * n_chunk_w + c) * MORLAX_MAX_OUT + j) * W + i];
-        dtheta_mat[(int64_t)p * mat_len + mat_off + idx] = v;
-    }
-    if (idx < out_dim) {
-        float v = 0.f;
-        for (int c = 0; c < n_chunk_b; ++c) v += pb[((int64_t)p * n_chunk_b + c) * MORLAX_MAX_OUT + idx];
-        dtheta_vec[(int64_t)p * vec_len + vec_off + idx] = v;
-    }
-}
-
-// db_l(p)[o] = sum over the row blocks of the partial column sums of dZ_l.  A block takes 32 columns of one
-// preference; its eight groups of 32 threads each add a contiguous eighth of the row blocks in order, and the eight
-// sums are added in group order (a fixed association: results repeat bit for bit).
-__global__ __launch_bounds__(256) void k_colsum_final(const float* __restrict__ part, int n_part,
-                                                     float* __restrict__ dtheta_vec, int64_t vec_len,
-                                                     int64_t vec_off, int W) {
+// What the backward launches of a network leave as partial sums, added up by one launch at their end (one behind each of
+// them put some fifteen launches of 4 - 10 us on the dependent chain of a network's gradients).  Blocks of a preference, in
+// this order:
+//   bias sums  db_l(p)[o]: 32 columns of one layer; its eight groups of 32 threads each add a contiguous eighth of the row
+//              blocks in order, and the eight sums are added in group order
+//   output layer's dW (ranges in order); its first block also the bias sums (64-row sums, four to a block of 256 rows, the
+//              blocks in order) and the copy of the log-sigma gradient
+//   split dW   the ranges of a layer whose contraction was split, in order, four elements a thread
+//   first dW   the ranges' partials [i][o] of the narrow first layer, in order
+// Fixed associations throughout: results repeat bit for bit.
+struct BwdFinalArgs {
+    const float *part, *dlogsig;
+    float *dmat, *dvec;
+    int64_t mat_len, vec_len;
+    int32_t W, L, O, OP, out_dim, A;  // A: log-sigma components to write, 0: none
+    int32_t n_part[MORLAX_MAX_LAYERS], S[MORLAX_MAX_LAYERS], n_pb, first_ns;  // S: ranges of a split dW, 1: not split
+    int64_t colsum[MORLAX_MAX_LAYERS], split[MORLAX_MAX_LAYERS], first, pw, pb;  // offsets in part
+    int64_t mat_off[MORLAX_MAX_LAYERS], vec_off[MORLAX_MAX_LAYERS], n[MORLAX_MAX_LAYERS], logsig_off;  // (index L: output layer)
+    int32_t b_head, b_split[MORLAX_MAX_LAYERS], b_first;  // first block of each kind
+};
+__global__ __launch_bounds__(256) void k_bwd_final(BwdFinalArgs a) {
     __shared__ float sg[8][32];
-    const int p = blockIdx.y, c = threadIdx.x & 31, g = threadIdx.x >> 5, i = blockIdx.x * 32 + c;
-    const int per = (n_part + 7) / 8, q_lo = g * per, q_hi = (q_lo + per < n_part) ? q_lo + per : n_part;
-    float a = 0.f;
-    if (i < W)
-        for (int q = q_lo; q < q_hi; ++q) a += part[((int64_t)p * n_part + q) * W + i];
-    sg[g][c] = a;
-    __syncthreads();
-    if (g == 0 && i < W) {
-        float t = sg[0][c];
+    const int p = blockIdx.y, b = blockIdx.x, W = a.W;
+    float* dmat = a.dmat + (int64_t)p * a.mat_len;
+    float* dvec = a.dvec + (int64_t)p * a.vec_len;
+    if (b < a.b_head) {
+        const int cw = (W + 31) / 32, l = b / cw, np = a.n_part[l];
+        const float* part = a.part + a.colsum[l] + (int64_t)p * np * W;
+        const int c = threadIdx.x & 31, g = threadIdx.x >> 5, i = (b % cw) * 32 + c;
+        const int per = (np + 7) / 8, q_lo = g * per, q_hi = (q_lo + per < np) ? q_lo + per : np;
+        float t = 0.f;
+        if (i < W) {
+#pragma unroll 4
+            for (int q = q_lo; q < q_hi; ++q) t += part[(int64_t)q * W + i];
+        }
+        sg[g][c] = t;
+        __syncthreads();
+        if (g == 0 && i < W) {
+            t = sg[0][c];
 #pragma unroll
-        for (int k = 1; k < 8; ++k) t += sg[k][c];
-        dtheta_vec[(int64_t)p * vec_len + vec_off + i] = t;
+            for (int k = 1; k < 8; ++k) t += sg[k][c];
+            dvec[a.vec_off[l] + i] = t;
+        }
+        return;
     }
-}
-
-__global__ void k_copy_dlogsig(const float* __restrict__ dlogsig, float* __restrict__ dtheta_vec, int64_t vec_len,
-                               int64_t off, int P, int A) {
-    const int idx = blockIdx.x * blockDim.x + threadIdx.x;
-    if (idx >= P * A) return;
-    const int p = idx / A, a = idx % A;
-    dtheta_vec[(int64_t)p * vec_len + off + a] = dlogsig ? dlogsig[idx] : 0.f;
+    if (b < a.b_split[0]) {
+        const int idx = (b - a.b_head) * 256 + threadIdx.x;
+        if (idx < a.out_dim * W) {
+            const int j = idx / W, i = idx % W;
+            float v = 0.f;
+#pragma unroll
+            for (int c = 0; c < HB_SPLIT; ++c) v += a.part[a.pw + (((int64_t)p * HB_SPLIT + c) * MORLAX_MAX_OUT + j) * W + i];
+            dmat[a.mat_off[a.L] + idx] = v;
+        }
+        if (idx < a.out_dim) {
+            const float* pb = a.part + a.pb + (int64_t)p * a.n_pb * MORLAX_MAX_OUT + idx;
+            auto at = [&](int m) { return m < a.n_pb ? pb[(int64_t)m * MORLAX_MAX_OUT] : 0.f; };
+            float v = 0.f;
+#pragma unroll 2
+            for (int m = 0; m < a.n_pb; m += 4) v += (at(m) + at(m + 1)) + (at(m + 2) + at(m + 3));
+            dvec[a.vec_off[a.L] + idx] = v;
+        }
+        if (idx < a.A) dvec[a.logsig_off + idx] = a.dlogsig ? a.dlogsig[p * a.A + idx] : 0.f;
+        return;
+    }
+    if (b < a.b_first) {
+        int l = 0;
+        while (l + 1 < a.L && b >= a.b_split[l + 1]) ++l;
+        const int64_t n = a.n[l], i4 = ((int64_t)(b - a.b_split[l]) * 256 + threadIdx.x) * 4;
+        if (i4 >= n) return;
+        const int S = a.S[l];
+        const float* src = a.part + a.split[l] + (int64_t)p * S * n + i4;
+        float4 v = *reinterpret_cast<const float4*>(src);
+#pragma unroll 3
+        for (int c = 1; c < S; ++c) {
+            const float4 u = *reinterpret_cast<const float4*>(src + c * n);
+            v.x += u.x; v.y += u.y; v.z += u.z; v.w += u.w;
+        }
+        // W is a multiple of 16, so every matrix starts on a 16-byte boundary of the row
+        *reinterpret_cast<float4*>(dmat + a.mat_off[l] + i4) = v;
+        return;
+    }
+    const int idx = (b - a.b_first) * 256 + threadIdx.x;
+    if (idx >= W * a.O) return;
+    const int o = idx / a.O, i = idx % a.O;
+    float v = 0.f;
+#pragma unroll 4
+    for (int c = 0; c < a.first_ns; ++c) v += a.part[a.first + (((int64_t)p * a.first_ns + c) * a.OP + i) * W + o];
+    dmat[a.mat_off[0] + idx] = v;
 }
 
 // Rows of the fp32 observation tensor picked by the row map, rounded to the GEMM input type, as compact
@@ -2217,15 +2267,6 @@ int64_t mlp_saved_bytes(const morlax_ctx* c, int net, const RowSel& rs) {
     (void)net;
     return saved_x0_off(c, rs) + (first_skinny(c) ? 0 : x0_elems(c, rs) * esize(c));
 }
-// fp32 scratch behind the two activation buffers: [0, head_lo): partial column sums of dZ, or the output
-// layer's dW partials followed by its bias partials; [head_lo, ..): the compact dz rows of the output layer
-// (still read while the column sums of the layer below are written).
-static int64_t head_pw_elems(const morlax_ctx* c) { return (int64_t)c->d.P * HB_SPLIT * MORLAX_MAX_OUT * c->d.width; }
-static int64_t head_lo_elems(const morlax_ctx* c, const RowSel& rs) {
-    const int64_t colsum = (int64_t)c->d.P * ((pad_rows(rs) + 63) / 64) * c->d.width;
-    const int64_t head = head_pw_elems(c) + (int64_t)c->d.P * ((rs.M + 255) / 256) * MORLAX_MAX_OUT;
-    return align_up(colsum > head ? colsum : head, 64);
-}
 static int first_split(const morlax_ctx* c, const RowSel& rs) {
     const int tiles = ((c->d.width + 127) / 128) * c->d.P;
     int n = (1024 + tiles - 1) / tiles;
@@ -2233,11 +2274,6 @@ static int first_split(const morlax_ctx* c, const RowSel& rs) {
     n = n > 64 ? 64 : n;
     n = n > cap ? cap : n;
     return n < 1 ? 1 : n;
-}
-static int64_t first_skinny_elems(const morlax_ctx* c, const RowSel& rs) {  // padded rows, then the ranges' partials
-    if (!first_skinny(c)) return 0;
-    const int OP = c->d.obs_dim <= 16 ? 16 : 32;
-    return align_up((int64_t)c->d.P * rs.M * OP, 64) + align_up((int64_t)c->d.P * first_split(c, rs) * OP * c->d.width, 64);
 }
 // Ranges the contraction of a layer's dW is cut into (1 = the plain grouped GEMM), until there are DW_SPLIT_TARGET
 // workgroups (1024 measured slower: twice the partials).  fp32: ranges of 256 rows and more, of 64 while the workgroups
@@ -2260,15 +2296,29 @@ static int dw_split(const morlax_ctx* c, int M, int layer, bool room) {
     return S;
 }
 static int dw_range(const RowSel& rs, int S) { return (int)align_up((pad_rows(rs) + S - 1) / S, 64); }
-static int64_t dw_split_elems(const morlax_ctx* c, const RowSel& rs) {
-    const int W = c->d.width, O = c->d.obs_dim, Sh = dw_split(c, rs.M, 1, true), S0 = dw_split(c, rs.M, 0, true);
-    const int64_t h = Sh > 1 ? (int64_t)Sh * W * W : 0, f = S0 > 1 ? (int64_t)S0 * W * O : 0;
-    return align_up((int64_t)c->d.P * (h > f ? h : f), 64);
+// fp32 scratch behind the two activation buffers: the partial sums of a network's backward launches, each in a place of
+// its own until k_bwd_final has added it up (offsets in floats)
+struct BwdPart {
+    int64_t pw, pb, first, total;
+    int64_t colsum[MORLAX_MAX_LAYERS], split[MORLAX_MAX_LAYERS];
+};
+static BwdPart bwd_part(const morlax_ctx* c, const RowSel& rs) {
+    const int64_t P = c->d.P, W = c->d.width, n64 = (pad_rows(rs) + 63) / 64;
+    BwdPart B;
+    int64_t at = 0;
+    auto take = [&](int64_t n) { const int64_t o = at; at += align_up(n, 64); return o; };
+    B.pw = take(P * HB_SPLIT * MORLAX_MAX_OUT * W);
+    B.pb = take(P * n64 * MORLAX_MAX_OUT);
+    B.first = take(first_skinny(c) ? P * first_split(c, rs) * (c->d.obs_dim <= 16 ? 16 : 32) * W : 0);
+    for (int l = 0; l < c->d.n_hidden; ++l) {
+        const int S = dw_split(c, rs.M, l, true);
+        B.colsum[l] = take(P * n64 * W);
+        B.split[l] = take(S > 1 ? P * S * W * (l == 0 ? c->d.obs_dim : W) : 0);
+    }
+    B.total = at;
+    return B;
 }
-static int64_t part_elems(const morlax_ctx* c, const RowSel& rs) {
-    return head_lo_elems(c, rs) + align_up((int64_t)c->d.P * rs.M * MORLAX_MAX_OUT, 64) + first_skinny_elems(c, rs) +
-           dw_split_elems(c, rs);
-}
+static int64_t part_elems(const morlax_ctx* c, const RowSel& rs) { return bwd_part(c, rs).total; }
 static bool fused_fwd_dims_ok(const morlax_ctx* c) {
     return c->d.wdtype == 1 && (c->d.width == 512 || c->d.width == 256) && c->d.obs_dim <= c->d.width &&
            c->d.n_hidden >= 1;
@@ -2564,27 +2614,35 @@ static void policy_bwd_t(const morlax_ctx* c, int net, const T* theta_mat, const
     auto Gbuf = [&](int l) { return reinterpret_cast<const GT*>(sv + (int64_t)(2 * l + 1) * ae); };
     auto dZbuf = [&](int l) { return wsT + (int64_t)(l & 1) * ae; };
     float* part = reinterpret_cast<float*>(wsT + 2 * ae);
-    int n_part = (Mp + 63) / 64;  // row blocks of whichever kernel produced the current dZ
+    const BwdPart B = bwd_part(c, rs);
     const float* saved_out = reinterpret_cast<const float*>(sv + (int64_t)2 * L * ae);
-    const int tanh_cols = (net == MORLAX_ACTOR && c->d.mean_tanh) ? c->d.act_dim : 0;
     const LayerDev& Lh = nd.layer[L];
-    // output layer
-    {
-        const int n_chunk_b = (M + 255) / 256;
-        float* pw = part;
-        float* pb = part + head_pw_elems(c);
-        float* dzh = part + head_lo_elems(c, rs);
-        k_head_dzh<T><<<dim3(n_chunk_b, P), 256, 0, s>>>(dout, saved_out, dzh, pb, nd.out_dim, M, rm, tanh_cols);
-        k_head_bwd_dw<T><<<dim3((W + 127) / 128, HB_SPLIT, P), 256, 0, s>>>(dzh, Hbuf(L - 1), pw, W, M, Mp);
-        k_head_bwd_dw_final<<<dim3((nd.out_dim * W + 255) / 256, P), 256, 0, s>>>(
-            pw, pb, HB_SPLIT, n_chunk_b, dtheta_mat, dtheta_vec, nd.mat_len, nd.vec_len, Lh.mat_off, Lh.vec_off, W,
-            nd.out_dim);
-        k_head_bwd_dz<T><<<dim3((W + 127) / 128, (Mp + 63) / 64, P), 256, 0, s>>>(
-            dzh, theta_mat, nd.mat_len, Lh.mat_off, Gbuf(L - 1), dZbuf(L - 1), part, W, nd.out_dim, M, Mp);
+    const int n64 = (Mp + 63) / 64;
+    BwdFinalArgs fin;
+    fin.part = part; fin.dlogsig = dlogsig; fin.dmat = dtheta_mat; fin.dvec = dtheta_vec;
+    fin.mat_len = nd.mat_len; fin.vec_len = nd.vec_len;
+    fin.W = W; fin.L = L; fin.O = O; fin.OP = O <= 16 ? 16 : 32; fin.out_dim = nd.out_dim;
+    fin.A = net == MORLAX_ACTOR && !c->d.sigma_state ? c->d.act_dim : 0;  // (a state-dependent log sigma is part of dout)
+    fin.n_pb = n64; fin.first_ns = 0; fin.first = B.first; fin.pw = B.pw; fin.pb = B.pb;
+    fin.mat_off[L] = Lh.mat_off; fin.vec_off[L] = Lh.vec_off; fin.logsig_off = Lh.vec_off + Lh.d_out;
+    for (int l = 0; l < L; ++l) {
+        fin.n_part[l] = n64;  // row blocks of whichever kernel produced the layer's dZ
+        fin.S[l] = 1;
+        fin.colsum[l] = B.colsum[l]; fin.split[l] = B.split[l];
+        fin.mat_off[l] = nd.layer[l].mat_off; fin.vec_off[l] = nd.layer[l].vec_off;
+        fin.n[l] = (int64_t)W * nd.layer[l].d_in;
+    }
+    {  // output layer
+        HeadDz hz;
+        hz.dout = dout; hz.saved_out = saved_out; hz.out_dim = nd.out_dim; hz.M = M; hz.rm = rm;
+        hz.tanh_cols = (net == MORLAX_ACTOR && c->d.mean_tanh) ? c->d.act_dim : 0;
+        const int ncol = (W + 127) / 128;
+        k_head_bwd<T><<<dim3(ncol * (HB_SPLIT + n64), P), 256, 0, s>>>(hz, Hbuf(L - 1), theta_mat, nd.mat_len, Lh.mat_off,
+                                                                     Gbuf(L - 1), dZbuf(L - 1), part + B.pw, part + B.pb,
+                                                                     part + B.colsum[L - 1], W, Mp);
     }
     for (int l = L - 1; l >= 0; --l) {
         const LayerDev& Ld = nd.layer[l];
-        k_colsum_final<<<dim3((W + 31) / 32, P), 256, 0, s>>>(part, n_part, dtheta_vec, nd.vec_len, Ld.vec_off, W);
         // dW_l = dZ_l^T in: `in` the layer's compact input, [P][Mp][ld]
         auto weight_grad = [&](int kind, const T* in, int ld) {
             GemmArgs<T, SRC_KSTRIDED, SRC_KSTRIDED, EpiDw, true, GEMM_NCH> g;
@@ -2595,19 +2653,13 @@ static void policy_bwd_t(const morlax_ctx* c, int net, const T* theta_mat, const
             g.epi.dW = dtheta_mat + Ld.mat_off; g.epi.ld = Ld.d_in; g.epi.part = nullptr;
             g.e0_pstride = nd.mat_len; g.e1_pstride = 0; g.e2_pstride = 0;
             const int S = dw_split(c, M, l, false);
-            if (S == 1) {
-                run_gemm(c, kind, g, P, s);
-                return;
+            if (S > 1) {
+                g.range = dw_range(rs, S);
+                g.ranges = (Mp + g.range - 1) / g.range;
+                g.epi.dW = part + B.split[l]; g.e0_pstride = fin.n[l];
+                fin.S[l] = g.ranges;
             }
-            float* pws = part + head_lo_elems(c, rs) + align_up((int64_t)P * M * MORLAX_MAX_OUT, 64) + first_skinny_elems(c, rs);
-            const int64_t n = (int64_t)W * Ld.d_in;
-            g.range = dw_range(rs, S);
-            g.ranges = (Mp + g.range - 1) / g.range;
-            g.epi.dW = pws; g.e0_pstride = n;
             run_gemm(c, kind, g, P * g.ranges, s);
-            k_dw_split_final<<<dim3((unsigned)((n / 4 + 255) / 256), P), 256, 0, s>>>(pws, g.ranges, n, dtheta_mat, nd.mat_len,
-                                                                                    Ld.mat_off);
-            prof_extend(c, s);
         };
         if (l > 0) {
             weight_grad(3, Hbuf(l - 1), W);
@@ -2615,32 +2667,33 @@ static void policy_bwd_t(const morlax_ctx* c, int net, const T* theta_mat, const
             h.a.base = dZbuf(l); h.a.ld = W; h.a.rows = Mp; h.a.kdim = W; h.a.rm = rm;
             h.b.base = theta_mat + Ld.mat_off; h.b.ld = W; h.b.rows = W; h.b.kdim = W; h.b.rm = rm;
             h.a_pstride = (int64_t)Mp * W; h.b_pstride = nd.mat_len;
-            h.epi.G = Gbuf(l - 1); h.epi.dZ = dZbuf(l - 1); h.epi.ld = W; h.epi.part = part;
+            h.epi.G = Gbuf(l - 1); h.epi.dZ = dZbuf(l - 1); h.epi.ld = W; h.epi.part = part + B.colsum[l - 1];
             h.e0_pstride = (int64_t)Mp * W; h.e1_pstride = 0; h.e2_pstride = 0;
             run_gemm(c, 2, h, P, s);
-            n_part = h.tiles_m;  // row tiles of the kernel that ran (128 or 256 rows)
+            fin.n_part[l - 1] = h.tiles_m;  // row tiles of the kernel that ran (128 or 256 rows)
         } else if (first_skinny(c)) {
-            const int OP = O <= 16 ? 16 : 32, ns = first_split(c, rs);
-            float* xz = part + head_lo_elems(c, rs) + align_up((int64_t)P * M * MORLAX_MAX_OUT, 64);
-            float* pw1 = xz + align_up((int64_t)P * M * OP, 64);
-            const int64_t n = (int64_t)M * OP;
+            const int ns = first_split(c, rs);
             GemmProf::Rec* r = prof_take(c, 4, 2.0 * W * (double)O * M * P);
             if (r) (void)hipEventRecord(r->a, s);
-            k_gather_x_pad<T><<<dim3((unsigned)((n + 255) / 256), P), 256, 0, s>>>(x, xz, O, OP, M, rm);
             const dim3 grid((W + 127) / 128, ns, P);
-            if (OP == 16) k_first_bwd_dw<T, 1><<<grid, 256, 0, s>>>(xz, dZbuf(0), pw1, W, M, Mp, ns);
-            else k_first_bwd_dw<T, 2><<<grid, 256, 0, s>>>(xz, dZbuf(0), pw1, W, M, Mp, ns);
-            k_first_dw_final<<<dim3((W * O + 255) / 256, P), 256, 0, s>>>(pw1, ns, OP, dtheta_mat, nd.mat_len, Ld.mat_off, W, O);
+            if (fin.OP == 16) k_first_bwd_dw<T, 1><<<grid, 256, 0, s>>>(x, dZbuf(0), part + B.first, O, W, M, Mp, ns, rm);
+            else k_first_bwd_dw<T, 2><<<grid, 256, 0, s>>>(x, dZbuf(0), part + B.first, O, W, M, Mp, ns, rm);
             if (r) (void)hipEventRecord(r->b, s);
+            fin.first_ns = ns;
         } else {
             weight_grad(4, reinterpret_cast<const T*>(reinterpret_cast<const char*>(sv) + saved_x0_off(c, rs)), x0_ld(c));
         }
     }
-    if (net == MORLAX_ACTOR && !c->d.sigma_state) {  // (a state-dependent log sigma is part of dout)
-        const int n = P * c->d.act_dim;
-        k_copy_dlogsig<<<(n + 255) / 256, 256, 0, s>>>(dlogsig, dtheta_vec, nd.vec_len, Lh.vec_off + Lh.d_out, P,
-                                                      c->d.act_dim);
+    int b = L * ((W + 31) / 32);
+    fin.b_head = b;
+    b += (nd.out_dim * W + 255) / 256;
+    for (int l = 0; l < L; ++l) {
+        fin.b_split[l] = b;
+        if (fin.S[l] > 1) b += (int)((fin.n[l] / 4 + 255) / 256);
     }
+    fin.b_first = b;
+    if (fin.first_ns > 0) b += (W * O + 255) / 256;
+    k_bwd_final<<<dim3(b, P), 256, 0, s>>>(fin);
 }
 
 void launch_policy_fwd(const morlax_ctx* c, int net, const void* theta_mat, const float* theta_vec,

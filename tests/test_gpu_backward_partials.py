@@ -1,0 +1,30 @@
+"""Backward of the target networks at the edges of what its launches leave as partial sums, against the oracle with the
+bounds of the parity tests: rows around the 64-row blocks of the output layer's sums, the 128-row tiles and the four blocks
+to a 256-row group, columns around the 128 of a workgroup, observation widths around the 16 and 32 columns of the narrow
+first layer, the smallest and the largest output layers, split and unsplit contractions side by side."""
+import pytest
+
+import test_gpu_parity as parity
+from paper_2603_09237_amd.configs import scaled
+from test_gpu_parity import RAGGED, _float32_default, binding, torch  # noqa: F401  (fixtures)
+
+pytestmark = pytest.mark.gpu
+
+
+def case(M, W, O, A, K, L, P, **over):
+    return scaled(RAGGED, name=f"M{M}-W{W}-O{O}-A{A}-K{K}-L{L}-P{P}" + "".join(f"-{k}{v}" for k, v in over.items()), T=1, N=P * M,
+                  P=P, K=K, obs_dim=O, act_dim=A, n_hidden=L, width=W, **over)
+
+
+CASES = [case(M, W, O, A, K, L, P, wdtype=b)
+         for b in (0, 1)
+         for M, W, O, A, K, L, P in ((1, 16, 1, 1, 1, 1, 2), (63, 48, 16, 2, 3, 2, 3), (64, 128, 17, 16, 5, 2, 2), (65, 144, 31, 4, 16, 3, 2),
+                                     (255, 112, 32, 3, 2, 2, 4), (256, 272, 33, 5, 4, 2, 2), (257, 64, 5, 8, 2, 3, 2),
+                                     (513, 32, 11, 9, 7, 2, 5), (1025, 128, 8, 3, 3, 2, 2))]
+CASES += [case(300, 256, 40, 7, 6, 3, 2, wdtype=1, act=0), case(770, 512, 64, 10, 6, 2, 2, wdtype=1),
+          case(130, 96, 9, 4, 2, 2, 3, wdtype=1, sigma_state=1), case(130, 96, 9, 4, 2, 2, 3, wdtype=0, mean_tanh=0)]
+
+
+@pytest.mark.parametrize("cfg", CASES, ids=lambda c: c.name)
+def test_backward_at_the_edges_of_its_partial_sums(cfg, torch, binding):  # noqa: F811
+    parity.test_policy_bwd_matches_oracle(cfg, None, torch, binding)
