@@ -732,6 +732,9 @@ struct DmaTile {
     int64_t kstep;
     uint32_t roff[MBLK];  // LDS byte offset of the lane's fragment of block b, ks 0
 
+    // K-strided tiles: what the chunk index is XORed with at contraction index k, so that the four consecutive indices of a
+    // transposing read fall into different banks (eight chunks to an index: the neighbouring index already does)
+    __device__ static inline int swz(int k) { return CPR >= 16 ? 4 * (k & 3) : 4 * ((k >> 1) & 1); }
     __device__ inline void set_tile(const bf16_t* b, int ld, int rows, int t0) {
         base = reinterpret_cast<const char*>(b);
         const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -744,7 +747,7 @@ struct DmaTile {
                 gr = gr < rows ? gr : rows - 1;
                 voff[i] = (uint32_t)((gr * ld + 8 * c) * 2);
             } else {
-                const int pos = 64 * j + lane, k = pos / CPR, ic = (pos % CPR) ^ (4 * (k & 3));
+                const int pos = 64 * j + lane, k = pos / CPR, ic = (pos % CPR) ^ swz(k);
                 int gr = t0 + 8 * ic;
                 gr = gr < rows - 8 ? gr : rows - 8;
                 voff[i] = (uint32_t)((k * ld + gr) * 2);
@@ -764,7 +767,7 @@ struct DmaTile {
                 const int a = lane & 15, q0 = (lane >> 4) & 1, e = a >> 2, c = a & 3;
                 const int cs = brole ? (((c & 1) << 1) | (c >> 1)) : c;
                 const int col = wbase + 32 * b + 16 * q0 + 4 * cs, k = 8 * lg + e;
-                roff[b] = (uint32_t)((k * CPR + ((col >> 3) ^ (4 * (k & 3)))) * 16 + ((col >> 2) & 1) * 8);
+                roff[b] = (uint32_t)((k * CPR + ((col >> 3) ^ swz(k))) * 16 + ((col >> 2) & 1) * 8);
             }
         }
     }
@@ -1069,6 +1072,73 @@ __global__ __launch_bounds__(2 * TN, 2) void k_gemm_pers(GemmArgs<bf16_t, KA, KB
                                   reinterpret_cast<float*>(dlds + S::kLds), first, pc, tmc, g.tiles_m, tmc * PG_TM, tnc * TN,
                                   g.crows, g.ccols, wm, wn);
         if (!more) break;
+    }
+}
+
+// ---- bf16 weight gradients with few tiles: 64 x 64 outputs a workgroup --------------------------------------------
+// dW of few preferences on 128 x 128 tiles leaves CUs without a workgroup, and its contraction may only be split where the
+// grouping of its sums says so.  Smaller tiles keep every sum as it is.  A wave owns 32 x 32 outputs; a step of 32
+// contraction indices is two products, so what bounds a workgroup is the latency of its operands: eight stages of 8 KB,
+// seven of them on their way.
+#define SG_NST 8
+#define SG_STAGE 8192
+template <class Epi>
+__global__ __launch_bounds__(256) void k_gemm_small(GemmArgs<bf16_t, SRC_KSTRIDED, SRC_KSTRIDED, Epi, true, GEMM_NCH> g) {
+    __shared__ __align__(16) unsigned char dlds[SG_NST * SG_STAGE];
+    const int id = xcd_remap(blockIdx.x, gridDim.x);
+    const int per_p = g.tiles_m * g.tiles_n;
+    const int p = id / per_p, tm = (id % per_p) / g.tiles_n, tn = id % g.tiles_n;
+    Epi epi = g.epi;
+    shift_epi(epi, p, g.e0_pstride, g.e1_pstride, g.e2_pstride);
+    const int r0 = tm * 64, c0 = tn * 64;
+    const int wave = threadIdx.x >> 6, wm = (wave >> 1) * 32, wn = (wave & 1) * 32;
+    DmaTile<SRC_KSTRIDED, 64, 1, 4> A, B;
+    A.set_lane(wm, false);
+    B.set_lane(wn, true);
+    const auto grp = g.group(p);
+    A.set_tile(g.a_base(grp), (int)g.a.ld, g.a.rows, r0);
+    B.set_tile(g.b_base(grp), (int)g.b.ld, g.b.rows, c0);
+    float16_t acc;
+#pragma unroll
+    for (int e = 0; e < 16; ++e) acc[e] = 0.f;
+    const int nk = grp.kdim / 32;
+    const uint32_t lbase = (uint32_t)(size_t)dlds;
+    auto issue = [&](int kt) {
+        const uint32_t tile = lbase + (uint32_t)(kt % SG_NST) * SG_STAGE;
+        A.issue(kt, tile);
+        B.issue(kt, tile + SG_STAGE / 2);
+    };
+    for (int st = 0; st < SG_NST - 1 && st < nk; ++st) issue(st);
+    for (int kt = 0; kt < nk; ++kt) {
+        // two loads a stage and wave; the oldest stage is the one multiplied next
+        const int ahead = nk - 1 - kt;
+        if (ahead >= SG_NST - 2) wait_vm<2 * (SG_NST - 2)>();
+        else if (ahead >= 3) wait_vm<6>();
+        else if (ahead == 2) wait_vm<4>();
+        else if (ahead == 1) wait_vm<2>();
+        else wait_vm<0>();
+        __syncthreads();  // stage kt has landed for every wave, and everyone is done with stage kt - 1
+        if (kt + SG_NST - 1 < nk) issue(kt + SG_NST - 1);
+        const unsigned char* ta = dlds + (kt % SG_NST) * SG_STAGE;
+        uint4 fa[2], fb[2];
+#pragma unroll
+        for (int ks = 0; ks < 2; ++ks) {
+            fa[ks] = A.frag(ta, 0, ks);
+            fb[ks] = B.frag(ta + SG_STAGE / 2, 0, ks);
+        }
+#pragma unroll
+        for (int ks = 0; ks < 2; ++ks) Mma32<bf16_t>::run(fb[ks], fa[ks], acc);  // transposed tile
+    }
+    const int lr = threadIdx.x & 31, lg = (threadIdx.x & 63) >> 5, r = r0 + wm + lr;
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+        const int c = c0 + wn + 16 * h + 8 * lg;
+        float v[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) v[u] = acc[8 * h + u];
+        typename Epi::Out o;
+        epi.compute(r, c, 8, v, o);
+        if (r < g.crows && c < g.ccols) epi.flush(r, c, (g.ccols - c < 8) ? (g.ccols - c) : 8, o);
     }
 }
 
@@ -1556,6 +1626,16 @@ static bool launch_dma(GemmArgs<T, KA, KB, Epi, FAST, NCH>& g, int P, int nb, hi
             }
             if (ptm * ((g.ccols + 127) / 128) * P >= slots) {
                 launch_pers(std::integral_constant<int, 128>{}, slots);
+                return true;
+            }
+        }
+        if constexpr (std::is_same<Epi, EpiDw>::value) {
+            // fewer 128 x 128 tiles than CUs: 24 preferences x 1250 rows x 256 x 256 (96 tiles) 18 us, on 64 x 64 tiles 15
+            const int stm = (g.crows + 63) / 64, stn = (g.ccols + 63) / 64;
+            if (nb < resident_slots() / 2 && stm * stn > g.tiles_m * g.tiles_n) {
+                g.tiles_m = stm;
+                g.tiles_n = stn;
+                k_gemm_small<Epi><<<stm * stn * P, 256, 0, s>>>(g);
                 return true;
             }
         }
