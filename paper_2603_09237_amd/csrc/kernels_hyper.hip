@@ -67,24 +67,51 @@ int64_t hyper_ws_bytes(const morlax_ctx* c) {
 }
 
 // ------------------------------------------------------------------------------------------------
-// Trunk f(w): h1 = tanh(Wh1 w + bh1), f = tanh(Wh2 h1 + bh2).  One block per preference.
-__global__ __launch_bounds__(64) void k_hyper_trunk(const float* __restrict__ hp, const float* __restrict__ w,
-                                                   float* __restrict__ h1, float* __restrict__ f, int K, int F,
-                                                   int64_t o_wh1, int64_t o_bh1, int64_t o_wh2, int64_t o_bh2) {
+// Trunk f(w): h1 = tanh(Wh1 w + bh1), f = tanh(Wh2 h1 + bh2).
+struct Trunk {
+    const float* w;  // [P][K]
+    float *h1, *f;   // [P][F]
+    int32_t K;
+    int64_t o_wh1, o_bh1, o_wh2, o_bh2;
+    __device__ inline float hidden(const float* __restrict__ hp, int p, int j) const {
+        float a = hp[o_bh1 + j];
+        for (int k = 0; k < K; ++k) a += hp[o_wh1 + (int64_t)j * K + k] * w[p * K + k];
+        return tanhf(a);
+    }
+    // a workgroup's own copy of the features of all preferences in LDS: sw [F][F + 1], sh and sf [P][F]
+    __device__ inline void features(const float* __restrict__ hp, float* sw, float* sh, float* sf, int P, int F, bool keep) const {
+        for (int e = threadIdx.x; e < F * F; e += blockDim.x) sw[e / F * (F + 1) + e % F] = hp[o_wh2 + e];
+        for (int i = threadIdx.x; i < P * F; i += blockDim.x) {
+            const float a = hidden(hp, i / F, i % F);
+            sh[i] = a;
+            if (keep) h1[i] = a;
+        }
+        __syncthreads();
+        for (int i = threadIdx.x; i < P * F; i += blockDim.x) {
+            const int p = i / F, j = i % F;
+            float a = hp[o_bh2 + j];
+            for (int k = 0; k < F; ++k) a += sw[j * (F + 1) + k] * sh[p * F + k];
+            a = tanhf(a);
+            sf[i] = a;
+            if (keep) f[i] = a;
+        }
+        __syncthreads();
+    }
+};
+// One block per preference.
+__global__ __launch_bounds__(64) void k_hyper_trunk(Trunk t, const float* __restrict__ hp, int F) {
     __shared__ float sh[MORLAX_MAX_F];
     const int p = blockIdx.x, j = threadIdx.x;
     if (j < F) {
-        float a = hp[o_bh1 + j];
-        for (int k = 0; k < K; ++k) a += hp[o_wh1 + (int64_t)j * K + k] * w[p * K + k];
-        a = tanhf(a);
+        const float a = t.hidden(hp, p, j);
         sh[j] = a;
-        h1[p * F + j] = a;
+        t.h1[p * F + j] = a;
     }
     __syncthreads();
     if (j < F) {
-        float a = hp[o_bh2 + j];
-        for (int i = 0; i < F; ++i) a += hp[o_wh2 + (int64_t)j * F + i] * sh[i];
-        f[p * F + j] = tanhf(a);
+        float a = hp[t.o_bh2 + j];
+        for (int i = 0; i < F; ++i) a += hp[t.o_wh2 + (int64_t)j * F + i] * sh[i];
+        t.f[p * F + j] = tanhf(a);
     }
 }
 
@@ -126,8 +153,10 @@ __device__ inline void put_run4(bf16_t* d, const float (&v)[4]) {
 // fused multiply-adds of a thread per row would: the same bits.  That form (a thread's row of M from 32 loads a
 // 128-byte line apart, f through scalar loads whose latency nothing covered) took 45.9 us for 69 thousand rows x 128
 // preferences, of which the 36 MB of results are 7; here 22.2.  14.3 us at 15 thousand x 24, here 5.1.
-template <typename TF, int KS>  // TF: type of the leading rows' destination (float factors, or theta_mat: strictly affine form)
-__global__ __launch_bounds__(256) void k_hyper_affine(AffineTable at, const float* __restrict__ hp,
+// TRUNK: every workgroup forms the features f(w) of all preferences itself (in LDS; the first one leaves them and h1 for
+// the backward pass), which with few of them costs less than the launch in front that it replaces (rule: trunk_inside).
+template <typename TF, int KS, bool TRUNK>  // TF: type of the leading rows' destination (float factors, or theta_mat: strictly affine form)
+__global__ __launch_bounds__(256) void k_hyper_affine(AffineTable at, Trunk tk, const float* __restrict__ hp,
                                                      const float* __restrict__ f, TF* __restrict__ fac,
                                                      float* __restrict__ theta_vec, int P, int F,
                                                      int64_t fac_len, int64_t vec_len) {
@@ -143,15 +172,18 @@ __global__ __launch_bounds__(256) void k_hyper_affine(AffineTable at, const floa
         so[lane] = m;
         sc[lane] = hp[c];
     }
+    extern __shared__ float tl[];  // TRUNK: Wh2 [F][F + 1], h1 [P][F], f [P][F]
+    const float* fs = f;
+    if constexpr (TRUNK) fs = tl + F * (F + 1) + P * F;
     float a[KS];
     auto load_f = [&](int p0) {
-        const float* fp = f + (int64_t)(p0 + ln < P ? p0 + ln : P - 1) * F;
+        const float* fp = fs + (int64_t)(p0 + ln < P ? p0 + ln : P - 1) * F;
 #pragma unroll
         for (int k = 0; k < KS; ++k) a[k] = fp[4 * k + kg < F ? 4 * k + kg : 0];
 #pragma unroll
         for (int k = 0; k < KS; ++k) a[k] = 4 * k + kg < F ? a[k] : 0.f;
     };
-    if (16 * wave < P) load_f(16 * wave);
+    if (!TRUNK && 16 * wave < P) load_f(16 * wave);
     __syncthreads();
     {
         float v[K4 / 4];
@@ -159,6 +191,10 @@ __global__ __launch_bounds__(256) void k_hyper_affine(AffineTable at, const floa
         for (int i = 0; i < K4 / 4; ++i) {
             const int idx = threadIdx.x + 256 * i, k = idx % K4;
             v[i] = hp[so[idx / K4] + (k < F ? k : 0)];
+        }
+        if constexpr (TRUNK) {
+            tk.features(hp, tl, tl + F * (F + 1), tl + F * (F + 1) + P * F, P, F, blockIdx.x == 0);
+            if (16 * wave < P) load_f(16 * wave);
         }
 #pragma unroll
         for (int i = 0; i < K4 / 4; ++i) {
@@ -204,12 +240,27 @@ __global__ __launch_bounds__(256) void k_hyper_affine(AffineTable at, const floa
         }
     }
 }
+// Preferences x features up to which both trunks, forward and backward, share a launch with what is next to them.  Forward (us,
+// apart and together; a launch on the dependent chain is another 1.5 to 2): 128 2.5 + 4.8 and 6.4, 512 4.5 + 5.5 and 9.0, 768
+// 4.1 + 5.1 and 9.5, 1024 4.6 + 5.8 and 12.1.  Backward: 128 3.4 + 3.3 and 3.6, 320 6.2 + 4.6 and 9.4, 768 5.6 + 4.3 and
+// 12.7, 1024 6.1 + 4.5 and 15.8.
+static bool trunk_inside(int P, int F) { return P * F <= 512; }
 template <typename TF>
-static void launch_affine(const AffineTable& at, const float* hp, const float* f, TF* fac, float* theta_vec, int P, int F,
-                          int64_t fac_len, int64_t vec_len, hipStream_t s) {
+static void launch_trunk_affine(const AffineTable& at, const Trunk& tk, const float* hp, TF* fac, float* theta_vec, int P, int F,
+                                int64_t fac_len, int64_t vec_len, hipStream_t s) {
     const int nb = (at.q_total + 63) / 64;
-    if (F <= 32) k_hyper_affine<TF, 8><<<nb, 256, 0, s>>>(at, hp, f, fac, theta_vec, P, F, fac_len, vec_len);
-    else k_hyper_affine<TF, 16><<<nb, 256, 0, s>>>(at, hp, f, fac, theta_vec, P, F, fac_len, vec_len);
+    auto run = [&](auto ks) {
+        constexpr int KS = decltype(ks)::value;
+        if (trunk_inside(P, F)) {
+            const int lds = (F * (F + 1) + 2 * P * F) * 4;
+            k_hyper_affine<TF, KS, true><<<nb, 256, lds, s>>>(at, tk, hp, tk.f, fac, theta_vec, P, F, fac_len, vec_len);
+        } else {
+            k_hyper_trunk<<<P, 64, 0, s>>>(tk, hp, F);
+            k_hyper_affine<TF, KS, false><<<nb, 256, 0, s>>>(at, tk, hp, tk.f, fac, theta_vec, P, F, fac_len, vec_len);
+        }
+    };
+    if (F <= 32) run(std::integral_constant<int, 8>{});
+    else run(std::integral_constant<int, 16>{});
 }
 
 // W_l(p) = W0_l + A_l(p) B_l(p).  A block makes a 64 (d_out) x 128 (d_in) tile of one layer of one
@@ -279,14 +330,15 @@ __global__ __launch_bounds__(256) void k_hyper_materialize(NetDev nd, MatTiles m
     }
 }
 
-static void run_trunk_and_affine(const morlax_ctx* c, int net, const float* hp, const float* w,
-                                 const HyperWs& L, float* theta_vec_or_null, float* vec_scratch, hipStream_t s) {
+static Trunk trunk_of(const morlax_ctx* c, int net, const float* w, const HyperWs& L) {
     const NetDev& nd = c->net[net];
-    const AffineTable& at = c->aff[net];
-    const int P = c->d.P, F = c->d.hyper_width;
-    k_hyper_trunk<<<P, 64, 0, s>>>(hp, w, L.h1, L.f, c->d.K, F, nd.hp_wh1, nd.hp_bh1, nd.hp_wh2, nd.hp_bh2);
-    float* tv = theta_vec_or_null ? theta_vec_or_null : vec_scratch;
-    launch_affine<float>(at, hp, L.f, L.fac, tv, P, F, nd.fac_len, nd.vec_len, s);
+    return {w, L.h1, L.f, c->d.K, nd.hp_wh1, nd.hp_bh1, nd.hp_wh2, nd.hp_bh2};
+}
+static void run_trunk_and_affine(const morlax_ctx* c, int net, const float* hp, const float* w,
+                                 const HyperWs& L, float* theta_vec, hipStream_t s) {
+    const NetDev& nd = c->net[net];
+    launch_trunk_affine<float>(c->aff[net], trunk_of(c, net, w, L), hp, L.fac, theta_vec, c->d.P, c->d.hyper_width, nd.fac_len,
+                               nd.vec_len, s);
 }
 
 static MatTiles mat_tiles(const NetDev& nd) {
@@ -307,16 +359,16 @@ void launch_hypernet_fwd(const morlax_ctx* c, int net, const float* hparams, con
     HyperWs L = hyper_ws_layout(c, ws, nullptr);
     if (c->d.rank < 0) {
         // strictly affine form (Sec. III-B as written): the stacked map writes theta_mat and theta_vec directly
-        const AffineTable& at = c->aff[net];
-        const int P = c->d.P, F = c->d.hyper_width;
-        k_hyper_trunk<<<P, 64, 0, s>>>(hparams, w, L.h1, L.f, c->d.K, F, nd.hp_wh1, nd.hp_bh1, nd.hp_wh2, nd.hp_bh2);
+        const Trunk tk = trunk_of(c, net, w, L);
         if (c->d.wdtype == 1)
-            launch_affine<bf16_t>(at, hparams, L.f, (bf16_t*)theta_mat, theta_vec, P, F, nd.fac_len, nd.vec_len, s);
+            launch_trunk_affine<bf16_t>(c->aff[net], tk, hparams, (bf16_t*)theta_mat, theta_vec, c->d.P, c->d.hyper_width,
+                                        nd.fac_len, nd.vec_len, s);
         else
-            launch_affine<float>(at, hparams, L.f, (float*)theta_mat, theta_vec, P, F, nd.fac_len, nd.vec_len, s);
+            launch_trunk_affine<float>(c->aff[net], tk, hparams, (float*)theta_mat, theta_vec, c->d.P, c->d.hyper_width,
+                                       nd.fac_len, nd.vec_len, s);
         return;
     }
-    run_trunk_and_affine(c, net, hparams, w, L, theta_vec, nullptr, s);
+    run_trunk_and_affine(c, net, hparams, w, L, theta_vec, s);
     MatTiles mt = mat_tiles(nd);
     const dim3 grid(mt.tile0[nd.n_layers], c->d.P);
     if (c->d.wdtype == 1)
@@ -332,20 +384,10 @@ void launch_hypernet_fwd(const morlax_ctx* c, int net, const float* hparams, con
 __device__ inline void mrow_entry(const AffineTable& at, int32_t* __restrict__ mrow, int32_t* __restrict__ crow, int F, int q) {
     if (q < at.q_total) row_offsets(at, F, q, mrow[q], crow[q]);
 }
-__global__ __launch_bounds__(256) void k_hyper_mrow(AffineTable at, int32_t* __restrict__ mrow, int32_t* __restrict__ crow, int F) {
-    mrow_entry(at, mrow, crow, F, blockIdx.x * 256 + threadIdx.x);
-}
 
-// dW0_l = sum_p dW_l(p): four consecutive elements per thread, p ascending.  The blocks behind the first n_base make
-// the row offsets of the stacked affine matrix, which would otherwise take a launch of 5 us on the dependent chain.
-__global__ __launch_bounds__(256) void k_hyper_dbase(NetDev nd, const float* __restrict__ dmat,
-                                                    float* __restrict__ dhp, int P, int n_base, AffineTable at,
-                                                    int32_t* __restrict__ mrow, int32_t* __restrict__ crow, int F) {
-    if ((int)blockIdx.x >= n_base) {
-        mrow_entry(at, mrow, crow, F, ((int)blockIdx.x - n_base) * 256 + threadIdx.x);
-        return;
-    }
-    const int64_t e = ((int64_t)blockIdx.x * 256 + threadIdx.x) * 4;
+// dW0_l = sum_p dW_l(p): four consecutive elements per thread, p ascending.
+__device__ inline void dbase_block(const NetDev& nd, const float* __restrict__ dmat, float* __restrict__ dhp, int P, int blk) {
+    const int64_t e = ((int64_t)blk * 256 + threadIdx.x) * 4;
     if (e >= nd.mat_len) return;
     int l = 0;
     while (l + 1 < nd.n_layers && e >= nd.layer[l + 1].mat_off) ++l;
@@ -366,12 +408,29 @@ __global__ __launch_bounds__(256) void k_hyper_dbase(NetDev nd, const float* __r
     float* d = dhp + nd.layer[l].hp_w0 + (e - nd.layer[l].mat_off);
     d[0] = a.x; d[1] = a.y; d[2] = a.z; d[3] = a.w;
 }
+struct BaseWork {  // blocks of 256 threads behind (or, where there are factors, among) those of k_hyper_dAB
+    int32_t n_dw0, n_rows;  // blocks that add up dW0, blocks that make the row offsets of the stacked affine matrix
+    float* dhp;
+    int32_t *mrow, *crow;
+    int32_t F;
+};
+__device__ inline void base_block(const NetDev& nd, const AffineTable& at, const BaseWork& bw, const float* __restrict__ dmat,
+                                  int P, int blk) {
+    if (blk < bw.n_dw0) dbase_block(nd, dmat, bw.dhp, P, blk);
+    else mrow_entry(at, bw.mrow, bw.crow, bw.F, (blk - bw.n_dw0) * 256 + threadIdx.x);
+}
+__global__ __launch_bounds__(256) void k_hyper_base(NetDev nd, AffineTable at, BaseWork bw, const float* __restrict__ dmat, int P) {
+    base_block(nd, at, bw, dmat, P, blockIdx.x);
+}
 
 // Fused dA / dB on fp32 MFMA, one pass over dW:
 //   dA_l(p)[o, k] = sum_i dW_l(p)[o, i] B_l(p)[k, i],   dB_l(p)[k, i] = sum_o A_l(p)[o, k] dW_l(p)[o, i].
 // A block owns (p, layer, a run of <= DAB_COLS columns).  It walks the 64 x 64 tiles of dW row block by row
 // block: wave w multiplies rows 16 w .. of the tile by B^T (dA, finished after the columns of a row block)
 // and A^T by columns 16 w .. of the tile (dB, accumulated over all row blocks in registers).
+// dW0, which reads the same matrices, runs in blocks spread evenly among these: it is bound by memory, dA / dB by its
+// products (128 preferences of 4 x 512, rank 16: 87 us behind 133 as launches of their own, together 182; 24 of 3 x 256: 5.6
+// + 18 and 22.4).
 struct DabWork {
     int32_t n;
     int16_t layer[DAB_MAX_CS * MORLAX_MAX_LAYERS];
@@ -379,16 +438,21 @@ struct DabWork {
 };
 
 template <int RT>
-__global__ __launch_bounds__(256) void k_hyper_dAB(NetDev nd, DabWork wk, const float* __restrict__ dmat,
-                                                  const float* __restrict__ fac, float* __restrict__ dfac,
-                                                  float* __restrict__ da_part, int r, int P) {
+__global__ __launch_bounds__(256) void k_hyper_dAB(NetDev nd, DabWork wk, AffineTable at, BaseWork bw,
+                                                  const float* __restrict__ dmat, const float* __restrict__ fac,
+                                                  float* __restrict__ dfac, float* __restrict__ da_part, int r, int P) {
     constexpr int AP = 16 * RT + 4;
     __shared__ __align__(16) float sW[64][68];
     __shared__ float sA[64][AP];
     __shared__ float sB[DAB_NCT][16 * RT][68];
-    const int p = blockIdx.y;
-    const LayerDev L = nd.layer[wk.layer[blockIdx.x]];
-    const int cs = wk.cs[blockIdx.x];
+    const int64_t n_base = bw.n_dw0 + bw.n_rows, before = n_base * blockIdx.x / gridDim.x;  // base blocks in front of this one
+    if (n_base * (blockIdx.x + 1) / gridDim.x != before) {
+        base_block(nd, at, bw, dmat, P, (int)before);
+        return;
+    }
+    const int dab = blockIdx.x - (int)before, p = dab / wk.n, item = dab % wk.n;
+    const LayerDev L = nd.layer[wk.layer[item]];
+    const int cs = wk.cs[item];
     const int c_lo = cs * DAB_COLS;
     const int c_hi = (L.d_in < c_lo + DAB_COLS) ? L.d_in : (c_lo + DAB_COLS);
     const int nct = (c_hi - c_lo + 63) / 64;
@@ -795,6 +859,74 @@ __global__ __launch_bounds__(64) void k_hyper_trunk_bwd_b(const float* __restric
     if (idx < F) dhp[o_bh1 + idx] = trunk_dot(dz1 + idx, F, nullptr, 0, P);
 }
 
+// Both stages in one workgroup, where its one CU reads the partials in less time than the second launch costs
+// (trunk_inside).  The same sums.  LDS: dz2, dz1, h1 [P][F], w [P][K], the four shares [4][P F].
+__global__ __launch_bounds__(1024) void k_hyper_trunk_bwd(const float* __restrict__ hp, const float* __restrict__ part, int n_chunk,
+                                                         const float* __restrict__ f, const float* __restrict__ h1,
+                                                         const float* __restrict__ w, float* __restrict__ dhp, int P, int K,
+                                                         int F, int64_t o_wh1, int64_t o_bh1, int64_t o_wh2, int64_t o_bh2) {
+    extern __shared__ float tl[];
+    __shared__ float wh2[MORLAX_MAX_F * MORLAX_MAX_F];
+    const int PF = P * F, tid = threadIdx.x;
+    float *z2 = tl, *z1 = tl + PF, *sh = tl + 2 * PF, *red = tl + 3 * PF, *sw = tl + 7 * PF;
+    for (int e = tid; e < F * F; e += 1024) wh2[e] = hp[o_wh2 + e];
+    for (int e = tid; e < PF; e += 1024) sh[e] = h1[e];
+    for (int e = tid; e < P * K; e += 1024) sw[e] = w[e];
+    for (int e = tid; e < 4 * PF; e += 1024) {
+        const float* src = part + e % PF;
+        float a = 0.f;
+        int c = e / PF;
+        for (; c + 60 < n_chunk; c += 64) {  // sixteen chunks of this share per batch, loads in flight together
+            float v[16];
+#pragma unroll
+            for (int u = 0; u < 16; ++u) v[u] = src[(int64_t)(c + 4 * u) * PF];
+#pragma unroll
+            for (int u = 0; u < 16; ++u) a += v[u];
+        }
+        for (; c + 12 < n_chunk; c += 16) {
+            float v[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) v[u] = src[(int64_t)(c + 4 * u) * PF];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) a += v[u];
+        }
+        for (; c < n_chunk; c += 4) a += src[(int64_t)c * PF];
+        red[e] = a;
+    }
+    __syncthreads();
+    for (int i = tid; i < PF; i += 1024) {
+        const float fv = f[i];
+        z2[i] = (red[i] + red[PF + i] + red[2 * PF + i] + red[3 * PF + i]) * (1.f - fv * fv);
+    }
+    __syncthreads();
+    for (int i = tid; i < PF; i += 1024) {
+        const float* z = z2 + i / F * F;
+        float b = 0.f;
+        for (int j = 0; j < F; ++j) b += z[j] * wh2[j * F + i % F];
+        z1[i] = b * (1.f - sh[i] * sh[i]);
+    }
+    __syncthreads();
+    for (int e = tid; e < F * F + F * K + 2 * F; e += 1024) {
+        int idx = e;
+        const float *x, *y = nullptr;
+        int sy = 0;
+        float* dst;
+        if (idx < F * F) {
+            x = z2 + idx / F; y = sh + idx % F; sy = F; dst = dhp + o_wh2 + idx;
+        } else if ((idx -= F * F) < F * K) {
+            x = z1 + idx / K; y = sw + idx % K; sy = K; dst = dhp + o_wh1 + idx;
+        } else if ((idx -= F * K) < F) {
+            x = z2 + idx; dst = dhp + o_bh2 + idx;
+        } else {
+            idx -= F;
+            x = z1 + idx; dst = dhp + o_bh1 + idx;
+        }
+        float a = 0.f;
+        for (int p = 0; p < P; ++p) a += x[p * F] * (y ? y[p * sy] : 1.f);
+        *dst = a;
+    }
+}
+
 void launch_hypernet_bwd(const morlax_ctx* c, int net, const float* hparams, const float* w,
                          const float* dtheta_mat, const float* dtheta_vec, float* dhparams, void* ws,
                          bool kept, hipStream_t s) {
@@ -809,13 +941,13 @@ void launch_hypernet_bwd(const morlax_ctx* c, int net, const float* hparams, con
     if (affine) {
         // only f is needed again; dW0 and dMW come out of the dM pass below (W0 is the constant term of those rows)
         if (!kept)
-            k_hyper_trunk<<<P, 64, 0, s>>>(hparams, w, L.h1, L.f, K, F, nd.hp_wh1, nd.hp_bh1, nd.hp_wh2, nd.hp_bh2);
+            k_hyper_trunk<<<P, 64, 0, s>>>(trunk_of(c, net, w, L), hparams, F);
     } else {
         // recompute f and the factors; the theta_vec rows of the affine map land in a scratch nobody reads
-        if (!kept) run_trunk_and_affine(c, net, hparams, w, L, nullptr, L.vecs, s);
-        const int n_base = (int)((nd.mat_len / 4 + 255) / 256);
-        k_hyper_dbase<<<n_base + (at.q_total + 255) / 256, 256, 0, s>>>(nd, dtheta_mat, dhparams, P, n_base, at, L.mrow, L.crow, F);
+        if (!kept) run_trunk_and_affine(c, net, hparams, w, L, L.vecs, s);
     }
+    const BaseWork bw = {affine ? 0 : (int)((nd.mat_len / 4 + 255) / 256), (at.q_total + 255) / 256, dhparams, L.mrow, L.crow, F};
+    const int n_base = bw.n_dw0 + bw.n_rows;
     if (r > 0) {
         DabWork wk;
         wk.n = 0;
@@ -829,12 +961,13 @@ void launch_hypernet_bwd(const morlax_ctx* c, int net, const float* hparams, con
                 ++wk.n;
             }
         }
-        if (r <= 16) k_hyper_dAB<1><<<dim3(wk.n, P), 256, 0, s>>>(nd, wk, dtheta_mat, L.fac, L.dfac, L.da_part, r, P);
-        else k_hyper_dAB<2><<<dim3(wk.n, P), 256, 0, s>>>(nd, wk, dtheta_mat, L.fac, L.dfac, L.da_part, r, P);
+        const int nb = wk.n * P + n_base;
+        if (r <= 16) k_hyper_dAB<1><<<nb, 256, 0, s>>>(nd, wk, at, bw, dtheta_mat, L.fac, L.dfac, L.da_part, r, P);
+        else k_hyper_dAB<2><<<nb, 256, 0, s>>>(nd, wk, at, bw, dtheta_mat, L.fac, L.dfac, L.da_part, r, P);
         if (split)
             k_hyper_dA_merge<<<dim3((int)((nd.fac_len + 255) / 256), P), 256, 0, s>>>(nd, L.da_part, L.dfac, r, P);
     }
-    if (affine) k_hyper_mrow<<<(at.q_total + 255) / 256, 256, 0, s>>>(at, L.mrow, L.crow, F);
+    if (r <= 0) k_hyper_base<<<n_base, 256, 0, s>>>(nd, at, bw, dtheta_mat, P);
     // at least four tiles per chunk, about a thousand chunks at most
     const int n_tiles = (at.q_total + DMF_Q - 1) / DMF_Q, tpw = df_chunk_tiles(at.q_total);
     const int n_chunk = (n_tiles + tpw - 1) / tpw, n_df = (P + DMF_P - 1) / DMF_P, n_dm = (tpw + 3) / 4;
@@ -844,6 +977,12 @@ void launch_hypernet_bwd(const morlax_ctx* c, int net, const float* hparams, con
     };
     if (F <= 32) dM_df(k_hyper_dM_df<2>);
     else dM_df(k_hyper_dM_df<4>);
+    const int lds = (7 * P * F + P * K) * 4;  // (with the kernel's 16 KB at most 64)
+    if (trunk_inside(P, F) && lds <= 48 * 1024) {
+        k_hyper_trunk_bwd<<<1, 1024, lds, s>>>(hparams, L.df_part, n_chunk, L.f, L.h1, w, dhparams, P, K, F, nd.hp_wh1, nd.hp_bh1,
+                                               nd.hp_wh2, nd.hp_bh2);
+        return;
+    }
     const int ppb = 64 / F;  // preferences per block (F <= 64)
     k_hyper_trunk_bwd_a<<<(P + ppb - 1) / ppb, 256, 0, s>>>(hparams, L.df_part, n_chunk, L.f, L.h1, L.dz2, L.dz1, P, F,
                                                            nd.hp_wh2);
