@@ -263,69 +263,83 @@ static void launch_trunk_affine(const AffineTable& at, const Trunk& tk, const fl
     else run(std::integral_constant<int, 16>{});
 }
 
-// W_l(p) = W0_l + A_l(p) B_l(p).  A block makes a 64 (d_out) x 128 (d_in) tile of one layer of one
-// preference; each thread 4 x 8 outputs with the factor tiles in LDS.
+// W_l(p) = W0_l + A_l(p) B_l(p) on fp32 MFMA.  A block makes a 64 (d_out) x 128 (d_in) tile of one layer of one preference,
+// wave w its rows 16 w .. 16 w + 15.  Operands come straight from memory (B is shared by the four waves through the vector
+// cache): no LDS, no barrier, a wave's requests are all on their way at once.  Lane ln of accumulator j holds column 8 ln +
+// j, so that its eight accumulators are eight consecutive weights of a row.  Products add in ascending k, as one
+// multiply-add after the other would: the same bits.  On the vector ALU from LDS tiles 12.2 us for 24 preferences of 3 x
+// 256, here 8.3, 12.9 and 9.8 for 32; 91.6 for 128 of 4 x 512, the same here: 48 for the stores alone, W0 (twice the
+// results' bytes, from the caches) and the factors on top.  (W0 shared by two preferences in registers: 101; a
+// preference's tiles on one die: 120.)
 struct MatTiles {
     int32_t tile0[MORLAX_MAX_LAYERS + 1];  // first tile id of each layer
     int32_t tiles_i[MORLAX_MAX_LAYERS];    // tiles along d_in
 };
 
-template <typename T>
+template <typename T, int KS>
 __global__ __launch_bounds__(256) void k_hyper_materialize(NetDev nd, MatTiles mt, const float* __restrict__ hp,
-                                                          const float* __restrict__ fac,
-                                                          T* __restrict__ theta_mat, int r) {
-    __shared__ float sA[64][MORLAX_MAX_RANK + 1];
-    __shared__ float sB[MORLAX_MAX_RANK][128];
+                                                          const float* __restrict__ fac, T* __restrict__ theta_mat, int r) {
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, ln = lane & 15, kg = lane >> 4;
     const int p = blockIdx.y;
     int l = 0;
     while (l + 1 < nd.n_layers && (int)blockIdx.x >= mt.tile0[l + 1]) ++l;
     const LayerDev L = nd.layer[l];
     const int tl = blockIdx.x - mt.tile0[l];
-    const int o0 = (tl / mt.tiles_i[l]) * 64, i0 = (tl % mt.tiles_i[l]) * 128;
+    const int o0 = (tl / mt.tiles_i[l]) * 64 + 16 * wave, i0 = (tl % mt.tiles_i[l]) * 128 + 8 * ln;
+    if (o0 >= L.d_out) return;
+    const int oa = o0 + ln < L.d_out ? o0 + ln : L.d_out - 1;  // row of A this lane feeds
+    // the lane's columns i0 .. i0 + 7 of a row, zero beyond the matrix
+    auto row8 = [&](const float* row, bool ok, float (&v)[8]) {
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            const int i = i0 + 4 * h;
+            if (i + 4 <= L.d_in) {
+                const Run4 q = *reinterpret_cast<const Run4*>(row + i);
+#pragma unroll
+                for (int e = 0; e < 4; ++e) v[4 * h + e] = ok ? q.v[e] : 0.f;
+            } else {
+#pragma unroll
+                for (int e = 0; e < 4; ++e) v[4 * h + e] = ok && i + e < L.d_in ? row[i + e] : 0.f;
+            }
+        }
+    };
+    float w0[4][8];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+        const int o = o0 + 4 * kg + e;
+        row8(hp + L.hp_w0 + (int64_t)(o < L.d_out ? o : L.d_out - 1) * L.d_in, true, w0[e]);
+    }
     const float* fp = fac + (int64_t)p * nd.fac_len;
-    for (int idx = threadIdx.x; idx < 64 * r; idx += 256) {
-        const int oo = idx / r, k = idx % r;
-        sA[oo][k] = (o0 + oo < L.d_out) ? fp[L.fac_a + (int64_t)(o0 + oo) * r + k] : 0.f;
+    float a[KS + 1], b[KS + 1][8];  // (KS = 0, rank 0: W0 alone, there are no factors to read)
+#pragma unroll
+    for (int s = 0; s < KS; ++s) {
+        const int k = 4 * s + kg, kc = k < r ? k : 0;
+        a[s] = fp[L.fac_a + (int64_t)oa * r + kc];
+        a[s] = k < r ? a[s] : 0.f;
+        row8(fp + L.fac_b + (int64_t)kc * L.d_in, k < r, b[s]);
     }
-    for (int idx = threadIdx.x; idx < r * 128; idx += 256) {
-        const int k = idx / 128, ii = idx % 128;
-        sB[k][ii] = (i0 + ii < L.d_in) ? fp[L.fac_b + (int64_t)k * L.d_in + i0 + ii] : 0.f;
-    }
-    __syncthreads();
-    const int to = (threadIdx.x / 16) * 4, ti = (threadIdx.x % 16) * 8;
-    float acc[4][8];
+    float4_t acc[8];
 #pragma unroll
-    for (int a = 0; a < 4; ++a)
+    for (int j = 0; j < 8; ++j) acc[j] = float4_t{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-        for (int b = 0; b < 8; ++b) acc[a][b] = 0.f;
-    for (int k = 0; k < r; ++k) {
-        float bv[8], av[4];
+    for (int s = 0; s < KS; ++s)
 #pragma unroll
-        for (int b = 0; b < 8; ++b) bv[b] = sB[k][ti + b];
-#pragma unroll
-        for (int a = 0; a < 4; ++a) av[a] = sA[to + a][k];
-#pragma unroll
-        for (int a = 0; a < 4; ++a)
-#pragma unroll
-            for (int b = 0; b < 8; ++b) acc[a][b] += av[a] * bv[b];
-    }
+        for (int j = 0; j < 8; ++j) acc[j] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[s], b[s][j], acc[j], 0, 0, 0);
     T* dst = theta_mat + (int64_t)p * nd.mat_len + L.mat_off;
-    const float* w0 = hp + L.hp_w0;
-    const bool vec = (L.d_in % 8 == 0);
 #pragma unroll
-    for (int a = 0; a < 4; ++a) {
-        const int o = o0 + to + a;
+    for (int e = 0; e < 4; ++e) {
+        const int o = o0 + 4 * kg + e;
         if (o >= L.d_out) continue;
-        const int64_t base = (int64_t)o * L.d_in + i0 + ti;
-        if (vec && i0 + ti + 8 <= L.d_in) {
-            float v[8];
+        T* d = dst + (int64_t)o * L.d_in + i0;
+        float v[8];
 #pragma unroll
-            for (int b = 0; b < 8; ++b) v[b] = w0[base + b] + acc[a][b];
-            store8(dst + base, v);
+        for (int j = 0; j < 8; ++j) v[j] = w0[e][j] + acc[j][e];
+        if (i0 + 8 <= L.d_in && L.d_in % 8 == 0) {
+            store8(d, v);
         } else {
 #pragma unroll
-            for (int b = 0; b < 8; ++b)
-                if (i0 + ti + b < L.d_in) dst[base + b] = cvt<T>(w0[base + b] + acc[a][b]);
+            for (int j = 0; j < 8; ++j)
+                if (i0 + j < L.d_in) d[j] = cvt<T>(v[j]);
         }
     }
 }
@@ -371,10 +385,17 @@ void launch_hypernet_fwd(const morlax_ctx* c, int net, const float* hparams, con
     run_trunk_and_affine(c, net, hparams, w, L, theta_vec, s);
     MatTiles mt = mat_tiles(nd);
     const dim3 grid(mt.tile0[nd.n_layers], c->d.P);
-    if (c->d.wdtype == 1)
-        k_hyper_materialize<bf16_t><<<grid, 256, 0, s>>>(nd, mt, hparams, L.fac, (bf16_t*)theta_mat, c->d.rank);
-    else
-        k_hyper_materialize<float><<<grid, 256, 0, s>>>(nd, mt, hparams, L.fac, (float*)theta_mat, c->d.rank);
+    const int r = c->d.rank;
+    auto pick = [&](auto type) {
+        typedef decltype(type) T;
+        T* tm = reinterpret_cast<T*>(theta_mat);
+        if (r == 0) k_hyper_materialize<T, 0><<<grid, 256, 0, s>>>(nd, mt, hparams, L.fac, tm, r);
+        else if (r <= 8) k_hyper_materialize<T, 2><<<grid, 256, 0, s>>>(nd, mt, hparams, L.fac, tm, r);
+        else if (r <= 16) k_hyper_materialize<T, 4><<<grid, 256, 0, s>>>(nd, mt, hparams, L.fac, tm, r);
+        else k_hyper_materialize<T, 8><<<grid, 256, 0, s>>>(nd, mt, hparams, L.fac, tm, r);
+    };
+    if (c->d.wdtype == 1) pick(bf16_t{});
+    else pick(float{});
 }
 
 // ------------------------------------------------------------------------------------------------
