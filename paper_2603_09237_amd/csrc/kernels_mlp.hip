@@ -1075,6 +1075,70 @@ __global__ __launch_bounds__(2 * TN, 2) void k_gemm_pers(GemmArgs<bf16_t, KA, KB
     }
 }
 
+// ---- fp32 weight gradients on 64 x 64 tiles ------------------------------------------------------------------------
+// k_grouped_gemm's products for dW where 128 x 128 tiles would multiply more padding (160 x 160 outputs: 64 blocks of 32 x 32
+// on four tiles, 36 on nine small ones; 32 x 32: 16 and 4).  A wave owns one block; the contraction (whole 32-index steps)
+// runs in the same order, so the sums keep their bits.  Bound by the fp32 products as that kernel is.
+template <class Epi>
+__global__ __launch_bounds__(256) void k_gemm_f32_small(GemmArgs<float, SRC_KSTRIDED, SRC_KSTRIDED, Epi, true, GEMM_NCH> g) {
+    constexpr int PITCH = GEMM_NCH * 16 + 16;
+    __shared__ __align__(16) unsigned char lds[2][2][64 * PITCH];
+    const int id = xcd_remap(blockIdx.x, gridDim.x);
+    const int per_p = g.tiles_m * g.tiles_n;
+    const int p = id / per_p, tm = (id % per_p) / g.tiles_n, tn = id % g.tiles_n;
+    Epi epi = g.epi;
+    shift_epi(epi, p, g.e0_pstride, g.e1_pstride, g.e2_pstride);
+    const auto grp = g.group(p);
+    const int r0 = tm * 64, c0 = tn * 64;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, lr = lane & 31, lg = lane >> 5;
+    const int wm = (wave >> 1) * 32, wn = (wave & 1) * 32;
+    const int lrp = (lr & 0x13) | ((lr & 4) << 1) | ((lr & 8) >> 1);
+    // a thread stages contraction indices 4 wave .. + 3 of row `lane` of either operand (rows past the end: the last one)
+    const float* A = g.a_base(grp) + (int64_t)(4 * wave) * g.a.ld + (r0 + lane < g.a.rows ? r0 + lane : g.a.rows - 1);
+    const float* B = g.b_base(grp) + (int64_t)(4 * wave) * g.b.ld + (c0 + lane < g.b.rows ? c0 + lane : g.b.rows - 1);
+    float ra[4], rb[4];
+    auto load = [&](int k0) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            ra[e] = A[(int64_t)(k0 + e) * g.a.ld];
+            rb[e] = B[(int64_t)(k0 + e) * g.b.ld];
+        }
+    };
+    auto store = [&](int buf) {
+        *reinterpret_cast<float4*>(lds[buf][0] + lane * PITCH + wave * 16) = make_float4(ra[0], ra[1], ra[2], ra[3]);
+        *reinterpret_cast<float4*>(lds[buf][1] + lane * PITCH + wave * 16) = make_float4(rb[0], rb[1], rb[2], rb[3]);
+    };
+    float16_t acc;
+#pragma unroll
+    for (int e = 0; e < 16; ++e) acc[e] = 0.f;
+    const int nk = grp.kdim / 16;
+    load(0);
+    store(0);
+    __syncthreads();
+    for (int kt = 0; kt < nk; ++kt) {
+        const int cur = kt & 1;
+        if (kt + 1 < nk) load(16 * (kt + 1));
+        const unsigned char* ta = lds[cur][0] + (wm + lr) * PITCH + lg * 16;
+        const unsigned char* tb = lds[cur][1] + (wn + lrp) * PITCH + lg * 16;
+#pragma unroll
+        for (int ks = 0; ks < GEMM_NCH / 2; ++ks)
+            Mma32<float>::run(*reinterpret_cast<const uint4*>(tb + ks * 32), *reinterpret_cast<const uint4*>(ta + ks * 32), acc);
+        if (kt + 1 < nk) store(cur ^ 1);
+        __syncthreads();
+    }
+    const int r = r0 + wm + lr;
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+        const int c = c0 + wn + 16 * h + 8 * lg;
+        float v[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) v[u] = acc[8 * h + u];
+        typename Epi::Out o;
+        epi.compute(r, c, 8, v, o);
+        if (r < g.crows && c < g.ccols) epi.flush(r, c, (g.ccols - c < 8) ? (g.ccols - c) : 8, o);
+    }
+}
+
 // ---- bf16 weight gradients with few tiles: 64 x 64 outputs a workgroup --------------------------------------------
 // dW of few preferences on 128 x 128 tiles leaves CUs without a workgroup, and its contraction may only be split where the
 // grouping of its sums says so.  Smaller tiles keep every sum as it is.  A wave owns 32 x 32 outputs; a step of 32
@@ -1590,7 +1654,7 @@ static int resident_slots() {  // workgroups of the persistent kernel: two per C
 }
 
 template <typename T, int KA, int KB, class Epi, bool FAST, int NCH>
-static bool launch_dma(GemmArgs<T, KA, KB, Epi, FAST, NCH>& g, int P, int nb, hipStream_t s) {
+static bool launch_special(GemmArgs<T, KA, KB, Epi, FAST, NCH>& g, int P, int nb, hipStream_t s) {
     if constexpr (std::is_same<T, bf16_t>::value && FAST && (KA == SRC_KCONTIG || KA == SRC_KSTRIDED) &&
                   (KB == SRC_KCONTIG || KB == SRC_KSTRIDED)) {
         if (g.a.kdim < 32 || (g.a.kdim & 31)) return false;
@@ -1648,6 +1712,14 @@ static bool launch_dma(GemmArgs<T, KA, KB, Epi, FAST, NCH>& g, int P, int nb, hi
         }
         k_gemm_dma<KA, KB, Epi><<<nb, 256, lds_bytes, s>>>(g);
         return true;
+    } else if constexpr (std::is_same<T, float>::value && std::is_same<Epi, EpiDw>::value) {
+        // fewer blocks of 32 x 32 to multiply (10 preferences x 1850 rows x 160 x 160: 44 us on 128 x 128 tiles, 23)
+        const int stm = (g.crows + 63) / 64, stn = (g.ccols + 63) / 64;
+        if (stm * stn >= 4 * g.tiles_m * g.tiles_n || (g.a.kdim & 31)) return false;
+        g.tiles_m = stm;
+        g.tiles_n = stn;
+        k_gemm_f32_small<Epi><<<stm * stn * P, 256, 0, s>>>(g);
+        return true;
     } else {
         (void)g; (void)nb; (void)s;
         return false;
@@ -1663,7 +1735,7 @@ static void run_gemm(const morlax_ctx* c, int kind, GemmArgs<T, KA, KB, Epi, FAS
     const int nb = g.tiles_m * g.tiles_n * P;
     GemmProf::Rec* r = prof_take(c, kind, 2.0 * g.crows * (double)g.ccols * g.a.kdim * (P / g.ranges));
     if (r) (void)hipEventRecord(r->a, s);
-    if (!launch_dma(g, P, nb, s)) k_grouped_gemm<T, KA, KB, Epi, FAST, NCH><<<nb, 256, 0, s>>>(g);
+    if (!launch_special(g, P, nb, s)) k_grouped_gemm<T, KA, KB, Epi, FAST, NCH><<<nb, 256, 0, s>>>(g);
     if (r) (void)hipEventRecord(r->b, s);
 }
 
