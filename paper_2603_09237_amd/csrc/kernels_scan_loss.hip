@@ -602,26 +602,13 @@ __global__ __launch_bounds__(NT, 8) void k_ppo_loss_grad(
 }
 
 // blocks 0 .. P-1: dlogsig[p][:] (the preference's block partials in block order); block P: the statistics.
-// 1024 threads, so that the one block that adds up the statistics has enough loads in flight.
-__device__ inline double block_sum16(double v, double* sh) {  // 16 waves, fixed order
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v += __shfl_down(v, o, WAVE);
-    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-    if (lane == 0) sh[wv] = v;
-    __syncthreads();
-    double tot = sh[0];
-#pragma unroll
-    for (int i = 1; i < 16; ++i) tot += sh[i];
-    __syncthreads();
-    return tot;
-}
-
+// 1024 threads, so that the one block that adds up the statistics has enough loads in flight; its seven sums go through
+// one barrier together (one after the other: 7.8 us in the smallest step, 6.0 now).
 __global__ __launch_bounds__(1024) void k_loss_final(const double* __restrict__ stat_part,
                                                     const double* __restrict__ dls_part,
                                                     const double* __restrict__ adv_part, int n_adv, int nbx, int P,
                                                     int A, double cnt, float* __restrict__ dlogsig,
                                                     float* __restrict__ stats) {
-    __shared__ double sh[16];
     const int p = blockIdx.x;
     if (p < P) {
         if (!dlogsig) return;  // (state-dependent sigma: there is no per-preference log-sigma gradient)
@@ -649,9 +636,23 @@ __global__ __launch_bounds__(1024) void k_loss_final(const double* __restrict__ 
             s[5] += adv_part[2 * b];
             s[6] += adv_part[2 * b + 1];
         }
-        double acc[7];
-        for (int i = 0; i < 7; ++i) acc[i] = block_sum16(s[i], sh);
+        __shared__ double sh[7][16];
+        const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+#pragma unroll
+        for (int i = 0; i < 7; ++i) {
+#pragma unroll
+            for (int o = 32; o > 0; o >>= 1) s[i] += __shfl_down(s[i], o, WAVE);
+            if (lane == 0) sh[i][wv] = s[i];
+        }
+        __syncthreads();
         if (threadIdx.x == 0) {
+            double acc[7];  // the waves in order
+#pragma unroll
+            for (int i = 0; i < 7; ++i) {
+                acc[i] = sh[i][0];
+#pragma unroll
+                for (int w = 1; w < 16; ++w) acc[i] += sh[i][w];
+            }
             const double mean = acc[5] / cnt;
             double var = acc[6] / cnt - mean * mean;
             var = var < 0.0 ? 0.0 : var;
