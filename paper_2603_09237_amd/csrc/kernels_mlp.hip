@@ -1859,15 +1859,20 @@ __device__ inline short4_t lds_tr4(const E* word) {
 //       first column's workgroups, of dz_L (that of the output layer).
 // k_bwd_final adds the partials.  (As launches of their own behind one that wrote dz_L as compact rows: 20 + 78 + 109 us
 // for 128 preferences x 2048 rows of width 512, here 185; 7.2 + 8.7 + 12.9 for 24 x 1250 of 256, here 17.4.)
-#define HB_ROWS 128
+#define HB_ROWS 128  // row ranges are whole multiples of this
 #define HB_SPLIT 4
+// rows of h (of dZ_0 in the narrow first layer's dW) that a workgroup stages at a time: with 128 fp32 rows its LDS and the
+// next tile's registers leave a CU two workgroups, or one (16 preferences x 8192 rows x 256 in fp32, 64 rows instead of 128:
+// 137 -> 128 us here, 59 -> 39 us in the first layer's dW; 10 x 1850 of 160: 23.6 -> 18.1 us here)
+template <typename T> constexpr int hb_tile() { return sizeof(T) == 4 ? HB_ROWS / 2 : HB_ROWS; }
 template <typename T>
 struct HeadBwdLds {
+    static constexpr int R = hb_tile<T>();
     static constexpr int HP = 128 + Elems<T>::VE;          // h tile pitch in elements (16 bytes of padding)
     static constexpr bool kBf = std::is_same<T, bf16_t>::value;
-    float sdr[kBf ? 1 : HB_ROWS][MORLAX_MAX_OUT];          // fp32: dz rows as they lie
-    bf16_t sdT[kBf ? MORLAX_MAX_OUT : 1][HB_ROWS + 8];     // bf16: dz^T, contraction contiguous
-    T sh[HB_ROWS][HP];
+    float sdr[kBf ? 1 : R][MORLAX_MAX_OUT];                // fp32: dz rows as they lie
+    bf16_t sdT[kBf ? MORLAX_MAX_OUT : 1][R + 8];           // bf16: dz^T, contraction contiguous
+    T sh[R][HP];
 };
 struct HeadBwdLdsDz {
     float sdz[64][MORLAX_MAX_OUT], sdu[64][MORLAX_MAX_OUT + 1], red[16][128];
@@ -1973,7 +1978,9 @@ __global__ __launch_bounds__(256, sizeof(T) == 2 ? 4 : 2) void k_head_bwd(HeadDz
     }
     HeadBwdLds<T>& L = *reinterpret_cast<HeadBwdLds<T>*>(lds);
     constexpr int CPR = 128 / VE;                          // 16-byte pieces per tile row
-    constexpr int NPT = HB_ROWS * CPR / 256;               // pieces per thread
+    constexpr int R = hb_tile<T>();                        // rows of a tile
+    constexpr int NPT = R * CPR / 256;                     // pieces per thread
+    constexpr int ND = R * 4 / 256;                        // quarter rows of dz per thread
     constexpr bool kBf = HeadBwdLds<T>::kBf;
     const int rs = item / ncol;
     const int per = ((M + HB_SPLIT - 1) / HB_SPLIT + HB_ROWS - 1) / HB_ROWS * HB_ROWS;  // rows per range
@@ -1985,10 +1992,10 @@ __global__ __launch_bounds__(256, sizeof(T) == 2 ? 4 : 2) void k_head_bwd(HeadDz
 #pragma unroll
         for (int q = 0; q < 2; ++q) acc[c][q] = float4_t{0.f, 0.f, 0.f, 0.f};
     uint4 nxt[NPT];
-    HeadDz::Raw dnx[2];
+    HeadDz::Raw dnx[ND];
     auto fetch = [&](int m0) {
 #pragma unroll
-        for (int i = 0; i < 2; ++i) {
+        for (int i = 0; i < ND; ++i) {
             const int idx = threadIdx.x + 256 * i, m = m0 + idx / 4;
             hz.request(p, m < m_hi ? m : m_hi - 1, idx % 4, dnx[i]);
         }
@@ -2002,10 +2009,10 @@ __global__ __launch_bounds__(256, sizeof(T) == 2 ? 4 : 2) void k_head_bwd(HeadDz
         }
     };
     if (m_lo < m_hi) fetch(m_lo);
-    for (int m0 = m_lo; m0 < m_hi; m0 += HB_ROWS) {
+    for (int m0 = m_lo; m0 < m_hi; m0 += R) {
         __syncthreads();  // the previous tile has been multiplied
 #pragma unroll
-        for (int i = 0; i < 2; ++i) {
+        for (int i = 0; i < ND; ++i) {
             const int idx = threadIdx.x + 256 * i, mm = idx / 4, q = idx % 4;
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
@@ -2019,12 +2026,12 @@ __global__ __launch_bounds__(256, sizeof(T) == 2 ? 4 : 2) void k_head_bwd(HeadDz
             const int idx = threadIdx.x + 256 * q;
             *reinterpret_cast<uint4*>(&L.sh[idx / CPR][(idx % CPR) * VE]) = nxt[q];
         }
-        if (m0 + HB_ROWS < m_hi) fetch(m0 + HB_ROWS);
+        if (m0 + R < m_hi) fetch(m0 + R);
         __syncthreads();
         if constexpr (kBf) {
             // both operands are bf16 values: 16x16x16 bf16 MFMAs, eight times the fp32 rate for the same sums
 #pragma unroll
-            for (int ks = 0; ks < HB_ROWS / 16; ++ks) {
+            for (int ks = 0; ks < R / 16; ++ks) {
                 const short4_t a = *reinterpret_cast<const short4_t*>(&L.sdT[ln][16 * ks + 4 * kg]);  // dz^T[j = ln][4 m]
 #pragma unroll
                 for (int c = 0; c < 2; ++c)
@@ -2033,7 +2040,7 @@ __global__ __launch_bounds__(256, sizeof(T) == 2 ? 4 : 2) void k_head_bwd(HeadDz
             }
         } else {
 #pragma unroll
-            for (int kk = 0; kk < HB_ROWS / 4; ++kk) {
+            for (int kk = 0; kk < R / 4; ++kk) {
                 const int m = 4 * kk + kg;
                 const float a = L.sdr[m][ln];                              // dz^T[j = ln][m]
 #pragma unroll
@@ -2160,14 +2167,15 @@ __global__ __launch_bounds__(256) void k_first_bwd_dw(const float* __restrict__ 
     constexpr int VE = Elems<T>::VE;
     constexpr int HP = 128 + VE;
     constexpr int CPR = 128 / VE;
-    constexpr int NPT = HB_ROWS * CPR / 256;
+    constexpr int R = hb_tile<T>();         // rows of a tile
+    constexpr int NPT = R * CPR / 256;
     constexpr int OP = 16 * JB;
-    constexpr int NX = HB_ROWS * OP / 256;  // observation values per thread, at most
+    constexpr int NX = R * OP / 256;  // observation values per thread, at most
     constexpr bool kBf = std::is_same<T, bf16_t>::value;
-    __shared__ __align__(16) float sdr[kBf ? 1 : HB_ROWS][OP];        // fp32: observation rows as they lie
-    __shared__ __align__(16) bf16_t sdT[kBf ? OP : 1][HB_ROWS + 8];  // bf16: x^T, contraction contiguous
-    __shared__ __align__(16) T sh[HB_ROWS][HP];
-    __shared__ uint32_t sro[2][HB_ROWS];  // first element of a tile row's observation
+    __shared__ __align__(16) float sdr[kBf ? 1 : R][OP];        // fp32: observation rows as they lie
+    __shared__ __align__(16) bf16_t sdT[kBf ? OP : 1][R + 8];  // bf16: x^T, contraction contiguous
+    __shared__ __align__(16) T sh[R][HP];
+    __shared__ uint32_t sro[2][R];  // first element of a tile row's observation
     const int p = blockIdx.z, rs = blockIdx.y, i0 = blockIdx.x * 128;
     const int per = ((M + n_split - 1) / n_split + HB_ROWS - 1) / HB_ROWS * HB_ROWS;  // rows per range
     const int m_lo = rs * per, m_hi = (m_lo + per < M) ? (m_lo + per) : M;
@@ -2187,13 +2195,13 @@ __global__ __launch_bounds__(256) void k_first_bwd_dw(const float* __restrict__ 
         int mm = mm0, c = c0;
 #pragma unroll
         for (int i = 0; i < NX; ++i) {
-            if (mm < HB_ROWS) fn(i, mm, c);
+            if (mm < R) fn(i, mm, c);
             mm += dm; c += dc;
             if (c >= O) { c -= O; ++mm; }
         }
     };
     auto offsets = [&](int m0, int slot) {
-        if (threadIdx.x < HB_ROWS) {
+        if (threadIdx.x < R) {
             const int m = m0 + (int)threadIdx.x;
             sro[slot][threadIdx.x] = (uint32_t)(rm.row(p, m < m_hi ? m : m_hi - 1) * O);
         }
@@ -2209,8 +2217,8 @@ __global__ __launch_bounds__(256) void k_first_bwd_dw(const float* __restrict__ 
             nxt[q] = u;
         }
     };
-    for (int idx = threadIdx.x; idx < HB_ROWS * (OP - O); idx += 256) {  // columns beyond O
-        const int mm = idx % HB_ROWS, c = O + idx / HB_ROWS;
+    for (int idx = threadIdx.x; idx < R * (OP - O); idx += 256) {  // columns beyond O
+        const int mm = idx % R, c = O + idx / R;
         if constexpr (kBf) sdT[c][mm] = (bf16_t)0.f;
         else sdr[mm][c] = 0.f;
     }
@@ -2219,7 +2227,7 @@ __global__ __launch_bounds__(256) void k_first_bwd_dw(const float* __restrict__ 
         __syncthreads();
         fetch(m_lo, 0);
     }
-    for (int m0 = m_lo, slot = 0; m0 < m_hi; m0 += HB_ROWS, slot ^= 1) {
+    for (int m0 = m_lo, slot = 0; m0 < m_hi; m0 += R, slot ^= 1) {
         __syncthreads();  // the previous tile has been multiplied
 #pragma unroll
         for (int q = 0; q < NPT; ++q) {
@@ -2231,12 +2239,12 @@ __global__ __launch_bounds__(256) void k_first_bwd_dw(const float* __restrict__ 
             if constexpr (kBf) sdT[c][mm] = v;
             else sdr[mm][c] = to_f(v);
         });
-        if (m0 + HB_ROWS < m_hi) offsets(m0 + HB_ROWS, slot ^ 1);
+        if (m0 + R < m_hi) offsets(m0 + R, slot ^ 1);
         __syncthreads();
-        if (m0 + HB_ROWS < m_hi) fetch(m0 + HB_ROWS, slot ^ 1);
+        if (m0 + R < m_hi) fetch(m0 + R, slot ^ 1);
         if constexpr (kBf) {
 #pragma unroll
-            for (int ks = 0; ks < HB_ROWS / 16; ++ks) {
+            for (int ks = 0; ks < R / 16; ++ks) {
 #pragma unroll
                 for (int c = 0; c < 2; ++c) {
                     const short4_t b = lds_tr4(&sh[16 * ks + 4 * kg + (ln >> 2)][32 * wave + 16 * c + 4 * (ln & 3)]);
@@ -2248,7 +2256,7 @@ __global__ __launch_bounds__(256) void k_first_bwd_dw(const float* __restrict__ 
             }
         } else {
 #pragma unroll
-            for (int kk = 0; kk < HB_ROWS / 4; ++kk) {
+            for (int kk = 0; kk < R / 4; ++kk) {
                 const int m = 4 * kk + kg;
 #pragma unroll
                 for (int c = 0; c < 2; ++c) {
