@@ -23,13 +23,14 @@ sys.path.insert(0, ROOT)
 # MI355X published dense peaks used for the roofline fractions
 PEAK_TFLOPS = {"bf16": 2500.0, "f32": 157.3}
 # grouped-GEMM launch kinds -> kernels that serve them (bf16 with enough tiles: the persistent direct-to-LDS kernel
-# k_gemm_pers; bf16 with few tiles: k_gemm_dma; fp32 and shapes that need masking: k_grouped_gemm)
+# k_gemm_pers; bf16 with few tiles: k_gemm_dma, its dW k_gemm_small; fp32 and shapes that need masking: k_grouped_gemm,
+# its dW k_gemm_f32_small where 64 x 64 tiles multiply less padding)
 KERNEL_OF_KIND = {
     "fwd_first": "grouped GEMM <x rows, W0(p), EpiFwd> forward, first layer",
     "fwd_hidden": "grouped GEMM <SRC_KCONTIG, SRC_KCONTIG, EpiFwd> forward, W x W layers (rollout + update)",
     "dx_hidden": "grouped GEMM <SRC_KCONTIG, SRC_KSTRIDED, EpiDx> dX, W x W layers",
-    "dw_hidden": "grouped GEMM <SRC_KSTRIDED, SRC_KSTRIDED, EpiDw> dW, W x W layers (with the merge of a split contraction)",
-    "dw_first": "dW, first layer: grouped GEMM, or k_gather_x_pad + k_first_bwd_dw + k_first_dw_final for narrow observations",
+    "dw_hidden": "grouped GEMM <SRC_KSTRIDED, SRC_KSTRIDED, EpiDw> dW, W x W layers",
+    "dw_first": "dW, first layer: grouped GEMM, or k_first_bwd_dw for narrow observations",
     "fwd_fused": "k_mlp_fused_fwd / k_mlp_fwd: all layers of a row tile in one launch (rollout + update)",
 }
 

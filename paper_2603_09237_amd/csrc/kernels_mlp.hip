@@ -10,8 +10,8 @@
 // (32 bf16 or 16 fp32 values per step) and each of the four waves accumulates a 64 x 64 sub-tile with
 // v_mfma_f32_32x32x16_bf16 / v_mfma_f32_32x32x2_f32.  Operands whose contraction axis is the slow
 // axis in memory (W in the dX product, both operands of the dW product) are transposed on the way
-// into LDS.  The skinny output layer (<= 16 columns) uses 16x16 MFMA tiles straight from global
-// memory in the forward pass and plain vector code in the backward pass.
+// into LDS.  The skinny output layer (<= 16 columns) uses 16x16 MFMA tiles, straight from global
+// memory in the forward pass and on rows staged through LDS for its dW; its dZ is plain vector code.
 #include "fused_fwd.h"
 
 void launch_mlp_fwd_bf16_act(const FwdArgs& a, int rt, int n_tiles, hipStream_t s);
