@@ -1078,7 +1078,10 @@ __global__ __launch_bounds__(2 * TN, 2) void k_gemm_pers(GemmArgs<bf16_t, KA, KB
 // ---- fp32 weight gradients on 64 x 64 tiles ------------------------------------------------------------------------
 // k_grouped_gemm's products for dW where 128 x 128 tiles would multiply more padding (160 x 160 outputs: 64 blocks of 32 x 32
 // on four tiles, 36 on nine small ones; 32 x 32: 16 and 4).  A wave owns one block; the contraction (whole 32-index steps)
-// runs in the same order, so the sums keep their bits.  Bound by the fp32 products as that kernel is.
+// runs in the same order, so the sums keep their bits.  A step is sixteen contraction indices, two products' worth of work, so
+// the operands of the next F32S_AHEAD steps are on their way in registers (one step ahead: 3.6 us more a launch for 10
+// preferences x 1850 rows x 160 x 160).
+#define F32S_AHEAD 4
 template <class Epi>
 __global__ __launch_bounds__(256) void k_gemm_f32_small(GemmArgs<float, SRC_KSTRIDED, SRC_KSTRIDED, Epi, true, GEMM_NCH> g) {
     constexpr int PITCH = GEMM_NCH * 16 + 16;
@@ -1096,35 +1099,42 @@ __global__ __launch_bounds__(256) void k_gemm_f32_small(GemmArgs<float, SRC_KSTR
     // a thread stages contraction indices 4 wave .. + 3 of row `lane` of either operand (rows past the end: the last one)
     const float* A = g.a_base(grp) + (int64_t)(4 * wave) * g.a.ld + (r0 + lane < g.a.rows ? r0 + lane : g.a.rows - 1);
     const float* B = g.b_base(grp) + (int64_t)(4 * wave) * g.b.ld + (c0 + lane < g.b.rows ? c0 + lane : g.b.rows - 1);
-    float ra[4], rb[4];
-    auto load = [&](int k0) {
+    const int nk = grp.kdim / 16;
+    float ra[F32S_AHEAD][4], rb[F32S_AHEAD][4];
+    auto load = [&](int slot, int kt) {  // (steps past the end: the last one again, so that as many loads are in flight in every step)
+        const int64_t k0 = 16 * (int64_t)(kt < nk ? kt : nk - 1);
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
-            ra[e] = A[(int64_t)(k0 + e) * g.a.ld];
-            rb[e] = B[(int64_t)(k0 + e) * g.b.ld];
+            ra[slot][e] = A[(k0 + e) * g.a.ld];
+            rb[slot][e] = B[(k0 + e) * g.b.ld];
         }
     };
-    auto store = [&](int buf) {
-        *reinterpret_cast<float4*>(lds[buf][0] + lane * PITCH + wave * 16) = make_float4(ra[0], ra[1], ra[2], ra[3]);
-        *reinterpret_cast<float4*>(lds[buf][1] + lane * PITCH + wave * 16) = make_float4(rb[0], rb[1], rb[2], rb[3]);
+    auto store = [&](int slot, int buf) {
+        *reinterpret_cast<float4*>(lds[buf][0] + lane * PITCH + wave * 16) = make_float4(ra[slot][0], ra[slot][1], ra[slot][2], ra[slot][3]);
+        *reinterpret_cast<float4*>(lds[buf][1] + lane * PITCH + wave * 16) = make_float4(rb[slot][0], rb[slot][1], rb[slot][2], rb[slot][3]);
     };
     float16_t acc;
 #pragma unroll
     for (int e = 0; e < 16; ++e) acc[e] = 0.f;
-    const int nk = grp.kdim / 16;
-    load(0);
-    store(0);
-    __syncthreads();
-    for (int kt = 0; kt < nk; ++kt) {
-        const int cur = kt & 1;
-        if (kt + 1 < nk) load(16 * (kt + 1));
-        const unsigned char* ta = lds[cur][0] + (wm + lr) * PITCH + lg * 16;
-        const unsigned char* tb = lds[cur][1] + (wn + lrp) * PITCH + lg * 16;
 #pragma unroll
-        for (int ks = 0; ks < GEMM_NCH / 2; ++ks)
-            Mma32<float>::run(*reinterpret_cast<const uint4*>(tb + ks * 32), *reinterpret_cast<const uint4*>(ta + ks * 32), acc);
-        if (kt + 1 < nk) store(cur ^ 1);
-        __syncthreads();
+    for (int u = 0; u < F32S_AHEAD; ++u) load(u, u);
+    store(0, 0);
+    load(0, F32S_AHEAD);
+    __syncthreads();
+    for (int k0 = 0; k0 < nk; k0 += F32S_AHEAD) {
+#pragma unroll
+        for (int u = 0; u < F32S_AHEAD; ++u) {
+            const int kt = k0 + u, cur = u & 1, nxt = (u + 1) % F32S_AHEAD;
+            if (kt >= nk) break;
+            store(nxt, cur ^ 1);  // (its readers passed the barrier of the step before)
+            load(nxt, kt + 1 + F32S_AHEAD);
+            const unsigned char* ta = lds[cur][0] + (wm + lr) * PITCH + lg * 16;
+            const unsigned char* tb = lds[cur][1] + (wn + lrp) * PITCH + lg * 16;
+#pragma unroll
+            for (int ks = 0; ks < GEMM_NCH / 2; ++ks)
+                Mma32<float>::run(*reinterpret_cast<const uint4*>(tb + ks * 32), *reinterpret_cast<const uint4*>(ta + ks * 32), acc);
+            __syncthreads();
+        }
     }
     const int r = r0 + wm + lr;
 #pragma unroll
