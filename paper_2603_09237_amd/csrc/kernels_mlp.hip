@@ -1723,7 +1723,7 @@ static bool launch_special(GemmArgs<T, KA, KB, Epi, FAST, NCH>& g, int P, int nb
         k_gemm_dma<KA, KB, Epi><<<nb, 256, lds_bytes, s>>>(g);
         return true;
     } else if constexpr (std::is_same<T, float>::value && std::is_same<Epi, EpiDw>::value) {
-        // fewer blocks of 32 x 32 to multiply (10 preferences x 1850 rows x 160 x 160: 44 us on 128 x 128 tiles, 23)
+        // fewer blocks of 32 x 32 to multiply (10 preferences x 1850 rows x 160 x 160: 44 us on 128 x 128 tiles, 20)
         const int stm = (g.crows + 63) / 64, stn = (g.ccols + 63) / 64;
         if (stm * stn >= 4 * g.tiles_m * g.tiles_n || (g.a.kdim & 31)) return false;
         g.tiles_m = stm;

@@ -45,3 +45,14 @@ MAT_CASES = [scaled(RAGGED, name=f"r{r}-O{O}-W{W}-P{P}-{b}", rank=r, obs_dim=O, 
 @pytest.mark.parametrize("cfg", MAT_CASES, ids=lambda c: c.name)
 def test_weights_at_tile_and_rank_edges(cfg, torch, binding):  # noqa: F811
     parity.test_hypernet_fwd_matches_oracle(cfg, torch, binding)
+
+
+# dA added up from column runs: two to five runs of 128 columns beside layers of one, factors whose element counts are no
+# multiple of four, and more than one block of 1024 elements
+DA_CASES = [scaled(RAGGED, name=f"dA-r{r}-A{A}-O{O}-W{W}-P{P}", rank=r, act_dim=A, obs_dim=O, width=W, P=P, N=2 * P)
+            for r, A, O, W, P in ((1, 3, 129, 16, 2), (3, 5, 40, 272, 3), (5, 1, 513, 144, 2), (17, 7, 200, 96, 3))]
+
+
+@pytest.mark.parametrize("cfg", DA_CASES, ids=lambda c: c.name)
+def test_factor_gradients_from_several_column_runs(cfg, torch, binding):  # noqa: F811
+    parity.test_hypernet_bwd_matches_oracle(cfg, torch, binding)
