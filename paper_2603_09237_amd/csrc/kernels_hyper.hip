@@ -17,10 +17,20 @@ struct HyperWs {
     int n_chunk, n_cs;
 };
 
-// 64-row tiles of the stacked affine map per chunk of the df partials
-static int df_chunk_tiles(int64_t q_total) {
-    const int64_t t = ((q_total + 63) / 64 + 1023) / 1024;
-    return t < 4 ? 4 : (int)t;
+// 64-row tiles of the stacked affine map per chunk of the df partials.  Up to 128 preferences at least four, and about a
+// thousand chunks at most.  Above one, doubled until there are at most 4096 chunks: shorter sums, whose error is about a
+// quarter smaller (the trunk's gradients against 64 bits, 130 to 512 preferences: 2.2e-7 to 5.8e-7 of their norm, 3.0e-7 to
+// 6.9e-7 in chunks of four), for 124 instead of 122 us of a backward pass of 256 preferences of 3 x 256.
+#define DF_FEW_P 128
+static int df_chunk_tiles(int64_t q_total, int64_t P) {
+    const int64_t nt = (q_total + 63) / 64;
+    if (P <= DF_FEW_P) {
+        const int64_t t = (nt + 1023) / 1024;
+        return t < 4 ? 4 : (int)t;
+    }
+    int t = 1;
+    while ((nt + t - 1) / t > 4096) t *= 2;
+    return t;
 }
 
 static HyperWs hyper_ws_layout(const morlax_ctx* c, void* ws, int64_t* total) {
@@ -44,7 +54,7 @@ static HyperWs hyper_ws_layout(const morlax_ctx* c, void* ws, int64_t* total) {
     L.dfac = take(P * fac);
     L.n_chunk = 0;  // chunks of the df partials
     for (int n = 0; n < 2; ++n) {
-        const int64_t nt = (c->aff[n].q_total + 63) / 64, per = df_chunk_tiles(c->aff[n].q_total);
+        const int64_t nt = (c->aff[n].q_total + 63) / 64, per = df_chunk_tiles(c->aff[n].q_total, P);
         const int nc = (int)((nt + per - 1) / per);
         L.n_chunk = nc > L.n_chunk ? nc : L.n_chunk;
     }
@@ -630,31 +640,33 @@ __device__ inline float grad_row(const float* __restrict__ dfac, const float* __
 // From the gradient g of the stacked affine rows (fp32 MFMA, fixed orders):
 //   dM[q, :] = sum_p g[p, q] f[p, :],  dc[q] = sum_p g[p, q] (four interleaved shares of the preferences, each in
 //   order, added in a fixed order),  part[chunk, p, j] = sum over the chunk's rows q of g[p, q] M[q, j].
-// A chunk is tpw tiles of 64 rows.  Its workgroups have two roles, and being neighbours they find g in the caches
-// the other has filled:
+// A chunk is tpc tiles of 64 rows.  Workgroups have two roles, and the neighbours that share tpw tiles, a whole number of
+// chunks, find g in the caches the other has filled:
 //   dM: a wave takes one tile and all preferences, operands straight from memory: lane ln reads four consecutive rows
 //       of a preference, so that a request covers 256-byte runs; no LDS, no barrier, nothing carried between tiles.
-//   df: a workgroup takes 64 preferences (16 a wave) and walks the chunk's tiles in order; the tile of g (a preference's
+//   df: a workgroup takes 64 preferences (16 a wave) and walks the tpw tiles in order; the tile of g (a preference's
 //       64 values one 256-byte run) and of M go through LDS, the next ones are in flight in registers meanwhile.
 //       LDS pitches: g 68 floats, M 16 JT + 16 (reads free of conflicts).
+// FINE (more than DF_FEW_P preferences): a chunk may be less than tpw tiles, and a product takes four rows 4 apart of
+// sixteen instead of neighbours, which is where place() puts them.
 // Both in one role (a workgroup walked four tiles, each a chain of LDS exchanges and products of one accumulator) took
 // 59 us for 69 thousand rows x 128 preferences, 35 us for 15 thousand x 24 and 23 us for 2600 x 4; now 39, 11.4, 10.7.
 #define DMF_Q 64
 #define DMF_P 64  // preferences of a df workgroup
-template <int JT>
+template <int JT, bool FINE>
 __global__ __launch_bounds__(256) void k_hyper_dM_df(const float* __restrict__ hp, const int32_t* __restrict__ mrow,
                                                     const int32_t* __restrict__ crow, const float* __restrict__ f,
                                                     const float* __restrict__ dfac, const float* __restrict__ dvec,
                                                     float* __restrict__ dhp, float* __restrict__ part, int P, int F,
                                                     int64_t fac_len, int64_t vec_len, int q_total, int n_tiles, int tpw,
-                                                    int n_df, int n_dm) {
+                                                    int tpc, int n_df, int n_dm) {
     constexpr int PD = 68, PJ = 16 * JT + 16;
     __shared__ float Dl[DMF_P][PD];
     __shared__ float Ml[DMF_Q][PJ];
     __shared__ int32_t Rl[2][DMF_Q];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, ln = lane & 15, kg = lane >> 4;
-    const int chunk = blockIdx.x / (n_df + n_dm), role = blockIdx.x % (n_df + n_dm);
-    const int t_lo = chunk * tpw, t_hi = (t_lo + tpw < n_tiles) ? (t_lo + tpw) : n_tiles;
+    const int group = blockIdx.x / (n_df + n_dm), role = blockIdx.x % (n_df + n_dm);
+    const int t_lo = group * tpw, t_hi = (t_lo + tpw < n_tiles) ? (t_lo + tpw) : n_tiles;
     if (role >= n_df) {  // dM and dc of one tile a wave (no barrier: the waves are on their own)
         const int tile = t_lo + 4 * (role - n_df) + wave;
         if (tile >= t_hi) return;
@@ -729,8 +741,9 @@ __global__ __launch_bounds__(256) void k_hyper_dM_df(const float* __restrict__ h
         if (q4 + kg < q_total) dhp[crow[q4 + kg]] = mine;
         return;
     }
-    // df partial of preferences p0 .. p0 + 15 (this wave's)
+    // df partials of preferences p0 .. p0 + 15 (this wave's)
     const int pb = role * DMF_P, p0 = pb + 16 * wave;
+    auto place = [](int row) { return FINE ? (row & ~15) | ((row & 3) << 2) | ((row >> 2) & 3) : row; };
     constexpr int MPT = DMF_Q * 16 * JT / 256;
     float nxt[DMF_P / 4], mnx[MPT];
     auto row_of = [&](int tile) {  // (threads 0 .. 63) offset of a row of M
@@ -753,6 +766,17 @@ __global__ __launch_bounds__(256) void k_hyper_dM_df(const float* __restrict__ h
     float4_t accF[JT];
 #pragma unroll
     for (int jt = 0; jt < JT; ++jt) accF[jt] = float4_t{0.f, 0.f, 0.f, 0.f};
+    auto put_part = [&](int chunk) {  // lane holds feature j = 16 jt + ln of preferences p0 + 4 kg + e
+#pragma unroll
+        for (int jt = 0; jt < JT; ++jt) {
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const int pp = p0 + 4 * kg + e, j = 16 * jt + ln;
+                if (pp < P && j < F) part[((int64_t)chunk * P + pp) * F + j] = accF[jt][e];
+            }
+            accF[jt] = float4_t{0.f, 0.f, 0.f, 0.f};
+        }
+    };
     if (threadIdx.x < DMF_Q) Rl[t_lo & 1][threadIdx.x] = row_of(t_lo);
     int32_t rnext = row_of(t_lo + 1);
     __syncthreads();
@@ -760,11 +784,11 @@ __global__ __launch_bounds__(256) void k_hyper_dM_df(const float* __restrict__ h
     for (int tile = t_lo; tile < t_hi; ++tile) {
         __syncthreads();  // the previous tile's readers are done
 #pragma unroll
-        for (int i = 0; i < DMF_P / 4; ++i) Dl[wave + 4 * i][lane] = nxt[i];
+        for (int i = 0; i < DMF_P / 4; ++i) Dl[wave + 4 * i][place(lane)] = nxt[i];
 #pragma unroll
         for (int i = 0; i < MPT; ++i) {
             const int idx = threadIdx.x + 256 * i;
-            Ml[idx / (16 * JT)][idx % (16 * JT)] = mnx[i];
+            Ml[place(idx / (16 * JT))][idx % (16 * JT)] = mnx[i];
         }
         if (threadIdx.x < DMF_Q) Rl[(tile + 1) & 1][threadIdx.x] = rnext;
         __syncthreads();
@@ -781,15 +805,9 @@ __global__ __launch_bounds__(256) void k_hyper_dM_df(const float* __restrict__ h
                     accF[jt] = __builtin_amdgcn_mfma_f32_16x16x4f32(a, Ml[4 * kk + kg][16 * jt + ln], accF[jt], 0, 0, 0);
             }
         }
+        if (FINE && tile + 1 < t_hi && (tile + 1) % tpc == 0) put_part(tile / tpc);
     }
-    // lane holds feature j = 16 jt + ln of preferences p0 + 4 kg + e
-#pragma unroll
-    for (int jt = 0; jt < JT; ++jt)
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            const int pp = p0 + 4 * kg + e, j = 16 * jt + ln;
-            if (pp < P && j < F) part[((int64_t)chunk * P + pp) * F + j] = accF[jt][e];
-        }
+    put_part(FINE ? (t_hi - 1) / tpc : group);
 }
 
 // Trunk backward, stage 1: df[p, j] = sum_chunk part; dz2 = df * (1 - f^2); dz1 = (dz2 Wh2) * (1 - h1^2).  A block
@@ -1003,15 +1021,21 @@ void launch_hypernet_bwd(const morlax_ctx* c, int net, const float* hparams, con
             k_hyper_dA_merge<<<dim3((merged + 1023) / 1024, P, nd.n_layers), 256, 0, s>>>(nd, L.da_part, L.dfac, r, P);
     }
     if (r <= 0) k_hyper_base<<<n_base, 256, 0, s>>>(nd, at, bw, dtheta_mat, P);
-    // at least four tiles per chunk, about a thousand chunks at most
-    const int n_tiles = (at.q_total + DMF_Q - 1) / DMF_Q, tpw = df_chunk_tiles(at.q_total);
-    const int n_chunk = (n_tiles + tpw - 1) / tpw, n_df = (P + DMF_P - 1) / DMF_P, n_dm = (tpw + 3) / 4;
+    // (four tiles and more to a workgroup of either role, whatever the chunk)
+    const int n_tiles = (at.q_total + DMF_Q - 1) / DMF_Q, tpc = df_chunk_tiles(at.q_total, P), tpw = tpc < 4 ? 4 : tpc;
+    const int n_chunk = (n_tiles + tpc - 1) / tpc, n_group = (n_tiles + tpw - 1) / tpw;
+    const int n_df = (P + DMF_P - 1) / DMF_P, n_dm = (tpw + 3) / 4;
     auto dM_df = [&](auto kernel) {
-        kernel<<<n_chunk * (n_df + n_dm), 256, 0, s>>>(hparams, L.mrow, L.crow, L.f, dlead, dtheta_vec, dhparams, L.df_part, P,
-                                                       F, nd.fac_len, nd.vec_len, at.q_total, n_tiles, tpw, n_df, n_dm);
+        kernel<<<n_group * (n_df + n_dm), 256, 0, s>>>(hparams, L.mrow, L.crow, L.f, dlead, dtheta_vec, dhparams, L.df_part, P,
+                                                       F, nd.fac_len, nd.vec_len, at.q_total, n_tiles, tpw, tpc, n_df, n_dm);
     };
-    if (F <= 32) dM_df(k_hyper_dM_df<2>);
-    else dM_df(k_hyper_dM_df<4>);
+    if (P <= DF_FEW_P) {
+        if (F <= 32) dM_df(k_hyper_dM_df<2, false>);
+        else dM_df(k_hyper_dM_df<4, false>);
+    } else {
+        if (F <= 32) dM_df(k_hyper_dM_df<2, true>);
+        else dM_df(k_hyper_dM_df<4, true>);
+    }
     const int lds = (7 * P * F + P * K) * 4;  // (with the kernel's 16 KB at most 64)
     if (trunk_inside(P, F) && lds <= 48 * 1024) {
         k_hyper_trunk_bwd<<<1, 1024, lds, s>>>(hparams, L.df_part, n_chunk, L.f, L.h1, w, dhparams, P, K, F, nd.hp_wh1, nd.hp_bh1,

@@ -56,3 +56,39 @@ DA_CASES = [scaled(RAGGED, name=f"dA-r{r}-A{A}-O{O}-W{W}-P{P}", rank=r, act_dim=
 @pytest.mark.parametrize("cfg", DA_CASES, ids=lambda c: c.name)
 def test_factor_gradients_from_several_column_runs(cfg, torch, binding):  # noqa: F811
     parity.test_hypernet_bwd_matches_oracle(cfg, torch, binding)
+
+
+# more than 128 preferences: sums over chunks of one 64-row tile, of two where there are more than 4096 tiles
+MANY_P = [scaled(RAGGED, name=f"F{F}-P{P}", P=P, N=2 * P, rank=-1, hyper_width=F, obs_dim=16, width=16, n_hidden=1, act_dim=2,
+                 wdtype=0) for P, F in ((129, 32), (130, 64), (257, 5))]
+MANY_P += [scaled(RAGGED, name="F3-P129-many-rows", P=129, N=258, hyper_width=3, rank=-1, obs_dim=61, width=272, n_hidden=5)]
+
+
+@pytest.mark.parametrize("cfg", MANY_P, ids=lambda c: c.name)
+def test_feature_gradient_of_many_preferences_is_summed_by_tiles(cfg, torch, binding):  # noqa: F811
+    """df of a strictly affine network with f = 0, where dbh2 = sum_p df: 64 rows (or 128, the chunk of very many) that add up
+    to 2^26, as many that add up to 32 (64), as many that take the first away.  Every sum of one chunk and the sum of the
+    chunks are exact in fp32; a sum that runs on across the chunks loses the small one whole."""
+    ctx = binding.Context.from_config(cfg)
+    net = parity.ACTOR
+    lay = parity.orc.hparam_layout(cfg, net)
+    ml, vl = ctx.theta_mat_len(net), ctx.theta_vec_len(net)
+    chunk = 64 if (ml + vl + 63) // 64 <= 4096 else 128
+    hp = torch.zeros(ctx.hparam_count(net), device="cuda")
+    M = torch.zeros(ml, cfg.hyper_width, device="cuda")
+    big = 2.0 ** 26 / chunk
+    M[:chunk], M[chunk:2 * chunk], M[2 * chunk:3 * chunk] = big, 0.5, -big
+    at = 0
+    for (o, i), l in zip(parity.inputs.layer_shapes(cfg, net), range(cfg.n_hidden + 1)):
+        off = lay[f"MW_{l}"][0]
+        hp[off:off + o * i * cfg.hyper_width] = M[at:at + o * i].reshape(-1)
+        at += o * i
+    assert at == ml
+    dtm = torch.zeros(cfg.P, ml, device="cuda")
+    dtm[:, :3 * chunk] = 1.0
+    dtv, w = torch.zeros(cfg.P, vl, device="cuda"), torch.full((cfg.P, cfg.K), 1.0 / cfg.K, device="cuda")
+    dhp = torch.full_like(hp, 9.0)
+    ws = torch.empty(ctx.workspace_bytes((0, 1, 0, 1)), dtype=torch.uint8, device="cuda")
+    ctx.hypernet_bwd(net, hp, w, dtm, dtv, dhp, ws)
+    off = lay["bh2"][0]
+    assert (dhp[off:off + cfg.hyper_width] == cfg.P * chunk * 0.5).all(), dhp[off:off + cfg.hyper_width]
