@@ -164,7 +164,7 @@ __device__ inline void put_run4(bf16_t* d, const float (&v)[4]) {
 // 128-byte line apart, f through scalar loads whose latency nothing covered) took 45.9 us for 69 thousand rows x 128
 // preferences, of which the 36 MB of results are 7; here 22.2.  14.3 us at 15 thousand x 24, here 5.1.
 // TRUNK: every workgroup forms the features f(w) of all preferences itself (in LDS; the first one leaves them and h1 for
-// the backward pass), which with few of them costs less than the launch in front that it replaces (rule: trunk_inside).
+// the backward pass), which with few of them costs less than the launch in front that it replaces (rule: trunk_fwd_inside).
 template <typename TF, int KS, bool TRUNK>  // TF: type of the leading rows' destination (float factors, or theta_mat: strictly affine form)
 __global__ __launch_bounds__(256) void k_hyper_affine(AffineTable at, Trunk tk, const float* __restrict__ hp,
                                                      const float* __restrict__ f, TF* __restrict__ fac,
@@ -250,18 +250,25 @@ __global__ __launch_bounds__(256) void k_hyper_affine(AffineTable at, Trunk tk, 
         }
     }
 }
-// Preferences x features up to which both trunks, forward and backward, share a launch with what is next to them.  Forward (us,
-// apart and together; a launch on the dependent chain is another 1.5 to 2): 128 2.5 + 4.8 and 6.4, 512 4.5 + 5.5 and 9.0, 768
-// 4.1 + 5.1 and 9.5, 1024 4.6 + 5.8 and 12.1.  Backward: 128 3.4 + 3.3 and 3.6, 320 6.2 + 4.6 and 9.4, 768 5.6 + 4.3 and
-// 12.7, 1024 6.1 + 4.5 and 15.8.
-static bool trunk_inside(int P, int F) { return P * F <= 512; }
+// Whether a trunk shares a launch with what is next to it: up to 512 preferences x features (us, apart and together, of few
+// rows; a launch on the dependent chain is another 1.5 to 2; forward: 128 2.5 + 4.8 and 6.4, 512 4.5 + 5.5 and 9.0, 768
+// 4.1 + 5.1 and 9.5, 1024 4.6 + 5.8 and 12.1; backward: 128 3.4 + 3.3 and 3.6, 320 6.2 + 4.6 and 9.4, 768 5.6 + 4.3 and
+// 12.7, 1024 6.1 + 4.5 and 15.8), and there
+//   forward, where every workgroup of the affine map repeats it: while those are one round of what the chip holds, four a
+//     CU for F <= 32 and two above (hypernet_fwd, together and apart: 16 preferences of F = 32, 661 workgroups 9.1 and 10.3,
+//     2249 19.2 and 14.1, 12849 90.9 and 61.0; 4 of F = 64, 446 workgroups 1.1 less together, 661 3.5 more)
+//   backward, where one workgroup reads all partials: up to 20 million chunks x (preferences x features)^2 (hypernet_bwd: 16
+//     of F = 32, 30 chunks 0.5 less together, 101 0.4 more, 989 160 and 148; 8, 166 chunks 1.1 less, 582 0.6 more; 4, 989
+//     chunks 135 and 139)
+static bool trunk_fwd_inside(int P, int F, int workgroups) { return P * F <= 512 && workgroups <= (F <= 32 ? 1024 : 512); }
+static bool trunk_bwd_inside(int P, int F, int n_chunk) { return P * F <= 512 && (int64_t)n_chunk * (P * F) * (P * F) <= 20 << 20; }
 template <typename TF>
 static void launch_trunk_affine(const AffineTable& at, const Trunk& tk, const float* hp, TF* fac, float* theta_vec, int P, int F,
                                 int64_t fac_len, int64_t vec_len, hipStream_t s) {
     const int nb = (at.q_total + 63) / 64;
     auto run = [&](auto ks) {
         constexpr int KS = decltype(ks)::value;
-        if (trunk_inside(P, F)) {
+        if (trunk_fwd_inside(P, F, nb)) {
             const int lds = (F * (F + 1) + 2 * P * F) * 4;
             k_hyper_affine<TF, KS, true><<<nb, 256, lds, s>>>(at, tk, hp, tk.f, fac, theta_vec, P, F, fac_len, vec_len);
         } else {
@@ -913,7 +920,7 @@ __global__ __launch_bounds__(64) void k_hyper_trunk_bwd_b(const float* __restric
 }
 
 // Both stages in one workgroup, where its one CU reads the partials in less time than the second launch costs
-// (trunk_inside).  The same sums.  LDS: dz2, dz1, h1 [P][F], w [P][K], the four shares [4][P F].
+// (trunk_bwd_inside).  The same sums.  LDS: dz2, dz1, h1 [P][F], w [P][K], the four shares [4][P F].
 __global__ __launch_bounds__(1024) void k_hyper_trunk_bwd(const float* __restrict__ hp, const float* __restrict__ part, int n_chunk,
                                                          const float* __restrict__ f, const float* __restrict__ h1,
                                                          const float* __restrict__ w, float* __restrict__ dhp, int P, int K,
@@ -1037,7 +1044,7 @@ void launch_hypernet_bwd(const morlax_ctx* c, int net, const float* hparams, con
         else dM_df(k_hyper_dM_df<4, true>);
     }
     const int lds = (7 * P * F + P * K) * 4;  // (with the kernel's 16 KB at most 64)
-    if (trunk_inside(P, F) && lds <= 48 * 1024) {
+    if (trunk_bwd_inside(P, F, n_chunk) && lds <= 48 * 1024) {
         k_hyper_trunk_bwd<<<1, 1024, lds, s>>>(hparams, L.df_part, n_chunk, L.f, L.h1, w, dhparams, P, K, F, nd.hp_wh1, nd.hp_bh1,
                                                nd.hp_wh2, nd.hp_bh2);
         return;

@@ -92,3 +92,43 @@ def test_feature_gradient_of_many_preferences_is_summed_by_tiles(cfg, torch, bin
     ctx.hypernet_bwd(net, hp, w, dtm, dtv, dhp, ws)
     off = lay["bh2"][0]
     assert (dhp[off:off + cfg.hyper_width] == cfg.P * chunk * 0.5).all(), dhp[off:off + cfg.hyper_width]
+
+
+# few preferences on both sides of the numbers of stacked rows up to which the trunk shares a launch: workgroups of 64 rows
+# (1024, 512 above 32 features) forward, chunks of 256 rows backward
+TRUNK_CASES = [scaled(RAGGED, name=f"trunk-F{F}-P{P}-r{r}-O{O}-W{W}", P=P, N=2 * P, rank=r, hyper_width=F, obs_dim=O, width=W, n_hidden=2)
+               for F, P, r, O, W in ((32, 16, -1, 11, 128), (32, 16, -1, 40, 144), (32, 2, -1, 11, 240), (32, 2, -1, 40, 256),
+                                     (64, 8, -1, 30, 160), (64, 8, -1, 60, 160), (8, 64, 32, 300, 96), (20, 25, 16, 11, 272))]
+
+
+@pytest.mark.parametrize("cfg", TRUNK_CASES, ids=lambda c: c.name)
+def test_trunk_beside_few_and_many_rows(cfg, torch, binding):  # noqa: F811
+    parity.test_hypernet_fwd_matches_oracle(cfg, torch, binding)
+    parity.test_hypernet_bwd_matches_oracle(cfg, torch, binding)
+    parity.test_hypernet_bwd_kept_equals_hypernet_bwd(cfg, torch, binding)
+
+
+def test_few_preferences_of_a_wide_affine_network_take_no_longer_than_more(torch, binding):  # noqa: F811
+    """hypernet_fwd of 16 preferences against 17 of a strictly affine 4 x 512 network: 17 weight sets are more to write, so
+    the call with 16 is the shorter one (a quarter is left for the clock)."""
+    def passes(P):
+        cfg = scaled(RAGGED, name=f"affine-4x512-P{P}", P=P, N=2 * P, rank=-1, hyper_width=32, obs_dim=64, width=512, n_hidden=4, wdtype=1)
+        ctx, net = binding.Context.from_config(cfg), parity.ACTOR
+        hp, w = torch.zeros(ctx.hparam_count(net), device="cuda"), torch.zeros(P, cfg.K, device="cuda")
+        tm = torch.empty(P, ctx.theta_mat_len(net), dtype=torch.bfloat16, device="cuda")
+        tv = torch.empty(P, ctx.theta_vec_len(net), device="cuda")
+        ws = torch.empty(ctx.workspace_bytes((0, 1, 0, 1)), dtype=torch.uint8, device="cuda")
+
+        def once():
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            a.record()
+            for _ in range(20):
+                ctx.hypernet_fwd(net, hp, w, tm, tv, ws)
+            b.record()
+            b.synchronize()
+            return a.elapsed_time(b)
+        return once
+    few, more = passes(16), passes(17)
+    few(), more()
+    best = [min(t) for t in zip(*((few(), more()) for _ in range(9)))]
+    assert best[0] < 1.25 * best[1], best
