@@ -1723,9 +1723,15 @@ static bool launch_special(GemmArgs<T, KA, KB, Epi, FAST, NCH>& g, int P, int nb
         k_gemm_dma<KA, KB, Epi><<<nb, 256, lds_bytes, s>>>(g);
         return true;
     } else if constexpr (std::is_same<T, float>::value && std::is_same<Epi, EpiDw>::value) {
-        // fewer blocks of 32 x 32 to multiply (10 preferences x 1850 rows x 160 x 160: 44 us on 128 x 128 tiles, 20)
-        const int stm = (g.crows + 63) / 64, stn = (g.ccols + 63) / 64;
+        // fewer blocks of 32 x 32 to multiply, and fewer rounds of a workgroup per CU by the factor that a round is shorter:
+        // four times less work, but every operand is read twice as often.  Rounds, and us on large and on small tiles: 2 and 5
+        // 46 and 27 (10 preferences x 1850 rows x 160 x 160), 4 and 15 181 and 164 (6 x 512 x 1568 x 1568), 2 and 7 46 and 45 to
+        // 48 (4096 rows in all x 416 x 416), 3 and 12 125 and 133 (3 x 512 x 1952 x 1952), 9 and 34 344 and 356 (16 x 512 x
+        // 1440 x 1440), 2 and 8 559 and 652 (2 x 4096 x 1952 x 1952).
+        const int stm = (g.crows + 63) / 64, stn = (g.ccols + 63) / 64, cus = resident_slots() / 2;
+        auto rounds = [&](int64_t tiles) { return (tiles * P + cus - 1) / cus; };
         if (stm * stn >= 4 * g.tiles_m * g.tiles_n || (g.a.kdim & 31)) return false;
+        if (4 * rounds(stm * stn) > 15 * rounds(g.tiles_m * g.tiles_n)) return false;
         g.tiles_m = stm;
         g.tiles_n = stn;
         k_gemm_f32_small<Epi><<<stm * stn * P, 256, 0, s>>>(g);

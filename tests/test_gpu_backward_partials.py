@@ -33,3 +33,39 @@ CASES += [case(512, 128, 40, 3, 2, 2, 2, wdtype=1), case(2048, 64, 40, 3, 2, 3, 
 @pytest.mark.parametrize("cfg", CASES, ids=lambda c: c.name)
 def test_backward_at_the_edges_of_its_partial_sums(cfg, torch, binding):  # noqa: F811
     parity.test_policy_bwd_matches_oracle(cfg, None, torch, binding)
+
+
+# fp32 weight gradients on both sides of the line between 64 x 64 and 128 x 128 tiles: 7 and 8 rounds of small tiles in the
+# place of two
+LINE = [case(512, 1824, 34, 2, 2, 2, 2, wdtype=0, rank=2), case(512, 1952, 34, 2, 2, 2, 2, wdtype=0, rank=2)]
+
+
+@pytest.mark.parametrize("cfg", LINE, ids=lambda c: c.name)
+def test_backward_of_wide_fp32_networks(cfg, torch, binding):  # noqa: F811
+    parity.test_policy_bwd_matches_oracle(cfg, None, torch, binding)
+
+
+def test_fp32_weight_gradients_of_a_narrower_network_take_no_longer(torch, binding):  # noqa: F811
+    """dW of 2 preferences x 4096 rows x 1952 x 1952 against 2048 x 2048, which is as many 128 x 128 tiles and a tenth more
+    weights (5 % are left for the clock)."""
+    def passes(W):
+        cfg = case(4096, W, 16, 2, 2, 2, 2, wdtype=0, rank=2)
+        ctx, net, rows = binding.Context.from_config(cfg), parity.ACTOR, (0, 1, 0, 4096)
+        z = lambda *s: torch.zeros(*s, device="cuda")
+        tm, tv = z(2, ctx.theta_mat_len(net)), z(2, ctx.theta_vec_len(net))
+        x, mu, dls = z(2, 8192, 16), z(1, 8192, 2), z(2, 2)
+        saved, ws = (torch.empty(n, dtype=torch.uint8, device="cuda") for n in (ctx.saved_bytes(net, rows), ctx.workspace_bytes(rows)))
+        dtm, dtv = torch.empty_like(tm), torch.empty_like(tv)
+        ctx.policy_fwd(net, tm, tv, x, rows, mu, saved=saved, ws=ws)
+
+        def once():
+            ctx.profile_begin()
+            for _ in range(3):
+                ctx.policy_bwd(net, tm, tv, x, rows, saved, mu, dls, dtm, dtv, ws)
+            ms, n, _ = ctx.profile_end()["dw_hidden"]
+            return ms / n
+        return once
+    narrow, wide = passes(1952), passes(2048)
+    narrow(), wide()
+    best = [min(t) for t in zip(*((narrow(), wide()) for _ in range(7)))]
+    assert best[0] < 1.05 * best[1], best
