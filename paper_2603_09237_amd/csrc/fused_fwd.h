@@ -93,10 +93,10 @@ __device__ inline void fwd_act(float z, float& h, float& g) {
 
 // WHOLE: the waves' features are the network's, W = 64 NW (as a condition at run time: 31.6 against 29.1 us for
 // one step of 32 preferences x 256 rows of width 256, the two kinds of requests waiting for each other's registers).
-// fp32 tiles of one and two row blocks stay within the 168 registers of three waves a SIMD: with 169 the update step of 10
+// fp32 tiles stay within the 168 registers of three waves a SIMD: with 169 the update step of 10
 // preferences x 3700 rows of width 160 took 1.48 ms, 1.42 now.
 template <typename T, bool SAVE, int NW, int RT, bool WHOLE>
-__global__ __launch_bounds__(64 * NW, sizeof(T) == 4 && RT <= 2 ? 3 : 2) void k_mlp_fwd(FwdArgs a) {
+__global__ __launch_bounds__(64 * NW, sizeof(T) == 4 ? 3 : 2) void k_mlp_fwd(FwdArgs a) {
     constexpr int ES = sizeof(T), VE = 16 / ES;
     constexpr bool B32 = ES == 2;    // 32x32 products
     constexpr int KS = 8 * VE;       // contraction indices of a super-step: a 128-byte line of every W row
@@ -555,11 +555,11 @@ static void fwd_launch(const FwdArgs& a, int n_tiles, hipStream_t s) {
 }
 template <typename T, bool SAVE, int NW>
 static void fwd_launch_rt(const FwdArgs& a, int rt, int n_tiles, hipStream_t s) {
-    if constexpr (sizeof(T) == 4) {
-        if (rt == 1) { fwd_launch<T, SAVE, NW, 1>(a, n_tiles, s); return; }
+    constexpr int LOW = fwd_low(sizeof(T));
+    if constexpr (fwd_has_high(sizeof(T), NW)) {
+        if (rt == 2 * LOW) { fwd_launch<T, SAVE, NW, 2 * LOW>(a, n_tiles, s); return; }
     }
-    if (rt == 2) fwd_launch<T, SAVE, NW, 2>(a, n_tiles, s);
-    else fwd_launch<T, SAVE, NW, 4>(a, n_tiles, s);
+    fwd_launch<T, SAVE, NW, LOW>(a, n_tiles, s);
 }
 template <typename T, bool SAVE>
 static void fwd_launch_all(const FwdArgs& a, int rt, int n_tiles, hipStream_t s) {

@@ -7,6 +7,10 @@
 constexpr int kFwdMaxWidth = 512;
 constexpr int fwd_waves(int w) { return w <= 256 ? (w + 63) / 64 : w <= 384 ? 6 : 8; }
 
+// row tiles of 16 per workgroup: 1 in fp32 and 2 in bf16, and twice as many for networks of enough waves
+constexpr int fwd_low(int es) { return es == 4 ? 1 : 2; }
+constexpr bool fwd_has_high(int es, int nw) { return es == 4 ? nw > 1 : nw >= 3; }
+
 inline int fwd_lds_bytes(int es, int O, int W, int L, int rt) {
     const int nw = fwd_waves(W), pitch = (64 * nw * es + 255) / 256 * 256, pitch0 = (O * es + 255) / 256 * 256;
     return 16 * rt * (pitch0 > pitch ? pitch0 : pitch) + nw * 8192 + L * 64 * nw * 4;

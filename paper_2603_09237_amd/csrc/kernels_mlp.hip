@@ -2590,14 +2590,14 @@ static int fwd_row_tiles(const morlax_ctx* c, const NetDev& nd, const void* thet
         if (nw == 6 && tiles(4) >= 512) return 0;  // W 384: 64 x 700 141 and 145, 64 x 2048 327 and 408, 16 x 700 54 and 46
         // tiles of 64 rows once 32 would leave more than two rounds of workgroups: W 512 16 x 1024 59 against 63, 64 x 128
         // 59 against 38; W 144 64 x 700 55 against 63, 16 x 700 28 against 25; W 48 and 128 (2, 4 tiles at a time on a CU) never
-        return nw >= 3 && tiles(2) >= (nw == 3 ? 1024 : 512) && fits(4) ? 4 : 2;
+        return fwd_has_high(2, nw) && tiles(2) >= (nw == 3 ? 1024 : 512) && fits(4) ? 4 : 2;
     }
     // fp32: W 512 64 x 700 563 GEMMs, 601 here, 16 x 700 equal; W 384 16 x 2048 285 and 297, 64 x 128 101 and 78
     if ((nw == 8 && tiles(2) >= 512) || (nw == 6 && tiles(2) >= 768)) return 0;
     // 16 rows until they would leave more than two rounds of workgroups (of 8 waves per CU): W 256 64 x 128 (512 tiles) 41
     // against 40 of 32 rows, 16 x 700 56 against 61; W 128 64 x 700 69 against 83, 16 x 2048 61 against 43; W 32 64 x 2048 68
     // against 72
-    return nw > 1 && tiles(1) >= (nw == 2 ? 4096 : 1024) && fits(2) ? 2 : 1;
+    return fwd_has_high(4, nw) && tiles(1) >= (nw == 2 ? 4096 : 1024) && fits(2) ? 2 : 1;
 }
 
 static void run_mlp_fwd(const morlax_ctx* c, const NetDev& nd, FwdArgs& a, int rt, bool save, hipStream_t s) {
