@@ -2453,7 +2453,8 @@ static int first_split(const morlax_ctx* c, const RowSel& rs) {
 }
 // Ranges the contraction of a layer's dW is cut into (1 = the plain grouped GEMM), until there are DW_SPLIT_TARGET
 // workgroups (1024 measured slower: twice the partials).  fp32: ranges of 256 rows and more, of 64 while the workgroups
-// reach less than a quarter of the CUs (4 preferences x 256 rows x 64 x 64: 22.7 us unsplit, 12 us with the merge).
+// reach less than a quarter of the CUs (4 preferences x 256 rows x 64 x 64: 10.9 us unsplit, 6.8
+// split; the backward pass, the ranges added by k_bwd_final, 34.0 and 29.7).
 // bf16: hidden layers only into equal ranges of whole 64-row steps, 256 rows and more; the first layer, whose few columns
 // make few tiles, into ranges of 2048 rows and more, uneven ones too.  Uneven ranges of a bf16 hidden layer were timed at
 // one shape only, which has more tiles than the chip has CUs (23 preferences x 1120 rows x 512 x 512 in two: 4 % of the

@@ -28,6 +28,8 @@ CASES += [case(300, 256, 40, 7, 6, 3, 2, wdtype=1, act=0), case(770, 512, 64, 10
 CASES += [case(512, 128, 40, 3, 2, 2, 2, wdtype=1), case(2048, 64, 40, 3, 2, 3, 2, wdtype=1), case(4224, 80, 33, 3, 2, 2, 2, wdtype=1),
           case(20, 48, 40, 3, 2, 3, 2, wdtype=0), case(700, 160, 40, 3, 2, 2, 2, wdtype=0),
           case(333, 192, 70, 3, 2, 2, 3, wdtype=0), case(96, 32, 36, 3, 2, 4, 7, wdtype=0)]
+# bf16 first layers on small tiles whose last range is the shorter one (padded rows 2112 + 2016 and 2112 + 2048)
+CASES += [case(4115, 80, 33, 3, 2, 2, 2, wdtype=1), case(4160, 144, 70, 3, 2, 1, 2, wdtype=1)]
 
 
 @pytest.mark.parametrize("cfg", CASES, ids=lambda c: c.name)

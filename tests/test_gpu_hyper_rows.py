@@ -34,8 +34,8 @@ def test_stacked_rows_and_their_gradients_at_odd_sizes(cfg, torch, binding):  # 
     parity.test_hypernet_bwd_matches_oracle(cfg, torch, binding)
 
 
-# the weights themselves: ranks around the contraction steps, rows and columns around the 64 x 128 tiles and the pairs of
-# preferences (tiles x preferences beyond 4096), observation widths that are no multiple of 8
+# the weights themselves: ranks around the contraction steps, rows and columns around the 64 x 128 tiles, observation widths
+# that are no multiple of 8, many preferences
 MAT_CASES = [scaled(RAGGED, name=f"r{r}-O{O}-W{W}-P{P}-{b}", rank=r, obs_dim=O, width=W, P=P, N=2 * P, n_hidden=L, hyper_width=4, wdtype=b)
              for b in (0, 1)
              for r, O, W, L, P in ((0, 5, 16, 1, 2), (1, 8, 64, 2, 3), (8, 127, 80, 2, 5), (9, 129, 144, 1, 4), (16, 64, 272, 2, 3),
