@@ -1704,9 +1704,12 @@ static bool launch_special(GemmArgs<T, KA, KB, Epi, FAST, NCH>& g, int P, int nb
             }
         }
         if constexpr (std::is_same<Epi, EpiDw>::value) {
-            // fewer 128 x 128 tiles than CUs: 24 preferences x 1250 rows x 256 x 256 (96 tiles) 18 us, on 64 x 64 tiles 15
+            // fewer 128 x 128 tiles than CUs, and no more 64 x 64 ones than run at once (two per CU, by their LDS): beyond that
+            // the operands read twice as often cost more than the idle CUs.  us, large and small, by preferences x rows x 256 x
+            // 256: 24 x 1250 (384 small tiles) 19 and 14, 20 x 2369 (320) 29 and 19, 24 x 4531 (384) 51 and 49; 40 x 5786
+            // (640) 67 and 89, 60 x 789 (960) 18 and 20, 60 x 6838 104 and 144
             const int stm = (g.crows + 63) / 64, stn = (g.ccols + 63) / 64;
-            if (nb < resident_slots() / 2 && stm * stn > g.tiles_m * g.tiles_n) {
+            if (nb < resident_slots() / 2 && stm * stn > g.tiles_m * g.tiles_n && (int64_t)stm * stn * P <= resident_slots()) {
                 g.tiles_m = stm;
                 g.tiles_n = stn;
                 k_gemm_small<Epi><<<stm * stn * P, 256, 0, s>>>(g);

@@ -71,3 +71,49 @@ def test_fp32_weight_gradients_of_a_narrower_network_take_no_longer(torch, bindi
     narrow(), wide()
     best = [min(t) for t in zip(*((narrow(), wide()) for _ in range(7)))]
     assert best[0] < 1.05 * best[1], best
+
+
+@pytest.mark.parametrize("M,W,O,P", ((97, 256, 34, 33), (300, 80, 130, 129)))
+def test_bf16_weight_gradients_on_small_and_large_tiles_are_the_same_bits(M, W, O, P, torch, binding):  # noqa: F811
+    """P - 1 preferences make 512 tiles of 64 x 64 and run on those, P preferences more and run on 128 x 128: every sum keeps
+    its order, so the gradients of the first P - 1 are equal."""
+    g = torch.Generator(device="cuda").manual_seed(3)
+    n = lambda *s: torch.randn(*s, device="cuda", generator=g)
+    net, rows, grads, data = parity.ACTOR, (0, 1, 0, M), [], None
+    for q in (P, P - 1):
+        ctx = binding.Context.from_config(case(M, W, O, 2, 2, 2, q, wdtype=1, rank=2))
+        if data is None:
+            data = (n(P, ctx.theta_mat_len(net)) * W ** -0.5, n(P, ctx.theta_vec_len(net)) * 0.1, n(2, P * M, O), n(1, P * M, 2), n(P, 2))
+        tm, tv, x, dout, dls = data[0][:q].to(torch.bfloat16), data[1][:q], data[2][:, :q * M].contiguous(), data[3][:, :q * M].contiguous(), data[4][:q]
+        saved, ws = (torch.empty(b, dtype=torch.uint8, device="cuda") for b in (ctx.saved_bytes(net, rows), ctx.workspace_bytes(rows)))
+        dtm, dtv = torch.empty(q, tm.shape[1], device="cuda"), torch.empty(q, tv.shape[1], device="cuda")
+        ctx.policy_fwd(net, tm, tv, x, rows, torch.empty_like(dout), saved=saved, ws=ws)
+        ctx.policy_bwd(net, tm, tv, x, rows, saved, dout, dls, dtm, dtv, ws)
+        grads.append((dtm[:P - 1], dtv[:P - 1]))
+    for a, b in zip(*grads):
+        assert torch.equal(a, b)
+
+
+def test_bf16_weight_gradients_of_fewer_preferences_take_no_longer(torch, binding):  # noqa: F811
+    """dW of 60 preferences x 6838 rows x 256 x 256 against 64, which is more of the same work (a tenth is left for the clock)."""
+    def passes(P):
+        cfg = case(6838, 256, 16, 2, 2, 2, P, wdtype=1, rank=2)
+        ctx, net, rows, N = binding.Context.from_config(cfg), parity.ACTOR, (0, 1, 0, 6838), 6838 * P
+        z = lambda *s, **k: torch.zeros(*s, device="cuda", **k)
+        tm, tv = z(P, ctx.theta_mat_len(net), dtype=torch.bfloat16), z(P, ctx.theta_vec_len(net))
+        x, mu, dls = z(2, N, 16), z(1, N, 2), z(P, 2)
+        saved, ws = (torch.empty(n, dtype=torch.uint8, device="cuda") for n in (ctx.saved_bytes(net, rows), ctx.workspace_bytes(rows)))
+        dtm, dtv = z(P, ctx.theta_mat_len(net)), z(P, ctx.theta_vec_len(net))
+        ctx.policy_fwd(net, tm, tv, x, rows, mu, saved=saved, ws=ws)
+
+        def once():
+            ctx.profile_begin()
+            for _ in range(3):
+                ctx.policy_bwd(net, tm, tv, x, rows, saved, mu, dls, dtm, dtv, ws)
+            ms, n, _ = ctx.profile_end()["dw_hidden"]
+            return ms / n
+        return once
+    few, more = passes(60), passes(64)
+    few(), more()
+    best = [min(t) for t in zip(*((few(), more()) for _ in range(7)))]
+    assert best[0] < 1.1 * best[1], best
