@@ -2,6 +2,7 @@
 // shared base weights; with rank < 0 the strictly affine form, every weight its own row of M, which runs
 // entirely through the stacked affine map below).  fp32 arithmetic; theta_mat is rounded to bf16 (nearest even) on store when
 // the target networks run in bf16.  Every reduction is fixed-order.
+#include "mlp_device.h"
 #include "morlax_internal.h"
 #include "numeric.h"
 
@@ -17,20 +18,10 @@ struct HyperWs {
     int n_chunk, n_cs;
 };
 
-// 64-row tiles of the stacked affine map per chunk of the df partials.  Up to 128 preferences at least four, and about a
-// thousand chunks at most.  Above one, doubled until there are at most 4096 chunks: shorter sums, whose error is about a
-// quarter smaller (the trunk's gradients against 64 bits, 130 to 512 preferences: 2.2e-7 to 5.8e-7 of their norm, 3.0e-7 to
-// 6.9e-7 in chunks of four), for 124 instead of 122 us of a backward pass of 256 preferences of 3 x 256.
-#define DF_FEW_P 128
-static int df_chunk_tiles(int64_t q_total, int64_t P) {
-    const int64_t nt = (q_total + 63) / 64;
-    if (P <= DF_FEW_P) {
-        const int64_t t = (nt + 1023) / 1024;
-        return t < 4 ? 4 : (int)t;
-    }
-    int t = 1;
-    while ((nt + t - 1) / t > 4096) t *= 2;
-    return t;
+// 64-row tiles of the stacked affine map per chunk of the df partials: at least four, about a thousand chunks at most
+static int df_chunk_tiles(int64_t q_total) {
+    const int64_t t = ((q_total + 63) / 64 + 1023) / 1024;
+    return t < 4 ? 4 : (int)t;
 }
 
 static HyperWs hyper_ws_layout(const morlax_ctx* c, void* ws, int64_t* total) {
@@ -54,7 +45,7 @@ static HyperWs hyper_ws_layout(const morlax_ctx* c, void* ws, int64_t* total) {
     L.dfac = take(P * fac);
     L.n_chunk = 0;  // chunks of the df partials
     for (int n = 0; n < 2; ++n) {
-        const int64_t nt = (c->aff[n].q_total + 63) / 64, per = df_chunk_tiles(c->aff[n].q_total, P);
+        const int64_t nt = (c->aff[n].q_total + 63) / 64, per = df_chunk_tiles(c->aff[n].q_total);
         const int nc = (int)((nt + per - 1) / per);
         L.n_chunk = nc > L.n_chunk ? nc : L.n_chunk;
     }
@@ -647,36 +638,39 @@ __device__ inline float grad_row(const float* __restrict__ dfac, const float* __
 // From the gradient g of the stacked affine rows (fp32 MFMA, fixed orders):
 //   dM[q, :] = sum_p g[p, q] f[p, :],  dc[q] = sum_p g[p, q] (four interleaved shares of the preferences, each in
 //   order, added in a fixed order),  part[chunk, p, j] = sum over the chunk's rows q of g[p, q] M[q, j].
-// A chunk is tpc tiles of 64 rows.  Workgroups have two roles, and the neighbours that share tpw tiles, a whole number of
-// chunks, find g in the caches the other has filled:
+// A chunk is tpw tiles of 64 rows.  Workgroups of eight waves have two roles:
+//   df: 128 preferences (16 a wave) walk a chunk's tiles in order; the tile of g (a preference's 64 values one 256-byte
+//       run) and of M go through LDS, the next ones are in flight in registers meanwhile.  LDS pitches: g 68 floats,
+//       M 16 JT + 16 (reads free of conflicts).
 //   dM: a wave takes one tile and all preferences, operands straight from memory: lane ln reads four consecutive rows
 //       of a preference, so that a request covers 256-byte runs; no LDS, no barrier, nothing carried between tiles.
-//   df: a workgroup takes 64 preferences (16 a wave) and walks the tpw tiles in order; the tile of g (a preference's
-//       64 values one 256-byte run) and of M go through LDS, the next ones are in flight in registers meanwhile.
-//       LDS pitches: g 68 floats, M 16 JT + 16 (reads free of conflicts).
-// FINE (more than DF_FEW_P preferences): a chunk may be less than tpw tiles, and a product takes four rows 4 apart of
-// sixteen instead of neighbours, which is where place() puts them.
-// Both in one role (a workgroup walked four tiles, each a chain of LDS exchanges and products of one accumulator) took
-// 59 us for 69 thousand rows x 128 preferences, 35 us for 15 thousand x 24 and 23 us for 2600 x 4; now 39, 11.4, 10.7.
+// FINE (more than DMF_P preferences): every tile is summed by itself and added to those before it.  Sums of 64 rows are
+// what such problems had before; one sum over a chunk is less precise (the trunk's gradients against 64 bits, 130 to 512
+// preferences, means of eight inputs: 2.6e-7 to 4.9e-7 of their norm in sums of 64 rows, 3.3e-7 to 5.7e-7 in whole chunks,
+// 2.6e-7 to 5.1e-7 here).
+// Bound by the latency of g, which both roles read.  All df workgroups, the long ones, come first.  Dealt in turn, one to
+// every one or three of dM, they met on the same dies, and within a die on the same shader engines; with four waves and 64
+// preferences a workgroup, more than 64 preferences read M and walked the tiles twice.  hypernet_bwd (us) with both roles in
+// one, so dealt, and here: strictly affine 3 x 512, 32 preferences 158, 197, 89; 4 x 512, 100 preferences 331, 342, 251.
+// The kernel at low rank: 69 thousand rows x 128 preferences 59, 39, 32; 15 thousand x 24 35, 11.4, 11.1; 2600 x 4 23, 10.7, 10.2.
 #define DMF_Q 64
-#define DMF_P 64  // preferences of a df workgroup
+#define DMF_W 8             // waves of a workgroup
+#define DMF_P (16 * DMF_W)  // preferences of a df workgroup
 template <int JT, bool FINE>
-__global__ __launch_bounds__(256) void k_hyper_dM_df(const float* __restrict__ hp, const int32_t* __restrict__ mrow,
+__global__ __launch_bounds__(64 * DMF_W) void k_hyper_dM_df(const float* __restrict__ hp, const int32_t* __restrict__ mrow,
                                                     const int32_t* __restrict__ crow, const float* __restrict__ f,
                                                     const float* __restrict__ dfac, const float* __restrict__ dvec,
                                                     float* __restrict__ dhp, float* __restrict__ part, int P, int F,
                                                     int64_t fac_len, int64_t vec_len, int q_total, int n_tiles, int tpw,
-                                                    int tpc, int n_df, int n_dm) {
+                                                    int n_p, int n_df, int dm_t) {
     constexpr int PD = 68, PJ = 16 * JT + 16;
     __shared__ float Dl[DMF_P][PD];
     __shared__ float Ml[DMF_Q][PJ];
     __shared__ int32_t Rl[2][DMF_Q];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, ln = lane & 15, kg = lane >> 4;
-    const int group = blockIdx.x / (n_df + n_dm), role = blockIdx.x % (n_df + n_dm);
-    const int t_lo = group * tpw, t_hi = (t_lo + tpw < n_tiles) ? (t_lo + tpw) : n_tiles;
-    if (role >= n_df) {  // dM and dc of one tile a wave (no barrier: the waves are on their own)
-        const int tile = t_lo + 4 * (role - n_df) + wave;
-        if (tile >= t_hi) return;
+    if ((int)blockIdx.x >= n_df) {  // dM and dc of one tile a wave (no barrier: the waves are on their own)
+        const int tile = dm_t * xcd_remap(blockIdx.x - n_df, gridDim.x - n_df) + wave;
+        if (wave >= dm_t || tile >= n_tiles) return;
         const int q0 = tile * DMF_Q, q4 = q0 + 4 * ln;
         float4_t acc[4][JT];
         float dc[4] = {0.f, 0.f, 0.f, 0.f};
@@ -749,10 +743,10 @@ __global__ __launch_bounds__(256) void k_hyper_dM_df(const float* __restrict__ h
         return;
     }
     // df partials of preferences p0 .. p0 + 15 (this wave's)
-    const int pb = role * DMF_P, p0 = pb + 16 * wave;
-    auto place = [](int row) { return FINE ? (row & ~15) | ((row & 3) << 2) | ((row >> 2) & 3) : row; };
-    constexpr int MPT = DMF_Q * 16 * JT / 256;
-    float nxt[DMF_P / 4], mnx[MPT];
+    const int id = xcd_remap(blockIdx.x, n_df), chunk = id / n_p, pb = id % n_p * DMF_P, p0 = pb + 16 * wave;
+    const int t_lo = chunk * tpw, t_hi = (t_lo + tpw < n_tiles) ? (t_lo + tpw) : n_tiles;
+    constexpr int MPT = DMF_Q * 16 * JT / (64 * DMF_W);
+    float nxt[DMF_P / DMF_W], mnx[MPT];
     auto row_of = [&](int tile) {  // (threads 0 .. 63) offset of a row of M
         const int q = tile * DMF_Q + (int)threadIdx.x;
         return tile < t_hi && threadIdx.x < DMF_Q && q < q_total ? mrow[q] : 0;
@@ -760,30 +754,24 @@ __global__ __launch_bounds__(256) void k_hyper_dM_df(const float* __restrict__ h
     auto fetch = [&](int tile) {
         const int q = tile * DMF_Q + lane;
 #pragma unroll
-        for (int i = 0; i < DMF_P / 4; ++i) {
-            const int pp = pb + wave + 4 * i;
+        for (int i = 0; i < DMF_P / DMF_W; ++i) {
+            const int pp = pb + wave + DMF_W * i;
             nxt[i] = (pp < P && q < q_total) ? grad_row(dfac, dvec, pp, q, fac_len, vec_len) : 0.f;
         }
 #pragma unroll
         for (int i = 0; i < MPT; ++i) {
-            const int idx = threadIdx.x + 256 * i, qq = idx / (16 * JT), j = idx % (16 * JT);
+            const int idx = threadIdx.x + 64 * DMF_W * i, qq = idx / (16 * JT), j = idx % (16 * JT);
             mnx[i] = (tile * DMF_Q + qq < q_total && j < F) ? hp[Rl[tile & 1][qq] + j] : 0.f;
         }
     };
     float4_t accF[JT];
 #pragma unroll
     for (int jt = 0; jt < JT; ++jt) accF[jt] = float4_t{0.f, 0.f, 0.f, 0.f};
-    auto put_part = [&](int chunk) {  // lane holds feature j = 16 jt + ln of preferences p0 + 4 kg + e
+    float4_t sumF[FINE ? JT : 1];  // FINE: the sum of the tiles before this one
+    if constexpr (FINE) {
 #pragma unroll
-        for (int jt = 0; jt < JT; ++jt) {
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                const int pp = p0 + 4 * kg + e, j = 16 * jt + ln;
-                if (pp < P && j < F) part[((int64_t)chunk * P + pp) * F + j] = accF[jt][e];
-            }
-            accF[jt] = float4_t{0.f, 0.f, 0.f, 0.f};
-        }
-    };
+        for (int jt = 0; jt < JT; ++jt) sumF[jt] = accF[jt];
+    }
     if (threadIdx.x < DMF_Q) Rl[t_lo & 1][threadIdx.x] = row_of(t_lo);
     int32_t rnext = row_of(t_lo + 1);
     __syncthreads();
@@ -791,11 +779,11 @@ __global__ __launch_bounds__(256) void k_hyper_dM_df(const float* __restrict__ h
     for (int tile = t_lo; tile < t_hi; ++tile) {
         __syncthreads();  // the previous tile's readers are done
 #pragma unroll
-        for (int i = 0; i < DMF_P / 4; ++i) Dl[wave + 4 * i][place(lane)] = nxt[i];
+        for (int i = 0; i < DMF_P / DMF_W; ++i) Dl[wave + DMF_W * i][lane] = nxt[i];
 #pragma unroll
         for (int i = 0; i < MPT; ++i) {
-            const int idx = threadIdx.x + 256 * i;
-            Ml[place(idx / (16 * JT))][idx % (16 * JT)] = mnx[i];
+            const int idx = threadIdx.x + 64 * DMF_W * i;
+            Ml[idx / (16 * JT)][idx % (16 * JT)] = mnx[i];
         }
         if (threadIdx.x < DMF_Q) Rl[(tile + 1) & 1][threadIdx.x] = rnext;
         __syncthreads();
@@ -812,9 +800,23 @@ __global__ __launch_bounds__(256) void k_hyper_dM_df(const float* __restrict__ h
                     accF[jt] = __builtin_amdgcn_mfma_f32_16x16x4f32(a, Ml[4 * kk + kg][16 * jt + ln], accF[jt], 0, 0, 0);
             }
         }
-        if (FINE && tile + 1 < t_hi && (tile + 1) % tpc == 0) put_part(tile / tpc);
+        if constexpr (FINE) {
+#pragma unroll
+            for (int jt = 0; jt < JT; ++jt) {
+#pragma unroll
+                for (int e = 0; e < 4; ++e) sumF[jt][e] += accF[jt][e];
+                accF[jt] = float4_t{0.f, 0.f, 0.f, 0.f};
+            }
+        }
     }
-    put_part(FINE ? (t_hi - 1) / tpc : group);
+    // lane holds feature j = 16 jt + ln of preferences p0 + 4 kg + e
+#pragma unroll
+    for (int jt = 0; jt < JT; ++jt)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const int pp = p0 + 4 * kg + e, j = 16 * jt + ln;
+            if (pp < P && j < F) part[((int64_t)chunk * P + pp) * F + j] = FINE ? sumF[FINE ? jt : 0][e] : accF[jt][e];
+        }
 }
 
 // Trunk backward, stage 1: df[p, j] = sum_chunk part; dz2 = df * (1 - f^2); dz1 = (dz2 Wh2) * (1 - h1^2).  A block
@@ -987,6 +989,14 @@ __global__ __launch_bounds__(1024) void k_hyper_trunk_bwd(const float* __restric
     }
 }
 
+// Tiles, a wave each, of a dM workgroup: eight where there are enough, fewer so that few tiles still spread over the CUs
+// (hypernet_bwd with 1 tile, with the rule, with 8: 100 preferences of 4 x 256, 210 tiles 75, 75 and 81 us; 128 of 4 x 512, 1073
+// tiles 249, 235 and 236)
+static int dm_tiles(int n_tiles) {
+    const int t = (n_tiles + 127) / 128;
+    return t < DMF_W ? t : DMF_W;
+}
+
 void launch_hypernet_bwd(const morlax_ctx* c, int net, const float* hparams, const float* w,
                          const float* dtheta_mat, const float* dtheta_vec, float* dhparams, void* ws,
                          bool kept, hipStream_t s) {
@@ -1028,15 +1038,14 @@ void launch_hypernet_bwd(const morlax_ctx* c, int net, const float* hparams, con
             k_hyper_dA_merge<<<dim3((merged + 1023) / 1024, P, nd.n_layers), 256, 0, s>>>(nd, L.da_part, L.dfac, r, P);
     }
     if (r <= 0) k_hyper_base<<<n_base, 256, 0, s>>>(nd, at, bw, dtheta_mat, P);
-    // (four tiles and more to a workgroup of either role, whatever the chunk)
-    const int n_tiles = (at.q_total + DMF_Q - 1) / DMF_Q, tpc = df_chunk_tiles(at.q_total, P), tpw = tpc < 4 ? 4 : tpc;
-    const int n_chunk = (n_tiles + tpc - 1) / tpc, n_group = (n_tiles + tpw - 1) / tpw;
-    const int n_df = (P + DMF_P - 1) / DMF_P, n_dm = (tpw + 3) / 4;
+    const int n_tiles = (at.q_total + DMF_Q - 1) / DMF_Q, tpw = df_chunk_tiles(at.q_total);
+    const int n_chunk = (n_tiles + tpw - 1) / tpw;
+    const int n_p = (P + DMF_P - 1) / DMF_P, n_df = n_chunk * n_p, dm_t = dm_tiles(n_tiles), n_dm = (n_tiles + dm_t - 1) / dm_t;
     auto dM_df = [&](auto kernel) {
-        kernel<<<n_group * (n_df + n_dm), 256, 0, s>>>(hparams, L.mrow, L.crow, L.f, dlead, dtheta_vec, dhparams, L.df_part, P,
-                                                       F, nd.fac_len, nd.vec_len, at.q_total, n_tiles, tpw, tpc, n_df, n_dm);
+        kernel<<<n_df + n_dm, 64 * DMF_W, 0, s>>>(hparams, L.mrow, L.crow, L.f, dlead, dtheta_vec, dhparams, L.df_part, P, F,
+                                                  nd.fac_len, nd.vec_len, at.q_total, n_tiles, tpw, n_p, n_df, dm_t);
     };
-    if (P <= DF_FEW_P) {
+    if (n_p == 1) {
         if (F <= 32) dM_df(k_hyper_dM_df<2, false>);
         else dM_df(k_hyper_dM_df<4, false>);
     } else {

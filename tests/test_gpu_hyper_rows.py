@@ -58,7 +58,7 @@ def test_factor_gradients_from_several_column_runs(cfg, torch, binding):  # noqa
     parity.test_hypernet_bwd_matches_oracle(cfg, torch, binding)
 
 
-# more than 128 preferences: sums over chunks of one 64-row tile, of two where there are more than 4096 tiles
+# more than 128 preferences: every tile of 64 rows summed by itself, in chunks of four tiles, of five where there are more than 4096
 MANY_P = [scaled(RAGGED, name=f"F{F}-P{P}", P=P, N=2 * P, rank=-1, hyper_width=F, obs_dim=16, width=16, n_hidden=1, act_dim=2,
                  wdtype=0) for P, F in ((129, 32), (130, 64), (257, 5))]
 MANY_P += [scaled(RAGGED, name="F3-P129-many-rows", P=129, N=258, hyper_width=3, rank=-1, obs_dim=61, width=272, n_hidden=5)]
@@ -66,18 +66,16 @@ MANY_P += [scaled(RAGGED, name="F3-P129-many-rows", P=129, N=258, hyper_width=3,
 
 @pytest.mark.parametrize("cfg", MANY_P, ids=lambda c: c.name)
 def test_feature_gradient_of_many_preferences_is_summed_by_tiles(cfg, torch, binding):  # noqa: F811
-    """df of a strictly affine network with f = 0, where dbh2 = sum_p df: 64 rows (or 128, the chunk of very many) that add up
-    to 2^26, as many that add up to 32 (64), as many that take the first away.  Every sum of one chunk and the sum of the
-    chunks are exact in fp32; a sum that runs on across the chunks loses the small one whole."""
+    """df of a strictly affine network with f = 0, where dbh2 = sum_p df: 64 rows that add up to 2^26, as many that add up to
+    32, as many that take the first away.  Every sum of one tile and the sum of the tiles are exact in fp32; a sum that runs
+    on from row to row across the tiles loses the small one whole."""
     ctx = binding.Context.from_config(cfg)
     net = parity.ACTOR
     lay = parity.orc.hparam_layout(cfg, net)
     ml, vl = ctx.theta_mat_len(net), ctx.theta_vec_len(net)
-    chunk = 64 if (ml + vl + 63) // 64 <= 4096 else 128
     hp = torch.zeros(ctx.hparam_count(net), device="cuda")
     M = torch.zeros(ml, cfg.hyper_width, device="cuda")
-    big = 2.0 ** 26 / chunk
-    M[:chunk], M[chunk:2 * chunk], M[2 * chunk:3 * chunk] = big, 0.5, -big
+    M[:64], M[64:128], M[128:192] = 2.0 ** 20, 0.5, -2.0 ** 20
     at = 0
     for (o, i), l in zip(parity.inputs.layer_shapes(cfg, net), range(cfg.n_hidden + 1)):
         off = lay[f"MW_{l}"][0]
@@ -85,13 +83,13 @@ def test_feature_gradient_of_many_preferences_is_summed_by_tiles(cfg, torch, bin
         at += o * i
     assert at == ml
     dtm = torch.zeros(cfg.P, ml, device="cuda")
-    dtm[:, :3 * chunk] = 1.0
+    dtm[:, :192] = 1.0
     dtv, w = torch.zeros(cfg.P, vl, device="cuda"), torch.full((cfg.P, cfg.K), 1.0 / cfg.K, device="cuda")
     dhp = torch.full_like(hp, 9.0)
     ws = torch.empty(ctx.workspace_bytes((0, 1, 0, 1)), dtype=torch.uint8, device="cuda")
     ctx.hypernet_bwd(net, hp, w, dtm, dtv, dhp, ws)
     off = lay["bh2"][0]
-    assert (dhp[off:off + cfg.hyper_width] == cfg.P * chunk * 0.5).all(), dhp[off:off + cfg.hyper_width]
+    assert (dhp[off:off + cfg.hyper_width] == cfg.P * 32).all(), dhp[off:off + cfg.hyper_width]
 
 
 # few preferences on both sides of the numbers of stacked rows up to which the trunk shares a launch: workgroups of 64 rows
@@ -132,3 +130,26 @@ def test_few_preferences_of_a_wide_affine_network_take_no_longer_than_more(torch
     few(), more()
     best = [min(t) for t in zip(*((few(), more()) for _ in range(9)))]
     assert best[0] < 1.25 * best[1], best
+
+
+def test_gradient_of_fewer_affine_rows_takes_no_longer(torch, binding):  # noqa: F811
+    """hypernet_bwd of 32 preferences of a strictly affine 3 x 512 network against 4 x 512, which has half as many rows again."""
+    def passes(L):
+        cfg = scaled(RAGGED, name=f"affine-{L}x512", P=32, N=64, rank=-1, hyper_width=32, obs_dim=11, width=512, n_hidden=L, wdtype=1)
+        ctx, net, z = binding.Context.from_config(cfg), parity.ACTOR, lambda *s: torch.zeros(*s, device="cuda")
+        hp, w, dtm, dtv = z(ctx.hparam_count(net)), z(32, cfg.K), z(32, ctx.theta_mat_len(net)), z(32, ctx.theta_vec_len(net))
+        dhp, ws = torch.empty_like(hp), torch.empty(ctx.workspace_bytes((0, 1, 0, 1)), dtype=torch.uint8, device="cuda")
+
+        def once():
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            a.record()
+            for _ in range(10):
+                ctx.hypernet_bwd(net, hp, w, dtm, dtv, dhp, ws)
+            b.record()
+            b.synchronize()
+            return a.elapsed_time(b)
+        return once
+    few, more = passes(3), passes(4)
+    few(), more()
+    best = [min(t) for t in zip(*((few(), more()) for _ in range(9)))]
+    assert best[0] < best[1], best
