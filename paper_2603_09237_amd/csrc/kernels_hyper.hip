@@ -267,8 +267,20 @@ static void launch_trunk_affine(const AffineTable& at, const Trunk& tk, const fl
             k_hyper_affine<TF, KS, false><<<nb, 256, 0, s>>>(at, tk, hp, tk.f, fac, theta_vec, P, F, fac_len, vec_len);
         }
     };
-    if (F <= 32) run(std::integral_constant<int, 8>{});
-    else run(std::integral_constant<int, 16>{});
+    // as few contraction steps as the features fill, which are also what is read and staged of M (strictly affine 4 x 512, 4
+    // preferences, F = 8: 50 us in eight steps, 25 in two, 31 with a thread per row; F = 20: 60, 39 and 37)
+    switch ((F + 3) / 4) {
+        case 1: case 2: run(std::integral_constant<int, 2>{}); break;
+        case 3: run(std::integral_constant<int, 3>{}); break;
+        case 4: run(std::integral_constant<int, 4>{}); break;
+        case 5: run(std::integral_constant<int, 5>{}); break;
+        case 6: run(std::integral_constant<int, 6>{}); break;
+        case 7: run(std::integral_constant<int, 7>{}); break;
+        case 8: run(std::integral_constant<int, 8>{}); break;
+        case 9: case 10: run(std::integral_constant<int, 10>{}); break;
+        case 11: case 12: run(std::integral_constant<int, 12>{}); break;
+        default: run(std::integral_constant<int, 16>{}); break;
+    }
 }
 
 // W_l(p) = W0_l + A_l(p) B_l(p) on fp32 MFMA.  A block makes a 64 (d_out) x 128 (d_in) tile of one layer of one preference,

@@ -132,6 +132,39 @@ def test_few_preferences_of_a_wide_affine_network_take_no_longer_than_more(torch
     assert best[0] < 1.25 * best[1], best
 
 
+# feature widths on both sides of the contraction steps of the stacked map, with the trunk inside its launch and in front
+STEP_CASES = [scaled(RAGGED, name=f"steps-F{F}-P{P}", P=P, N=2 * P, hyper_width=F, width=32)
+              for F in (8, 9, 12, 13, 16, 17, 21, 24, 25, 28, 29, 36, 40, 41, 48, 49) for P in (5, 520 // F + 1)]
+
+
+@pytest.mark.parametrize("cfg", STEP_CASES, ids=lambda c: c.name)
+def test_stacked_rows_at_every_number_of_steps(cfg, torch, binding):  # noqa: F811
+    parity.test_hypernet_fwd_matches_oracle(cfg, torch, binding)
+
+
+def test_narrow_trunk_takes_less_time_than_a_wide_one(torch, binding):  # noqa: F811
+    """hypernet_fwd of 4 preferences of a strictly affine 4 x 512 network with 8 features against 32: a quarter of M to read."""
+    def passes(F):
+        cfg = scaled(RAGGED, name=f"affine-4x512-F{F}", P=4, N=8, rank=-1, hyper_width=F, obs_dim=16, width=512, n_hidden=4, wdtype=1)
+        ctx, net, z = binding.Context.from_config(cfg), parity.ACTOR, lambda *s: torch.zeros(*s, device="cuda")
+        hp, w, tm, tv = z(ctx.hparam_count(net)), z(4, cfg.K), z(4, ctx.theta_mat_len(net)).to(torch.bfloat16), z(4, ctx.theta_vec_len(net))
+        ws = torch.empty(ctx.workspace_bytes((0, 1, 0, 1)), dtype=torch.uint8, device="cuda")
+
+        def once():
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            a.record()
+            for _ in range(20):
+                ctx.hypernet_fwd(net, hp, w, tm, tv, ws)
+            b.record()
+            b.synchronize()
+            return a.elapsed_time(b)
+        return once
+    narrow, wide = passes(8), passes(32)
+    narrow(), wide()
+    best = [min(t) for t in zip(*((narrow(), wide()) for _ in range(9)))]
+    assert best[0] < 0.65 * best[1], best
+
+
 def test_gradient_of_fewer_affine_rows_takes_no_longer(torch, binding):  # noqa: F811
     """hypernet_bwd of 32 preferences of a strictly affine 3 x 512 network against 4 x 512, which has half as many rows again."""
     def passes(L):
