@@ -24,7 +24,8 @@ sys.path.insert(0, ROOT)
 PEAK_TFLOPS = {"bf16": 2500.0, "f32": 157.3}
 # grouped-GEMM launch kinds -> kernels that serve them (bf16 with enough tiles: the persistent direct-to-LDS kernel
 # k_gemm_pers; bf16 with few tiles: k_gemm_dma, its dW k_gemm_small; fp32 and shapes that need masking: k_grouped_gemm,
-# its dW k_gemm_f32_small where 64 x 64 tiles multiply less padding)
+# its dW k_gemm_f32_small where 64 x 64 tiles multiply less padding in few enough rounds).  The sums of split contractions
+# and of the narrow first layer's dW are part of k_bwd_final, which is in no kind.
 KERNEL_OF_KIND = {
     "fwd_first": "grouped GEMM <x rows, W0(p), EpiFwd> forward, first layer",
     "fwd_hidden": "grouped GEMM <SRC_KCONTIG, SRC_KCONTIG, EpiFwd> forward, W x W layers (rollout + update)",
