@@ -49,7 +49,7 @@ def test_backward_of_wide_fp32_networks(cfg, torch, binding):  # noqa: F811
 
 def test_fp32_weight_gradients_of_a_narrower_network_take_no_longer(torch, binding):  # noqa: F811
     """dW of 2 preferences x 4096 rows x 1952 x 1952 against 2048 x 2048, which is as many 128 x 128 tiles and a tenth more
-    weights (5 % are left for the clock)."""
+    weights (a tenth is left for the clock)."""
     def passes(W):
         cfg = case(4096, W, 16, 2, 2, 2, 2, wdtype=0, rank=2)
         ctx, net, rows = binding.Context.from_config(cfg), parity.ACTOR, (0, 1, 0, 4096)
@@ -70,7 +70,7 @@ def test_fp32_weight_gradients_of_a_narrower_network_take_no_longer(torch, bindi
     narrow, wide = passes(1952), passes(2048)
     narrow(), wide()
     best = [min(t) for t in zip(*((narrow(), wide()) for _ in range(7)))]
-    assert best[0] < 1.05 * best[1], best
+    assert best[0] < 1.1 * best[1], best
 
 
 @pytest.mark.parametrize("M,W,O,P", ((97, 256, 34, 33), (300, 80, 130, 129)))
