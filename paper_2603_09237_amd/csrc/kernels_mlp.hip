@@ -8,7 +8,7 @@
 // Hidden layers run on MFMA: a 256-thread workgroup owns a 128 x 128 output tile of one preference,
 // both operands are staged through LDS as rows of four 16-byte chunks along the contraction axis
 // (32 bf16 or 16 fp32 values per step) and each of the four waves accumulates a 64 x 64 sub-tile with
-// v_mfma_f32_32x32x16_bf16 / v_mfma_f32_32x32x2_f32.  Operands whose contraction axis is the slow
+// v_mfma_f32_32x32x16_bf16, fp32 operands as sums of three bf16 values (split3).  Operands whose contraction axis is the slow
 // axis in memory (W in the dX product, both operands of the dW product) are transposed on the way
 // into LDS.  The skinny output layer (<= 16 columns) uses 16x16 MFMA tiles, straight from global
 // memory in the forward pass and on rows staged through LDS for its dW; its dZ is plain vector code.
@@ -30,6 +30,22 @@ enum { SRC_KCONTIG = 0, SRC_KSTRIDED = 1, SRC_X_KCONTIG = 2 };
 // the shapes): loads are branch-free, out-of-range rows are clamped to a valid row (their results are
 // never stored) and out-of-range contraction indices are masked to zero.  !FAST = element-wise loads
 // with bounds checks, used only where a dimension is odd (first layer with an odd observation width).
+//
+// LDS row of a staged tile: bf16, the chunks as they are; fp32, the three bf16 parts of the step's values one after the other
+// (NCH * 8 bytes each).  112 bytes for the sixteen fp32 values of a step: the sixteen rows a fragment read serves at a time
+// start in sixteen different groups of four banks.
+template <typename T> constexpr int gemm_pitch(int nch) { return (sizeof(T) == 4 ? 3 * nch * 8 : nch * 16) + 16; }
+template <typename T, int NCH>
+__device__ inline void put_chunk(unsigned char* tile, int row, int chunk, const uint4& u) {
+    if constexpr (sizeof(T) == 4) {
+        uint2 part[3];
+        split3(u, part);
+#pragma unroll
+        for (int q = 0; q < 3; ++q) *reinterpret_cast<uint2*>(tile + row * gemm_pitch<T>(NCH) + q * NCH * 8 + chunk * 8) = part[q];
+    } else {
+        *reinterpret_cast<uint4*>(tile + row * gemm_pitch<T>(NCH) + chunk * 16) = u;
+    }
+}
 template <typename T, int KIND, bool FAST, int NCH>
 struct Operand {
     const void* base;  // T* (compact kinds) or float* (x kinds), already offset to preference p
@@ -39,7 +55,7 @@ struct Operand {
     int p;
 
     static constexpr int VE = Elems<T>::VE;
-    static constexpr int PITCH = NCH * 16 + 16;
+    static constexpr int PITCH = gemm_pitch<T>(NCH);
     static constexpr int CPT = NCH / 2;  // chunks per thread (128 * NCH / 256)
     static constexpr bool PAIR = (KIND == SRC_KSTRIDED && sizeof(T) == 2 && FAST);
 
@@ -133,6 +149,31 @@ struct Operand {
         }
     }
 
+    // fp32, FAST: the same values through a buffer descriptor, zero beyond the contraction range (a 32-bit offset a request;
+    // 64-bit addresses took the registers of a second step in flight)
+    __amdgpu_buffer_rsrc_t rsrc;
+    __device__ inline void describe() {
+        // K-strided tiles end with their last index; of the others an offset below the size of the tensor is asked for, or ~0
+        const uint32_t n = KIND == SRC_KSTRIDED ? (uint32_t)kdim * (uint32_t)ld * 4u : 0xfffffff0u;
+        rsrc = __builtin_amdgcn_make_buffer_rsrc(reinterpret_cast<void*>(uniform_addr(base)), 0, (int)n, 0x00020000);
+    }
+    __device__ inline void request(int k0, uint4 raw[NRAW]) const {
+        static_assert(!(FAST && sizeof(T) == 4) || NRAW == CPT, "one register quad a chunk");
+#pragma unroll
+        for (int i = 0; i < CPT; ++i) {
+            if (KIND == SRC_KSTRIDED) {
+                uint32_t d[4];
+#pragma unroll
+                for (int e = 0; e < 4; ++e)  // (a preference's operand stays below 2 GiB: no offset wraps)
+                    d[e] = __builtin_amdgcn_raw_buffer_load_b32(rsrc, (int)(voff[i] + (uint32_t)(k0 + e) * ((uint32_t)ld * 4u)), 0, 0);
+                raw[i] = make_uint4(d[0], d[1], d[2], d[3]);
+            } else {
+                const uint32_t at = k0 + tchunk(i) * VE < kdim ? voff[i] + (uint32_t)k0 * 4u : 0xffffffffu;
+                raw[i] = __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(rsrc, (int)at, 0, 0));
+            }
+        }
+    }
+
     __device__ static inline uint4 mask4(const uint4& u, bool ok) {
         const uint32_t m = ok ? 0xffffffffu : 0u;
         return make_uint4(u.x & m, u.y & m, u.z & m, u.w & m);
@@ -145,7 +186,7 @@ struct Operand {
 #pragma unroll
             for (int i = 0; i < CPT; ++i) {
                 const bool ok = !FAST || !TAIL || (k0 + tchunk(i) * VE < kdim);
-                *reinterpret_cast<uint4*>(tile + trow(i) * PITCH + tchunk(i) * 16) = mask4(raw[i], ok);
+                put_chunk<T, NCH>(tile, trow(i), tchunk(i), mask4(raw[i], ok));
             }
         } else if (PAIR) {
 #pragma unroll
@@ -171,7 +212,7 @@ struct Operand {
                 if (TAIL)
                     u = make_uint4(k < kdim ? u.x : 0u, k + 1 < kdim ? u.y : 0u, k + 2 < kdim ? u.z : 0u,
                                    k + 3 < kdim ? u.w : 0u);
-                *reinterpret_cast<uint4*>(tile + trow(i) * PITCH + tchunk(i) * 16) = u;
+                put_chunk<T, NCH>(tile, trow(i), tchunk(i), u);
             }
         } else {  // x source: fp32 -> T, whole chunks in or out of the contraction range
 #pragma unroll
@@ -184,7 +225,7 @@ struct Operand {
                     v[4 * q] = __uint_as_float(u.x); v[4 * q + 1] = __uint_as_float(u.y);
                     v[4 * q + 2] = __uint_as_float(u.z); v[4 * q + 3] = __uint_as_float(u.w);
                 }
-                *reinterpret_cast<uint4*>(tile + trow(i) * PITCH + tchunk(i) * 16) = mask4(pack_chunk<T>(v), ok);
+                put_chunk<T, NCH>(tile, trow(i), tchunk(i), mask4(pack_chunk<T>(v), ok));
             }
         }
     }
@@ -202,6 +243,7 @@ struct EpiFwd {  // h = act(z + b) and, when SAVE, act'(z); compact [M][ld] stor
     typename GradT<T>::type* G;  // used when SAVE
     int ld;
     static constexpr bool kColSum = false;
+    static constexpr bool kAhead = false;
     float* part;  // unused
     struct Out { Pack8 h, g; };
     __device__ inline void compute(int r, int c, int n, float v[8], Out& o) const {
@@ -240,10 +282,15 @@ struct EpiDx {  // dZ_{l-1} = (dZ_l W_l) * act'(z_{l-1})
     static constexpr bool kColSum = true;  // column sums of the unrounded dZ feed the bias gradient
     float* part;                           // [P][tiles_m][ld] partial column sums
     struct Out { Pack8 d; };
-    __device__ inline void compute(int r, int c, int n, float v[8], Out& o) const {
-        (void)n;
+    // the derivatives of an octet, requested together with those of the lane's other octets: one round trip a tile
+    static constexpr bool kAhead = true;
+    __device__ inline void request(int r, int c, Pack8& g) const {
+        const uint4* src = reinterpret_cast<const uint4*>(G + (int64_t)r * ld + c);
+        g.lo = src[0];
+    }
+    __device__ inline void compute_ahead(const Pack8& q, float v[8], Out& o) const {  // (bf16; fp32: epilogue_f32)
         float g[8];
-        get8(G + (int64_t)r * ld + c, g);
+        unpack8(q.lo, g);
 #pragma unroll
         for (int i = 0; i < 8; ++i) v[i] *= g[i];
         o.d = pack8(v, (const T*)nullptr);
@@ -274,6 +321,7 @@ struct EpiDw {  // dW_l(p)[o, i]
     float* dW;
     int ld;
     static constexpr bool kColSum = false;
+    static constexpr bool kAhead = false;
     float* part;  // unused
     struct Out { Pack8 w; };
     __device__ inline void compute(int r, int c, int n, float v[8], Out& o) const {
@@ -347,6 +395,16 @@ __device__ inline void gemm_epilogue(const Epi& epi, float16_t (&acc)[2][2], uns
     constexpr int PPR = 64 * ES / 16;           // 16-byte pieces per patch row
     constexpr int NB = Epi::kStage ? 4 : 2;     // octets computed before their stores are issued
     unsigned char* patch = lds0 + wave * (32 * WP);
+    Pack8 ahead[Epi::kAhead ? 2 : 1][Epi::kAhead ? 4 : 1];
+    if constexpr (Epi::kAhead) {
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+#pragma unroll
+            for (int o = 0; o < 4; ++o) {
+                const int r = r0 + wm + 32 * i + lr, c = c0 + wn + 16 * o + 8 * lg;
+                epi.request(r < rows ? r : rows - 1, c < cols ? c : 0, ahead[i][o]);
+            }
+    }
 #pragma unroll
     for (int i = 0; i < 2; ++i) {
         const int r = r0 + wm + 32 * i + lr;
@@ -364,7 +422,8 @@ __device__ inline void gemm_epilogue(const Epi& epi, float16_t (&acc)[2][2], uns
                 // out-of-range octets are computed on a clamped, valid position and not stored
                 const int rc = r < rows ? r : rows - 1;
                 const int cc = c < cols ? c : 0;
-                epi.compute(rc, cc, 8, v, outs[o]);
+                if constexpr (Epi::kAhead) epi.compute_ahead(ahead[i][NB == 4 ? o : 2 * jb + o], v, outs[o]);
+                else epi.compute(rc, cc, 8, v, outs[o]);
                 if (Epi::kColSum) {
 #pragma unroll
                     for (int u = 0; u < 8; ++u) {
@@ -428,6 +487,115 @@ __device__ inline void gemm_epilogue(const Epi& epi, float16_t (&acc)[2][2], uns
     }
 }
 
+// ---- epilogue of the fp32 products.  Their operands are not swapped: lane (lr, lg) of a 32 x 32 block holds column lr of the rows
+// 8 (e / 4) + 4 lg + e % 4, so that an access of a wave is two whole 128-byte lines.  (As above, a row and eight columns a lane:
+// 64 pieces of 16 bytes an access.  16 preferences x 8192 rows x 256 x 256, dX, which loads act' and stores dZ: 144 us, of which
+// 60 were the epilogue's.)  Rows and columns beyond the edge fall to the buffer descriptors' bounds: their loads give zero,
+// their stores do nothing.
+struct TileF32 {
+    uint32_t at;   // byte offset of the lane's element of row 0 of the block; beyond every tensor where its column is
+    uint32_t ld4;  // bytes per row
+    __device__ inline TileF32(int r, int c, int cols, int ld)
+        : at(c < cols ? (uint32_t)(r * ld + c) * 4u : 0x80000000u), ld4((uint32_t)ld * 4u) {}
+    __device__ static inline int row(int e) { return 8 * (e >> 2) + (e & 3); }
+    __device__ inline int off(int e) const { return (int)(at + (uint32_t)row(e) * ld4); }
+    // (a preference's tensor stays below 2 GiB)
+    __device__ static inline __amdgpu_buffer_rsrc_t tensor(const float* base, int rows, int ld) {
+        return __builtin_amdgcn_make_buffer_rsrc(reinterpret_cast<void*>(uniform_addr(base)), 0, rows * ld * 4, 0x00020000);
+    }
+    __device__ inline void put(__amdgpu_buffer_rsrc_t t, int e, float v) const {
+        __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(v), t, off(e), 0, 0);
+    }
+    __device__ inline float get(__amdgpu_buffer_rsrc_t t, int e) const {
+        return __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(t, off(e), 0, 0));
+    }
+};
+// NI x NJ blocks of a wave at (r, c); `red`: 128 floats of LDS, used by the whole workgroup of four waves where the epilogue
+// has column sums
+template <typename T, int ACT, bool SAVE, int NI, int NJ>
+__device__ inline void epilogue_f32(const EpiFwd<T, ACT, SAVE>& epi, float16_t (&acc)[NI][NJ], float*, int, int, int, int r, int c,
+                                    int rows, int cols) {
+    const int lr = threadIdx.x & 31, lg = (threadIdx.x >> 5) & 1;
+    const auto H = TileF32::tensor(reinterpret_cast<const float*>(epi.H), rows, epi.ld);
+    const auto G = TileF32::tensor(reinterpret_cast<const float*>(SAVE ? (const void*)epi.G : (const void*)epi.H), rows, epi.ld);
+#pragma unroll
+    for (int j = 0; j < NJ; ++j) {
+        const int col = c + 32 * j + lr;
+        const float b = epi.bias[col < cols ? col : 0];
+#pragma unroll
+        for (int i = 0; i < NI; ++i) {
+            const TileF32 t(r + 32 * i + 4 * lg, col, cols, epi.ld);
+#pragma unroll
+            for (int e = 0; e < 16; ++e) {
+                float h, g;
+                act_pair<T, ACT, false>(acc[i][j][e] + b, h, g);
+                t.put(H, e, h);
+                if (SAVE) t.put(G, e, g);
+            }
+        }
+    }
+}
+template <int NI, int NJ>
+__device__ inline void epilogue_f32(const EpiDw& epi, float16_t (&acc)[NI][NJ], float*, int, int, int, int r, int c, int rows, int cols) {
+    const int lr = threadIdx.x & 31, lg = (threadIdx.x >> 5) & 1;
+    const auto D = TileF32::tensor(epi.dW, rows, epi.ld);
+#pragma unroll
+    for (int i = 0; i < NI; ++i)
+#pragma unroll
+        for (int j = 0; j < NJ; ++j) {
+            const TileF32 t(r + 32 * i + 4 * lg, c + 32 * j + lr, cols, epi.ld);
+#pragma unroll
+            for (int e = 0; e < 16; ++e) t.put(D, e, acc[i][j][e]);
+        }
+}
+template <int NI, int NJ>
+__device__ inline void epilogue_f32(const EpiDx<float>& epi, float16_t (&acc)[NI][NJ], float* red, int p, int tm, int tiles_m, int r, int c,
+                                    int rows, int cols) {
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, lr = lane & 31, lg = lane >> 5;
+    const auto G = TileF32::tensor(epi.G, rows, epi.ld), D = TileF32::tensor(epi.dZ, rows, epi.ld);
+    float16_t g[NI][NJ];  // all on their way together
+#pragma unroll
+    for (int i = 0; i < NI; ++i)
+#pragma unroll
+        for (int j = 0; j < NJ; ++j) {
+            const TileF32 t(r + 32 * i + 4 * lg, c + 32 * j + lr, cols, epi.ld);
+#pragma unroll
+            for (int e = 0; e < 16; ++e) g[i][j][e] = t.get(G, e);
+        }
+    float part[NJ][4];  // (short chains: a quarter of the lane's rows each)
+#pragma unroll
+    for (int j = 0; j < NJ; ++j) part[j][0] = part[j][1] = part[j][2] = part[j][3] = 0.f;
+#pragma unroll
+    for (int i = 0; i < NI; ++i)
+#pragma unroll
+        for (int j = 0; j < NJ; ++j) {
+            const int row0 = r + 32 * i + 4 * lg;
+            const TileF32 t(row0, c + 32 * j + lr, cols, epi.ld);
+#pragma unroll
+            for (int e = 0; e < 16; ++e) {
+                const float v = acc[i][j][e] * g[i][j][e];
+                t.put(D, e, v);
+                part[j][e & 3] += row0 + TileF32::row(e) < rows ? v : 0.f;
+            }
+        }
+    float sum[NJ];
+    // column sums over the tile's 128 rows: lane groups, then the two waves above each other
+#pragma unroll
+    for (int j = 0; j < NJ; ++j) {
+        sum[j] = (part[j][0] + part[j][1]) + (part[j][2] + part[j][3]);
+        sum[j] += __shfl_xor(sum[j], 32, 64);
+        if (wave >= 2 && lg == 0) red[(wave & 1) * 64 + 32 * j + lr] = sum[j];
+    }
+    __syncthreads();
+    if (wave < 2 && lg == 0) {
+#pragma unroll
+        for (int j = 0; j < NJ; ++j) {
+            const int col = c + 32 * j + lr;
+            if (col < cols) epi.part[((int64_t)p * tiles_m + tm) * epi.ld + col] = sum[j] + red[wave * 64 + 32 * j + lr];
+        }
+    }
+}
+
 template <typename T, int KA, int KB, class Epi, bool FAST, int NCH>
 struct GemmArgs {
     Operand<T, KA, FAST, NCH> a;
@@ -456,12 +624,24 @@ struct GemmArgs {
     }
 };
 
-// C[rows_a x rows_b] = A[rows_a x K] * B[rows_b x K]^T for every preference.
+// One 32 x 32 block of an fp32 product once more, on the fp32 matrix instructions and from memory: what is left to do where
+// the sums of split operands came out undefined (see split3: an infinite operand does that).
+template <class OpA, class OpB>
+__device__ inline void plain_products(const OpA& A, const OpB& B, int r, int c, int kdim, float16_t& acc) {
+    const int lg = (threadIdx.x >> 5) & 1;
+#pragma unroll
+    for (int e = 0; e < 16; ++e) acc[e] = 0.f;
+#pragma unroll 1
+    for (int k = 0; k < kdim; k += 2) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(A.elem(r, k + lg), B.elem(c, k + lg), acc, 0, 0, 0);
+}
+
+// C[rows_a x rows_b] = A[rows_a x K] * B[rows_b x K]^T for every preference.  fp32 on split operands, us a launch, 16 preferences x
+// 8192 rows x 256 x 256: dX 203 -> 120 (of which the loop is 72; its products alone 43 at the matrix pipe's rate), dW 165 -> 96.
 template <typename T, int KA, int KB, class Epi, bool FAST, int NCH>
-__global__ __launch_bounds__(256) void k_grouped_gemm(GemmArgs<T, KA, KB, Epi, FAST, NCH> g) {
-    constexpr int PITCH = NCH * 16 + 16;
+__global__ __launch_bounds__(256, sizeof(T) == 4 ? 2 : 1) void k_grouped_gemm(GemmArgs<T, KA, KB, Epi, FAST, NCH> g) {
+    constexpr int PITCH = gemm_pitch<T>(NCH);
     constexpr int TILE = 128 * PITCH;
-    constexpr int CPT = NCH / 2;
+    constexpr bool SPLIT = sizeof(T) == 4;
     __shared__ __align__(16) unsigned char lds[2][2][TILE];
     constexpr int VE = Elems<T>::VE;
     constexpr int BK = NCH * VE;
@@ -496,61 +676,140 @@ __global__ __launch_bounds__(256) void k_grouped_gemm(GemmArgs<T, KA, KB, Epi, F
         for (int j = 0; j < 2; ++j)
 #pragma unroll
             for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.f;
+    float16_t low[SPLIT ? 2 : 1][2];  // fp32: the products of the smaller parts
+    if constexpr (SPLIT) {
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+#pragma unroll
+            for (int j = 0; j < 2; ++j) low[i][j] = acc[i][j];
+    }
 
     const int kdim = A.kdim;
     const int nk = (kdim + BK - 1) / BK;
-    // Register stage + two LDS stages: the loads of step kt+1 are in flight while step kt is multiplied
-    // out of LDS; they are converted and written to the other LDS stage after the products.  Only the last
-    // step can cross the end of the contraction range; it alone runs the clamped / masked loader.
     constexpr int NRA = Operand<T, KA, FAST, NCH>::NRAW, NRB = Operand<T, KB, FAST, NCH>::NRAW;
-    uint4 ra[NRA], rb[NRB];
     const int nfull = kdim / BK;  // steps [0, nfull) are entirely inside the contraction range
-    if (nfull > 0) {
-        A.template load<false>(r0, 0, ra);
-        B.template load<false>(c0, 0, rb);
-        A.template store<false>(lds[0][0], ra, 0);
-        B.template store<false>(lds[0][1], rb, 0);
+    if constexpr (SPLIT) {
+        // Two steps are on their way in registers.  The older one is split and written to the other LDS stage between the
+        // products of the step in LDS: 24 of them, 32 cycles each, against some 100 vector instructions.
+        static_assert(!SPLIT || NCH == 4, "a step is one product deep");
+        uint4 ra[2][NRA], rb[2][NRB];
+        if constexpr (FAST) { A.describe(); B.describe(); }
+        auto request = [&](int kt, auto set_tag) __attribute__((always_inline)) {
+            constexpr int U = decltype(set_tag)::value;
+            if constexpr (FAST) {
+                A.request(kt * BK, ra[U]);
+                B.request(kt * BK, rb[U]);
+            } else {
+                A.template load<true>(r0, kt * BK, ra[U]);
+                B.template load<true>(c0, kt * BK, rb[U]);
+            }
+        };
+        auto step = [&](int kt, auto set_tag) __attribute__((always_inline)) {
+            constexpr int U = decltype(set_tag)::value;
+            const unsigned char* ta = lds[U ^ 1][0] + (wm + lr) * PITCH + lg * 16;
+            const unsigned char* tb = lds[U ^ 1][1] + (wn + lr) * PITCH + lg * 16;
+            uint4 fa[2][3], fb[2][3];
+#pragma unroll
+            for (int q = 0; q < 3; ++q) {
+#pragma unroll
+                for (int i = 0; i < 2; ++i) fa[i][q] = *reinterpret_cast<const uint4*>(ta + 32 * i * PITCH + q * 32);
+#pragma unroll
+                for (int j = 0; j < 2; ++j) fb[j][q] = *reinterpret_cast<const uint4*>(tb + 32 * j * PITCH + q * 32);
+            }
+            A.template store<false>(lds[U][0], ra[U], 0);
+            B.template store<false>(lds[U][1], rb[U], 0);
+            request(kt + 3, set_tag);
+#pragma unroll
+            for (int t = 0; t < 6; ++t)  // (one round over all blocks a term: no product waits for the one before)
+#pragma unroll
+                for (int i = 0; i < 2; ++i)
+#pragma unroll
+                    for (int j = 0; j < 2; ++j) split_mma(t, fa[i], fb[j], acc[i][j], low[i][j]);
+            if (FAST) {
+#pragma unroll
+                for (int u = 0; u < 24; ++u) {
+                    __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);  // a product,
+                    __builtin_amdgcn_sched_group_barrier(0x002, 5, 0);  // vector instructions,
+                    __builtin_amdgcn_sched_group_barrier(0x200, 1, 0);  // a write to LDS
+                }
+            }
+            __syncthreads();
+        };
+        constexpr std::integral_constant<int, 0> even{};
+        constexpr std::integral_constant<int, 1> odd{};
+        request(0, even);
+        request(1, odd);
+        A.template store<false>(lds[0][0], ra[0], 0);
+        B.template store<false>(lds[0][1], rb[0], 0);
+        request(2, even);
+        __syncthreads();
+        for (int kt = 0; kt < nk; kt += 2) {
+            step(kt, odd);
+            if (kt + 1 < nk) step(kt + 1, even);
+        }
     } else {
-        A.template load<true>(r0, 0, ra);
-        B.template load<true>(c0, 0, rb);
-        A.template store<true>(lds[0][0], ra, 0);
-        B.template store<true>(lds[0][1], rb, 0);
-    }
-    __syncthreads();
-    for (int kt = 0; kt < nk; ++kt) {
-        const int cur = kt & 1;
-        const bool more = kt + 1 < nk, full = kt + 1 < nfull;
-        if (full) {
-            A.template load<false>(r0, (kt + 1) * BK, ra);
-            B.template load<false>(c0, (kt + 1) * BK, rb);
-        } else if (more) {
-            A.template load<true>(r0, (kt + 1) * BK, ra);
-            B.template load<true>(c0, (kt + 1) * BK, rb);
-        }
-        const unsigned char* ta = lds[cur][0] + (wm + lr) * PITCH + lg * 16;
-        const unsigned char* tb = lds[cur][1] + (wn + lrp) * PITCH + lg * 16;
-#pragma unroll
-        for (int ks = 0; ks < NCH / 2; ++ks) {
-            uint4 fa[2], fb[2];
-#pragma unroll
-            for (int i = 0; i < 2; ++i) fa[i] = *reinterpret_cast<const uint4*>(ta + 32 * i * PITCH + ks * 32);
-#pragma unroll
-            for (int j = 0; j < 2; ++j) fb[j] = *reinterpret_cast<const uint4*>(tb + 32 * j * PITCH + ks * 32);
-#pragma unroll
-            for (int i = 0; i < 2; ++i)
-#pragma unroll
-                for (int j = 0; j < 2; ++j) Mma32<T>::run(fb[j], fa[i], acc[i][j]);  // transposed tile
-        }
-        if (full) {
-            A.template store<false>(lds[cur ^ 1][0], ra, (kt + 1) * BK);
-            B.template store<false>(lds[cur ^ 1][1], rb, (kt + 1) * BK);
-        } else if (more) {
-            A.template store<true>(lds[cur ^ 1][0], ra, (kt + 1) * BK);
-            B.template store<true>(lds[cur ^ 1][1], rb, (kt + 1) * BK);
+        // Register stage + two LDS stages: the loads of step kt+1 are in flight while step kt is multiplied
+        // out of LDS; they are converted and written to the other LDS stage after the products.  Only the last
+        // step can cross the end of the contraction range; it alone runs the clamped / masked loader.
+        uint4 ra[NRA], rb[NRB];
+        if (nfull > 0) {
+            A.template load<false>(r0, 0, ra);
+            B.template load<false>(c0, 0, rb);
+            A.template store<false>(lds[0][0], ra, 0);
+            B.template store<false>(lds[0][1], rb, 0);
+        } else {
+            A.template load<true>(r0, 0, ra);
+            B.template load<true>(c0, 0, rb);
+            A.template store<true>(lds[0][0], ra, 0);
+            B.template store<true>(lds[0][1], rb, 0);
         }
         __syncthreads();
+        for (int kt = 0; kt < nk; ++kt) {
+            const int cur = kt & 1;
+            const bool more = kt + 1 < nk, full = kt + 1 < nfull;
+            if (full) {
+                A.template load<false>(r0, (kt + 1) * BK, ra);
+                B.template load<false>(c0, (kt + 1) * BK, rb);
+            } else if (more) {
+                A.template load<true>(r0, (kt + 1) * BK, ra);
+                B.template load<true>(c0, (kt + 1) * BK, rb);
+            }
+            const unsigned char* ta = lds[cur][0] + (wm + lr) * PITCH + lg * 16;
+            const unsigned char* tb = lds[cur][1] + (wn + lrp) * PITCH + lg * 16;
+#pragma unroll
+            for (int ks = 0; ks < NCH / 2; ++ks) {
+                uint4 fa[2], fb[2];
+#pragma unroll
+                for (int i = 0; i < 2; ++i) fa[i] = *reinterpret_cast<const uint4*>(ta + 32 * i * PITCH + ks * 32);
+#pragma unroll
+                for (int j = 0; j < 2; ++j) fb[j] = *reinterpret_cast<const uint4*>(tb + 32 * j * PITCH + ks * 32);
+#pragma unroll
+                for (int i = 0; i < 2; ++i)
+#pragma unroll
+                    for (int j = 0; j < 2; ++j) Mma32<T>::run(fb[j], fa[i], acc[i][j]);  // transposed tile
+            }
+            if (full) {
+                A.template store<false>(lds[cur ^ 1][0], ra, (kt + 1) * BK);
+                B.template store<false>(lds[cur ^ 1][1], rb, (kt + 1) * BK);
+            } else if (more) {
+                A.template store<true>(lds[cur ^ 1][0], ra, (kt + 1) * BK);
+                B.template store<true>(lds[cur ^ 1][1], rb, (kt + 1) * BK);
+            }
+            __syncthreads();
+        }
     }
-    gemm_epilogue(epi, acc, &lds[0][0][0], p, tm, g.tiles_m, r0, c0, g.crows, g.ccols);
+    if constexpr (SPLIT) {
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+#pragma unroll
+            for (int j = 0; j < 2; ++j) {
+                acc[i][j] += low[i][j];
+                if (any_nan(acc[i][j])) plain_products(A, B, r0 + wm + 32 * i + lr, c0 + wn + 32 * j + lr, kdim, acc[i][j]);
+            }
+        epilogue_f32(epi, acc, reinterpret_cast<float*>(&lds[0][0][0]), p, tm, g.tiles_m, r0 + wm, c0 + wn, g.crows, g.ccols);
+    } else {
+        gemm_epilogue(epi, acc, &lds[0][0][0], p, tm, g.tiles_m, r0, c0, g.crows, g.ccols);
+    }
 }
 
 // ---- bf16 grouped GEMM with direct-to-LDS loads ------------------------------------------------
@@ -1078,13 +1337,13 @@ __global__ __launch_bounds__(2 * TN, 2) void k_gemm_pers(GemmArgs<bf16_t, KA, KB
 // ---- fp32 weight gradients on 64 x 64 tiles ------------------------------------------------------------------------
 // k_grouped_gemm's products for dW where 128 x 128 tiles would multiply more padding (160 x 160 outputs: 64 blocks of 32 x 32
 // on four tiles, 36 on nine small ones; 32 x 32: 16 and 4).  A wave owns one block; the contraction (whole 32-index steps)
-// runs in the same order, so the sums keep their bits.  A step is sixteen contraction indices, two products' worth of work, so
+// runs in the same order, so the sums keep their bits.  A step is sixteen contraction indices, six products' worth of work, so
 // the operands of the next F32S_AHEAD steps are on their way in registers (one step ahead: 3.6 us more a launch for 10
 // preferences x 1850 rows x 160 x 160).
 #define F32S_AHEAD 4
 template <class Epi>
 __global__ __launch_bounds__(256) void k_gemm_f32_small(GemmArgs<float, SRC_KSTRIDED, SRC_KSTRIDED, Epi, true, GEMM_NCH> g) {
-    constexpr int PITCH = GEMM_NCH * 16 + 16;
+    constexpr int PITCH = gemm_pitch<float>(GEMM_NCH);
     __shared__ __align__(16) unsigned char lds[2][2][64 * PITCH];
     const int id = xcd_remap(blockIdx.x, gridDim.x);
     const int per_p = g.tiles_m * g.tiles_n;
@@ -1095,7 +1354,6 @@ __global__ __launch_bounds__(256) void k_gemm_f32_small(GemmArgs<float, SRC_KSTR
     const int r0 = tm * 64, c0 = tn * 64;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, lr = lane & 31, lg = lane >> 5;
     const int wm = (wave >> 1) * 32, wn = (wave & 1) * 32;
-    const int lrp = (lr & 0x13) | ((lr & 4) << 1) | ((lr & 8) >> 1);
     // a thread stages contraction indices 4 wave .. + 3 of row `lane` of either operand (rows past the end: the last one)
     const float* A = g.a_base(grp) + (int64_t)(4 * wave) * g.a.ld + (r0 + lane < g.a.rows ? r0 + lane : g.a.rows - 1);
     const float* B = g.b_base(grp) + (int64_t)(4 * wave) * g.b.ld + (c0 + lane < g.b.rows ? c0 + lane : g.b.rows - 1);
@@ -1110,12 +1368,12 @@ __global__ __launch_bounds__(256) void k_gemm_f32_small(GemmArgs<float, SRC_KSTR
         }
     };
     auto store = [&](int slot, int buf) {
-        *reinterpret_cast<float4*>(lds[buf][0] + lane * PITCH + wave * 16) = make_float4(ra[slot][0], ra[slot][1], ra[slot][2], ra[slot][3]);
-        *reinterpret_cast<float4*>(lds[buf][1] + lane * PITCH + wave * 16) = make_float4(rb[slot][0], rb[slot][1], rb[slot][2], rb[slot][3]);
+        put_chunk<float, GEMM_NCH>(lds[buf][0], lane, wave, __builtin_bit_cast(uint4, make_float4(ra[slot][0], ra[slot][1], ra[slot][2], ra[slot][3])));
+        put_chunk<float, GEMM_NCH>(lds[buf][1], lane, wave, __builtin_bit_cast(uint4, make_float4(rb[slot][0], rb[slot][1], rb[slot][2], rb[slot][3])));
     };
-    float16_t acc;
+    float16_t acc[1][1], low;
 #pragma unroll
-    for (int e = 0; e < 16; ++e) acc[e] = 0.f;
+    for (int e = 0; e < 16; ++e) acc[0][0][e] = low[e] = 0.f;
 #pragma unroll
     for (int u = 0; u < F32S_AHEAD; ++u) load(u, u);
     store(0, 0);
@@ -1129,24 +1387,26 @@ __global__ __launch_bounds__(256) void k_gemm_f32_small(GemmArgs<float, SRC_KSTR
             store(nxt, cur ^ 1);  // (its readers passed the barrier of the step before)
             load(nxt, kt + 1 + F32S_AHEAD);
             const unsigned char* ta = lds[cur][0] + (wm + lr) * PITCH + lg * 16;
-            const unsigned char* tb = lds[cur][1] + (wn + lrp) * PITCH + lg * 16;
+            const unsigned char* tb = lds[cur][1] + (wn + lr) * PITCH + lg * 16;
+            uint4 fa[3], fb[3];
 #pragma unroll
-            for (int ks = 0; ks < GEMM_NCH / 2; ++ks)
-                Mma32<float>::run(*reinterpret_cast<const uint4*>(tb + ks * 32), *reinterpret_cast<const uint4*>(ta + ks * 32), acc);
+            for (int q = 0; q < 3; ++q) {
+                fa[q] = *reinterpret_cast<const uint4*>(ta + q * 32);
+                fb[q] = *reinterpret_cast<const uint4*>(tb + q * 32);
+            }
+#pragma unroll
+            for (int t = 0; t < 6; ++t) split_mma(t, fa, fb, acc[0][0], low);
             __syncthreads();
         }
     }
-    const int r = r0 + wm + lr;
-#pragma unroll
-    for (int h = 0; h < 2; ++h) {
-        const int c = c0 + wn + 16 * h + 8 * lg;
-        float v[8];
-#pragma unroll
-        for (int u = 0; u < 8; ++u) v[u] = acc[8 * h + u];
-        typename Epi::Out o;
-        epi.compute(r, c, 8, v, o);
-        if (r < g.crows && c < g.ccols) epi.flush(r, c, (g.ccols - c < 8) ? (g.ccols - c) : 8, o);
+    acc[0][0] += low;
+    if (any_nan(acc[0][0])) {
+        Operand<float, SRC_KSTRIDED, true, GEMM_NCH> a = g.a, b = g.b;
+        a.base = g.a_base(grp); b.base = g.b_base(grp);
+        a.kdim = b.kdim = grp.kdim;
+        plain_products(a, b, r0 + wm + lr, c0 + wn + lr, grp.kdim, acc[0][0]);
     }
+    epilogue_f32(epi, acc, nullptr, p, tm, g.tiles_m, r0 + wm, c0 + wn, g.crows, g.ccols);
 }
 
 // ---- bf16 weight gradients with few tiles: 64 x 64 outputs a workgroup --------------------------------------------
