@@ -53,6 +53,7 @@ struct FwdArgs {
     FwdNet net;
     int32_t L, O, W, act;
     int32_t perm, narrow;  // bf16: contraction order, first layer by multiply-adds (see above)
+    int32_t split;         // fp32: 32-row blocks of a tile of fused_fwd_split.h, 0: tiles of this file's kernel
     int32_t Mp, ldh, ldx;  // saving: rows per preference and row lengths of the compact buffers
     int64_t lstride;       // bytes
 };

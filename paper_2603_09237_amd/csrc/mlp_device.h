@@ -67,6 +67,13 @@ __device__ inline void split3(const uint4& u, uint2 part[3]) {
         }
     }
 }
+__device__ inline void split3(const float (&v)[8], uint4 (&part)[3]) {
+    uint2 lo[3], hi[3];
+    split3(make_uint4(__float_as_uint(v[0]), __float_as_uint(v[1]), __float_as_uint(v[2]), __float_as_uint(v[3])), lo);
+    split3(make_uint4(__float_as_uint(v[4]), __float_as_uint(v[5]), __float_as_uint(v[6]), __float_as_uint(v[7])), hi);
+#pragma unroll
+    for (int q = 0; q < 3; ++q) part[q] = make_uint4(lo[q].x, lo[q].y, hi[q].x, hi[q].y);
+}
 // term t = 0 .. 5 of a product of split operands, smallest first
 __device__ inline void split_mma(int t, const uint4 (&a)[3], const uint4 (&b)[3], float16_t& acc, float16_t& low) {
     const int i = t == 0 ? 0 : t == 1 ? 2 : t == 2 ? 1 : t == 3 ? 0 : t == 4 ? 1 : 0;

@@ -74,3 +74,45 @@ def test_accepted_networks_are_read_inside_their_matrices(tmp_path):
     # refused: one hidden layer of width 16, 32 or 48 and 3, 1 or 1 outputs at most (bf16), of width 16 and 1 output (fp32)
     refused = int(r.stdout.split("refused")[1])
     assert refused == (3 + 1 + 1 + 1) * 17, r.stdout
+
+
+# The same for fp32 networks on split operands (csrc/fused_fwd_split.h): request b of lane l = sixteen bytes of row 8 b + (l >> 3)
+# of a wave's 32 features, whole super-steps of 32 elements to the end of the waves' features.
+SPLIT_PROGRAM = r"""
+#include <cstdio>
+#include "fwd_shape.h"
+int main() {
+    const int Os[] = {1, 2, 8, 11, 31, 32, 33, 63, 64, 65, 100, 127, 128, 129, 300, 513, 1024};
+    long n = 0, wrong = 0;
+    for (int W = 16; W <= kSplitMaxWidth; W += 16)
+        for (int L = 1; L <= 8; ++L)
+            for (int O : Os)
+                for (int out = 1; out <= 16; ++out) {
+                    if (!fwd_reads_inside(4, W, L, out)) continue;
+                    const int nw = split_waves(W);
+                    const long mat_len = (long)W * O + (long)(L - 1) * W * W + (long)out * W;
+                    long last = (long)(W - 1) * O + (O + 31) / 32 * 32 - 1;                     // first layer
+                    if (L > 1) last = (long)W * O + (long)(L - 2) * W * W + (long)(W - 1) * W + 32 * nw - 1;
+                    if (L > 1 && (long)(W - 1) * O + (O + 31) / 32 * 32 - 1 > last) last = (long)(W - 1) * O + (O + 31) / 32 * 32 - 1;
+                    // the tile: chunks of sixteen bytes inside a row's pitch, whatever they are XORed with (3, 7 or 15)
+                    const int ks[] = {O, 32 * nw};
+                    for (int k : ks) {
+                        const int pitch = split_pitch(k), x = pitch == 64 ? 3 : (pitch & 128) ? 7 : 15;
+                        if (((((k + 31) / 32 * 4 - 1) | x) + 1) * 16 > pitch) ++wrong;
+                    }
+                    ++n;
+                    if (32 * nw < W || last >= mat_len) ++wrong;
+                }
+    printf("shapes %ld wrong %ld\n", n, wrong);
+    return wrong ? 1 : 0;
+}
+"""
+
+
+@pytest.mark.skipif(shutil.which("g++") is None, reason="needs a host compiler")
+def test_split_networks_are_read_inside_their_matrices(tmp_path):
+    src, exe = tmp_path / "walk.cpp", tmp_path / "walk"
+    src.write_text(SPLIT_PROGRAM)
+    subprocess.run(["g++", "-O2", "-std=c++17", "-I" + CSRC, str(src), "-o", str(exe)], check=True)
+    r = subprocess.run([str(exe)], capture_output=True, text=True)
+    assert r.returncode == 0, r.stdout

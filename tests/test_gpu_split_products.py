@@ -57,20 +57,25 @@ def inputs_of(cfg, torch, seed):
             torch.randn(1, cfg.N, out_dim(cfg, ACTOR), device="cuda", generator=g) / cfg.N)
 
 
-# (width, observation width, rows, hidden layers): tiles of 128 and of 64 with remainders, contractions that end inside a step
-# of 16, split and unsplit; a width that goes layer by layer, its first layer from aligned and from odd rows
-SHAPES = [(32, 9, 65, 2), (48, 33, 131, 2), (128, 45, 257, 3), (160, 100, 331, 2), (256, 19, 512, 3), (272, 37, 97, 2),
-          (528, 44, 129, 2), (528, 45, 40, 1)]
+# (preferences, width, observation width, rows, hidden layers): tiles of 128 and of 64 with remainders, contractions that end
+# inside a step of 16, split and unsplit; a width that goes layer by layer, its first layer from aligned and from odd rows
+SHAPES = [(3, 32, 9, 65, 2), (3, 48, 33, 131, 2), (3, 128, 45, 257, 3), (3, 160, 100, 331, 2), (3, 256, 19, 512, 3),
+          (3, 272, 37, 97, 2), (3, 528, 44, 129, 2), (3, 528, 45, 40, 1)]
+# the one-launch forward on split operands: every number of waves, tiles of 32, 64 and 96 rows with remainders, widths between two
+# multiples of 32, observations of one and of many super-steps
+SHAPES += [(24, 32, 9, 950, 2), (24, 48, 33, 2070, 2), (24, 64, 8, 2050, 3), (8, 80, 45, 525, 2), (8, 96, 12, 1100, 2),
+           (8, 128, 19, 1100, 2), (3, 144, 100, 33, 3), (10, 160, 20, 1850, 2), (8, 176, 130, 545, 2), (10, 192, 45, 1890, 2),
+           (8, 208, 65, 1090, 2), (8, 256, 27, 545, 2), (8, 256, 300, 1090, 2)]
 
 
-@pytest.mark.parametrize("W,O,M,L", SHAPES)
+@pytest.mark.parametrize("P,W,O,M,L", SHAPES)
 @pytest.mark.parametrize("act", (0, 1))
-def test_fp32_networks_against_64_bits(W, O, M, L, act, torch, binding):  # noqa: F811
+def test_fp32_networks_against_64_bits(P, W, O, M, L, act, torch, binding):  # noqa: F811
     """Error of a whole tensor, 2-norm over 2-norm, in roundings of fp32 (2^-24).  The running sums of k products each take a
     rounding on average half as large as the sum's share of them: sqrt(k) / 4 in all; an activation, its derivative and the
     product with it three more; the 2 L + 1 products an output gradient goes through add up independently.  A product of
     parts left out shows: 3.5e-6 for a missing middle one."""
-    cfg = scaled(BASE, name=f"split-W{W}-O{O}-M{M}-L{L}", width=W, obs_dim=O, n_hidden=L, act=act, P=3, N=3 * M)
+    cfg = scaled(BASE, name=f"split-P{P}-W{W}-O{O}-M{M}-L{L}", width=W, obs_dim=O, n_hidden=L, act=act, P=P, N=P * M)
     ctx = binding.Context.from_config(cfg)
     tm, tv = make_theta(cfg, ctx, ACTOR, torch, 11)
     x, dout = inputs_of(cfg, torch, 12)
