@@ -471,7 +471,10 @@ __global__ __launch_bounds__(256) void k_hyper_base(NetDev nd, AffineTable at, B
 // and A^T by columns 16 w .. of the tile (dB, accumulated over all row blocks in registers).
 // dW0, which reads the same matrices, runs in blocks spread evenly among these: it is bound by memory, dA / dB by its
 // products (128 preferences of 4 x 512, rank 16: 87 us behind 133 as launches of their own, together 182; 24 of 3 x 256: 5.6
-// + 18 and 22.4).
+// + 18 and 22.4).  Both go through the layers in order, all preferences of one before the next: what either reads first the
+// other finds in the memory-side cache (128 matrices of 512 x 512 are 134 of its 256 MB).  Preference by preference 183 us for
+// the 128, layer by layer 165; 22.5 and 19 for the 24, 25 and 22 for 32 of 3 x 256, rank 8.  (A wave on sixteen rows by itself,
+// operands four columns a lane, no barrier: 181 and 19.7.)
 struct DabWork {
     int32_t n;
     int16_t layer[DAB_MAX_CS * MORLAX_MAX_LAYERS];
@@ -491,7 +494,7 @@ __global__ __launch_bounds__(256) void k_hyper_dAB(NetDev nd, DabWork wk, Affine
         base_block(nd, at, bw, dmat, P, (int)before);
         return;
     }
-    const int dab = blockIdx.x - (int)before, p = dab / wk.n, item = dab % wk.n;
+    const int dab = blockIdx.x - (int)before, p = dab % P, item = dab / P;
     const LayerDev L = nd.layer[wk.layer[item]];
     const int cs = wk.cs[item];
     const int c_lo = cs * DAB_COLS;
