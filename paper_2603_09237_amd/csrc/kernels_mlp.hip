@@ -487,10 +487,11 @@ __device__ inline void gemm_epilogue(const Epi& epi, float16_t (&acc)[2][2], uns
     }
 }
 
-// ---- epilogue of the fp32 products.  Their operands are not swapped: lane (lr, lg) of a 32 x 32 block holds column lr of the rows
+// ---- epilogue of the fp32 products, and of fp32 results of bf16 ones.  Their operands are not swapped: lane (lr, lg) of a 32 x 32 block holds column lr of the rows
 // 8 (e / 4) + 4 lg + e % 4, so that an access of a wave is two whole 128-byte lines.  (As above, a row and eight columns a lane:
 // 64 pieces of 16 bytes an access.  16 preferences x 8192 rows x 256 x 256, dX, which loads act' and stores dZ: 144 us, of which
-// 60 were the epilogue's.)  Rows and columns beyond the edge fall to the buffer descriptors' bounds: their loads give zero,
+// 60 were the epilogue's.  dW of bf16 operands, us a launch: 128 preferences x 2048 x 512 x 512 174.5 -> 166.5, 32 x 8192 x 256 x 256
+// 65 -> 63, 24 x 1250 x 256 x 256 15.1 -> 14.4.)  Rows and columns beyond the edge fall to the buffer descriptors' bounds: their loads give zero,
 // their stores do nothing.
 struct TileF32 {
     uint32_t at;   // byte offset of the lane's element of row 0 of the block; beyond every tensor where its column is
@@ -909,11 +910,12 @@ __global__ __launch_bounds__(256) void k_gemm_dma(GemmArgs<bf16_t, KA, KB, Epi, 
     const int r0 = tm * BM, c0 = tn * BN;
     const int wave = threadIdx.x >> 6;
     const int wm = (wave >> 1) * 64, wn = (wave & 1) * 64;
+    constexpr bool LINES = std::is_same<Epi, EpiDw>::value;  // fp32 results: stored as whole lines (epilogue_f32)
     DmaOperand<KA> A;
     DmaOperand<KB> B;
     const auto grp = g.group(p);
     A.init(g.a_base(grp), (int)g.a.ld, g.a.rows, r0, wm, false);
-    B.init(g.b_base(grp), (int)g.b.ld, g.b.rows, c0, wn, true);
+    B.init(g.b_base(grp), (int)g.b.ld, g.b.rows, c0, wn, !LINES);
 
     float16_t acc[2][2];
 #pragma unroll
@@ -955,11 +957,18 @@ __global__ __launch_bounds__(256) void k_gemm_dma(GemmArgs<bf16_t, KA, KB, Epi, 
 #pragma unroll
             for (int i = 0; i < 2; ++i)
 #pragma unroll
-                for (int j = 0; j < 2; ++j) Mma32<bf16_t>::run(fb[j], fa[i], acc[i][j]);  // transposed tile
+                for (int j = 0; j < 2; ++j) {
+                    if (LINES) Mma32<bf16_t>::run(fa[i], fb[j], acc[i][j]);
+                    else Mma32<bf16_t>::run(fb[j], fa[i], acc[i][j]);  // transposed tile
+                }
         }
     }
-    __syncthreads();
-    gemm_epilogue(epi, acc, dlds, p, tm, g.tiles_m, r0, c0, g.crows, g.ccols);
+    if constexpr (LINES) {
+        epilogue_f32(epi, acc, nullptr, p, tm, g.tiles_m, r0 + wm, c0 + wn, g.crows, g.ccols);
+    } else {
+        __syncthreads();
+        gemm_epilogue(epi, acc, dlds, p, tm, g.tiles_m, r0, c0, g.crows, g.ccols);
+    }
 }
 
 // ---- persistent bf16 grouped GEMM, 256 x TN tiles -----------------------------------------------
@@ -1212,6 +1221,7 @@ __device__ inline void tile_epilogue(const Epi& epi, float16_t (&acc)[MB][2], un
 template <int KA, int KB, class Epi, int TN>
 __global__ __launch_bounds__(2 * TN, 2) void k_gemm_pers(GemmArgs<bf16_t, KA, KB, Epi, true, GEMM_NCH> g, int n_tiles) {
     typedef PgShape<TN> S;
+    constexpr bool LINES = std::is_same<Epi, EpiDw>::value;  // fp32 results: stored as whole lines (epilogue_f32)
     extern __shared__ __align__(16) unsigned char dlds[];
     const int wave = threadIdx.x >> 6;
     const int wm = (wave / (TN / 64)) * 128, wn = (wave % (TN / 64)) * 64;
@@ -1221,7 +1231,7 @@ __global__ __launch_bounds__(2 * TN, 2) void k_gemm_pers(GemmArgs<bf16_t, KA, KB
     DmaTile<KA, PG_TM, 4, S::kWaves> A;
     DmaTile<KB, TN, 2, S::kWaves> B;
     A.set_lane(wm, false);
-    B.set_lane(wn, true);
+    B.set_lane(wn, !LINES);
 
     // tile ids of this workgroup: blockIdx.x, + gridDim.x, ...; the XCD remap keeps the tiles that the
     // workgroups of one XCD work on at the same time next to each other (same preference, same W(p))
@@ -1311,7 +1321,10 @@ __global__ __launch_bounds__(2 * TN, 2) void k_gemm_pers(GemmArgs<bf16_t, KA, KB
 #pragma unroll
                 for (int i = 0; i < 4; ++i)
 #pragma unroll
-                    for (int j = 0; j < 2; ++j) Mma32<bf16_t>::run(fb[ks][j], fa[ks][i], acc[i][j]);  // transposed tile
+                    for (int j = 0; j < 2; ++j) {
+                        if (LINES) Mma32<bf16_t>::run(fa[ks][i], fb[ks][j], acc[i][j]);
+                        else Mma32<bf16_t>::run(fb[ks][j], fa[ks][i], acc[i][j]);  // transposed tile
+                    }
             constexpr int kReads = ((KA == SRC_KCONTIG) ? 8 : 16) + ((KB == SRC_KCONTIG) ? 4 : 8);
             __builtin_amdgcn_sched_group_barrier(0x100, kReads, 0);  // LDS reads
             __builtin_amdgcn_sched_group_barrier(0x008, 16, 0);      // MFMAs
@@ -1327,7 +1340,10 @@ __global__ __launch_bounds__(2 * TN, 2) void k_gemm_pers(GemmArgs<bf16_t, KA, KB
             locate(vid, p, tm, tn);
             request(p, tm, tn);  // stages 0 and 1; the epilogue below stages its stores in the third
         }
-        tile_epilogue<Epi, 4, TN>(epi, acc, dlds + (PG_NST - 1) * S::kStage, lds_bias,
+        if constexpr (LINES)
+            epilogue_f32(epi, acc, nullptr, pc, tmc, g.tiles_m, tmc * PG_TM + wm, tnc * TN + wn, g.crows, g.ccols);
+        else
+            tile_epilogue<Epi, 4, TN>(epi, acc, dlds + (PG_NST - 1) * S::kStage, lds_bias,
                                   reinterpret_cast<float*>(dlds + S::kLds), first, pc, tmc, g.tiles_m, tmc * PG_TM, tnc * TN,
                                   g.crows, g.ccols, wm, wn);
         if (!more) break;
@@ -1428,13 +1444,13 @@ __global__ __launch_bounds__(256) void k_gemm_small(GemmArgs<bf16_t, SRC_KSTRIDE
     const int wave = threadIdx.x >> 6, wm = (wave >> 1) * 32, wn = (wave & 1) * 32;
     DmaTile<SRC_KSTRIDED, 64, 1, 4> A, B;
     A.set_lane(wm, false);
-    B.set_lane(wn, true);
+    B.set_lane(wn, false);
     const auto grp = g.group(p);
     A.set_tile(g.a_base(grp), (int)g.a.ld, g.a.rows, r0);
     B.set_tile(g.b_base(grp), (int)g.b.ld, g.b.rows, c0);
-    float16_t acc;
+    float16_t acc[1][1];
 #pragma unroll
-    for (int e = 0; e < 16; ++e) acc[e] = 0.f;
+    for (int e = 0; e < 16; ++e) acc[0][0][e] = 0.f;
     const int nk = grp.kdim / 32;
     const uint32_t lbase = (uint32_t)(size_t)dlds;
     auto issue = [&](int kt) {
@@ -1461,19 +1477,9 @@ __global__ __launch_bounds__(256) void k_gemm_small(GemmArgs<bf16_t, SRC_KSTRIDE
             fb[ks] = B.frag(ta + SG_STAGE / 2, 0, ks);
         }
 #pragma unroll
-        for (int ks = 0; ks < 2; ++ks) Mma32<bf16_t>::run(fb[ks], fa[ks], acc);  // transposed tile
+        for (int ks = 0; ks < 2; ++ks) Mma32<bf16_t>::run(fa[ks], fb[ks], acc[0][0]);
     }
-    const int lr = threadIdx.x & 31, lg = (threadIdx.x & 63) >> 5, r = r0 + wm + lr;
-#pragma unroll
-    for (int h = 0; h < 2; ++h) {
-        const int c = c0 + wn + 16 * h + 8 * lg;
-        float v[8];
-#pragma unroll
-        for (int u = 0; u < 8; ++u) v[u] = acc[8 * h + u];
-        typename Epi::Out o;
-        epi.compute(r, c, 8, v, o);
-        if (r < g.crows && c < g.ccols) epi.flush(r, c, (g.ccols - c < 8) ? (g.ccols - c) : 8, o);
-    }
+    epilogue_f32(epi, acc, nullptr, p, tm, g.tiles_m, r0 + wm, c0 + wn, g.crows, g.ccols);
 }
 
 // ---- fused forward: observations -> every hidden layer -> output layer (bf16, width 512 or 256) -------
