@@ -899,6 +899,107 @@ struct DmaOperand {
     }
 };
 
+// Epilogue of dX (bf16) on tiles of 64 MB x 64 STRIPS.  The derivatives of a 32-row block (32 x 64 codes, 4 KB a wave) come by
+// direct-to-LDS loads of whole 128-byte row segments, two blocks ahead: fetched into registers as a lane needs them, 16 bytes of each of 64 rows a
+// request, the vector cache looks up four times as many addresses.  Two patches a wave, `even` and `odd`, take a block's
+// derivatives and then its results, which leave as whole row segments as well.  Requested so far: block 0 into `even`, behind
+// it `behind` loads of the next tile's first stages.  us a launch, as it was and so: 128 preferences x 2048 x 512 x 512 232 and
+// 219, 64 x 4096 x 512 x 512 257 and 232, 32 x 8192 x 256 x 256 93 and 82; on 128 x 128 tiles 24 x 1250 x 256 x 256 15.8 and 13.6.
+struct DxBlocks {
+    const char* G;  // of the preference
+    int rows, ld2, row0;
+    uint32_t col;
+    // (r, c): the wave's first row and column.  Rows and columns beyond the edge repeat the last row, column 0 (their results are
+    // not stored)
+    __device__ inline DxBlocks(const EpiDx<bf16_t>& epi, int r, int c, int rows_, int cols) {
+        const int lane = threadIdx.x & 63;
+        G = reinterpret_cast<const char*>(epi.G);
+        rows = rows_; ld2 = epi.ld * 2;
+        row0 = r + (lane >> 3);
+        const int cc = c + 8 * ((lane & 7) ^ (lane >> 3));  // piece c of row q of a block lies at c ^ (q & 7)
+        col = (uint32_t)(cc < cols ? cc : 0) * 2u;
+    }
+    __device__ inline void request(int i, const unsigned char* patch) const {
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const int r = row0 + 32 * i + 8 * j;
+            dma16(G, (uint32_t)((r < rows ? r : rows - 1) * ld2) + col,
+                  __builtin_amdgcn_readfirstlane((uint32_t)(size_t)patch + (uint32_t)j * 1024u));
+        }
+    }
+};
+template <int MB, int STRIPS>
+__device__ inline void dx_epilogue(const EpiDx<bf16_t>& epi, const DxBlocks& blocks, float16_t (&acc)[MB][2], unsigned char* even,
+                                   unsigned char* odd, float* red, int behind, int p, int tm, int tiles_m, int r0, int c0, int rows, int cols,
+                                   int wm, int wn) {
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, lr = lane & 31, lg = lane >> 5;
+    // a tile inside the matrix stores four times a block, so that the loads behind the ones waited for can be counted
+    const bool inside = r0 + 64 * MB <= rows && c0 + 64 * STRIPS <= cols;
+    blocks.request(1, odd);
+    float cs[32];
+    char* base = reinterpret_cast<char*>(epi.dZ);
+#pragma unroll
+    for (int i = 0; i < MB; ++i) {
+        unsigned char* patch = (i & 1) ? odd : even;
+        if (!inside) wait_vm<0>();
+        else if (i == 0) {  // behind block 0: the next tile's first stages, block 1
+            if (behind == 8) wait_vm<12>();
+            else if (behind == 0) wait_vm<4>();
+            else wait_vm<0>();
+        } else if (i + 1 < MB) wait_vm<8>();  // the stores of the block before, the loads of the block after
+        else wait_vm<4>();
+        const int r = r0 + wm + 32 * i + lr;
+        uint4 gq[4];
+#pragma unroll
+        for (int o = 0; o < 4; ++o)
+            gq[o] = *reinterpret_cast<const uint4*>(patch + lr * 128 + (((2 * o + lg) ^ (lr & 7)) * 16));
+        typename EpiDx<bf16_t>::Out out[4];
+#pragma unroll
+        for (int o = 0; o < 4; ++o) {
+            const bool ok = inside || ((r < rows) && (c0 + wn + 16 * o + 8 * lg < cols));
+            float v[8];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) v[u] = acc[i][o >> 1][8 * (o & 1) + u];
+            epi.compute_fetched(gq[o], v, out[o]);
+#pragma unroll
+            for (int u = 0; u < 8; ++u) cs[8 * o + u] = (i == 0 ? 0.f : cs[8 * o + u]) + (ok ? v[u] : 0.f);
+        }
+#pragma unroll
+        for (int o = 0; o < 4; ++o) *reinterpret_cast<uint4*>(patch + lr * 128 + (((2 * o + lg) ^ (lr & 7)) * 16)) = out[o].d.lo;
+        __builtin_amdgcn_wave_barrier();
+        uint4 q[4];
+#pragma unroll
+        for (int it = 0; it < 4; ++it) {
+            const int prow = it * 8 + (lane >> 3), pc = lane & 7;
+            q[it] = *reinterpret_cast<const uint4*>(patch + prow * 128 + ((pc ^ (prow & 7)) * 16));
+        }
+#pragma unroll
+        for (int it = 0; it < 4; ++it) {
+            const int gr = r0 + wm + 32 * i + it * 8 + (lane >> 3), gc = c0 + wn + (lane & 7) * 8;
+            if (inside || (gr < rows && gc < cols)) *reinterpret_cast<uint4*>(base + ((int64_t)gr * epi.ld + gc) * 2) = q[it];
+        }
+        __builtin_amdgcn_wave_barrier();
+        // (the stores hold what was read from the patch, so it is free)
+        if (i + 2 < MB) blocks.request(i + 2, patch);
+    }
+    // column sums, as in tile_epilogue
+    fold_slots<16>(cs, lr);
+    fold_slots<8>(cs, lr);
+    fold_slots<4>(cs, lr);
+    fold_slots<2>(cs, lr);
+    fold_slots<1>(cs, lr);
+    {
+        const int j = lr >> 4, h = (lr >> 3) & 1, u = lr & 7;
+        red[wave * 64 + 32 * j + 16 * h + 8 * lg + u] = cs[0];
+    }
+    __syncthreads();
+    if (threadIdx.x < 64 * STRIPS) {  // the two waves of a 64-column strip: wave ids s and s + STRIPS
+        const int strip = threadIdx.x >> 6, col = threadIdx.x & 63;
+        const float v = red[strip * 64 + col] + red[(STRIPS + strip) * 64 + col];
+        if (c0 + threadIdx.x < cols) epi.part[((int64_t)p * tiles_m + tm) * epi.ld + c0 + threadIdx.x] = v;
+    }
+}
+
 template <int KA, int KB, class Epi>
 __global__ __launch_bounds__(256) void k_gemm_dma(GemmArgs<bf16_t, KA, KB, Epi, true, GEMM_NCH> g) {
     extern __shared__ __align__(16) unsigned char dlds[];
@@ -910,6 +1011,7 @@ __global__ __launch_bounds__(256) void k_gemm_dma(GemmArgs<bf16_t, KA, KB, Epi, 
     const int r0 = tm * BM, c0 = tn * BN;
     const int wave = threadIdx.x >> 6;
     const int wm = (wave >> 1) * 64, wn = (wave & 1) * 64;
+    constexpr bool DX = std::is_same<Epi, EpiDx<bf16_t>>::value;
     constexpr bool LINES = std::is_same<Epi, EpiDw>::value;  // fp32 results: stored as whole lines (epilogue_f32)
     DmaOperand<KA> A;
     DmaOperand<KB> B;
@@ -945,6 +1047,10 @@ __global__ __launch_bounds__(256) void k_gemm_dma(GemmArgs<bf16_t, KA, KB, Epi, 
             A.issue(kt + DMA_NST - 1, tile);
             B.issue(kt + DMA_NST - 1, tile + 8192);
         }
+        if constexpr (DX) {  // the epilogue's first block, into a stage that nobody reads any more
+            if (kt == nk - 1)
+                DxBlocks(epi, r0 + wm, c0 + wn, g.crows, g.ccols).request(0, dlds + (nk % DMA_NST) * DMA_STAGE_BYTES + wave * 4096);
+        }
         const unsigned char* ta = dlds + (kt % DMA_NST) * DMA_STAGE_BYTES;
         const unsigned char* tb = ta + 8192;
 #pragma unroll
@@ -965,6 +1071,12 @@ __global__ __launch_bounds__(256) void k_gemm_dma(GemmArgs<bf16_t, KA, KB, Epi, 
     }
     if constexpr (LINES) {
         epilogue_f32(epi, acc, nullptr, p, tm, g.tiles_m, r0 + wm, c0 + wn, g.crows, g.ccols);
+    } else if constexpr (DX) {
+        // (the stages of steps nk - 4, nk - 3 and nk - 2, which every wave has left)
+        dx_epilogue<2, 2>(epi, DxBlocks(epi, r0 + wm, c0 + wn, g.crows, g.ccols), acc, dlds + (nk % DMA_NST) * DMA_STAGE_BYTES + wave * 4096,
+                          dlds + ((nk + 1) % DMA_NST) * DMA_STAGE_BYTES + wave * 4096,
+                          reinterpret_cast<float*>(dlds + ((nk + 2) % DMA_NST) * DMA_STAGE_BYTES), 0, p, tm, g.tiles_m, r0, c0, g.crows,
+                          g.ccols, wm, wn);
     } else {
         __syncthreads();
         gemm_epilogue(epi, acc, dlds, p, tm, g.tiles_m, r0, c0, g.crows, g.ccols);
@@ -1219,107 +1331,6 @@ __device__ inline void tile_epilogue(const Epi& epi, float16_t (&acc)[MB][2], un
 }
 
 template <class Epi, int TN> constexpr bool pg_dx() { return std::is_same<Epi, EpiDx<bf16_t>>::value && TN == 256; }
-// Epilogue of dX on 256 x 256 tiles.  The derivatives of a 32-row block (32 x 64 codes, 4 KB a wave) come by direct-to-LDS loads
-// of whole 128-byte row segments, two blocks ahead: fetched into registers as a lane needs them, 16 bytes of each of 64 rows a
-// request, the vector cache looks up four times as many addresses.  Two patches a wave, `even` and `odd`, take a block's
-// derivatives and then its results, which leave as whole row segments as well.  Requested so far: block 0 into `even`, behind
-// it `behind` loads of the next tile's first stages.  us a launch, as it was and so: 128 preferences x 2048 x 512 x 512 232 and
-// 219, 64 x 4096 x 512 x 512 257 and 232, 32 x 8192 x 256 x 256 93 and 82.
-struct DxBlocks {
-    const char* G;  // of the preference
-    int rows, ld2, row0;
-    uint32_t col;
-    // (r, c): the wave's first row and column.  Rows and columns beyond the edge repeat the last row, column 0 (their results are
-    // not stored)
-    __device__ inline DxBlocks(const EpiDx<bf16_t>& epi, int r, int c, int rows_, int cols) {
-        const int lane = threadIdx.x & 63;
-        G = reinterpret_cast<const char*>(epi.G);
-        rows = rows_; ld2 = epi.ld * 2;
-        row0 = r + (lane >> 3);
-        const int cc = c + 8 * ((lane & 7) ^ (lane >> 3));  // piece c of row q of a block lies at c ^ (q & 7)
-        col = (uint32_t)(cc < cols ? cc : 0) * 2u;
-    }
-    __device__ inline void request(int i, const unsigned char* patch) const {
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            const int r = row0 + 32 * i + 8 * j;
-            dma16(G, (uint32_t)((r < rows ? r : rows - 1) * ld2) + col,
-                  __builtin_amdgcn_readfirstlane((uint32_t)(size_t)patch + (uint32_t)j * 1024u));
-        }
-    }
-};
-template <int MB>
-__device__ inline void dx_epilogue(const EpiDx<bf16_t>& epi, const DxBlocks& blocks, float16_t (&acc)[MB][2], unsigned char* even,
-                                   unsigned char* odd, float* red, int behind, int p, int tm, int tiles_m, int r0, int c0, int rows, int cols,
-                                   int wm, int wn) {
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, lr = lane & 31, lg = lane >> 5;
-    // a tile inside the matrix stores four times a block, so that the loads behind the ones waited for can be counted
-    const bool inside = r0 + 32 * MB * 2 <= rows && c0 + 256 <= cols;
-    blocks.request(1, odd);
-    float cs[32];
-    char* base = reinterpret_cast<char*>(epi.dZ);
-#pragma unroll
-    for (int i = 0; i < MB; ++i) {
-        unsigned char* patch = (i & 1) ? odd : even;
-        if (!inside) wait_vm<0>();
-        else if (i == 0) {  // behind block 0: the next tile's first stages, block 1
-            if (behind == 8) wait_vm<12>();
-            else if (behind == 0) wait_vm<4>();
-            else wait_vm<0>();
-        } else if (i + 1 < MB) wait_vm<8>();  // the stores of the block before, the loads of the block after
-        else wait_vm<4>();
-        const int r = r0 + wm + 32 * i + lr;
-        uint4 gq[4];
-#pragma unroll
-        for (int o = 0; o < 4; ++o)
-            gq[o] = *reinterpret_cast<const uint4*>(patch + lr * 128 + (((2 * o + lg) ^ (lr & 7)) * 16));
-        typename EpiDx<bf16_t>::Out out[4];
-#pragma unroll
-        for (int o = 0; o < 4; ++o) {
-            const bool ok = inside || ((r < rows) && (c0 + wn + 16 * o + 8 * lg < cols));
-            float v[8];
-#pragma unroll
-            for (int u = 0; u < 8; ++u) v[u] = acc[i][o >> 1][8 * (o & 1) + u];
-            epi.compute_fetched(gq[o], v, out[o]);
-#pragma unroll
-            for (int u = 0; u < 8; ++u) cs[8 * o + u] = (i == 0 ? 0.f : cs[8 * o + u]) + (ok ? v[u] : 0.f);
-        }
-#pragma unroll
-        for (int o = 0; o < 4; ++o) *reinterpret_cast<uint4*>(patch + lr * 128 + (((2 * o + lg) ^ (lr & 7)) * 16)) = out[o].d.lo;
-        __builtin_amdgcn_wave_barrier();
-        uint4 q[4];
-#pragma unroll
-        for (int it = 0; it < 4; ++it) {
-            const int prow = it * 8 + (lane >> 3), pc = lane & 7;
-            q[it] = *reinterpret_cast<const uint4*>(patch + prow * 128 + ((pc ^ (prow & 7)) * 16));
-        }
-#pragma unroll
-        for (int it = 0; it < 4; ++it) {
-            const int gr = r0 + wm + 32 * i + it * 8 + (lane >> 3), gc = c0 + wn + (lane & 7) * 8;
-            if (inside || (gr < rows && gc < cols)) *reinterpret_cast<uint4*>(base + ((int64_t)gr * epi.ld + gc) * 2) = q[it];
-        }
-        __builtin_amdgcn_wave_barrier();
-        // (the stores hold what was read from the patch, so it is free)
-        if (i + 2 < MB) blocks.request(i + 2, patch);
-    }
-    // column sums, as in tile_epilogue
-    fold_slots<16>(cs, lr);
-    fold_slots<8>(cs, lr);
-    fold_slots<4>(cs, lr);
-    fold_slots<2>(cs, lr);
-    fold_slots<1>(cs, lr);
-    {
-        const int j = lr >> 4, h = (lr >> 3) & 1, u = lr & 7;
-        red[wave * 64 + 32 * j + 16 * h + 8 * lg + u] = cs[0];
-    }
-    __syncthreads();
-    if (threadIdx.x < 256) {  // the two waves of a 64-column strip: wave ids s and s + 4
-        const int strip = threadIdx.x >> 6, col = threadIdx.x & 63;
-        const float v = red[strip * 64 + col] + red[(4 + strip) * 64 + col];
-        if (c0 + threadIdx.x < cols) epi.part[((int64_t)p * tiles_m + tm) * epi.ld + c0 + threadIdx.x] = v;
-    }
-}
-
 template <int KA, int KB, class Epi, int TN>
 __global__ __launch_bounds__(2 * TN, 2) void k_gemm_pers(GemmArgs<bf16_t, KA, KB, Epi, true, GEMM_NCH> g, int n_tiles) {
     typedef PgShape<TN> S;
@@ -1453,7 +1464,7 @@ __global__ __launch_bounds__(2 * TN, 2) void k_gemm_pers(GemmArgs<bf16_t, KA, KB
         if constexpr (LINES)
             epilogue_f32(epi, acc, nullptr, pc, tmc, g.tiles_m, tmc * PG_TM + wm, tnc * TN + wn, g.crows, g.ccols);
         else if constexpr (DX)
-            dx_epilogue(epi, DxBlocks(epi, tmc * PG_TM + wm, tnc * TN + wn, g.crows, g.ccols), acc, dx_even,
+            dx_epilogue<4, 4>(epi, DxBlocks(epi, tmc * PG_TM + wm, tnc * TN + wn, g.crows, g.ccols), acc, dx_even,
                         dlds + (PG_NST - 1) * S::kStage + wave * 4096, reinterpret_cast<float*>(dlds + S::kLds),
                         more ? (nk < PG_NST - 1 ? nk : PG_NST - 1) * S::kLoads : 0, pc, tmc, g.tiles_m, tmc * PG_TM, tnc * TN, g.crows,
                         g.ccols, wm, wn);
