@@ -8,11 +8,40 @@ No arithmetic happens here.
 """
 from __future__ import annotations
 
+import threading
+
 import numpy as np
 
 from . import binding
 from .binding import ACTOR, CRITIC
 from .configs import Config, WDTYPE_BF16
+
+# Floating-point operations of one network's minibatch from which the two networks' chains run beside each other; up to two
+# hidden layers, whose chains are short, and above.  us, one stream and two: one minibatch of 4 preferences x 640 rows of 2 x 256
+# in bf16 (1.2e9) 277 and 294, 16 x 3200 of 2 x 128 (6.3e9) 434 and 368; four of 4 x 96 of 4 x 256 (4.8e8) 1230 and 1482, one of 4 x
+# 192 (9.6e8) 364 and 333, four of 4 x 96 of 3 x 512 (1.3e9) 1350 and 950
+OVERLAP_FLOPS_SHORT, OVERLAP_FLOPS = 3e9, 9e8
+
+_PAIRS = threading.local()
+
+
+def _pair(torch, device):
+    """The calling thread's two streams on a device and the three events that order them, made once and used by every step
+    the thread submits (an event stands for what its stream holds when it is recorded, so the next step may record it again).
+
+    Two streams made one after the other, and not the caller's and another: streams share a few hardware queues in turn,
+    and one in four made later shares the caller's (10 preferences of 2 x 160, fp32: 771 us beside it, 922 behind it)."""
+    pairs = _PAIRS.__dict__.setdefault("of", {})
+    if device not in pairs:
+        with torch.cuda.device(device):
+            streams = [torch.cuda.Stream() for _ in range(2)]
+            events = [torch.cuda.Event() for _ in range(3)]
+            for e in events:
+                for s in streams:
+                    e.record(s)
+                    s.wait_event(e)
+        pairs[device] = (streams, events)
+    return pairs[device]
 
 
 class UpdateStep:
@@ -22,7 +51,9 @@ class UpdateStep:
         after every minibatch (a true PPO update); None: gradients only, parameters stay fixed.
         side_hypernet: the hypernet calls (backward, optimiser step, the next minibatch's forward) run on a second
         stream next to the grouped GEMMs of the other network / the next minibatch; the GEMM chain stays on the
-        caller's stream.  two_streams: the older split, one stream per network family.
+        caller's stream.  two_streams: the older split, one stream per network family.  Neither: `run` gives either
+        network's calls a stream of its own where `overlap` says so (an attribute; False keeps every call on the caller's
+        stream).
         adv_norm: "scalar" = the scalarised advantage is normalised over the minibatch (inside the loss call);
         "per_objective" = every objective is standardised over the minibatch before scalarisation
         (scalarize_normalized, then the loss without further normalisation)."""
@@ -82,6 +113,15 @@ class UpdateStep:
         self.ws = self.wsn[ACTOR]
         self.streams = {net: torch.cuda.Stream(device=self.dev) for net in (ACTOR, CRITIC)} if two_streams else None
         self.side = torch.cuda.Stream(device=self.dev) if side_hypernet else None
+        # The two chains share nothing but the loss, and neither fills the chip by itself: one's launches, tails and waits for
+        # memory run beside the other's products.  (us, one stream and two: hopper 3 x 256 1798 and 1724, quadruped fp32 2604
+        # and 2525, 24 preferences of 3 x 256 with Adam 2636 and 2088, the largest 45800 and 44470.)  Handing over costs the
+        # host some 7 us each time, so a step that the host's submission bounds stays on one stream (tiny: 214 and 296).
+        rows_mb = P * T * (c.n_g // c.minibatches)
+        self.overlap = (6.0 * rows_mb * ctx.theta_mat_len(CRITIC) >=
+                        (OVERLAP_FLOPS_SHORT if c.n_hidden <= 2 else OVERLAP_FLOPS))
+        if self.overlap:
+            _pair(torch, torch.cuda.current_stream().device)   # (made here: a stream's first use takes the host half a millisecond)
         # a workspace per hypernetwork, touched by nothing but its forward and backward: the backward pass then
         # reads the trunk features and factors that the forward pass left there instead of computing them again
         self.hws = {net: torch.empty(ctx.workspace_bytes((0, 1, 0, 1)), dtype=torch.uint8, device=self.dev)
@@ -123,59 +163,60 @@ class UpdateStep:
     def rollout(self):
         c, ctx = self.cfg, self.ctx
 
-        def fwd(net, ws):
-            ctx.hypernet_fwd(net, self.hp_old[net], self.w, self.theta_mat[net], self.theta_vec[net], ws)
-            if net == ACTOR:
-                ctx.policy_fwd(ACTOR, self.theta_mat[ACTOR], self.theta_vec[ACTOR], self.obs, self.full_T, self.mu_old,
-                               eps=self.eps, act=self.act, logp=self.logp_old, saved=None, ws=ws)
-            else:
-                ctx.policy_fwd(CRITIC, self.theta_mat[CRITIC], self.theta_vec[CRITIC], self.obs, self.full_T1,
-                               self.v_roll, saved=None, ws=ws)
-
-        self._per_net(fwd)
+        self._per_net(self._rollout_net)
         ctx.vec_gae(self.rewards, self.v_roll, self.dones, self.w, c.gamma, c.lam, self.adv_vec, self.vtarg,
                     self.adv_s)
 
+    def _rollout_net(self, net, ws, stream=None):
+        ctx = self.ctx
+        ctx.hypernet_fwd(net, self.hp_old[net], self.w, self.theta_mat[net], self.theta_vec[net], ws, stream=stream)
+        if net == ACTOR:
+            ctx.policy_fwd(ACTOR, self.theta_mat[ACTOR], self.theta_vec[ACTOR], self.obs, self.full_T, self.mu_old,
+                           eps=self.eps, act=self.act, logp=self.logp_old, saved=None, ws=ws, stream=stream)
+        else:
+            ctx.policy_fwd(CRITIC, self.theta_mat[CRITIC], self.theta_vec[CRITIC], self.obs, self.full_T1,
+                           self.v_roll, saved=None, ws=ws, stream=stream)
+
+    def _forward_net(self, rows, net, ws, stream=None):
+        self.ctx.hypernet_fwd(net, self.hp[net], self.w, self.theta_mat[net], self.theta_vec[net], self.hws[net],
+                              stream=stream)
+        self.ctx.policy_fwd(net, self.theta_mat[net], self.theta_vec[net], self.obs, rows,
+                            self.mu if net == ACTOR else self.v, saved=self.saved[net], ws=ws, stream=stream)
+
+    def _backward_net(self, rows, net, ws, stream=None):
+        ctx, o = self.ctx, self.optimizer
+        ctx.policy_bwd(net, self.theta_mat[net], self.theta_vec[net], self.obs, rows, self.saved[net],
+                       self.dmu if net == ACTOR else self.dv, self.dlogsig if net == ACTOR else None,
+                       self.dtheta_mat[net], self.dtheta_vec[net], ws, stream=stream)
+        ctx.hypernet_bwd_kept(net, self.hp[net], self.w, self.dtheta_mat[net], self.dtheta_vec[net], self.dhp[net],
+                              self.hws[net], stream=stream)
+        if o is not None:
+            ctx.adam_step(net, self.hp[net], self.dhp[net], self.adam_m[net], self.adam_v[net],
+                          o["lr_actor"] if net == ACTOR else o["lr_critic"], o["beta1"], o["beta2"], o["eps"],
+                          self.opt_step, stream=stream)
+
     def minibatch(self, rows):
-        c, ctx = self.cfg, self.ctx
-        out = {ACTOR: self.mu, CRITIC: self.v}
-        dout = {ACTOR: self.dmu, CRITIC: self.dv}
-
-        def fwd(net, ws):
-            ctx.hypernet_fwd(net, self.hp[net], self.w, self.theta_mat[net], self.theta_vec[net], self.hws[net])
-            ctx.policy_fwd(net, self.theta_mat[net], self.theta_vec[net], self.obs, rows, out[net],
-                           saved=self.saved[net], ws=ws)
-
         if self.optimizer is not None:
             self.opt_step += 1
-        o = self.optimizer
+        self._per_net(lambda net, ws: self._forward_net(rows, net, ws))
+        self._loss(rows, self._logsig())
+        self._per_net(lambda net, ws: self._backward_net(rows, net, ws))
 
-        def bwd(net, ws):
-            ctx.policy_bwd(net, self.theta_mat[net], self.theta_vec[net], self.obs, rows, self.saved[net], dout[net],
-                           self.dlogsig if net == ACTOR else None, self.dtheta_mat[net], self.dtheta_vec[net], ws)
-            ctx.hypernet_bwd_kept(net, self.hp[net], self.w, self.dtheta_mat[net], self.dtheta_vec[net], self.dhp[net],
-                                  self.hws[net])
-            if o is not None:
-                ctx.adam_step(net, self.hp[net], self.dhp[net], self.adam_m[net], self.adam_v[net],
-                              o["lr_actor"] if net == ACTOR else o["lr_critic"], o["beta1"], o["beta2"], o["eps"],
-                              self.opt_step)
+    def _logsig(self):
+        return None if self.cfg.sigma_state else self.theta_vec[ACTOR].data_ptr() + 4 * self.logsig_off
 
-        self._per_net(fwd)
-        logsig = None if c.sigma_state else self.theta_vec[ACTOR].data_ptr() + 4 * self.logsig_off
-        self._loss(rows, logsig)
-        self._per_net(bwd)
-
-    def _loss(self, rows, logsig):
+    def _loss(self, rows, logsig, stream=None):
         c, ctx = self.cfg, self.ctx
         adv, norm = self.adv_s, 1
         if self.adv_norm == "per_objective":
-            ctx.scalarize_normalized(rows, self.adv_vec, self.w, self.adv_mb, self.ws)
+            ctx.scalarize_normalized(rows, self.adv_vec, self.w, self.adv_mb, self.ws, stream=stream)
             adv, norm = self.adv_mb, 0
         ctx.ppo_loss_grad(rows, self.mu, logsig, ctx.theta_vec_len(ACTOR), self.act, self.logp_old, adv,
-                          self.v, self.vtarg, c.clip_eps, norm, self.dmu, self.dlogsig, self.dv, self.stats, self.ws)
+                          self.v, self.vtarg, c.clip_eps, norm, self.dmu, self.dlogsig, self.dv, self.stats, self.ws,
+                          stream=stream)
 
     def capture(self):
-        """Record one whole update step into a HIP graph (the default one-stream schedule, no optimiser step: its step
+        """Record one whole update step into a HIP graph (the one-stream schedule, no optimiser step: its step
         counter is a host-side argument).  The few hundred launches of a step then cost one submission; what they
         compute is unchanged.  One eager step runs first, so that one-time set-up inside the library (function
         attributes, device queries) happens outside the capture.  Nothing in the step allocates or clears memory
@@ -199,12 +240,64 @@ class UpdateStep:
         """One whole update step.  `on_minibatch(e, b)` (optional) is called after each minibatch."""
         if self.side is not None:
             return self._run_side(on_minibatch)
+        # (a caller's own graph records the calls on the one stream it captures)
+        if self.overlap and self.streams is None and not self.torch.cuda.is_current_stream_capturing():
+            return self._run_beside(on_minibatch)
         self.rollout()
         for e in range(self.cfg.epochs):
             for b, rows in enumerate(self.mb_rows):
                 self.minibatch(rows)
                 if on_minibatch is not None:
                     on_minibatch(e, b)
+
+    def _run_beside(self, on_minibatch):
+        """The same calls, each network's on a stream of its own, the advantages and the loss on the actor's.  Both wait
+        for the caller's stream at the start (inputs, parameters), the caller's stream for both at the end.  In between
+        the critic's waits behind every loss (dv; v may be overwritten), the actor's for it ahead of the advantages
+        (v_roll) and of every loss (v).  Every buffer but those is one network's: its workspaces, theta, saved
+        activations, gradients, moments."""
+        t, c, ctx = self.torch, self.cfg, self.ctx
+        main = t.cuda.current_stream()
+        (actor, critic), (at_main, at_actor, at_critic) = _pair(t, main.device)
+        on = {ACTOR: actor.cuda_stream, CRITIC: critic.cuda_stream}
+
+        def wait(stream, event, of):    # what follows on `stream` waits for what `of` holds so far
+            event.record(of)
+            stream.wait_event(event)
+
+        def begin():
+            at_main.record(main)
+            actor.wait_event(at_main)
+            critic.wait_event(at_main)
+
+        def end():
+            wait(main, at_actor, actor)
+            wait(main, at_critic, critic)
+
+        begin()
+        try:
+            for net in (ACTOR, CRITIC):
+                self._rollout_net(net, self.wsn[net], on[net])
+            wait(actor, at_critic, critic)
+            ctx.vec_gae(self.rewards, self.v_roll, self.dones, self.w, c.gamma, c.lam, self.adv_vec, self.vtarg,
+                        self.adv_s, stream=on[ACTOR])
+            for e in range(c.epochs):
+                for b, rows in enumerate(self.mb_rows):
+                    if self.optimizer is not None:
+                        self.opt_step += 1
+                    for net in (ACTOR, CRITIC):
+                        self._forward_net(rows, net, self.wsn[net], on[net])
+                    wait(actor, at_critic, critic)
+                    self._loss(rows, self._logsig(), on[ACTOR])
+                    wait(critic, at_actor, actor)
+                    for net in (ACTOR, CRITIC):
+                        self._backward_net(rows, net, self.wsn[net], on[net])
+                    if on_minibatch is not None:
+                        end()
+                        on_minibatch(e, b)
+                        begin()
+        finally:
+            end()
 
     def _run_side(self, on_minibatch):
         """The same calls with the hypernet work of one network overlapping the grouped GEMMs of the other:

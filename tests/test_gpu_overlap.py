@@ -1,0 +1,71 @@
+"""The two networks' chains on streams of their own give the bits that one stream gives: gradients, updated parameters, roll-out
+and loss, step after step, from a caller's stream that is not the default one, with inputs that change in between."""
+import pytest
+
+from paper_2603_09237_amd import inputs
+from paper_2603_09237_amd.configs import CONFIGS, scaled
+from test_gpu_parity import RAGGED, _float32_default, binding, torch  # noqa: F401  (fixtures)
+
+pytestmark = pytest.mark.gpu
+
+ADAM = dict(lr_actor=3e-3, lr_critic=1e-2, beta1=0.9, beta2=0.999, eps=1e-8)
+CASES = [(scaled(CONFIGS[1], name="overlap-adam", minibatches=2, epochs=2), dict(optimizer=ADAM)),
+         (scaled(RAGGED, name="overlap-per-objective"), dict(adv_norm="per_objective", optimizer=ADAM)),
+         (scaled(CONFIGS[3], name="overlap-sigma-bf16", sigma_state=1, P=8, N=8 * 60, T=9, minibatches=3), dict(keep_adv_vec=True))]
+
+
+@pytest.mark.parametrize("cfg,kw", CASES, ids=lambda x: getattr(x, "name", ""))
+@pytest.mark.parametrize("callback", (False, True))
+def test_streams_of_their_own_give_the_same_bits(cfg, kw, callback, torch, binding):  # noqa: F811
+    from paper_2603_09237_amd.step import UpdateStep
+    d = inputs.make_all(cfg)
+    got = {}
+    for overlap in (False, True):
+        stream = torch.cuda.Stream()
+        with torch.cuda.stream(stream):
+            st = UpdateStep(cfg, **kw)
+            st.overlap = overlap
+            st.load_inputs(d)
+            out = []
+
+            def keep(*_):   # behind what the caller's stream holds, before anything it is given next
+                out.extend(t.clone() for n in (0, 1) for t in (st.dhp[n], st.hp[n], st.theta_vec[n]))
+                out.extend(t.clone() for t in (st.mu_old, st.act, st.logp_old, st.v_roll, st.vtarg, st.adv_s, st.mu, st.v, st.stats))
+
+            for i in range(3):
+                st.run(on_minibatch=keep if callback else None)
+                keep()
+                st.obs.mul_(0.9)
+                st.rewards.add_(0.125)
+                for n in (0, 1):
+                    st.hp_old[n].copy_(st.hp[n])
+        torch.cuda.synchronize()
+        got[overlap] = out
+    assert len(got[False]) == len(got[True])
+    wrong = [i for i, (a, b) in enumerate(zip(got[False], got[True])) if not torch.equal(a, b)]
+    print(f"[gpu-overlap] {cfg.name} callback={callback}: {len(got[True])} tensors, different {wrong[:5]}", flush=True)
+    assert not wrong
+
+
+def test_rule_and_capture_stay_on_the_callers_stream(torch, binding):  # noqa: F811
+    """A step bound by its submission stays on one stream; a caller's own graph records the one-stream schedule whatever
+    `overlap` says, and its replays equal the eager steps."""
+    from paper_2603_09237_amd.step import UpdateStep
+    assert not UpdateStep(CONFIGS[1]).overlap
+    cfg = scaled(CONFIGS[1], name="overlap-capture", minibatches=2)
+    st = UpdateStep(cfg)
+    st.load_inputs(inputs.make_all(cfg))
+    st.overlap = True
+    st.run()
+    torch.cuda.synchronize()
+    ref = [t.clone() for t in (st.dhp[0], st.dhp[1], st.stats)]
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g):
+        st.run()
+    for _ in range(3):
+        for n in (0, 1):
+            st.dhp[n].zero_()
+        g.replay()
+        torch.cuda.synchronize()
+        assert all(torch.equal(a, b) for a, b in zip(ref, (st.dhp[0], st.dhp[1], st.stats)))
+        st.run()
