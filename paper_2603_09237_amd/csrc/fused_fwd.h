@@ -21,7 +21,8 @@
 // bf16 products are 32x32x16 in the contraction order of the kernels that serve taller selections of the same network
 // (k_mlp_fused_fwd: `perm`, chunks jj and 4 + jj of a line together, bias first; the tiled GEMMs: ascending, bias last;
 // k_first_fwd_narrow: one fused multiply-add after the other), so that an output does not depend on how many rows are
-// asked for.  fp32 products are 16x16x4, whose smaller tiles reach more CUs.
+// asked for.  fp32 products are 16x16x4, whose smaller tiles reach more CUs; the launcher takes them while tiles are few
+// (fwd_row_tiles), else those of fused_fwd_split.h or the layer-by-layer GEMMs.
 #pragma once
 
 #include <atomic>

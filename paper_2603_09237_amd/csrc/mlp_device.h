@@ -39,15 +39,6 @@ template <> struct Mma32<bf16_t> {
                                                     0, 0, 0);
     }
 };
-template <> struct Mma32<float> {
-    static __device__ inline void run(const uint4& a, const uint4& b, float16_t& c) {
-        c = __builtin_amdgcn_mfma_f32_32x32x2f32(__uint_as_float(a.x), __uint_as_float(b.x), c, 0, 0, 0);
-        c = __builtin_amdgcn_mfma_f32_32x32x2f32(__uint_as_float(a.y), __uint_as_float(b.y), c, 0, 0, 0);
-        c = __builtin_amdgcn_mfma_f32_32x32x2f32(__uint_as_float(a.z), __uint_as_float(b.z), c, 0, 0, 0);
-        c = __builtin_amdgcn_mfma_f32_32x32x2f32(__uint_as_float(a.w), __uint_as_float(b.w), c, 0, 0, 0);
-    }
-};
-
 // An fp32 value as the sum of three bf16 values, each the nearest to what those before it leave: 24 bits exactly.  A product
 // of two such values is nine products of parts; the three smallest (2^-24 of it and less) are dropped, and the other six run on
 // the bf16 matrix instructions, sixteen times as fast as the fp32 ones.  Sums of the five smaller ones are kept apart from those
