@@ -22,7 +22,7 @@
 // (k_mlp_fused_fwd: `perm`, chunks jj and 4 + jj of a line together, bias first; the tiled GEMMs: ascending, bias last;
 // k_first_fwd_narrow: one fused multiply-add after the other), so that an output does not depend on how many rows are
 // asked for.  fp32 products are 16x16x4, whose smaller tiles reach more CUs; the launcher takes them while tiles are few
-// (fwd_row_tiles), else those of fused_fwd_split.h or the layer-by-layer GEMMs.
+// (fwd_plan), else those of fused_fwd_split.h or the layer-by-layer GEMMs.
 #pragma once
 
 #include <atomic>
@@ -559,7 +559,7 @@ template <typename T, bool SAVE, int NW>
 static void fwd_launch_rt(const FwdArgs& a, int rt, int n_tiles, hipStream_t s) {
     constexpr int LOW = fwd_low(sizeof(T));
     if constexpr (fwd_has_high(sizeof(T), NW)) {
-        if (rt == 2 * LOW) { fwd_launch<T, SAVE, NW, 2 * LOW>(a, n_tiles, s); return; }
+        if (fwd_compiled(sizeof(T), NW, rt) == 2 * LOW) { fwd_launch<T, SAVE, NW, 2 * LOW>(a, n_tiles, s); return; }
     }
     fwd_launch<T, SAVE, NW, LOW>(a, n_tiles, s);
 }

@@ -1,5 +1,5 @@
-// Shapes of the one-launch forward (fused_fwd.h): waves of a workgroup, LDS, and which networks it may read.  Plain C++,
-// so that the host test of the last one compiles it without a GPU toolchain.
+// Shapes of the one-launch forward (fused_fwd.h): waves of a workgroup, LDS, which networks it may read, and which tiles a
+// call takes.  Plain C++, so that the host tests of the last two compile it without a GPU toolchain.
 #pragma once
 
 #include <stdint.h>
@@ -7,10 +7,11 @@
 constexpr int kFwdMaxWidth = 512;
 constexpr int fwd_waves(int w) { return w <= 256 ? (w + 63) / 64 : w <= 384 ? 6 : 8; }
 
-// row tiles of 16 per workgroup: 1 in fp32 and 2 in bf16, and twice as many for bf16 networks of enough waves and for the fp32
-// networks that tiles of split operands (below) do not always serve
+// row tiles of 16 per workgroup: 1 in fp32 and 2 in bf16, and twice as many for bf16 networks of enough waves
 constexpr int fwd_low(int es) { return es == 4 ? 1 : 2; }
-constexpr bool fwd_has_high(int es, int nw) { return es == 4 ? nw == 2 : nw >= 3; }
+constexpr bool fwd_has_high(int es, int nw) { return es == 2 && nw >= 3; }
+// the row tiles of the kernel that runs where `rt` are asked for: the launch and its count of workgroups both take this
+constexpr int fwd_compiled(int es, int nw, int rt) { return fwd_has_high(es, nw) && rt == 2 * fwd_low(es) ? rt : fwd_low(es); }
 
 inline int fwd_lds_bytes(int es, int O, int W, int L, int rt) {
     const int nw = fwd_waves(W), pitch = (64 * nw * es + 255) / 256 * 256, pitch0 = (O * es + 255) / 256 * 256;
@@ -34,4 +35,64 @@ constexpr int split_most(int nw) { return nw <= 2 ? 1 : nw == 5 || nw == 6 ? 3 :
 inline int split_lds_bytes(int O, int W, int L, int rb) {
     const int nw = split_waves(W), p0 = split_pitch(O), p1 = split_pitch(32 * nw);
     return 3 * 32 * rb * (p0 > p1 ? p0 : p1) + nw * 4096 + L * 32 * nw * 4;
+}
+
+// The tiles of a one-launch forward of `rows` rows per preference: row tiles of 16 a workgroup (0: not this kernel, but the one
+// that multiplies four times the rows per fetched weight for tall selections of width 512 or 256, `tall_kernel`, or the
+// layer-by-layer GEMMs) and, on split operands, their 32-row blocks.  The lines are measured ones (saving variant, three hidden
+// layers, preferences x rows; us).
+struct FwdPlan { int rt, split; };
+inline FwdPlan fwd_plan(int es, int W, int L, int O, int out_dim, int P, int64_t rows, int cus, bool tall_kernel) {
+    const int nw = fwd_waves(W);
+    if (!fwd_reads_inside(es, W, L, out_dim)) return {0, 0};
+    auto tiles = [&](int r) { return (int64_t)P * ((rows + 16 * r - 1) / (16 * r)); };
+    auto fits = [&](int r) { return fwd_lds_bytes(es, O, W, L, r) <= 160 * 1024; };
+    if (!fits(fwd_low(es))) return {0, 0};
+    if (es == 2) {
+        // W 512: 64 x 512 107 tall, 137 here; 16 x 1024 (128 tall tiles) 72 and 59.  W 256: 64 x 1024 71 and 87, 64 x 512
+        // (256 tall tiles) 52 and 42
+        if ((W == 512 && tiles(8) >= 192) || (W == 256 && tiles(8) >= 384))
+            if (tall_kernel) return {0, 0};
+        if (nw == 8 && !tall_kernel && tiles(4) >= 512) return {0, 0};
+        if (nw == 6 && tiles(4) >= 512) return {0, 0};  // W 384: 64 x 700 141 and 145, 64 x 2048 327 and 408, 16 x 700 54 and 46
+        // tiles of 64 rows once 32 would leave more than two rounds of workgroups: W 512 16 x 1024 59 against 63, 64 x 128
+        // 59 against 38; W 144 64 x 700 55 against 63, 16 x 700 28 against 25; W 48 and 128 (2, 4 tiles at a time on a CU) never
+        return {fwd_has_high(2, nw) && tiles(2) >= (nw == 3 ? 1024 : 512) && fits(4) ? 4 : 2, 0};
+    }
+    if (W <= kSplitMaxWidth) {
+        // Tiles of 32, 64 or 96 rows on split operands (fused_fwd_split.h), of 16 on the fp32 instructions while there are too few
+        // for more than the length of one tile's chain to matter.  16 and 32 rows, plain / saving: W 256 16 x 128 24 / 26 and
+        // 24 / 27, 64 x 128 35 / 38 and 28 / 33; W 160 16 x 20 20 / 20 and 18 / 20; W 128 16 x 128 14 / 15.5 and 14 / 16, 64 x 128
+        // 20 / 23 and 14 / 18; W 64 64 x 128 11 / 13 and 11 / 13.4, 16 x 700 11.8 / 14.8 and 14.8 / 18.7, 16 x 2048 19 / 24 and 17 / 22;
+        // W 32 16 x 700 12.3 / 13.7 and 12.5 / 14.8, 16 x 2048 19 / 21 and 13 / 18
+        const int snw = split_waves(W);
+        auto fits_split = [&](int rb) { return rb <= split_most(snw) && split_lds_bytes(O, W, L, rb) <= 160 * 1024; };
+        // One hidden layer, whose products are few: W 128 10 x 1065 10.7 / 12.5 and 11.9 / 14.6, W 144 5 x 141 10.9 / 10.6 and 10.9 / 11.6;
+        // W 208 107 x 119 17 / 19 and 11 / 15
+        const int least_tiles = snw <= 2 || (L == 1 && snw <= 4) ? 704 : snw == 5 && L > 1 ? 0 : 128;
+        if (tiles(2) < least_tiles || !fits_split(1) || (snw == 2 && (tiles(2) < 1536 || O > 64))) {
+            if (snw == 2) return {1, 0};
+            return {tiles(1) < 1408 ? 1 : 0, 0};
+        }
+        int split = 1;
+        if (snw <= 2) return {2, 1};
+        // W 65 to 128, several tiles at a time on a CU, 32 and 64 rows: 16 x 300 14 / 17 and 17 / 22, 16 x 700 20 / 25 and 18 / 25,
+        // 64 x 2048 108 / 167 and 89 / 155
+        if (snw <= 4) split = tiles(2) > cus && fits_split(2) ? 2 : 1;
+        // above, one tile at a time on a CU: whichever takes fewest rounds of them, in the time one tile of 32, 64 or 96 rows
+        // takes (W 160 18, 24.5 and 34 us for three layers; W 256 24 and 34).  W 160, 32, 64 and 96 rows: 16 x 700 34, 24, 33; 10 x 1850
+        // 51, 48, 34; 10 x 3700 84, 71, 66; 16 x 2048 67, 47, 65; 64 x 2048 268, 189, 197
+        const int cost[] = {30, snw == 8 ? 43 : 41, 56};
+        int64_t least = INT64_MAX;
+        for (int rb = 1; rb <= 3 && snw > 4; ++rb) {
+            const int64_t c = (tiles(2 * rb) + cus - 1) / cus * cost[rb - 1];
+            if (fits_split(rb) && c < least) { split = rb; least = c; }
+        }
+        return {2 * split, split};
+    }
+    // wider ones, tiles of 16 rows while there is a CU for each: 16 rows and the layer-by-layer GEMMs, W 512 16 x 256 56 / 60 and
+    // 78 / 81, 64 x 128 109 / 118 and 87 / 93; W 384 64 x 64 43 / 47 and 65 / 68, 64 x 128 79 / 85 and 71 / 74; W 272 64 x 64
+    // 45 / 46 and 51 / 55, 16 x 700 117 / 123 and 75 / 77
+    // (one hidden layer: W 512 25 x 198 28 / 32 and 37 / 38)
+    return {tiles(1) <= (L == 1 ? 768 : 256) ? 1 : 0, 0};
 }

@@ -2967,72 +2967,13 @@ static void fill_fwd_net(const morlax_ctx* c, int net, const void* theta_mat, co
     n.H = H; n.G = G; n.x0 = x0;
 }
 
-// Row tiles of 16 per workgroup of the one-launch forward, `rows` rows per preference; 0: not this kernel (tall selections
-// of width 512 or 256 have one that multiplies four times the rows per fetched weight, other tall ones the layer-by-layer
-// GEMMs).  The lines are measured ones (saving variant, three hidden layers, preferences x rows; us).
-static int fwd_row_tiles(const morlax_ctx* c, const NetDev& nd, const void* theta_mat, int64_t rows, int& split) {
-    split = 0;
-    const int W = c->d.width, L = c->d.n_hidden, O = c->d.obs_dim, P = c->d.P, nw = fwd_waves(W);
-    const bool bf = c->d.wdtype == 1;
-    if (!fwd_reads_inside((int)esize(c), W, L, nd.out_dim)) return 0;
-    auto tiles = [&](int r) { return (int64_t)P * ((rows + 16 * r - 1) / (16 * r)); };
-    auto fits = [&](int r) { return fwd_lds_bytes(bf ? 2 : 4, O, W, L, r) <= 160 * 1024; };
-    if (!fits(bf ? 2 : 1)) return 0;
-    if (bf) {
-        // W 512: 64 x 512 107 tall, 137 here; 16 x 1024 (128 tall tiles) 72 and 59.  W 256: 64 x 1024 71 and 87, 64 x 512
-        // (256 tall tiles) 52 and 42
-        if ((W == 512 && tiles(8) >= 192) || (W == 256 && tiles(8) >= 384))
-            if (fused_fwd_ok(c, nd, theta_mat)) return 0;
-        if (nw == 8 && !fused_fwd_ok(c, nd, theta_mat) && tiles(4) >= 512) return 0;
-        if (nw == 6 && tiles(4) >= 512) return 0;  // W 384: 64 x 700 141 and 145, 64 x 2048 327 and 408, 16 x 700 54 and 46
-        // tiles of 64 rows once 32 would leave more than two rounds of workgroups: W 512 16 x 1024 59 against 63, 64 x 128
-        // 59 against 38; W 144 64 x 700 55 against 63, 16 x 700 28 against 25; W 48 and 128 (2, 4 tiles at a time on a CU) never
-        return fwd_has_high(2, nw) && tiles(2) >= (nw == 3 ? 1024 : 512) && fits(4) ? 4 : 2;
-    }
-    if (W <= kSplitMaxWidth) {
-        // Tiles of 32, 64 or 96 rows on split operands (fused_fwd_split.h), of 16 on the fp32 instructions while there are too few
-        // for more than the length of one tile's chain to matter.  16 and 32 rows, plain / saving: W 256 16 x 128 24 / 26 and
-        // 24 / 27, 64 x 128 35 / 38 and 28 / 33; W 160 16 x 20 20 / 20 and 18 / 20; W 128 16 x 128 14 / 15.5 and 14 / 16, 64 x 128
-        // 20 / 23 and 14 / 18; W 64 64 x 128 11 / 13 and 11 / 13.4, 16 x 700 11.8 / 14.8 and 14.8 / 18.7, 16 x 2048 19 / 24 and 17 / 22;
-        // W 32 16 x 700 12.3 / 13.7 and 12.5 / 14.8, 16 x 2048 19 / 21 and 13 / 18
-        const int snw = split_waves(W), cus = resident_slots() / 2;
-        auto fits_split = [&](int rb) { return rb <= split_most(snw) && split_lds_bytes(O, W, L, rb) <= 160 * 1024; };
-        // One hidden layer, whose products are few: W 128 10 x 1065 10.7 / 12.5 and 11.9 / 14.6, W 144 5 x 141 10.9 / 10.6 and 10.9 / 11.6;
-        // W 208 107 x 119 17 / 19 and 11 / 15
-        const int least_tiles = snw <= 2 || (L == 1 && snw <= 4) ? 704 : snw == 5 && L > 1 ? 0 : 128;
-        if (tiles(2) < least_tiles || !fits_split(1) || (snw == 2 && (tiles(2) < 1536 || O > 64))) {
-            if (snw == 2) return tiles(1) >= 4096 && fits(2) ? 2 : 1;
-            return tiles(1) < 1408 && fits(1) ? 1 : 0;
-        }
-        split = 1;
-        if (snw <= 2) return 2;
-        // W 65 to 128, several tiles at a time on a CU, 32 and 64 rows: 16 x 300 14 / 17 and 17 / 22, 16 x 700 20 / 25 and 18 / 25,
-        // 64 x 2048 108 / 167 and 89 / 155
-        if (snw <= 4) split = tiles(2) > cus && fits_split(2) ? 2 : 1;
-        // above, one tile at a time on a CU: whichever takes fewest rounds of them, in the time one tile of 32, 64 or 96 rows
-        // takes (W 160 18, 24.5 and 34 us for three layers; W 256 24 and 34).  W 160, 32, 64 and 96 rows: 16 x 700 34, 24, 33; 10 x 1850
-        // 51, 48, 34; 10 x 3700 84, 71, 66; 16 x 2048 67, 47, 65; 64 x 2048 268, 189, 197
-        const int cost[] = {30, snw == 8 ? 43 : 41, 56};
-        int64_t least = INT64_MAX;
-        for (int rb = 1; rb <= 3 && snw > 4; ++rb) {
-            const int64_t c = (tiles(2 * rb) + cus - 1) / cus * cost[rb - 1];
-            if (fits_split(rb) && c < least) { split = rb; least = c; }
-        }
-        return 2 * split;
-    }
-    // wider ones, tiles of 16 rows while there is a CU for each: 16 rows and the layer-by-layer GEMMs, W 512 16 x 256 56 / 60 and
-    // 78 / 81, 64 x 128 109 / 118 and 87 / 93; W 384 64 x 64 43 / 47 and 65 / 68, 64 x 128 79 / 85 and 71 / 74; W 272 64 x 64
-    // 45 / 46 and 51 / 55, 16 x 700 117 / 123 and 75 / 77
-    // (one hidden layer: W 512 25 x 198 28 / 32 and 37 / 38)
-    return tiles(1) <= (L == 1 ? 768 : 256) ? 1 : 0;
-}
-
 static void run_mlp_fwd(const morlax_ctx* c, const NetDev& nd, FwdArgs& a, int rt, bool save, hipStream_t s) {
     const int W = c->d.width, L = c->d.n_hidden, O = c->d.obs_dim, P = c->d.P;
     a.L = L; a.O = O; a.W = W; a.act = c->d.act;
     a.perm = fused_fwd_ok(c, nd, a.net.theta_mat) ? 1 : 0;
     a.narrow = !a.perm && !use_x0(c) && first_fwd_narrow_ok(c) ? 1 : 0;
-    a.net.tiles_m = ((save ? a.Mp : a.net.M) + 16 * rt - 1) / (16 * rt);
+    const int th = a.split ? 32 * a.split : 16 * fwd_compiled((int)esize(c), fwd_waves(W), rt);
+    a.net.tiles_m = ((save ? a.Mp : a.net.M) + th - 1) / th;
     const int n_tiles = a.net.tiles_m * P;
     GemmProf::Rec* r = prof_take(c, 5, 2.0 * W * ((double)O + (double)(L - 1) * W) * a.net.M * P);
     if (r) (void)hipEventRecord(r->a, s);
@@ -3122,13 +3063,15 @@ static void policy_fwd_t(const morlax_ctx* c, int net, const T* theta_mat, const
             run_gemm(c, 1, g, P, s);
         }
     };
-    FwdArgs a;
-    const int rt = fwd_row_tiles(c, nd, theta_mat, M, a.split);
-    if (rt > 0) {
+    const FwdPlan plan = fwd_plan((int)sizeof(T), W, L, O, nd.out_dim, P, M, resident_slots() / 2,
+                                  std::is_same<T, bf16_t>::value && fused_fwd_ok(c, nd, theta_mat));
+    if (plan.rt > 0) {
+        FwdArgs a;
+        a.split = plan.split;
         fill_fwd_net(c, net, theta_mat, theta_vec, rs, out, saved_out, eps, act, logp, reinterpret_cast<char*>(sv),
                      reinterpret_cast<char*>(sv ? sv + ae : nullptr), reinterpret_cast<char*>(sv_x0), a.net);
         a.x = x; a.Mp = Mp; a.ldh = W; a.ldx = x0_ld(c); a.lstride = 2 * ae * (int64_t)sizeof(T);
-        run_mlp_fwd(c, nd, a, rt, sv != nullptr, s);
+        run_mlp_fwd(c, nd, a, plan.rt, sv != nullptr, s);
         return;
     }
     bool fused = false;

@@ -1,6 +1,7 @@
 """The one-launch forward requests the first layer's weights in whole 128-byte pieces; which networks it may serve is a rule
 on their shape (csrc/fwd_shape.h).  Here every request of a preference is walked on the host, lane by lane, for every width,
-output width and element type: what the rule accepts must end inside that preference's matrices."""
+output width and element type: what the rule accepts must end inside that preference's matrices.  And which tiles a call takes
+is a rule too: what it plans must be compiled and cover every row."""
 import os
 import shutil
 import subprocess
@@ -113,6 +114,62 @@ int main() {
 def test_split_networks_are_read_inside_their_matrices(tmp_path):
     src, exe = tmp_path / "walk.cpp", tmp_path / "walk"
     src.write_text(SPLIT_PROGRAM)
+    subprocess.run(["g++", "-O2", "-std=c++17", "-I" + CSRC, str(src), "-o", str(exe)], check=True)
+    r = subprocess.run([str(exe)], capture_output=True, text=True)
+    assert r.returncode == 0, r.stdout
+
+
+# The rule on tiles: what it asks for is compiled, and each compiled variant is asked for by something; a workgroup's LDS holds the
+# tile; and the workgroups that the launch counts cover every row, once, whatever their number.
+PLAN_PROGRAM = r"""
+#include <cstdio>
+#include "fwd_shape.h"
+int main() {
+    const int Os[] = {1, 8, 27, 32, 33, 64, 65, 100, 128, 129, 300, 513, 700, 1024}, Ps[] = {2, 3, 10, 16, 24, 64, 200, 4096, 65535};
+    const int cuss[] = {64, 256, 304};
+    const long Ms[] = {1, 15, 16, 17, 31, 32, 33, 63, 64, 65, 95, 96, 97, 127, 129, 255, 257, 512, 700, 1025, 2048, 4095, 4096, 4100, 8192, 100001};
+    long n = 0, wrong = 0, rt_seen[5][9][5] = {}, split_seen[9][4] = {};
+    for (int es = 2; es <= 4; es += 2)
+        for (int W = 16; W <= 560; W += 16)
+            for (int L = 1; L <= 4; ++L)
+                for (int O : Os) for (int P : Ps) for (long M : Ms) for (int cus : cuss) for (int tall = 0; tall < 2; ++tall) {
+                    const FwdPlan f = fwd_plan(es, W, L, O, 4, P, M, cus, es == 2 && tall);
+                    ++n;
+                    if (f.rt == 0) { wrong += f.split != 0; continue; }
+                    const int nw = fwd_waves(W), snw = split_waves(W);
+                    bool ok;
+                    if (f.split) {
+                        ok = es == 4 && W <= kSplitMaxWidth && f.split <= split_most(snw) && f.rt == 2 * f.split &&
+                             split_lds_bytes(O, W, L, f.split) <= 160 * 1024;
+                        if (ok) ++split_seen[snw][f.split];
+                    } else {
+                        ok = W <= kFwdMaxWidth && f.rt == fwd_compiled(es, nw, f.rt) && fwd_lds_bytes(es, O, W, L, f.rt) <= 160 * 1024;
+                        if (ok) ++rt_seen[es][nw][f.rt];
+                    }
+                    const long th = 16 * (f.split ? 2 * f.split : fwd_compiled(es, nw, f.rt)), planned = (M + 16 * f.rt - 1) / (16 * f.rt);
+                    if (!ok || planned * th < M || (planned - 1) * th >= M)
+                        if (wrong++ < 10)
+                            printf("W %d O %d L %d, %d x %ld, %d bytes, %d CUs: row tiles %d, split %d: %ld tiles of %ld rows\n", W, O, L, P,
+                                   M, es, cus, f.rt, f.split, planned, th);
+                }
+    for (int es = 2; es <= 4; es += 2)
+        for (int W = 16; W <= kFwdMaxWidth; W += 16)
+            for (int rt = fwd_low(es); rt <= 4; rt *= 2)
+                if (rt == fwd_compiled(es, fwd_waves(W), rt) && !rt_seen[es][fwd_waves(W)][rt] && ++wrong)
+                    printf("nothing takes %d row tiles of %d waves, %d bytes\n", rt, fwd_waves(W), es);
+    for (int W = 16; W <= kSplitMaxWidth; W += 16)
+        for (int rb = 1; rb <= split_most(split_waves(W)); ++rb)
+            if (!split_seen[split_waves(W)][rb] && ++wrong) printf("nothing takes %d blocks of %d split waves\n", rb, split_waves(W));
+    printf("shapes %ld wrong %ld\n", n, wrong);
+    return wrong ? 1 : 0;
+}
+"""
+
+
+@pytest.mark.skipif(shutil.which("g++") is None, reason="needs a host compiler")
+def test_planned_tiles_are_compiled_and_cover_all_rows(tmp_path):
+    src, exe = tmp_path / "walk.cpp", tmp_path / "walk"
+    src.write_text(PLAN_PROGRAM)
     subprocess.run(["g++", "-O2", "-std=c++17", "-I" + CSRC, str(src), "-o", str(exe)], check=True)
     r = subprocess.run([str(exe)], capture_output=True, text=True)
     assert r.returncode == 0, r.stdout
