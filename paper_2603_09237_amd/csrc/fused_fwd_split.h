@@ -110,7 +110,7 @@ __global__ __launch_bounds__(64 * NW, 2) void k_mlp_fwd_split(FwdArgs a) {
 #pragma unroll
                     for (int e = 0; e < 8; ++e) v[g][e] = 8 * c + e < O ? v[g][e] : 0.f;
                     uint4 part[3];
-                    split3(v[g], part);
+                    split3<true>(v[g], part);
 #pragma unroll
                     for (int q = 0; q < 3; ++q)
                         *reinterpret_cast<uint4*>(dlds + q * plane + r * pitch0 + ((c ^ split_swz(r, pitch0)) * 16)) = part[q];
@@ -172,19 +172,19 @@ __global__ __launch_bounds__(64 * NW, 2) void k_mlp_fwd_split(FwdArgs a) {
                 for (int i = 0; i < RB; ++i) split_mma(t, w[kk], fa[i], acc[i], low[i]);
         }
     };
-    // a value of the tile, from its parts (an infinite one has undefined smaller ones)
+    // a value of the tile, from its parts (an infinite one's second part is infinite, its third undefined)
     auto tile_value = [&](int row, int k, int pitch) __attribute__((always_inline)) {
         const unsigned char* at = dlds + row * pitch + (((k >> 3) ^ split_swz(row, pitch)) * 16) + (k & 7) * 2;
         const float v0 = to_f(*reinterpret_cast<const bf16_t*>(at)), v1 = to_f(*reinterpret_cast<const bf16_t*>(at + plane)),
                     v2 = to_f(*reinterpret_cast<const bf16_t*>(at + 2 * plane));
-        return __builtin_isinf(v0) ? v0 : v0 + (v1 + v2);
+        return __builtin_isinf(v1) ? v1 : v0 + (v1 + v2);
     };
-    // the sums of a layer whose input is d_in wide; undefined ones once more on the fp32 instructions
+    // the sums of a layer whose input is d_in wide; undefined and infinite ones once more on the fp32 instructions
     auto finish_sums = [&](int l, const float* Wl, int d_in, int pitch) __attribute__((always_inline)) {
 #pragma unroll
         for (int i = 0; i < RB; ++i) {
             acc[i] += low[i];
-            if (any_nan(acc[i])) {
+            if (any_undefined(acc[i])) {
                 const int f = 32 * wave + wrow;
                 const float* wr = Wl + (int64_t)(f < W ? f : W - 1) * d_in;
 #pragma unroll
@@ -219,7 +219,7 @@ __global__ __launch_bounds__(64 * NW, 2) void k_mlp_fwd_split(FwdArgs a) {
                     if (!WHOLE && f >= W) v[h][u] = g[h][u] = 0.f;
                 }
                 uint4 part[3];
-                split3(v[h], part);
+                split3<MODE != kActTanh>(v[h], part);  // (SiLU's may be as large as its argument)
 #pragma unroll
                 for (int q = 0; q < 3; ++q)
                     *reinterpret_cast<uint4*>(dlds + q * plane + row * PITCH + (((f >> 3) ^ split_swz(row, PITCH)) * 16)) = part[q];
@@ -340,7 +340,7 @@ __global__ __launch_bounds__(64 * NW, 2) void k_mlp_fwd_split(FwdArgs a) {
         c += c2;
         {
             const float t = (c[0] + c[1]) + (c[2] + c[3]);
-            if (__any(t != t)) {  // as in the hidden layers
+            if (any_undefined(t)) {  // as in the hidden layers
                 c = float4_t{0.f, 0.f, 0.f, 0.f};
 #pragma unroll 1
                 for (int k = 0; k < W; k += 4)

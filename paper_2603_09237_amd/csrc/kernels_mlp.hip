@@ -626,7 +626,7 @@ struct GemmArgs {
 };
 
 // One 32 x 32 block of an fp32 product once more, on the fp32 matrix instructions and from memory: what is left to do where
-// the sums of split operands came out undefined (see split3: an infinite operand does that).
+// the sums of split operands came out undefined or infinite (see split3: an infinite operand does that).
 template <class OpA, class OpB>
 __device__ inline void plain_products(const OpA& A, const OpB& B, int r, int c, int kdim, float16_t& acc) {
     const int lg = (threadIdx.x >> 5) & 1;
@@ -805,7 +805,7 @@ __global__ __launch_bounds__(256, sizeof(T) == 4 ? 2 : 1) void k_grouped_gemm(Ge
 #pragma unroll
             for (int j = 0; j < 2; ++j) {
                 acc[i][j] += low[i][j];
-                if (any_nan(acc[i][j])) plain_products(A, B, r0 + wm + 32 * i + lr, c0 + wn + 32 * j + lr, kdim, acc[i][j]);
+                if (any_undefined(acc[i][j])) plain_products(A, B, r0 + wm + 32 * i + lr, c0 + wn + 32 * j + lr, kdim, acc[i][j]);
             }
         epilogue_f32(epi, acc, reinterpret_cast<float*>(&lds[0][0][0]), p, tm, g.tiles_m, r0 + wm, c0 + wn, g.crows, g.ccols);
     } else {
@@ -1542,7 +1542,7 @@ __global__ __launch_bounds__(256) void k_gemm_f32_small(GemmArgs<float, SRC_KSTR
         }
     }
     acc[0][0] += low;
-    if (any_nan(acc[0][0])) {
+    if (any_undefined(acc[0][0])) {
         Operand<float, SRC_KSTRIDED, true, GEMM_NCH> a = g.a, b = g.b;
         a.base = g.a_base(grp); b.base = g.b_base(grp);
         a.kdim = b.kdim = grp.kdim;

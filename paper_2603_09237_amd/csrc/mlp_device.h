@@ -39,29 +39,37 @@ template <> struct Mma32<bf16_t> {
                                                     0, 0, 0);
     }
 };
+constexpr float kBf16Largest = 0x1.fep127f;
 // An fp32 value as the sum of three bf16 values, each the nearest to what those before it leave: 24 bits exactly.  A product
 // of two such values is nine products of parts; the three smallest (2^-24 of it and less) are dropped, and the other six run on
 // the bf16 matrix instructions, sixteen times as fast as the fp32 ones.  Sums of the five smaller ones are kept apart from those
 // of the leading parts, which then take one rounding per sixteen products.  Against 64 bits, normal operands: 3.0e-8 of the
 // result for 16 products, 9.3e-8 for 256, 6.0e-7 for 8192, where the fp32 instructions give 7.0e-8, 2.9e-7 and 1.7e-6 (all nine
 // products: the same figures; all six in one accumulator: 3.2e-8, 2.5e-7, 1.5e-6).
-// An infinite value leaves undefined smaller parts (and so does one within 2^-9 of the largest): any_nan tells, and the block is
-// multiplied again by the fp32 instructions.
+// An infinite value leaves undefined smaller parts, and so does a finite one that rounds to an infinite bf16 value (beyond 3.396e38,
+// within 2^-9 of the largest); a leading product within as much of it may overflow where the exact one does not.  any_undefined
+// tells, and the block is multiplied again by the fp32 instructions.  BOUNDED: the leading part stops at the largest bf16 value, so
+// that the parts of every finite value add up to it; an infinite one's second part is infinite.
+template <bool BOUNDED = false>
 __device__ inline void split3(const uint4& u, uint2 part[3]) {
     float v[4] = {__uint_as_float(u.x), __uint_as_float(u.y), __uint_as_float(u.z), __uint_as_float(u.w)};
 #pragma unroll
     for (int q = 0; q < 3; ++q) {
-        part[q] = make_uint2(pack2(v[0], v[1]), pack2(v[2], v[3]));
+        float t[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) t[e] = BOUNDED && q == 0 ? __builtin_amdgcn_fmed3f(v[e], -kBf16Largest, kBf16Largest) : v[e];
+        part[q] = make_uint2(pack2(t[0], t[1]), pack2(t[2], t[3]));
         if (q < 2) {
             v[0] -= __uint_as_float(part[q].x << 16); v[1] -= __uint_as_float(part[q].x & 0xffff0000u);
             v[2] -= __uint_as_float(part[q].y << 16); v[3] -= __uint_as_float(part[q].y & 0xffff0000u);
         }
     }
 }
+template <bool BOUNDED = false>
 __device__ inline void split3(const float (&v)[8], uint4 (&part)[3]) {
     uint2 lo[3], hi[3];
-    split3(make_uint4(__float_as_uint(v[0]), __float_as_uint(v[1]), __float_as_uint(v[2]), __float_as_uint(v[3])), lo);
-    split3(make_uint4(__float_as_uint(v[4]), __float_as_uint(v[5]), __float_as_uint(v[6]), __float_as_uint(v[7])), hi);
+    split3<BOUNDED>(make_uint4(__float_as_uint(v[0]), __float_as_uint(v[1]), __float_as_uint(v[2]), __float_as_uint(v[3])), lo);
+    split3<BOUNDED>(make_uint4(__float_as_uint(v[4]), __float_as_uint(v[5]), __float_as_uint(v[6]), __float_as_uint(v[7])), hi);
 #pragma unroll
     for (int q = 0; q < 3; ++q) part[q] = make_uint4(lo[q].x, lo[q].y, hi[q].x, hi[q].y);
 }
@@ -71,12 +79,13 @@ __device__ inline void split_mma(int t, const uint4 (&a)[3], const uint4 (&b)[3]
     const int j = t == 0 ? 2 : t == 1 ? 0 : t == 2 ? 1 : t == 3 ? 1 : 0;
     Mma32<bf16_t>::run(a[i], b[j], t == 5 ? acc : low);
 }
-// does a wave hold an undefined sum (or sums of both infinite signs in one lane)
-__device__ inline bool any_nan(const float16_t& v) {
+// does a wave hold an undefined or infinite sum (or sums of one lane that add up to one: multiplied again for nothing)
+__device__ inline bool any_undefined(float t) { return __any(!(__builtin_fabsf(t) < __builtin_inff())); }
+__device__ inline bool any_undefined(const float16_t& v) {
     float t = 0.f;
 #pragma unroll
     for (int e = 0; e < 16; ++e) t += v[e];
-    return __any(t != t);
+    return any_undefined(t);
 }
 
 __device__ inline float chunk_f32(const uint4& u, int e) {  // e a compile-time constant after unrolling

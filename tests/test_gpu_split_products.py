@@ -57,6 +57,9 @@ def inputs_of(cfg, torch, seed):
             torch.randn(1, cfg.N, out_dim(cfg, ACTOR), device="cuda", generator=g) / cfg.N)
 
 
+LARGEST, BF16_LARGEST = 3.4028234663852886e38, 3.3895313892515355e38
+
+
 # (preferences, width, observation width, rows, hidden layers): tiles of 128 and of 64 with remainders, contractions that end
 # inside a step of 16, split and unsplit; a width that goes layer by layer, its first layer from aligned and from odd rows
 SHAPES = [(3, 32, 9, 65, 2), (3, 48, 33, 131, 2), (3, 128, 45, 257, 3), (3, 160, 100, 331, 2), (3, 256, 19, 512, 3),
@@ -93,10 +96,11 @@ def test_fp32_networks_against_64_bits(P, W, O, M, L, act, torch, binding):  # n
 
 
 @pytest.mark.parametrize("W,O,M,L", [(64, 33, 70, 2), (160, 20, 131, 2), (272, 40, 33, 2)])
-@pytest.mark.parametrize("where", ("weight", "observation", "gradient", "largest"))
+@pytest.mark.parametrize("where", ("weight", "observation", "gradient", "largest", "largest observation"))
 def test_fp32_infinite_and_undefined_results(where, W, O, M, L, torch, binding):  # noqa: F811
     """An infinite weight, observation or output gradient, and a weight that no bf16 value reaches, show in the same gradients
-    as in float64, with the same sign; every other preference and element is as without it."""
+    as in float64, with the same sign; every other preference and element is as without it.  The largest observation beside a weight
+    of zero is a zero."""
     cfg = scaled(BASE, name=f"inf-{where}-W{W}-O{O}-M{M}", width=W, obs_dim=O, n_hidden=L, act=0, P=2, N=2 * M)
     ctx = binding.Context.from_config(cfg)
     tm, tv = make_theta(cfg, ctx, ACTOR, torch, 21)
@@ -108,6 +112,9 @@ def test_fp32_infinite_and_undefined_results(where, W, O, M, L, torch, binding):
         tm[1, off1 + 7 * W + 3] = 3.4e38
     elif where == "observation":
         x[0, M + 5, 2] = float("-inf")               # a row of the second preference
+    elif where == "largest observation":
+        x[0, M + 5, 2], x[0, M + 6, 2] = LARGEST, -LARGEST
+        tm[1, 9 * O + 2] = 0.0                       # feature 9 of the first layer
     else:
         dout[0, M + 5, 1] = float("inf")
     ref = reference(cfg, tm, tv, x, dout, torch)
@@ -120,3 +127,41 @@ def test_fp32_infinite_and_undefined_results(where, W, O, M, L, torch, binding):
         assert same, (name, n)
         ok = want32.isfinite()
         assert bool(((got - want32).abs() <= 1e-5 + 1e-4 * want32.abs())[ok].all()), name   # (the bounds of the parity tests)
+
+
+@pytest.mark.parametrize("P,W,O,M,L", [(2, 160, 20, 131, 2), (24, 32, 9, 950, 2), (8, 256, 45, 545, 3), (8, 208, 65, 1090, 1), (2, 64, 33, 70, 2)])
+def test_fp32_finite_results_of_the_largest_values(P, W, O, M, L, torch, binding):  # noqa: F811
+    """SiLU networks whose features reach the largest float, which no bf16 value does, and a product whose leading parts alone
+    overflow: finite in float64 and in fp32, on split operands as well (all but the last shape)."""
+    cfg = scaled(BASE, name=f"large-P{P}-W{W}-O{O}-M{M}-L{L}", width=W, obs_dim=O, n_hidden=L, act=1, mean_tanh=0, P=P, N=P * M)
+    ctx = binding.Context.from_config(cfg)
+    tm, tv = make_theta(cfg, ctx, ACTOR, torch, 31)
+    x, _ = inputs_of(cfg, torch, 32)
+    p, row = 1, M + 5
+    Ws = [tm[p, off:off + do * di].view(do, di) for do, di, off in layers(cfg, ACTOR)]
+    Ws[0][:, 1], Ws[0][:, 4] = 0.01, 0.0
+    Ws[0][7, 1], Ws[0][9, 1], Ws[0][11, 4] = 1.0, 0.0, 1.00391   # (its leading part is 1.0078)
+    for w in Ws[1:]:
+        w[:, 7] *= 1e-3
+        w[:, 11] *= 1e-3
+    Ws[1][3, 7] = 0.0
+    tv[p, 7] = tv[p, 11] = 0.0
+    x[0, row], x[0, row + 1], x[0, row + 2] = 0.0, 0.0, 0.0
+    x[0, row, 1], x[0, row + 1, 1], x[0, row + 2, 4] = LARGEST, -LARGEST, BF16_LARGEST
+    rows = (0, 1, 0, cfg.n_g)
+    ws = torch.empty(ctx.workspace_bytes(rows), dtype=torch.uint8, device="cuda")
+    saved = torch.zeros(ctx.saved_bytes(ACTOR, rows), dtype=torch.uint8, device="cuda")
+    h, voff = x.view(P, M, O)[p].double().cpu(), 0
+    for l, w in enumerate(Ws):
+        z = h @ w.double().cpu().t() + tv[p, voff:voff + len(w)].double().cpu()
+        voff += len(w)
+        h = z * torch.sigmoid(z) if l < L else z
+        assert bool((h.abs() <= LARGEST).all())
+    for sv in (None, saved):
+        out = torch.zeros(1, cfg.N, out_dim(cfg, ACTOR), device="cuda")
+        ctx.policy_fwd(ACTOR, tm, tv, x, rows, out, saved=sv, ws=ws)
+        got = out.view(P, M, -1)[p].double().cpu()
+        err = float(((got - h).norm(dim=1) / h.norm(dim=1)).nan_to_num(float("inf")).max())
+        print(f"[gpu-split] {cfg.name} saving={sv is not None}: largest error of a row {err:.2e}", flush=True)
+        assert bool(torch.isfinite(out).all())
+        assert err < 1e-4   # (the relative bound of the parity tests)
