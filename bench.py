@@ -323,8 +323,7 @@ def main():
     median_ms = step_ms[len(step_ms) // 2] if len(step_ms) % 2 else 0.5 * (step_ms[len(step_ms) // 2 - 1] + step_ms[len(step_ms) // 2])
     # second pass, outside the timed region: the library brackets every grouped-GEMM launch with its own event pair,
     # which gives the per-kind kernel times behind `roofline`
-    # (on one stream: a launch's time is then its own, not shared with the other network's)
-    st.overlap = False
+    # (the steps stay on one stream meanwhile: a launch's time is its own, not shared with the other network's)
     st.ctx.profile_begin()
     for _ in range(a.steps):
         st.run()

@@ -152,6 +152,7 @@ class Context:
         if rc != OK:
             raise MorlaxError(rc, self.lib.morlax_last_error().decode())
         self.h = h
+        self.profiling = False   # between profile_begin and profile_end
 
     @classmethod
     def from_config(cls, cfg):
@@ -190,11 +191,13 @@ class Context:
 
     def profile_begin(self):
         self._check(self.lib.morlax_profile_begin(self.h))
+        self.profiling = True
 
     def profile_end(self):
         """-> {kind: (total_ms, launches, total_flops)} for the grouped-GEMM launches since profile_begin."""
         n = len(GEMM_KINDS)
         ms, cnt, fl = (C.c_double * n)(), (C.c_int64 * n)(), (C.c_double * n)()
+        self.profiling = False
         self._check(self.lib.morlax_profile_end(self.h, ms, cnt, fl))
         return {k: (ms[i], cnt[i], fl[i]) for i, k in enumerate(GEMM_KINDS)}
 

@@ -2009,9 +2009,9 @@ int prof_end(morlax_ctx* c, double* ms, int64_t* launches, double* flops) {
     pr->on = false;
     for (int k = 0; k < MORLAX_GEMM_KINDS; ++k) { ms[k] = 0.0; launches[k] = 0; flops[k] = 0.0; }
     if (pr->used == 0) return 0;
-    if (hipEventSynchronize(pr->recs[pr->used - 1].b) != hipSuccess) return -1;
     for (size_t i = 0; i < pr->used; ++i) {
         float t = 0.f;
+        if (hipEventSynchronize(pr->recs[i].b) != hipSuccess) return -1;  // (launches may be spread over streams)
         if (hipEventElapsedTime(&t, pr->recs[i].a, pr->recs[i].b) != hipSuccess) return -1;
         ms[pr->recs[i].kind] += t;
         launches[pr->recs[i].kind] += 1;

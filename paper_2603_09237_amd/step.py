@@ -53,7 +53,7 @@ class UpdateStep:
         stream next to the grouped GEMMs of the other network / the next minibatch; the GEMM chain stays on the
         caller's stream.  two_streams: the older split, one stream per network family.  Neither: `run` gives either
         network's calls a stream of its own where `overlap` says so (an attribute; False keeps every call on the caller's
-        stream).
+        stream, and so do a capture and the context's profile).
         adv_norm: "scalar" = the scalarised advantage is normalised over the minibatch (inside the loss call);
         "per_objective" = every objective is standardised over the minibatch before scalarisation
         (scalarize_normalized, then the loss without further normalisation)."""
@@ -240,8 +240,10 @@ class UpdateStep:
         """One whole update step.  `on_minibatch(e, b)` (optional) is called after each minibatch."""
         if self.side is not None:
             return self._run_side(on_minibatch)
-        # (a caller's own graph records the calls on the one stream it captures)
-        if self.overlap and self.streams is None and not self.torch.cuda.is_current_stream_capturing():
+        # (a caller's own graph records the calls on the one stream it captures; a profile is of launches that have the chip to
+        # themselves)
+        if (self.overlap and self.streams is None and not self.ctx.profiling and
+                not self.torch.cuda.is_current_stream_capturing()):
             return self._run_beside(on_minibatch)
         self.rollout()
         for e in range(self.cfg.epochs):

@@ -69,3 +69,29 @@ def test_rule_and_capture_stay_on_the_callers_stream(torch, binding):  # noqa: F
         torch.cuda.synchronize()
         assert all(torch.equal(a, b) for a, b in zip(ref, (st.dhp[0], st.dhp[1], st.stats)))
         st.run()
+
+
+def test_profile_of_launches_on_two_streams(torch, binding):  # noqa: F811
+    """The profile waits for every stream that was launched on, not for the last launch alone; a step that is profiled stays on the
+    caller's stream."""
+    from paper_2603_09237_amd.step import UpdateStep
+    cfg = scaled(CONFIGS[3], name="overlap-profile", P=16, N=16 * 256, T=16)
+    st = UpdateStep(cfg)
+    st.load_inputs(inputs.make_all(cfg))
+    ctx, fwd = st.ctx, lambda net, rows, stream: st.ctx.policy_fwd(
+        net, st.theta_mat[net], st.theta_vec[net], st.obs, rows, st.mu_old if net == 0 else st.v_roll, ws=st.wsn[net], stream=stream)
+    st.run()
+    torch.cuda.synchronize()
+    long, *others = [torch.cuda.Stream() for _ in range(6)]   # (some of them share the first one's hardware queue)
+    for short in others:
+        ctx.profile_begin()
+        for _ in range(200):
+            fwd(1, st.full_T1, long.cuda_stream)
+        fwd(0, (0, 1, 0, 1), short.cuda_stream)
+        assert sum(v[1] for v in ctx.profile_end().values()) >= 201
+        assert long.query() and short.query()
+    st.overlap = True
+    st._run_beside = None
+    ctx.profile_begin()
+    st.run()
+    assert ctx.profile_end()["fwd_fused"][1] > 0
