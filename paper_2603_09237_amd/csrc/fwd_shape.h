@@ -70,10 +70,18 @@ inline FwdPlan fwd_plan(int es, int W, int L, int O, int out_dim, int P, int64_t
         // One hidden layer, whose products are few: W 128 10 x 1065 10.7 / 12.5 and 11.9 / 14.6, W 144 5 x 141 10.9 / 10.6 and 10.9 / 11.6;
         // W 208 107 x 119 17 / 19 and 11 / 15
         const int least_tiles = snw <= 2 || (L == 1 && snw <= 4) ? 704 : snw == 5 && L > 1 ? 0 : 128;
-        if (tiles(2) < least_tiles || !fits_split(1) || (snw == 2 && (tiles(2) < 1536 || O > 64))) {
-            if (snw == 2) return {1, 0};
-            return {tiles(1) < 1408 ? 1 : 0, 0};
-        }
+        // Up to 64 features, one or two waves a workgroup split all of a tile's observations: worth it only while the first layer is
+        // short beside the hidden ones.  Times of 16-row tiles over split ones, plain / saving, 704 to 8192 tiles of 32 rows: W 32, one
+        // hidden layer, O 33 0.98 - 1.14 / 0.97 - 1.10, O 64 0.86 - 0.96 / 0.88 - 0.94; two, O 64 1.05 - 1.35 / 0.96 - 1.16, O 100 0.96 -
+        // 1.14 / 0.87 - 1.04, O 200 0.90 - 1.16 / 0.77 - 1.03, O 513 0.53 - 0.70 / 0.67 - 0.80; three, O 128 1.01 - 1.19 / 0.92 - 1.06.
+        // From 1536 tiles on, W 64, two, O 33 1.06 - 1.18 / 1.03 - 1.14, O 64 0.97 - 0.99 / 0.93 - 0.98 and from 4096 1.05 - 1.10 / 1.00 -
+        // 1.08, O 200 0.86 - 0.96 / 0.87 - 0.90; three, O 64 1.18 - 1.33 / 1.11 - 1.20, O 128 1.03 - 1.06 / 0.94 - 1.07.  W 48, a quarter
+        // of whose products are padding, two, O 33 0.96 - 1.08 / 0.89 - 1.00 and from 6144 1.12 - 1.15 / 0.99 - 1.03; three, O 64 1.18 -
+        // 1.20 / 1.03 - 1.07
+        const bool long_first = O > (snw == 1 ? 48 : 32) * L;
+        if (snw <= 2 && long_first && fits_split(1)) return {1, 0};
+        if (snw == 2 && (!fits_split(1) || tiles(2) < (W < 64 && L < 3 ? 6144 : O > 24 * L ? 4096 : 1536))) return {1, 0};
+        if (tiles(2) < least_tiles || !fits_split(1)) return {tiles(1) < 1408 ? 1 : 0, 0};
         int split = 1;
         if (snw <= 2) return {2, 1};
         // W 65 to 128, several tiles at a time on a CU, 32 and 64 rows: 16 x 300 14 / 17 and 17 / 22, 16 x 700 20 / 25 and 18 / 25,

@@ -139,8 +139,9 @@ int main() {
                     const int nw = fwd_waves(W), snw = split_waves(W);
                     bool ok;
                     if (f.split) {
+                        // (up to 64 features: not where the first layer is so much longer than the hidden ones)
                         ok = es == 4 && W <= kSplitMaxWidth && f.split <= split_most(snw) && f.rt == 2 * f.split &&
-                             split_lds_bytes(O, W, L, f.split) <= 160 * 1024;
+                             split_lds_bytes(O, W, L, f.split) <= 160 * 1024 && (W > 64 || O <= 64 * L);
                         if (ok) ++split_seen[snw][f.split];
                     } else {
                         ok = W <= kFwdMaxWidth && f.rt == fwd_compiled(es, nw, f.rt) && fwd_lds_bytes(es, O, W, L, f.rt) <= 160 * 1024;

@@ -69,8 +69,9 @@ SHAPES = [(3, 32, 9, 65, 2), (3, 48, 33, 131, 2), (3, 128, 45, 257, 3), (3, 160,
 SHAPES += [(24, 32, 9, 950, 2), (24, 48, 33, 2070, 2), (24, 64, 8, 2050, 3), (8, 80, 45, 525, 2), (8, 96, 12, 1100, 2),
            (8, 128, 19, 1100, 2), (3, 144, 100, 33, 3), (10, 160, 20, 1850, 2), (8, 176, 130, 545, 2), (10, 192, 45, 1890, 2),
            (8, 208, 65, 1090, 2), (8, 256, 27, 545, 2), (8, 256, 300, 1090, 2)]
-# many rows of networks of two split waves whose observations are too wide for it: tiles of 16 rows
-SHAPES += [(64, 48, 65, 1025, 2), (16, 64, 100, 4096, 2)]
+SHAPES += [(24, 48, 33, 2070, 3)]
+# many rows of networks of one and two split waves whose observations are too wide for it: tiles of 16 rows
+SHAPES += [(64, 48, 65, 1025, 2), (16, 64, 100, 4096, 2), (16, 32, 129, 1450, 2)]
 
 
 @pytest.mark.parametrize("P,W,O,M,L", SHAPES)
