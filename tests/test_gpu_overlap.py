@@ -47,6 +47,39 @@ def test_streams_of_their_own_give_the_same_bits(cfg, kw, callback, torch, bindi
     assert not wrong
 
 
+# steps that take two streams by themselves: the split forward of fp32 networks of width 256, the persistent kernels of bf16 ones of
+# width 512
+OWN = [scaled(CONFIGS[2], name="overlap-own-fp32-W256", P=8, N=8 * 109, T=5), scaled(CONFIGS[4], name="overlap-own-bf16-W512", P=32, N=32 * 64, T=16, rank=4, n_hidden=3)]
+
+
+@pytest.mark.parametrize("cfg", OWN, ids=lambda c: c.name)
+def test_streams_that_a_step_takes_by_itself_give_the_same_bits(cfg, torch, binding):  # noqa: F811
+    from paper_2603_09237_amd.step import UpdateStep
+    d, got = inputs.make_all(cfg), []
+    for one in (False, True):
+        st = UpdateStep(cfg, optimizer=ADAM)
+        assert st.overlap
+        if one:
+            st.overlap = False
+        st.load_inputs(d)
+        for _ in range(3):
+            st.run()
+        torch.cuda.synchronize()
+        got.append([t.clone() for n in (0, 1) for t in (st.dhp[n], st.hp[n], st.theta_vec[n])] +
+                   [t.clone() for t in (st.act, st.logp_old, st.v_roll, st.adv_s, st.mu, st.v, st.stats)])
+    wrong = [i for i, (a, b) in enumerate(zip(*got)) if not torch.equal(a, b)]
+    print(f"[gpu-overlap] {cfg.name}: {len(got[0])} tensors, different {wrong[:5]}", flush=True)
+    assert not wrong
+
+
+# either side of the two lines of the rule, and what is far beyond them
+@pytest.mark.parametrize("P,rows,L,W,two", [(4, 640, 2, 256, False), (16, 3200, 2, 128, True), (4, 96, 4, 256, False), (4, 192, 4, 256, True)])
+def test_which_steps_take_two_streams(P, rows, L, W, two, torch, binding):  # noqa: F811
+    from paper_2603_09237_amd.step import UpdateStep
+    assert UpdateStep(scaled(CONFIGS[3], name="overlap-rule", P=P, N=P * rows // 16, T=16, n_hidden=L, width=W)).overlap is two
+    assert UpdateStep(CONFIGS[3]).overlap is True
+
+
 def test_rule_and_capture_stay_on_the_callers_stream(torch, binding):  # noqa: F811
     """A step bound by its submission stays on one stream; a caller's own graph records the one-stream schedule whatever
     `overlap` says, and its replays equal the eager steps."""

@@ -70,8 +70,10 @@ SHAPES += [(24, 32, 9, 950, 2), (24, 48, 33, 2070, 2), (24, 64, 8, 2050, 3), (8,
            (8, 128, 19, 1100, 2), (3, 144, 100, 33, 3), (10, 160, 20, 1850, 2), (8, 176, 130, 545, 2), (10, 192, 45, 1890, 2),
            (8, 208, 65, 1090, 2), (8, 256, 27, 545, 2), (8, 256, 300, 1090, 2)]
 SHAPES += [(24, 48, 33, 2070, 3)]
+# one hidden layer on it: no ring of weights
+SHAPES += [(40, 32, 20, 950, 1), (24, 64, 20, 2070, 1), (8, 144, 45, 2900, 1), (8, 208, 65, 1090, 1)]
 # many rows of networks of one and two split waves whose observations are too wide for it: tiles of 16 rows
-SHAPES += [(64, 48, 65, 1025, 2), (16, 64, 100, 4096, 2), (16, 32, 129, 1450, 2)]
+SHAPES += [(64, 48, 65, 1025, 2), (16, 64, 100, 4096, 2), (16, 64, 100, 4100, 3), (16, 32, 129, 1450, 2)]
 
 
 @pytest.mark.parametrize("P,W,O,M,L", SHAPES)
