@@ -190,17 +190,10 @@ __global__ __launch_bounds__(64 * NW, 2) void k_mlp_fwd_split(FwdArgs a) {
 #pragma unroll
                 for (int e = 0; e < 16; ++e) acc[i][e] = sbias[l * WP + 32 * wave + 16 * (e >> 3) + 8 * lg + (e & 7)];
 #pragma unroll 1
-                for (int k = 0; k < d_in; k += 8) {  // (the operands of four products requested together)
-                    float w[4], v[4];
-#pragma unroll
-                    for (int u = 0; u < 4; ++u) {
-                        const int kk = k + 2 * u + lg, at = kk < d_in ? kk : d_in - 1;
-                        w[u] = wr[at];
-                        v[u] = tile_value(32 * i + lr, at, pitch);
-                        if (kk >= d_in) w[u] = v[u] = 0.f;
-                    }
-#pragma unroll
-                    for (int u = 0; u < 4; ++u) acc[i] = __builtin_amdgcn_mfma_f32_32x32x2f32(w[u], v[u], acc[i], 0, 0, 0);
+                for (int k = 0; k < d_in; k += 2) {
+                    const int kk = k + lg;
+                    acc[i] = __builtin_amdgcn_mfma_f32_32x32x2f32(kk < d_in ? wr[kk] : 0.f, kk < d_in ? tile_value(32 * i + lr, kk, pitch) : 0.f,
+                                                                  acc[i], 0, 0, 0);
                 }
             }
         }

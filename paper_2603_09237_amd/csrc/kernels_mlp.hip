@@ -69,11 +69,6 @@ struct Operand {
         if (KIND == SRC_KSTRIDED) return to_f(reinterpret_cast<const T*>(base)[(int64_t)k * ld + r]);
         return reinterpret_cast<const float*>(base)[rm.row(p, r) * ld + k];
     }
-    // the same without a branch: beyond the operand its last row or index is loaded
-    __device__ inline float elem_near(int r, int k) const {
-        const float v = elem(r < rows ? r : rows - 1, k < kdim ? k : kdim - 1);
-        return r < rows && k < kdim ? v : 0.f;
-    }
 
     // thread -> (tile row, chunk) of its i-th chunk
     __device__ static inline int trow(int i) {
@@ -631,25 +626,14 @@ struct GemmArgs {
 };
 
 // One 32 x 32 block of an fp32 product once more, on the fp32 matrix instructions and from memory: what is left to do where
-// the sums of split operands came out undefined or infinite (see split3: an infinite operand does that).  Sixteen contraction
-// indices are requested together: one at a time, a backward pass of 16 preferences x 8192 rows of 3 x 256 with an undefined
-// value took 2000 us, 1510 so, 660 without (910 on the fp32 instructions throughout).
+// the sums of split operands came out undefined or infinite (see split3: an infinite operand does that).
 template <class OpA, class OpB>
 __device__ inline void plain_products(const OpA& A, const OpB& B, int r, int c, int kdim, float16_t& acc) {
     const int lg = (threadIdx.x >> 5) & 1;
 #pragma unroll
     for (int e = 0; e < 16; ++e) acc[e] = 0.f;
 #pragma unroll 1
-    for (int k = 0; k < kdim; k += 16) {
-        float a[8], b[8];
-#pragma unroll
-        for (int u = 0; u < 8; ++u) {
-            a[u] = A.elem_near(r, k + 2 * u + lg);
-            b[u] = B.elem_near(c, k + 2 * u + lg);
-        }
-#pragma unroll
-        for (int u = 0; u < 8; ++u) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a[u], b[u], acc, 0, 0, 0);
-    }
+    for (int k = 0; k < kdim; k += 2) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(A.elem(r, k + lg), B.elem(c, k + lg), acc, 0, 0, 0);
 }
 
 // C[rows_a x rows_b] = A[rows_a x K] * B[rows_b x K]^T for every preference.  fp32 on split operands, us a launch, 16 preferences x
