@@ -7,8 +7,10 @@
 // for all rows, so its slice of W_l(p) is used by no other wave.  W travels a super-step (a 128-byte line of each of the 32 rows,
 // 4 KB) at a time: requested into registers D super-steps ahead, across layer ends, through 4 KB of LDS of the wave's own into
 // fragment order one super-step ahead, and split there: some 100 vector instructions beside 12 RB products of 32 cycles.
-// Clock readings of a tile of 64 rows x 256 features: 13.2 thousand cycles a hidden layer's products, of which the matrix pipe is
-// busy 12.3; 3.1 its epilogue; observations and first layer 6, output layer 7.  (64 features a wave, four waves: 15.8 thousand;
+// What bounds it: one tile runs on a CU, so its ends and epilogues leave the matrix pipe idle.  16 preferences x 8192 rows of 3 x
+// 256: the pipe is busy 0.39 of the time (0.33 saving) at 1.95 GHz; of 61 to 67 thousand cycles of a tile of 64 rows each hidden
+// layer's products take 12.5 to 17.6 (12.3 of the pipe's), its epilogue with the barriers 4.8 to 9.8, observations and first layer 7 to 8,
+// the output layer up to 9.  us plain / saving: 374 / 430 on the fp32 instructions, 268 / 341 so.  (64 features a wave, four waves: 306;
 // fragments and the split of W another half super-step ahead: no change; the waves of a SIMD at two priorities: none.)
 #pragma once
 

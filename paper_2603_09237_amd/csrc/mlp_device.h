@@ -40,7 +40,10 @@ template <> struct Mma32<bf16_t> {
     }
 };
 constexpr float kBf16Largest = 0x1.fep127f;
-// An fp32 value as the sum of three bf16 values, each the nearest to what those before it leave: 24 bits exactly.  A product
+// An fp32 value as the sum of three bf16 values, each the nearest to what those before it leave: 24 bits exactly, down to
+// some 1e-30; below, the smallest part and then the middle one are subnormal, and the matrix instructions take those for zero (a
+// backward pass whose largest dW is 5e-30, 5e-33, 3e-34, 1e-36: off by 1e-9, 2e-7, 4e-6, 9e-4 of itself; on the fp32 instructions
+// by 1e-7 at the last).  A product
 // of two such values is nine products of parts; the three smallest (2^-24 of it and less) are dropped, and the other six run on
 // the bf16 matrix instructions, sixteen times as fast as the fp32 ones.  Sums of the five smaller ones are kept apart from those
 // of the leading parts, which then take one rounding per sixteen products.  Against 64 bits, normal operands: 3.0e-8 of the
