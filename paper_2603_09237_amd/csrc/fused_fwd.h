@@ -14,8 +14,8 @@
 // requests three 512 x 512 matrices, one workgroup of eight waves a CU and 16 KB a wave in flight, takes 46 us that way (16
 // bytes per clock and CU) and 19 us with eight lanes to a line, while the caches serve the weights (32 workgroups on 16
 // networks; 256 on 8: 47 and 20 us).  With every CU on weights of its own the way from memory bounds both: 59 and 63 us; the
-// largest policies are there (a step of 128 preferences x 128 rows of 4 x 512: 70.6 us a network, 10.6 bytes per clock and
-// CU, 3.0 TB/s).  (Copying the matrices into fragment order first, as the kernel for tall selections does, is a launch of 87
+// largest policies are there (a step of 128 preferences x 128 rows of 4 x 512: 56.7 us a network, 3.7 TB/s; 62.6 before the ring
+// was filled ahead of the first layer).  (Copying the matrices into fragment order first, as the kernel for tall selections does, is a launch of 87
 // us at that size.)
 //
 // bf16 products are 32x32x16 in the contraction order of the kernels that serve taller selections of the same network
@@ -61,7 +61,34 @@ struct FwdArgs {
 
 typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));  // (HIP's uint4 keeps arrays of it out of registers)
 typedef u32x4_t chunk2_t __attribute__((aligned(2)));          // 16 bytes at any element boundary
-struct __attribute__((packed, aligned(4))) FloatRun4 { float4 q; };
+
+// Piece c of a row of O >= VE values: VE of them, zeros beyond O.  obs_get requests the VE values that end with the row where the
+// piece runs past it, obs_place moves them down.  (With whole pieces and single values in branches of their own the compiler
+// waits for one piece before it requests the next.)
+template <int NQ>
+__device__ inline void obs_get(u32x4_t (&q)[NQ], const float* row, int c, int O) {
+    constexpr int VE = 4 * NQ;
+    typedef u32x4_t word_t __attribute__((aligned(4)));
+    const float* at = row + (VE * c + VE <= O ? VE * c : O - VE);
+#pragma unroll
+    for (int e = 0; e < NQ; ++e) q[e] = *reinterpret_cast<const word_t*>(at + 4 * e);
+}
+template <int VE>
+__device__ inline void obs_place(float (&v)[VE], const u32x4_t (&q)[VE / 4], int c, int O) {
+#pragma unroll
+    for (int e = 0; e < VE; ++e) v[e] = __uint_as_float(q[e >> 2][e & 3]);
+    const bool end = VE * c + VE > O, in = VE * c < O;
+    const int d = (VE - O % VE) % VE;  // (the same for every row)
+    if (d)
+#pragma unroll
+        for (int b = 1; b < VE; b *= 2) {
+            const bool move = end && (d & b);
+#pragma unroll
+            for (int e = 0; e < VE; ++e) v[e] = move ? (e + b < VE ? v[e + b < VE ? e + b : 0] : 0.f) : v[e];
+        }
+#pragma unroll
+    for (int e = 0; e < VE; ++e) v[e] = in ? v[e] : 0.f;
+}
 
 // super-steps of W requested ahead: what the registers leave room for, as long as it divides those of a hidden layer
 // (fp32: a super-step's products take so long that two cover the latency)
@@ -107,6 +134,10 @@ __global__ __launch_bounds__(64 * NW, sizeof(T) == 4 ? 3 : 2) void k_mlp_fwd(Fwd
     constexpr int PITCH = (WP * ES + 255) / 256 * 256;
     constexpr int ROWS = 16 * RT;
     constexpr int D = fwd_depth(ES, NW, RT);
+    // The ring is filled with the tile's other first requests, where tall saving tiles do not wait for each other's stores: ahead
+    // of the first layer and behind it, 20 preferences x 850 rows of 3 x 256, saving, 29.6 and 27.3 us, 128 x 128 of 4 x 512
+    // 79.8 and 78.6 (acting, ahead: 51.6 -> 46.1)
+    constexpr bool EARLY = !SAVE || RT <= 2;
     static_assert(S1 % D == 0, "the ring of requests wraps at layer ends");
     extern __shared__ __align__(16) unsigned char dlds[];
     const int lane = threadIdx.x & 63;
@@ -159,14 +190,16 @@ __global__ __launch_bounds__(64 * NW, sizeof(T) == 4 ? 3 : 2) void k_mlp_fwd(Fwd
     };
     u32x4_t w0[8];
     const bool narrow = B32 && a.narrow;
-    if (narrow) {  // (O <= 32) lane = feature: its whole row
-        const int f = 64 * wave + lane;
-        const char* row = Wp + (uint32_t)((f < W ? f : W - 1) * O) * ES;
+    auto load_w0 = [&]() __attribute__((always_inline)) {
+        if (narrow) {  // (O <= 32) lane = feature: its whole row
+            const int f = 64 * wave + lane;
+            const char* row = Wp + (uint32_t)((f < W ? f : W - 1) * O) * ES;
 #pragma unroll
-        for (int b = 0; b < 4; ++b) w0[b] = *reinterpret_cast<const chunk2_t*>(row + 16 * b);
-    } else {
-        load_w(w0, Wp, O, KS);
-    }
+            for (int b = 0; b < 4; ++b) w0[b] = *reinterpret_cast<const chunk2_t*>(row + 16 * b);
+        } else {
+            load_w(w0, Wp, O, KS);
+        }
+    };
     // The first layer's last super-step runs past the end of the rows into the next ones, or into the matrix behind
     // (fwd_reads_inside: the launcher checks that there is enough of it).  The observations it meets there are zero, but an
     // infinite or undefined weight of another row would make a NaN of them, so those elements are zeroed: `kept` of register
@@ -204,45 +237,79 @@ __global__ __launch_bounds__(64 * NW, sizeof(T) == 4 ? 3 : 2) void k_mlp_fwd(Fwd
         }
     };
 
-    // the tile's observations in the GEMM input type, zero-filled to whole steps; rows past the end repeat the
-    // last row (their outputs are never stored)
+    // What the tile starts from is requested together, what is needed first ahead of the rest: observations, biases (a register
+    // load later on would stand behind the ring's requests), W_0, the ring.  us, as a loop of pieces with two divisions each,
+    // the biases layer by layer behind it, and so: acting, 128 preferences x 128 rows of 4 x 512 51.4 and 45.6, 32 x 256 of 3 x 256
+    // 14.2 and 13.6, 64 x 6000 of 3 x 64 with 120 observations 126 and 78; saving, 38 x 850 of 3 x 256 47.8 and 43.9.
     {
-        constexpr int NT = 64 * NW, G = 4;  // pieces a thread requests together
-        const int cpr = n0 * 8, n_id = ROWS * cpr;
+        constexpr int NT = 64 * NW, NB = 4;  // layers whose biases come along
+        constexpr int G = 4 * RT >= 4 * NW ? 4 : (4 * RT + NW - 1) / NW;  // pieces a thread requests together: 128 observations in bf16, 64 in fp32
+        // 2^sh pieces of VE values a row, those behind the last super-step skipped, those behind the observations zero
+        const int np = 8 * n0, nc = ((O + 7) & ~7) / VE, sh = 32 - __builtin_clz(np - 1), n_id = ROWS << sh;
         const int mlim = SAVE ? a.Mp - m0 : 0;
-        for (int id0 = threadIdx.x; id0 < n_id; id0 += G * NT) {
-            float v[G][8];
+        const int bf = (int)threadIdx.x < W ? threadIdx.x : W - 1;
+        // the observations in the GEMM input type, zero-filled to whole steps; rows past the end repeat the last row (their
+        // outputs are never stored)
+        auto obs_row = [&](int r) __attribute__((always_inline)) {
+            return a.x + (uint32_t)net.rm.row(p, m0 + r < net.M ? m0 + r : net.M - 1) * (uint32_t)O;  // (the tensor stays below 4 GiB)
+        };
+        auto load_x = [&](u32x4_t (&v)[G][VE / 4], int first) __attribute__((always_inline)) {
 #pragma unroll
             for (int g = 0; g < G; ++g) {
-                const int id = id0 + g * NT < n_id ? id0 + g * NT : id0, r = id / cpr, c = id - r * cpr;
-                const int m = m0 + r < net.M ? m0 + r : net.M - 1;
-                const float* xr = a.x + net.rm.row(p, m) * O;
-                if (VE * c + VE <= O) {
-#pragma unroll
-                    for (int e = 0; e < VE / 4; ++e) {
-                        const float4 q = reinterpret_cast<const FloatRun4*>(xr + VE * c + 4 * e)->q;
-                        v[g][4 * e] = q.x; v[g][4 * e + 1] = q.y; v[g][4 * e + 2] = q.z; v[g][4 * e + 3] = q.w;
-                    }
-                } else {
-#pragma unroll
-                    for (int e = 0; e < VE; ++e) v[g][e] = xr[VE * c + e < O ? VE * c + e : O - 1];
-                }
+                const int i = first + g * NT + (int)threadIdx.x, id = i < n_id ? i : n_id - 1;
+                obs_get(v[g], obs_row(id >> sh), id & ((1 << sh) - 1), O);
             }
+        };
+        auto put_piece = [&](const float (&v)[VE], int r, int c) __attribute__((always_inline)) {
+            const uint4 q = pack_chunk<T>(v);
+            *reinterpret_cast<uint4*>(dlds + r * pitch0 + ((c ^ (r & 15)) * 16)) = q;
+            if (SAVE && net.x0 && r < mlim && c < nc)
+                *reinterpret_cast<uint4*>(net.x0 + (((int64_t)p * a.Mp + m0 + r) * a.ldx + VE * c) * ES) = q;
+        };
+        auto put_x = [&](u32x4_t (&v)[G][VE / 4], int first) __attribute__((always_inline)) {
 #pragma unroll
             for (int g = 0; g < G; ++g) {
-                const int id = id0 + g * NT, r = id / cpr, c = id - r * cpr;
-                if (id < n_id) {
+                const int id = first + g * NT + (int)threadIdx.x, r = id >> sh, c = id & ((1 << sh) - 1);
+                float w[VE];
+                obs_place(w, v[g], c, O);
+                if (id < n_id && c < np) put_piece(w, r, c);
+            }
+        };
+        u32x4_t v[G][VE / 4];
+        int first = 0;
+        if (O >= VE) {
+            for (; first + G * NT < n_id; first += G * NT) {
+                load_x(v, first);
+                put_x(v, first);
+            }
+            load_x(v, first);
+        }
+        float bv[NB];
 #pragma unroll
-                    for (int e = 0; e < VE; ++e) v[g][e] = VE * c + e < O ? v[g][e] : 0.f;
-                    const uint4 q = pack_chunk<T>(v[g]);
-                    *reinterpret_cast<uint4*>(dlds + r * pitch0 + ((c ^ (r & 15)) * 16)) = q;
-                    if (SAVE && net.x0 && r < mlim && VE * c < a.ldx)
-                        *reinterpret_cast<uint4*>(net.x0 + (((int64_t)p * a.Mp + m0 + r) * a.ldx + VE * c) * ES) = q;
+        for (int l = 0; l < NB; ++l) bv[l] = bp[(l < L ? l : L - 1) * W + bf];
+        __builtin_amdgcn_sched_barrier(0);
+        load_w0();
+        if (EARLY) fill();
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int l = 0; l < NB; ++l)
+            if (l < L) sbias[l * WP + threadIdx.x] = bv[l];
+        for (int l = NB; l < L; ++l) sbias[l * WP + threadIdx.x] = bp[l * W + bf];
+        if (O >= VE) {
+            put_x(v, first);
+        } else {  // rows shorter than a piece, element by element
+            for (int r = threadIdx.x; r < ROWS; r += NT) {
+                const float* row = obs_row(r);
+                float w[VE];
+#pragma unroll
+                for (int e = 0; e < VE; ++e) w[e] = e < O ? row[e < O ? e : O - 1] : 0.f;
+                put_piece(w, r, 0);
+                for (int c = 1; c < np; ++c) {
+                    const float zero[VE] = {};
+                    put_piece(zero, r, c);
                 }
             }
         }
-        // every layer's biases (a register load would stand in front of the ring's requests)
-        for (int l = 0; l < L; ++l) sbias[l * WP + threadIdx.x] = bp[l * W + ((int)threadIdx.x < W ? threadIdx.x : W - 1)];
     }
     if (narrow) {  // W_0 transposed: [input][feature] of the wave
         const uint32_t wq[16] = {w0[0].x, w0[0].y, w0[0].z, w0[0].w, w0[1].x, w0[1].y, w0[1].z, w0[1].w,
@@ -251,7 +318,6 @@ __global__ __launch_bounds__(64 * NW, sizeof(T) == 4 ? 3 : 2) void k_mlp_fwd(Fwd
         for (int i = 0; i < 32; ++i)
             reinterpret_cast<uint16_t*>(wst)[i * 64 + lane] = (uint16_t)(wq[i >> 1] >> (16 * (i & 1)));
     }
-    if (RT <= 2) fill();  // (higher tiles: once the first layer's registers are free)
 
     // accumulators.  bf16: 32-row block i, feature block j: lane (lr, lg) holds row 32 i + lr, features 32 j + 16 h + 8 lg
     // + u in element 8 h + u.  fp32: row tile i, feature block b: row 16 i + ln, features 16 b + 4 kg + e in element e.
@@ -425,7 +491,7 @@ __global__ __launch_bounds__(64 * NW, sizeof(T) == 4 ? 3 : 2) void k_mlp_fwd(Fwd
             if (s + 1 < n0) load_w(w0, Wp + (s + 1) * 128, O, KS);
         }
     }
-    if (RT > 2) fill();
+    if (!EARLY) fill();
     finish_layer(0, bias_last && !narrow);
     for (int l = 1; l < L; ++l) {
         __syncthreads();  // the layer's input is complete in LDS

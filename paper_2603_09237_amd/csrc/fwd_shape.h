@@ -4,6 +4,25 @@
 
 #include <stdint.h>
 
+#ifdef __HIPCC__
+#define MORLAX_HD __host__ __device__
+#else
+#define MORLAX_HD
+#endif
+
+// Division of numbers below 2^31 by one divisor d, exact, as a product and a shift: with s = ceil(log2 d) and mul = floor(2^(31 +
+// s) / d) + 1 the excess mul d - 2^(31 + s) lies in (0, d], d <= 2^s, so that m mul / 2^(31 + s) is above m / d by less than 1 / d.
+struct RowDiv {
+    uint32_t mul;
+    int32_t sh;
+    MORLAX_HD uint32_t quotient(uint32_t m) const { return (uint32_t)(((uint64_t)m * mul) >> sh); }
+};
+inline RowDiv row_div(int32_t d) {
+    int s = 0;
+    while ((int64_t)1 << s < d) ++s;
+    return {(uint32_t)(((uint64_t)1 << (31 + s)) / (uint32_t)d + 1), 31 + s};
+}
+
 constexpr int kFwdMaxWidth = 512;
 constexpr int fwd_waves(int w) { return w <= 256 ? (w + 63) / 64 : w <= 384 ? 6 : 8; }
 

@@ -3,6 +3,7 @@
 
 #include <type_traits>
 
+#include "fwd_shape.h"
 #include "morlax_internal.h"
 #include "numeric.h"
 
@@ -10,8 +11,10 @@
 
 struct RowMap {  // compact row m of preference p -> row of a time-major tensor
     int32_t t0, j0, j_cnt, N, n_g;
+    RowDiv by;  // of j_cnt (a division by the compiler is some twenty instructions for every row a lane looks up)
     __device__ inline int64_t row(int p, int m) const {
-        return (int64_t)(t0 + m / j_cnt) * N + (int64_t)p * n_g + j0 + m % j_cnt;
+        const int t = (int)by.quotient((uint32_t)m);
+        return (int64_t)(t0 + t) * N + (int64_t)p * n_g + j0 + (m - t * j_cnt);
     }
 };
 
