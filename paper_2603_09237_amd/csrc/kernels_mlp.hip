@@ -2940,7 +2940,7 @@ int64_t mlp_ws_bytes(const morlax_ctx* c, const RowSel& rs) {
 static RowMap make_rowmap(const morlax_ctx* c, const RowSel& rs) {
     RowMap rm;
     rm.t0 = rs.t0; rm.j0 = rs.j0; rm.j_cnt = rs.j_cnt; rm.N = c->d.N; rm.n_g = c->n_g;
-    rm.by = row_div(rs.j_cnt);
+    rm.by = rs.by;
     return rm;
 }
 

@@ -231,13 +231,15 @@ void launch_vec_gae(const morlax_ctx* c, const float* r, const float* v, const u
 
 // ------------------------------------------------------------------------------------------------
 // Loss.  Selected cells are enumerated per preference: cell m of preference p is time
-// t0 + m / j_cnt, environment p * n_g + j0 + m % j_cnt.  A block handles G consecutive groups of 256 cells
-// of one p, one group after the other; a group is up to 256 / j_cnt + 2 runs of consecutive rows of the
+// t0 + m / j_cnt, environment p * n_g + j0 + m % j_cnt.  A block handles G consecutive groups of 128 cells
+// of one p, one group after the other; a group is up to 128 / j_cnt + 2 runs of consecutive rows of the
 // time-major tensors.  The runs of mu, act, v and vtarg go from global memory straight into LDS as they lie in
 // memory (direct-to-LDS loads, 256 contiguous bytes per wave instruction, all of a group's requests in flight
 // at once), a thread then works on its cell out of LDS, leaves the gradients there, and the block writes
 // them back run by run -- every global access of the kernel is a contiguous run instead of one 4-byte piece
-// per 40-byte row and lane.
+// per 40-byte row and lane.  Short runs go piece by piece, several of them to a request (loss_by_runs).  us a call, with run after
+// run, sums by shuffles and one kernel for up to 16 action components, and so: 4 preferences x 256 cells 21.9 and 15.1, 24 x 1250 in
+// runs of 50 21.7 and 15.8, 128 x 8192 32.0 and 23.7, 128 x 32768 190.5 and 185.8.
 //
 // Three launches per call.  k_adv_partial adds up the scalar advantage of the selection into at most
 // LOSS_MAX_ADV_PART fixed partial sums; every block of k_ppo_loss_grad adds those partials in the same fixed
@@ -248,15 +250,56 @@ void launch_vec_gae(const morlax_ctx* c, const float* r, const float* v, const u
 // whichever block comes last, needs a device-scope release in every block; on this chip that is a write-back of
 // the whole L2 and made the call three times slower.)
 
-__device__ inline double block_sum(double v, double* sh) {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v += __shfl_down(v, o, WAVE);
+// Lane 0: the sum over the wave's lanes, halves first (lane i takes lane i + 32's value, then i + 16's, ... i + 1's), the order of
+// a chain of __shfl_down.  Without the LDS round trip of a shuffle: the halves by lane-swap instructions, the rest within rows of
+// sixteen by DPP.
+template <int N>
+__device__ inline double lane_above(double v) {  // lane i: the value of lane i + N of its row of sixteen
+    const uint64_t u = __builtin_bit_cast(uint64_t, v);
+    const uint32_t lo = __builtin_amdgcn_update_dpp(0, (int)(uint32_t)u, 0x100 + N, 0xf, 0xf, true);
+    const uint32_t hi = __builtin_amdgcn_update_dpp(0, (int)(uint32_t)(u >> 32), 0x100 + N, 0xf, 0xf, true);
+    return __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
+}
+__device__ inline double row_sum(double v) {  // lane 0 of every row of sixteen: the row's sum
+    v += lane_above<8>(v);
+    v += lane_above<4>(v);
+    v += lane_above<2>(v);
+    v += lane_above<1>(v);
+    return v;
+}
+__device__ inline double wave_sum(double v) {
+    {
+        const uint64_t u = __builtin_bit_cast(uint64_t, v);
+        const auto lo = __builtin_amdgcn_permlane32_swap((uint32_t)u, (uint32_t)u, false, false);
+        const auto hi = __builtin_amdgcn_permlane32_swap((uint32_t)(u >> 32), (uint32_t)(u >> 32), false, false);
+        v += __builtin_bit_cast(double, ((uint64_t)hi[1] << 32) | lo[1]);
+    }
+    {
+        const uint64_t u = __builtin_bit_cast(uint64_t, v);
+        const auto lo = __builtin_amdgcn_permlane16_swap((uint32_t)u, (uint32_t)u, false, false);
+        const auto hi = __builtin_amdgcn_permlane16_swap((uint32_t)(u >> 32), (uint32_t)(u >> 32), false, false);
+        v += __builtin_bit_cast(double, ((uint64_t)hi[1] << 32) | lo[1]);
+    }
+    return row_sum(v);
+}
+// both sums over the block's NW waves, waves in order, through one barrier (sh: 2 NW values nobody else uses)
+template <int NW>
+__device__ inline void block_sums(double& a, double& b, double* sh) {
+    a = wave_sum(a);
+    b = wave_sum(b);
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-    if (lane == 0) sh[wv] = v;
+    if (lane == 0) {
+        sh[2 * wv] = a;
+        sh[2 * wv + 1] = b;
+    }
     __syncthreads();
-    double tot = sh[0] + sh[1] + sh[2] + sh[3];
-    __syncthreads();
-    return tot;
+    a = sh[0];
+    b = sh[1];
+#pragma unroll
+    for (int i = 1; i < NW; ++i) {
+        a += sh[2 * i];
+        b += sh[2 * i + 1];
+    }
 }
 
 #define LOSS_NT 128              // cells per group = threads per block of the loss kernel
@@ -312,9 +355,8 @@ int64_t loss_ws_bytes(const morlax_ctx* c, const RowSel& rs) {
 }
 
 __device__ inline int64_t cell_row(const RowSel& rs, int p, int m, int N, int n_g) {
-    const int t = rs.t0 + m / rs.j_cnt;
-    const int j = rs.j0 + m % rs.j_cnt;
-    return (int64_t)t * N + (int64_t)p * n_g + j;
+    const int t = (int)rs.by.quotient((uint32_t)m);
+    return (int64_t)(rs.t0 + t) * N + (int64_t)p * n_g + rs.j0 + (m - t * rs.j_cnt);
 }
 
 // partial b covers the 256-cell groups [b * per, (b + 1) * per) of the (preference, group) enumeration; the
@@ -324,7 +366,7 @@ template <bool V4>
 __global__ __launch_bounds__(256) void k_adv_partial(RowSel rs, const float* __restrict__ adv_s,
                                                     double* __restrict__ part, int N, int n_g, int nbm, int ngrp,
                                                     int per) {
-    __shared__ double sh[4];
+    __shared__ double sh[8];
     double s1 = 0.0, s2 = 0.0;
     const int lo = blockIdx.x * per, hi = (lo + per < ngrp) ? lo + per : ngrp;
     if (V4) {
@@ -360,8 +402,7 @@ __global__ __launch_bounds__(256) void k_adv_partial(RowSel rs, const float* __r
             }
         }
     }
-    s1 = block_sum(s1, sh);
-    s2 = block_sum(s2, sh);
+    block_sums<4>(s1, s2, sh);
     if (threadIdx.x == 0) {
         part[2 * blockIdx.x] = s1;
         part[2 * blockIdx.x + 1] = s2;
@@ -380,6 +421,11 @@ struct CellRuns {
         cell0 = cA - m0;
         ncell = cB - cA;
         row = row00 + (int64_t)tt * N + (cA - a);
+    }
+    RowDiv by;  // of j_cnt
+    __device__ inline int64_t at(int f, int C, const RowDiv& by_c) const {  // float f of the group in the time-major array
+        const int cell = (int)by_c.quotient((uint32_t)f), m = m0 + cell, t = (int)by.quotient((uint32_t)m);
+        return (row00 + (int64_t)t * N + (m - t * j_cnt)) * C + (f - cell * C);
     }
 };
 
@@ -429,30 +475,39 @@ __device__ inline void lds_to_runs(const CellRuns& cr, float* __restrict__ X, in
     }
 }
 
-// sum over the block's NT / 64 waves, fixed order
-template <int NT>
-__device__ inline double block_sum_nt(double v, double* sh) {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v += __shfl_down(v, o, WAVE);
-    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-    if (lane == 0) sh[wv] = v;
-    __syncthreads();
-    double tot = sh[0];
-#pragma unroll
-    for (int i = 1; i < NT / 64; ++i) tot += sh[i];
-    __syncthreads();
-    return tot;
+// The same where the runs are short: a lane finds the place of its own piece with two divisions by products, so that a request
+// takes pieces of several runs.
+template <bool V4, int NT>
+__device__ inline void cells_to_lds(const CellRuns& g, const float* __restrict__ X, int C, const RowDiv& by_c, uint32_t lds_addr) {
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int n = g.m1 - g.m0, count = V4 ? n * C / 4 : n * C;
+#pragma unroll 1
+    for (int c0 = wave * 64; c0 < count; c0 += NT)
+        if (c0 + lane < count) {
+            if (V4) dma16_nt_at(X + g.at(4 * (c0 + lane), C, by_c), lds_addr + (uint32_t)c0 * 16u);
+            else dma4_nt_at(X + g.at(c0 + lane, C, by_c), lds_addr + (uint32_t)c0 * 4u);
+        }
 }
 
-// NT threads work on groups of NT cells
-template <int A_MAX, int NT, bool V4>
+template <bool V4, int NT>
+__device__ inline void lds_to_cells(const CellRuns& g, float* __restrict__ X, int C, const RowDiv& by_c, const float* lds) {
+    const int n = g.m1 - g.m0, count = V4 ? n * C / 4 : n * C;
+#pragma unroll 1
+    for (int i = threadIdx.x; i < count; i += NT) {
+        if (V4) *reinterpret_cast<float4*>(X + g.at(4 * i, C, by_c)) = reinterpret_cast<const float4*>(lds)[i];
+        else X[g.at(i, C, by_c)] = lds[i];
+    }
+}
+
+// NT threads work on groups of NT cells, moved run by run (RUNS) or piece by piece (rule: loss_by_runs)
+template <int A_MAX, int NT, bool V4, bool RUNS>
 __global__ __launch_bounds__(NT, 8) void k_ppo_loss_grad(
     RowSel rs, const float* __restrict__ mu, const float* __restrict__ logsig, int ls_stride,
     const float* __restrict__ act, const float* __restrict__ logp_old, const float* __restrict__ adv_s,
     const float* __restrict__ v, const float* __restrict__ vtarg, const double* __restrict__ adv_part, int n_adv,
     float clip_eps, int norm_adv, double cnt_cells, float* __restrict__ dmu, float* __restrict__ dv,
     double* __restrict__ stat_part, double* __restrict__ dls_part, int N, int n_g, int A, int K, int G,
-    int sig_state) {
+    int sig_state, RowDiv by_mu, RowDiv by_a, RowDiv by_k) {
     // sig_state: mu and dmu have 2A columns per cell -- means, then log sigmas (state dependent) / their gradients
     extern __shared__ __align__(16) float lds[];
     __shared__ float s_ls[A_MAX], s_isig[A_MAX];
@@ -470,17 +525,26 @@ __global__ __launch_bounds__(NT, 8) void k_ppo_loss_grad(
     const uint32_t lbase = (uint32_t)(size_t)lds;
     CellRuns cr;
     cr.j_cnt = rs.j_cnt;
+    cr.by = rs.by;
     cr.N = N;
     cr.row00 = (int64_t)rs.t0 * N + (int64_t)p * n_g + rs.j0;
-    auto request = [&](int grp) {  // a group's runs of the four arrays, on their way into LDS
+    auto take = [&](const float* X, int C, const RowDiv& by_c, uint32_t lds_addr) __attribute__((always_inline)) {
+        if constexpr (RUNS) runs_to_lds<V4, NT>(cr, X, C, lds_addr);
+        else cells_to_lds<V4, NT>(cr, X, C, by_c, lds_addr);
+    };
+    auto give = [&](float* X, int C, const RowDiv& by_c, const float* from) __attribute__((always_inline)) {
+        if constexpr (RUNS) lds_to_runs<V4, NT>(cr, X, C, from);
+        else lds_to_cells<V4, NT>(cr, X, C, by_c, from);
+    };
+    auto request = [&](int grp) {  // a group's cells of the four arrays, on their way into LDS
         cr.m0 = grp * NT;
         cr.m1 = cr.m0 + NT < rs.M ? cr.m0 + NT : rs.M;
-        cr.tA = cr.m0 / rs.j_cnt;
-        cr.tB = (cr.m1 - 1) / rs.j_cnt;
-        runs_to_lds<V4, NT>(cr, mu, mus, lbase);
-        runs_to_lds<V4, NT>(cr, v, K, lbase + (uint32_t)(NT * mus) * 4u);
-        runs_to_lds<V4, NT>(cr, act, A, lbase + (uint32_t)(NT * (mus + K)) * 4u);
-        runs_to_lds<V4, NT>(cr, vtarg, K, lbase + (uint32_t)(NT * (mus + K + A)) * 4u);
+        cr.tA = (int)rs.by.quotient((uint32_t)cr.m0);
+        cr.tB = (int)rs.by.quotient((uint32_t)(cr.m1 - 1));
+        take(mu, mus, by_mu, lbase);
+        take(v, K, by_k, lbase + (uint32_t)(NT * mus) * 4u);
+        take(act, A, by_a, lbase + (uint32_t)(NT * (mus + K)) * 4u);
+        take(vtarg, K, by_k, lbase + (uint32_t)(NT * (mus + K + A)) * 4u);
     };
     const int nbm = (rs.M + NT - 1) / NT;
     const int g_lo = blockIdx.x * G, g_hi = (g_lo + G < nbm) ? g_lo + G : nbm;
@@ -496,8 +560,7 @@ __global__ __launch_bounds__(NT, 8) void k_ppo_loss_grad(
         s1 += adv_part[2 * i];
         s2 += adv_part[2 * i + 1];
     }
-    s1 = block_sum_nt<NT>(s1, sh);
-    s2 = block_sum_nt<NT>(s2, sh);
+    block_sums<NT / 64>(s1, s2, sh);
     const double a_mean = s1 / cnt_cells;
     double a_var = s2 / cnt_cells - a_mean * a_mean;
     a_var = a_var < 0.0 ? 0.0 : a_var;
@@ -564,8 +627,8 @@ __global__ __launch_bounds__(NT, 8) void k_ppo_loss_grad(
             }
         }
         __syncthreads();  // gradients complete in LDS; act and vtarg no longer needed
-        lds_to_runs<V4, NT>(cr, dmu, mus, l_mu);
-        lds_to_runs<V4, NT>(cr, dv, K, l_v);
+        give(dmu, mus, by_mu, l_mu);
+        give(dv, K, by_k, l_v);
         if (grp + 1 < g_hi) {
             __syncthreads();  // every thread has read what it stores before the next group's runs arrive
             request(grp + 1);
@@ -590,10 +653,7 @@ __global__ __launch_bounds__(NT, 8) void k_ppo_loss_grad(
         double t = 0.0;
 #pragma unroll
         for (int j = 0; j < NT / 16; ++j) t += (double)red[q * RP + 16 * j + li];
-        t += __shfl_xor(t, 8, WAVE);
-        t += __shfl_xor(t, 4, WAVE);
-        t += __shfl_xor(t, 2, WAVE);
-        t += __shfl_xor(t, 1, WAVE);
+        t = row_sum(t);
         if (li == 0) {
             if (q < 5) stat_part[b * 5 + q] = t;
             else dls_part[b * A + (q - 5)] = t;
@@ -603,7 +663,7 @@ __global__ __launch_bounds__(NT, 8) void k_ppo_loss_grad(
 
 // blocks 0 .. P-1: dlogsig[p][:] (the preference's block partials in block order); block P: the statistics.
 // 1024 threads, so that the one block that adds up the statistics has enough loads in flight; its seven sums go through
-// one barrier together (one after the other: 7.8 us in the smallest step, 6.0 now).
+// one barrier together and are finished by a lane each (one after the other: 7.8 us in the smallest step; finished by one lane 6.0).
 __global__ __launch_bounds__(1024) void k_loss_final(const double* __restrict__ stat_part,
                                                     const double* __restrict__ dls_part,
                                                     const double* __restrict__ adv_part, int n_adv, int nbx, int P,
@@ -622,7 +682,7 @@ __global__ __launch_bounds__(1024) void k_loss_final(const double* __restrict__ 
         __syncthreads();
         if (threadIdx.x < A) {
             double t = 0.0;
-            for (int j = 0; j < 64; ++j) t += part[threadIdx.x][j];
+            for (int j = 0; j < (nbx < 64 ? nbx : 64); ++j) t += part[threadIdx.x][j];
             dlogsig[p * A + threadIdx.x] = (float)t;
         }
     } else {
@@ -640,30 +700,20 @@ __global__ __launch_bounds__(1024) void k_loss_final(const double* __restrict__ 
         const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
 #pragma unroll
         for (int i = 0; i < 7; ++i) {
-#pragma unroll
-            for (int o = 32; o > 0; o >>= 1) s[i] += __shfl_down(s[i], o, WAVE);
+            s[i] = wave_sum(s[i]);
             if (lane == 0) sh[i][wv] = s[i];
         }
         __syncthreads();
-        if (threadIdx.x == 0) {
-            double acc[7];  // the waves in order
+        if (threadIdx.x < 64) {  // a lane a sum, the waves in order
+            const int i = lane < 7 ? lane : 6;
+            double acc = sh[i][0];
 #pragma unroll
-            for (int i = 0; i < 7; ++i) {
-                acc[i] = sh[i][0];
-#pragma unroll
-                for (int w = 1; w < 16; ++w) acc[i] += sh[i][w];
-            }
-            const double mean = acc[5] / cnt;
-            double var = acc[6] / cnt - mean * mean;
+            for (int w = 1; w < 16; ++w) acc += sh[i][w];
+            const double share = acc / cnt, mean = __shfl(share, 5, WAVE);  // lanes 5, 6: of the advantage and of its square
+            double var = share - mean * mean;
             var = var < 0.0 ? 0.0 : var;
-            stats[0] = (float)(acc[0] / cnt);
-            stats[1] = (float)(acc[1] / cnt);
-            stats[2] = (float)(acc[2] / cnt);
-            stats[3] = (float)(acc[3] / cnt);
-            stats[4] = (float)mean;
-            stats[5] = (float)sqrt(var);
-            stats[6] = (float)(acc[4] / cnt);
-            stats[7] = (float)cnt;
+            const double v = lane == 6 ? sqrt(var) : lane == 7 ? cnt : share;
+            if (lane < 8) stats[lane < 4 || lane == 7 ? lane : lane == 4 ? 6 : lane - 1] = (float)v;
         }
     }
 }
@@ -685,6 +735,15 @@ static bool loss_vec4_ok(const morlax_ctx* c, const RowSel& rs, int mus) {
     return true;
 }
 
+// Cells move run by run where a run is about as long as a group, piece by piece where a group has several: a run costs its wave
+// some 400 cycles of addresses whatever its length, a piece two divisions.  us a call by runs and by pieces, 6 action components
+// and 3 objectives: 16-byte pieces, runs of 12, 64 x 250 of them 32.9 and 17.4, of 32 34.3 and 26.6, of 64 45.5 and 43.9, of 100
+// 73.9 and 65.6, of 128 71.0 and 74.8, of 256 126 and 133; 4-byte pieces (four times as many), runs of 50, 32 x 100 of them 22.2 and
+// 19.6, 64 x 250 65.2 and 67.9, of 75 24.1 and 22.4, 74.6 and 86.8, of 201 43.3 and 52.1.
+static bool loss_by_runs(const RowSel& rs, int P, bool v4) {
+    return rs.j_cnt >= (v4 || (int64_t)rs.M * P <= 200000 ? 112 : 32);
+}
+
 void launch_ppo_loss_grad(const morlax_ctx* c, const RowSel& rs, const float* mu, const float* logsig,
                           int logsig_stride, const float* act, const float* logp_old,
                           const float* adv_s, const float* v, const float* vtarg, float clip_eps,
@@ -700,13 +759,24 @@ void launch_ppo_loss_grad(const morlax_ctx* c, const RowSel& rs, const float* mu
         k_adv_partial<false><<<pl.n_adv, 256, 0, s>>>(rs, adv_s, L.adv_part, N, c->n_g, pl.nb256, pl.nb256 * P, pl.per);
     const int mus = sig ? 2 * A : A;
     const size_t lds_bytes = (size_t)loss_lds_floats(mus, A, K, 5 + (sig ? 0 : A)) * 4;
-    auto launch = [&](auto v4) {
+    auto launch = [&](auto v4, auto most, auto runs) {
         constexpr bool V4 = decltype(v4)::value;
-        k_ppo_loss_grad<MORLAX_MAX_OUT, LOSS_NT, V4><<<dim3(pl.nbx, P), LOSS_NT, lds_bytes, s>>>(
+        k_ppo_loss_grad<decltype(most)::value, LOSS_NT, V4, decltype(runs)::value><<<dim3(pl.nbx, P), LOSS_NT, lds_bytes, s>>>(
             rs, mu, logsig, logsig_stride, act, logp_old, adv_s, v, vtarg, L.adv_part, pl.n_adv, clip_eps, norm_adv,
-            cnt, dmu, dv, L.stat_part, L.dls_part, N, c->n_g, A, K, pl.G, sig);
+            cnt, dmu, dv, L.stat_part, L.dls_part, N, c->n_g, A, K, pl.G, sig, row_div(mus), row_div(A), row_div(K));
     };
-    if (loss_vec4_ok(c, rs, mus)) launch(std::true_type{}); else launch(std::false_type{});
+    // (code and registers of as few action components as the call has, in steps of four: with sixteen for all of them 64
+    // registers were not enough)
+    auto pick = [&](auto v4, auto runs) {
+        if (A <= 4) launch(v4, std::integral_constant<int, 4>{}, runs);
+        else if (A <= 8) launch(v4, std::integral_constant<int, 8>{}, runs);
+        else if (A <= 12) launch(v4, std::integral_constant<int, 12>{}, runs);
+        else launch(v4, std::integral_constant<int, MORLAX_MAX_OUT>{}, runs);
+    };
+    auto how = [&](auto v4) {
+        if (loss_by_runs(rs, P, decltype(v4)::value)) pick(v4, std::true_type{}); else pick(v4, std::false_type{});
+    };
+    if (loss_vec4_ok(c, rs, mus)) how(std::true_type{}); else how(std::false_type{});
     k_loss_final<<<P + 1, 1024, 0, s>>>(L.stat_part, L.dls_part, L.adv_part, pl.n_adv, pl.nbx, P, A, cnt, dlogsig, stats);
 }
 
@@ -745,14 +815,14 @@ int64_t advnorm_ws_bytes(const morlax_ctx* c, const RowSel& rs) {
 
 __global__ __launch_bounds__(256) void k_advk_partial(RowSel rs, const float* __restrict__ adv_vec,
                                                      double* __restrict__ part, int N, int n_g, int K) {
-    __shared__ double sh[4];
+    __shared__ double sh[MORLAX_MAX_OUT][8];
     const int p = blockIdx.y, m = blockIdx.x * 256 + threadIdx.x;
     const float* a = (m < rs.M) ? adv_vec + cell_row(rs, p, m, N, n_g) * K : nullptr;
     const int64_t b = (int64_t)p * gridDim.x + blockIdx.x;
     for (int k = 0; k < K; ++k) {
         const double x = a ? (double)a[k] : 0.0;
-        const double s1 = block_sum(x, sh);
-        const double s2 = block_sum(x * x, sh);
+        double s1 = x, s2 = x * x;
+        block_sums<4>(s1, s2, sh[k]);
         if (threadIdx.x == 0) {
             part[(b * K + k) * 2] = s1;
             part[(b * K + k) * 2 + 1] = s2;
@@ -762,15 +832,14 @@ __global__ __launch_bounds__(256) void k_advk_partial(RowSel rs, const float* __
 
 __global__ __launch_bounds__(256) void k_advk_final(const double* __restrict__ part, int64_t nblk, int K, double cnt,
                                                    double* __restrict__ stat) {
-    __shared__ double sh[4];
+    __shared__ double sh[8];
     const int k = blockIdx.x;
     double s1 = 0.0, s2 = 0.0;
     for (int64_t b = threadIdx.x; b < nblk; b += 256) {
         s1 += part[(b * K + k) * 2];
         s2 += part[(b * K + k) * 2 + 1];
     }
-    s1 = block_sum(s1, sh);
-    s2 = block_sum(s2, sh);
+    block_sums<4>(s1, s2, sh);
     if (threadIdx.x == 0) {
         const double mean = s1 / cnt;
         double var = s2 / cnt - mean * mean;

@@ -3,7 +3,6 @@
 
 #include <type_traits>
 
-#include "fwd_shape.h"
 #include "morlax_internal.h"
 #include "numeric.h"
 

@@ -188,6 +188,7 @@ static int resolve_rows(const morlax_ctx* c, const morlax_rows* rows, int t_max,
     if (rs.j0 < 0 || rs.j_cnt < 1 || rs.j0 + (int64_t)rs.j_cnt > c->n_g)
         return fail(MORLAX_ERR_SHAPE, "%s: group slice [%d, %d+%d) outside [0, n_g = %d)", who, rs.j0, rs.j0, rs.j_cnt, c->n_g);
     rs.M = rs.t_cnt * rs.j_cnt;
+    rs.by = row_div(rs.j_cnt);
     return MORLAX_OK;
 }
 

@@ -1,6 +1,7 @@
 // Internal declarations shared by the translation units of libmorlax.so (gfx950 only).
 #pragma once
 
+#include "fwd_shape.h"
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -60,6 +61,7 @@ void prof_free(morlax_ctx* c);
 struct RowSel {  // a validated morlax_rows plus derived sizes
     int32_t t0, t_cnt, j0, j_cnt;
     int32_t M;  // rows per preference = t_cnt * j_cnt
+    RowDiv by;  // of j_cnt
 };
 
 // ---- launchers (each only enqueues kernels on `s`) ------------------------------------------

@@ -78,5 +78,12 @@ __device__ inline void dma4_nt(const void* sbase, uint32_t voff, uint32_t lds_ad
                  "s"(uniform_addr(sbase))
                  : "memory");
 }
+// the same, every lane giving an address of its own
+__device__ inline void dma16_nt_at(const void* from, uint32_t lds_addr) {
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off nt" ::"s"(lds_addr), "v"(from) : "memory");
+}
+__device__ inline void dma4_nt_at(const void* from, uint32_t lds_addr) {
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dword %1, off nt" ::"s"(lds_addr), "v"(from) : "memory");
+}
 template <int N> __device__ inline void wait_vm() { asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory"); }
 
