@@ -6,15 +6,14 @@
 #include "morlax_internal.h"
 #include "numeric.h"
 
+#include <atomic>
 #include <type_traits>
 
 #define DAB_COLS 128  // columns of dW one block of the fused dA/dB kernel walks
 #define DAB_NCT (DAB_COLS / 64)
-#define DAB_MAX_CS (2048 / DAB_COLS)  // column runs of the widest layer
 
 struct HyperWs {
     float *h1, *f, *fac, *dfac, *df_part, *df, *dz2, *dz1, *vecs, *da_part;
-    int32_t *mrow, *crow;  // [q_total] offsets inside hparams of row q of the stacked affine matrix and of its constant
     int n_chunk, n_cs;
 };
 
@@ -28,7 +27,6 @@ static HyperWs hyper_ws_layout(const morlax_ctx* c, void* ws, int64_t* total) {
     const int64_t P = c->d.P, F = c->d.hyper_width;
     const bool affine = c->d.rank < 0;  // no factor vector: the leading stacked rows are theta_mat itself
     int64_t fac = affine ? 0 : (c->net[0].fac_len > c->net[1].fac_len ? c->net[0].fac_len : c->net[1].fac_len);
-    int64_t q = c->aff[0].q_total > c->aff[1].q_total ? c->aff[0].q_total : c->aff[1].q_total;
     HyperWs L;
     float* p = reinterpret_cast<float*>(ws);
     auto take = [&](int64_t n) { float* r = p; p += align_up(n, 64); return r; };
@@ -50,8 +48,6 @@ static HyperWs hyper_ws_layout(const morlax_ctx* c, void* ws, int64_t* total) {
         L.n_chunk = nc > L.n_chunk ? nc : L.n_chunk;
     }
     L.df_part = take((int64_t)L.n_chunk * P * F);
-    L.mrow = reinterpret_cast<int32_t*>(take(q));
-    L.crow = reinterpret_cast<int32_t*>(take(q));
     {
         int wmax = c->d.width > c->d.obs_dim ? c->d.width : c->d.obs_dim;
         L.n_cs = (wmax + DAB_COLS - 1) / DAB_COLS;
@@ -116,18 +112,87 @@ __global__ __launch_bounds__(64) void k_hyper_trunk(Trunk t, const float* __rest
     }
 }
 
-__device__ inline int find_seg(const AffineTable& at, int q) {
-    int s = 0;
-    while (s + 1 < at.n_seg && q >= at.q0[s + 1]) ++s;
-    return s;
+// Kernel arguments lie in host memory: the first use of each of their cache lines takes a workgroup about half a microsecond,
+// and a use whose place depends on another argument takes its own after that one's.  So what a workgroup looks up by its number
+// or its row is computed from arguments at fixed places, all of which are on their way at once.  us a call of hypernet_fwd, with
+// tables and searches and requests row by row, and so: 4 preferences of 2 x 32 12.6 and 10.8, 11 of 4 x 512 21.4 and 17.7, 128 106
+// and 96.
+
+// Offsets inside hparams of the rows of the stacked affine matrix and of their constants: row q of segment s reads M at m[s] + q F
+// and c at c[s] + q.  Segments behind the last one start beyond every row.
+struct AffineRows {
+    int32_t q_total;
+    int32_t q0[MORLAX_MAX_SEG], m[MORLAX_MAX_SEG], c[MORLAX_MAX_SEG];
+    __device__ inline void offsets(int F, int q, int32_t& mo, int32_t& co) const {
+        mo = m[0];
+        co = c[0];
+#pragma unroll
+        for (int s = 1; s < MORLAX_MAX_SEG; ++s) {
+            const bool in = q >= q0[s];
+            mo = in ? m[s] : mo;
+            co = in ? c[s] : co;
+        }
+        mo += q * F;
+        co += q;
+    }
+};
+static AffineRows affine_rows(const AffineTable& at, int F) {
+    AffineRows r;
+    r.q_total = at.q_total;
+    for (int s = 0; s < MORLAX_MAX_SEG; ++s) {
+        const bool in = s < at.n_seg;
+        r.q0[s] = in ? at.q0[s] : INT32_MAX;
+        r.m[s] = in ? (int32_t)(at.hp_m[s] - (int64_t)at.q0[s] * F) : 0;
+        r.c[s] = in ? (int32_t)at.hp_c[s] - at.q0[s] : 0;
+    }
+    return r;
 }
 
-// offsets inside hparams of row q of the stacked affine matrix and of its constant
-__device__ inline void row_offsets(const AffineTable& at, int F, int q, int32_t& m, int32_t& c) {
-    const int s = find_seg(at, q), loc = q - at.q0[s];
-    m = (int32_t)at.hp_m[s] + loc * F;
-    c = (int32_t)at.hp_c[s] + loc;
+// Where the layers of a network are: the first, the first of the square ones with the distance to the next, the output layer.
+// (All offsets inside hparams, theta_mat and the factor vector of a preference stay below 2^31.)
+struct LayerPlace { int32_t d_out, d_in, hp_w0, mat, fac_a, fac_b; };
+struct LayerRule {
+    LayerPlace first, hidden, last;
+    int32_t hp_step, mat_step, fac_step, n_hidden;  // hidden layers 1 .. n_hidden - 1 are square
+    __device__ inline LayerPlace at(int l) const {
+        LayerPlace p = l == 0 ? first : l < n_hidden ? hidden : last;
+        const int k = l > 0 && l < n_hidden ? l - 1 : 0;
+        p.hp_w0 += k * hp_step;
+        p.mat += k * mat_step;
+        p.fac_a += k * fac_step;
+        p.fac_b += k * fac_step;
+        return p;
+    }
+};
+static LayerRule layer_rule(const NetDev& nd) {
+    auto place = [&](int l) {
+        const LayerDev& L = nd.layer[l];
+        return LayerPlace{L.d_out, L.d_in, (int32_t)L.hp_w0, (int32_t)L.mat_off, (int32_t)L.fac_a, (int32_t)L.fac_b};
+    };
+    const int L = nd.n_layers - 1;
+    LayerRule r = {place(0), place(1), place(L), 0, 0, 0, L};  // (one hidden layer: `hidden` is not used)
+    if (L > 2) {
+        r.hp_step = (int32_t)(nd.layer[2].hp_w0 - nd.layer[1].hp_w0);
+        r.mat_step = (int32_t)(nd.layer[2].mat_off - nd.layer[1].mat_off);
+        r.fac_step = (int32_t)(nd.layer[2].fac_a - nd.layer[1].fac_a);
+    }
+    return r;
 }
+// Items of a kernel that takes n0 of the first layer, nh of every square one, the rest of the output layer: item -> layer, item of it
+struct LayerItems {
+    int32_t n0, nh;
+    RowDiv by_nh;
+    __device__ inline int layer(const LayerRule& r, int item, int& rest) const {
+        if (item < n0) {
+            rest = item;
+            return 0;
+        }
+        const int y = item - n0, q = nh > 0 ? (int)by_nh.quotient((uint32_t)y) : 0, k = q < r.n_hidden - 1 ? q : r.n_hidden - 1;
+        rest = y - k * nh;
+        return 1 + k;
+    }
+};
+static LayerItems layer_items(int n0, int nh) { return {n0, nh, row_div(nh > 0 ? nh : 1)}; }
 
 struct __attribute__((packed, aligned(4))) Run4 { float v[4]; };  // four consecutive floats at any 4-byte boundary
 
@@ -157,7 +222,7 @@ __device__ inline void put_run4(bf16_t* d, const float (&v)[4]) {
 // TRUNK: every workgroup forms the features f(w) of all preferences itself (in LDS; the first one leaves them and h1 for
 // the backward pass), which with few of them costs less than the launch in front that it replaces (rule: trunk_fwd_inside).
 template <typename TF, int KS, bool TRUNK>  // TF: type of the leading rows' destination (float factors, or theta_mat: strictly affine form)
-__global__ __launch_bounds__(256) void k_hyper_affine(AffineTable at, Trunk tk, const float* __restrict__ hp,
+__global__ __launch_bounds__(256) void k_hyper_affine(AffineRows at, Trunk tk, const float* __restrict__ hp,
                                                      const float* __restrict__ f, TF* __restrict__ fac,
                                                      float* __restrict__ theta_vec, int P, int F,
                                                      int64_t fac_len, int64_t vec_len) {
@@ -167,11 +232,12 @@ __global__ __launch_bounds__(256) void k_hyper_affine(AffineTable at, Trunk tk, 
     __shared__ int32_t so[64];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, ln = lane & 15, kg = lane >> 4;
     const int q0 = blockIdx.x * 64, q4 = q0 + 4 * ln;
+    float cv = 0.f;
     if (threadIdx.x < 64) {  // (rows past the end repeat the last one; they are not stored)
         int32_t m, c;
-        row_offsets(at, F, q0 + lane < at.q_total ? q0 + lane : at.q_total - 1, m, c);
+        at.offsets(F, q0 + lane < at.q_total ? q0 + lane : at.q_total - 1, m, c);
         so[lane] = m;
-        sc[lane] = hp[c];
+        cv = hp[c];
     }
     extern __shared__ float tl[];  // TRUNK: Wh2 [F][F + 1], h1 [P][F], f [P][F]
     const float* fs = f;
@@ -181,8 +247,6 @@ __global__ __launch_bounds__(256) void k_hyper_affine(AffineTable at, Trunk tk, 
         const float* fp = fs + (int64_t)(p0 + ln < P ? p0 + ln : P - 1) * F;
 #pragma unroll
         for (int k = 0; k < KS; ++k) a[k] = fp[4 * k + kg < F ? 4 * k + kg : 0];
-#pragma unroll
-        for (int k = 0; k < KS; ++k) a[k] = 4 * k + kg < F ? a[k] : 0.f;
     };
     if (!TRUNK && 16 * wave < P) load_f(16 * wave);
     __syncthreads();
@@ -202,6 +266,7 @@ __global__ __launch_bounds__(256) void k_hyper_affine(AffineTable at, Trunk tk, 
             const int idx = threadIdx.x + 256 * i, k = idx % K4;
             sm[idx / K4][k] = k < F ? v[i] : 0.f;
         }
+        if (threadIdx.x < 64) sc[lane] = cv;
     }
     __syncthreads();
     float b[4][KS];
@@ -211,6 +276,10 @@ __global__ __launch_bounds__(256) void k_hyper_affine(AffineTable at, Trunk tk, 
         for (int k = 0; k < KS; ++k) b[j][k] = sm[4 * ln + j][4 * k + kg];
     const bool lead = q4 + 3 < fac_len, vec = q4 >= fac_len && q4 + 3 < at.q_total;
     for (int p0 = 16 * wave; p0 < P; p0 += 64) {
+        if (F < K4) {  // (masked here and not where they are requested: nobody waits for them before)
+#pragma unroll
+            for (int k = 0; k < KS; ++k) a[k] = 4 * k + kg < F ? a[k] : 0.f;
+        }
         float4_t acc[4];
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
@@ -254,8 +323,9 @@ __global__ __launch_bounds__(256) void k_hyper_affine(AffineTable at, Trunk tk, 
 static bool trunk_fwd_inside(int P, int F, int workgroups) { return P * F <= 512 && workgroups <= (F <= 32 ? 1024 : 512); }
 static bool trunk_bwd_inside(int P, int F, int n_chunk) { return P * F <= 512 && (int64_t)n_chunk * (P * F) * (P * F) <= 20 << 20; }
 template <typename TF>
-static void launch_trunk_affine(const AffineTable& at, const Trunk& tk, const float* hp, TF* fac, float* theta_vec, int P, int F,
+static void launch_trunk_affine(const AffineTable& table, const Trunk& tk, const float* hp, TF* fac, float* theta_vec, int P, int F,
                                 int64_t fac_len, int64_t vec_len, hipStream_t s) {
+    const AffineRows at = affine_rows(table, F);
     const int nb = (at.q_total + 63) / 64;
     auto run = [&](auto ks) {
         constexpr int KS = decltype(ks)::value;
@@ -291,77 +361,83 @@ static void launch_trunk_affine(const AffineTable& at, const Trunk& tk, const fl
 // 256, here 8.3, 12.9 and 9.8 for 32; 91.6 for 128 of 4 x 512, the same here: 48 for the stores alone, W0 (twice the
 // results' bytes, from the caches) and the factors on top.  (W0 shared by two preferences in registers: 101; a
 // preference's tiles on one die: 120.)
-struct MatTiles {
-    int32_t tile0[MORLAX_MAX_LAYERS + 1];  // first tile id of each layer
-    int32_t tiles_i[MORLAX_MAX_LAYERS];    // tiles along d_in
-};
-
 template <typename T, int KS>
-__global__ __launch_bounds__(256) void k_hyper_materialize(NetDev nd, MatTiles mt, const float* __restrict__ hp,
-                                                          const float* __restrict__ fac, T* __restrict__ theta_mat, int r) {
+__global__ __launch_bounds__(256) void k_hyper_materialize(LayerRule lr, LayerItems tiles, RowDiv by_ti0, RowDiv by_ti, const float* __restrict__ hp,
+                                                          const float* __restrict__ fac, T* __restrict__ theta_mat, int r,
+                                                          int64_t fac_len, int64_t mat_len) {
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, ln = lane & 15, kg = lane >> 4;
     const int p = blockIdx.y;
-    int l = 0;
-    while (l + 1 < nd.n_layers && (int)blockIdx.x >= mt.tile0[l + 1]) ++l;
-    const LayerDev L = nd.layer[l];
-    const int tl = blockIdx.x - mt.tile0[l];
-    const int o0 = (tl / mt.tiles_i[l]) * 64 + 16 * wave, i0 = (tl % mt.tiles_i[l]) * 128 + 8 * ln;
+    int tl;
+    const int l = tiles.layer(lr, blockIdx.x, tl);
+    const LayerPlace L = lr.at(l);
+    const int ti = (L.d_in + 127) / 128, to = (int)(l == 0 ? by_ti0 : by_ti).quotient((uint32_t)tl);  // tiles along d_in
+    const int o0 = to * 64 + 16 * wave, i0 = (tl - to * ti) * 128 + 8 * ln;
     if (o0 >= L.d_out) return;
     const int oa = o0 + ln < L.d_out ? o0 + ln : L.d_out - 1;  // row of A this lane feeds
-    // the lane's columns i0 .. i0 + 7 of a row, zero beyond the matrix
-    auto row8 = [&](const float* row, bool ok, float (&v)[8]) {
+    const float* fp = fac + (int64_t)p * fac_len;
+    T* dst = theta_mat + (int64_t)p * mat_len + L.mat;
+    // WHOLE: rows of a multiple of four columns, so that four consecutive ones are either all in the matrix or all beyond it.  (With
+    // both kinds of requests in branches of their own, as they are here for other rows, the compiler waits for one row before it
+    // requests the next.)
+    auto tile = [&](auto whole) __attribute__((always_inline)) {
+        constexpr bool WHOLE = decltype(whole)::value;
+        // the lane's columns i0 .. i0 + 7 of a row; what lies beyond the matrix is not stored
+        auto row8 = [&](const float* row, float (&v)[8]) __attribute__((always_inline)) {
 #pragma unroll
-        for (int h = 0; h < 2; ++h) {
-            const int i = i0 + 4 * h;
-            if (i + 4 <= L.d_in) {
-                const Run4 q = *reinterpret_cast<const Run4*>(row + i);
+            for (int h = 0; h < 2; ++h) {
+                const int i = i0 + 4 * h;
+                if (WHOLE || i + 4 <= L.d_in) {
+                    const Run4 q = *reinterpret_cast<const Run4*>(row + (!WHOLE || i < L.d_in ? i : 0));
 #pragma unroll
-                for (int e = 0; e < 4; ++e) v[4 * h + e] = ok ? q.v[e] : 0.f;
+                    for (int e = 0; e < 4; ++e) v[4 * h + e] = q.v[e];
+                } else {
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) v[4 * h + e] = i + e < L.d_in ? row[i + e] : 0.f;
+                }
+            }
+        };
+        float w0[4][8];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const int o = o0 + 4 * kg + e;
+            row8(hp + L.hp_w0 + (int64_t)(o < L.d_out ? o : L.d_out - 1) * L.d_in, w0[e]);
+        }
+        float a[KS + 1], b[KS + 1][8];  // (KS = 0, rank 0: W0 alone, there are no factors to read)
+#pragma unroll
+        for (int s = 0; s < KS; ++s) {
+            const int k = 4 * s + kg, kc = k < r ? k : 0;
+            a[s] = fp[L.fac_a + (int64_t)oa * r + kc];
+            row8(fp + L.fac_b + (int64_t)kc * L.d_in, b[s]);
+        }
+        float4_t acc[8];
+#pragma unroll
+        for (int j = 0; j < 8; ++j) acc[j] = float4_t{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int s = 0; s < KS; ++s) {
+            const bool in = 4 * s + kg < r;  // (both factors: an infinite one beyond the rank would leave an undefined product)
+            a[s] = in ? a[s] : 0.f;
+#pragma unroll
+            for (int j = 0; j < 8; ++j) acc[j] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[s], in ? b[s][j] : 0.f, acc[j], 0, 0, 0);
+        }
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const int o = o0 + 4 * kg + e;
+            if (o >= L.d_out) continue;
+            T* d = dst + (int64_t)o * L.d_in + i0;
+            float v[8];
+#pragma unroll
+            for (int j = 0; j < 8; ++j) v[j] = w0[e][j] + acc[j][e];
+            if (i0 + 8 <= L.d_in && L.d_in % 8 == 0) {
+                store8(d, v);
             } else {
 #pragma unroll
-                for (int e = 0; e < 4; ++e) v[4 * h + e] = ok && i + e < L.d_in ? row[i + e] : 0.f;
+                for (int j = 0; j < 8; ++j)
+                    if (i0 + j < L.d_in) d[j] = cvt<T>(v[j]);
             }
         }
     };
-    float w0[4][8];
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-        const int o = o0 + 4 * kg + e;
-        row8(hp + L.hp_w0 + (int64_t)(o < L.d_out ? o : L.d_out - 1) * L.d_in, true, w0[e]);
-    }
-    const float* fp = fac + (int64_t)p * nd.fac_len;
-    float a[KS + 1], b[KS + 1][8];  // (KS = 0, rank 0: W0 alone, there are no factors to read)
-#pragma unroll
-    for (int s = 0; s < KS; ++s) {
-        const int k = 4 * s + kg, kc = k < r ? k : 0;
-        a[s] = fp[L.fac_a + (int64_t)oa * r + kc];
-        a[s] = k < r ? a[s] : 0.f;
-        row8(fp + L.fac_b + (int64_t)kc * L.d_in, k < r, b[s]);
-    }
-    float4_t acc[8];
-#pragma unroll
-    for (int j = 0; j < 8; ++j) acc[j] = float4_t{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-    for (int s = 0; s < KS; ++s)
-#pragma unroll
-        for (int j = 0; j < 8; ++j) acc[j] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[s], b[s][j], acc[j], 0, 0, 0);
-    T* dst = theta_mat + (int64_t)p * nd.mat_len + L.mat_off;
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-        const int o = o0 + 4 * kg + e;
-        if (o >= L.d_out) continue;
-        T* d = dst + (int64_t)o * L.d_in + i0;
-        float v[8];
-#pragma unroll
-        for (int j = 0; j < 8; ++j) v[j] = w0[e][j] + acc[j][e];
-        if (i0 + 8 <= L.d_in && L.d_in % 8 == 0) {
-            store8(d, v);
-        } else {
-#pragma unroll
-            for (int j = 0; j < 8; ++j)
-                if (i0 + j < L.d_in) d[j] = cvt<T>(v[j]);
-        }
-    }
+    if (L.d_in % 4 == 0) tile(std::true_type{});
+    else tile(std::false_type{});
 }
 
 static Trunk trunk_of(const morlax_ctx* c, int net, const float* w, const HyperWs& L) {
@@ -373,18 +449,6 @@ static void run_trunk_and_affine(const morlax_ctx* c, int net, const float* hp, 
     const NetDev& nd = c->net[net];
     launch_trunk_affine<float>(c->aff[net], trunk_of(c, net, w, L), hp, L.fac, theta_vec, c->d.P, c->d.hyper_width, nd.fac_len,
                                nd.vec_len, s);
-}
-
-static MatTiles mat_tiles(const NetDev& nd) {
-    MatTiles mt;
-    int t = 0;
-    for (int l = 0; l < nd.n_layers; ++l) {
-        mt.tile0[l] = t;
-        mt.tiles_i[l] = (nd.layer[l].d_in + 127) / 128;
-        t += mt.tiles_i[l] * ((nd.layer[l].d_out + 63) / 64);
-    }
-    mt.tile0[nd.n_layers] = t;
-    return mt;
 }
 
 void launch_hypernet_fwd(const morlax_ctx* c, int net, const float* hparams, const float* w,
@@ -403,16 +467,22 @@ void launch_hypernet_fwd(const morlax_ctx* c, int net, const float* hparams, con
         return;
     }
     run_trunk_and_affine(c, net, hparams, w, L, theta_vec, s);
-    MatTiles mt = mat_tiles(nd);
-    const dim3 grid(mt.tile0[nd.n_layers], c->d.P);
+    auto ti = [&](int l) { return (nd.layer[l].d_in + 127) / 128; };
+    auto tiles = [&](int l) { return ti(l) * ((nd.layer[l].d_out + 63) / 64); };
+    const int n_hidden = nd.n_layers - 1, th = n_hidden > 1 ? tiles(1) : 0;
+    const dim3 grid(tiles(0) + (n_hidden - 1) * th + tiles(n_hidden), c->d.P);
     const int r = c->d.rank;
     auto pick = [&](auto type) {
         typedef decltype(type) T;
         T* tm = reinterpret_cast<T*>(theta_mat);
-        if (r == 0) k_hyper_materialize<T, 0><<<grid, 256, 0, s>>>(nd, mt, hparams, L.fac, tm, r);
-        else if (r <= 8) k_hyper_materialize<T, 2><<<grid, 256, 0, s>>>(nd, mt, hparams, L.fac, tm, r);
-        else if (r <= 16) k_hyper_materialize<T, 4><<<grid, 256, 0, s>>>(nd, mt, hparams, L.fac, tm, r);
-        else k_hyper_materialize<T, 8><<<grid, 256, 0, s>>>(nd, mt, hparams, L.fac, tm, r);
+        auto run = [&](auto ks) {
+            k_hyper_materialize<T, decltype(ks)::value><<<grid, 256, 0, s>>>(layer_rule(nd), layer_items(tiles(0), th), row_div(ti(0)),
+                                                                         row_div(ti(1)), hparams, L.fac, tm, r, nd.fac_len, nd.mat_len);
+        };
+        if (r == 0) run(std::integral_constant<int, 0>{});
+        else if (r <= 8) run(std::integral_constant<int, 2>{});
+        else if (r <= 16) run(std::integral_constant<int, 4>{});
+        else run(std::integral_constant<int, 8>{});
     };
     if (c->d.wdtype == 1) pick(bf16_t{});
     else pick(float{});
@@ -421,47 +491,38 @@ void launch_hypernet_fwd(const morlax_ctx* c, int net, const float* hparams, con
 // ------------------------------------------------------------------------------------------------
 // Backward.
 
-// Offsets inside hparams of every row of the stacked affine matrix and of its constant (built once per call).
-__device__ inline void mrow_entry(const AffineTable& at, int32_t* __restrict__ mrow, int32_t* __restrict__ crow, int F, int q) {
-    if (q < at.q_total) row_offsets(at, F, q, mrow[q], crow[q]);
-}
-
 // dW0_l = sum_p dW_l(p): four consecutive elements per thread, p ascending.
-__device__ inline void dbase_block(const NetDev& nd, const float* __restrict__ dmat, float* __restrict__ dhp, int P, int blk) {
-    const int64_t e = ((int64_t)blk * 256 + threadIdx.x) * 4;
-    if (e >= nd.mat_len) return;
-    int l = 0;
-    while (l + 1 < nd.n_layers && e >= nd.layer[l + 1].mat_off) ++l;
+__device__ inline void dbase_block(const LayerRule& lr, const LayerItems& elems, int64_t mat_len, const float* __restrict__ dmat,
+                                   float* __restrict__ dhp, int P, int blk) {
+    const int e = (blk * 256 + (int)threadIdx.x) * 4;
+    if (e >= mat_len) return;
+    int at;
+    const int l = elems.layer(lr, e, at);
     float4 a = make_float4(0.f, 0.f, 0.f, 0.f);
     const float* src = dmat + e;
     int p = 0;
     for (; p + 8 <= P; p += 8) {  // eight preferences' loads in flight together
         float4 v[8];
 #pragma unroll
-        for (int u = 0; u < 8; ++u) v[u] = *reinterpret_cast<const float4*>(src + (int64_t)(p + u) * nd.mat_len);
+        for (int u = 0; u < 8; ++u) v[u] = *reinterpret_cast<const float4*>(src + (int64_t)(p + u) * mat_len);
 #pragma unroll
         for (int u = 0; u < 8; ++u) { a.x += v[u].x; a.y += v[u].y; a.z += v[u].z; a.w += v[u].w; }
     }
     for (; p < P; ++p) {
-        const float4 v = *reinterpret_cast<const float4*>(src + (int64_t)p * nd.mat_len);
+        const float4 v = *reinterpret_cast<const float4*>(src + (int64_t)p * mat_len);
         a.x += v.x; a.y += v.y; a.z += v.z; a.w += v.w;
     }
-    float* d = dhp + nd.layer[l].hp_w0 + (e - nd.layer[l].mat_off);
+    float* d = dhp + lr.at(l).hp_w0 + at;
     d[0] = a.x; d[1] = a.y; d[2] = a.z; d[3] = a.w;
 }
-struct BaseWork {  // blocks of 256 threads behind (or, where there are factors, among) those of k_hyper_dAB
-    int32_t n_dw0, n_rows;  // blocks that add up dW0, blocks that make the row offsets of the stacked affine matrix
+struct BaseWork {  // blocks of 256 threads that add up dW0: by themselves or, where there are factors, among those of k_hyper_dAB
     float* dhp;
-    int32_t *mrow, *crow;
-    int32_t F;
+    int64_t mat_len;
+    LayerItems elems;  // elements of theta_mat
+    uint64_t share;    // among others: base blocks a block, 2^32 times and rounded up (so all of them end up in front of the end)
 };
-__device__ inline void base_block(const NetDev& nd, const AffineTable& at, const BaseWork& bw, const float* __restrict__ dmat,
-                                  int P, int blk) {
-    if (blk < bw.n_dw0) dbase_block(nd, dmat, bw.dhp, P, blk);
-    else mrow_entry(at, bw.mrow, bw.crow, bw.F, (blk - bw.n_dw0) * 256 + threadIdx.x);
-}
-__global__ __launch_bounds__(256) void k_hyper_base(NetDev nd, AffineTable at, BaseWork bw, const float* __restrict__ dmat, int P) {
-    base_block(nd, at, bw, dmat, P, blockIdx.x);
+__global__ __launch_bounds__(256) void k_hyper_base(LayerRule lr, BaseWork bw, const float* __restrict__ dmat, int P) {
+    dbase_block(lr, bw.elems, bw.mat_len, dmat, bw.dhp, P, blockIdx.x);
 }
 
 // Fused dA / dB on fp32 MFMA, one pass over dW:
@@ -475,37 +536,32 @@ __global__ __launch_bounds__(256) void k_hyper_base(NetDev nd, AffineTable at, B
 // other finds in the memory-side cache (128 matrices of 512 x 512 are 134 of its 256 MB).  Preference by preference 183 us for
 // the 128, layer by layer 165; 22.5 and 19 for the 24, 25 and 22 for 32 of 3 x 256, rank 8.  (A wave on sixteen rows by itself,
 // operands four columns a lane, no barrier: 181 and 19.7.)
-struct DabWork {
-    int32_t n;
-    int16_t layer[DAB_MAX_CS * MORLAX_MAX_LAYERS];
-    int16_t cs[DAB_MAX_CS * MORLAX_MAX_LAYERS];
-};
-
 template <int RT>
-__global__ __launch_bounds__(256) void k_hyper_dAB(NetDev nd, DabWork wk, AffineTable at, BaseWork bw,
+__global__ __launch_bounds__(256) void k_hyper_dAB(LayerRule lr, LayerItems runs, RowDiv by_p, BaseWork bw,
                                                   const float* __restrict__ dmat, const float* __restrict__ fac,
-                                                  float* __restrict__ dfac, float* __restrict__ da_part, int r, int P) {
+                                                  float* __restrict__ dfac, float* __restrict__ da_part, int r, int P,
+                                                  int64_t fac_len) {
     constexpr int AP = 16 * RT + 4;
     __shared__ __align__(16) float sW[64][68];
     __shared__ float sA[64][AP];
     __shared__ float sB[DAB_NCT][16 * RT][68];
-    const int64_t n_base = bw.n_dw0 + bw.n_rows, before = n_base * blockIdx.x / gridDim.x;  // base blocks in front of this one
-    if (n_base * (blockIdx.x + 1) / gridDim.x != before) {
-        base_block(nd, at, bw, dmat, P, (int)before);
+    const int before = (int)(bw.share * blockIdx.x >> 32);  // base blocks in front of this one
+    if ((int)(bw.share * (blockIdx.x + 1) >> 32) != before) {
+        dbase_block(lr, bw.elems, bw.mat_len, dmat, bw.dhp, P, before);
         return;
     }
-    const int dab = blockIdx.x - (int)before, p = dab % P, item = dab / P;
-    const LayerDev L = nd.layer[wk.layer[item]];
-    const int cs = wk.cs[item];
+    const int dab = blockIdx.x - before, item = (int)by_p.quotient((uint32_t)dab), p = dab - item * P;
+    int cs;
+    const LayerPlace L = lr.at(runs.layer(lr, item, cs));
     const int c_lo = cs * DAB_COLS;
     const int c_hi = (L.d_in < c_lo + DAB_COLS) ? L.d_in : (c_lo + DAB_COLS);
     const int nct = (c_hi - c_lo + 63) / 64;
     const int n_cs = (L.d_in + DAB_COLS - 1) / DAB_COLS;
-    const float* dW = dmat + (int64_t)p * nd.mat_len + L.mat_off;
-    const float* Ap = fac + (int64_t)p * nd.fac_len + L.fac_a;
-    const float* Bp = fac + (int64_t)p * nd.fac_len + L.fac_b;
-    float* dAp = (n_cs > 1 ? da_part + ((int64_t)cs * P + p) * nd.fac_len : dfac + (int64_t)p * nd.fac_len) + L.fac_a;
-    float* dBp = dfac + (int64_t)p * nd.fac_len + L.fac_b;
+    const float* dW = dmat + (int64_t)p * bw.mat_len + L.mat;
+    const float* Ap = fac + (int64_t)p * fac_len + L.fac_a;
+    const float* Bp = fac + (int64_t)p * fac_len + L.fac_b;
+    float* dAp = (n_cs > 1 ? da_part + ((int64_t)cs * P + p) * fac_len : dfac + (int64_t)p * fac_len) + L.fac_a;
+    float* dBp = dfac + (int64_t)p * fac_len + L.fac_b;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, ln = lane & 15, kg = lane >> 4;
     const bool vec = (L.d_in % 4 == 0);
     float4_t accB[DAB_NCT][RT];
@@ -536,11 +592,6 @@ __global__ __launch_bounds__(256) void k_hyper_dAB(NetDev nd, DabWork wk, Affine
             regs[q] = v;
         }
     };
-    // the block's columns of B(p): the same for every row block
-    for (int idx = threadIdx.x; idx < DAB_NCT * 16 * RT * 64; idx += 256) {
-        const int ct = idx / (16 * RT * 64), k = (idx / 64) % (16 * RT), cc = idx % 64, i = c_lo + ct * 64 + cc;
-        sB[ct][k][cc] = (k < r && i < c_hi) ? Bp[(int64_t)k * L.d_in + i] : 0.f;
-    }
     // a row block's rows of A(p), requested one row block ahead
     constexpr int APT = 64 * 16 * RT / 256;
     float anx[APT];
@@ -554,6 +605,11 @@ __global__ __launch_bounds__(256) void k_hyper_dAB(NetDev nd, DabWork wk, Affine
     float4 nxt[4];
     fetch(0, nxt);
     fetch_a(0);
+    // the block's columns of B(p): the same for every row block
+    for (int idx = threadIdx.x; idx < DAB_NCT * 16 * RT * 64; idx += 256) {
+        const int ct = idx / (16 * RT * 64), k = (idx / 64) % (16 * RT), cc = idx % 64, i = c_lo + ct * 64 + cc;
+        sB[ct][k][cc] = (k < r && i < c_hi) ? Bp[(int64_t)k * L.d_in + i] : 0.f;
+    }
     for (int rb = 0; rb < nrb; ++rb) {
         const int o0 = rb * 64;
         __syncthreads();
@@ -671,22 +727,30 @@ __device__ inline float grad_row(const float* __restrict__ dfac, const float* __
 #define DMF_Q 64
 #define DMF_W 8             // waves of a workgroup
 #define DMF_P (16 * DMF_W)  // preferences of a df workgroup
-template <int JT, bool FINE>
-__global__ __launch_bounds__(64 * DMF_W) void k_hyper_dM_df(const float* __restrict__ hp, const int32_t* __restrict__ mrow,
-                                                    const int32_t* __restrict__ crow, const float* __restrict__ f,
+#define DMF_TB 4            // tiles of a short chunk
+// SHORT (up to so many preferences, 32 or 64, in chunks of four tiles; 0: any): a df workgroup requests all of its chunk together
+// instead of tile by tile, each behind the one before; the products are the same, in the same order.
+// us a call of hypernet_bwd, with row offsets in memory besides, and so: 4 preferences of 2 x 32 18.8 and 15.2, 24 of 3 x 256 40.7 and
+// 35.6, 64 46.2 and 43.4, 32 of 4 x 512, rank 16 97 and 78; strictly affine, 10 of 2 x 160 22.3 and 19.5.
+template <int JT, bool FINE, int SHORT>
+__global__ __launch_bounds__(64 * DMF_W) void k_hyper_dM_df(const float* __restrict__ hp, AffineRows at, const float* __restrict__ f,
                                                     const float* __restrict__ dfac, const float* __restrict__ dvec,
                                                     float* __restrict__ dhp, float* __restrict__ part, int P, int F,
-                                                    int64_t fac_len, int64_t vec_len, int q_total, int n_tiles, int tpw,
+                                                    int64_t fac_len, int64_t vec_len, int n_tiles, int tpw,
                                                     int n_p, int n_df, int dm_t) {
-    constexpr int PD = 68, PJ = 16 * JT + 16;
-    __shared__ float Dl[DMF_P][PD];
-    __shared__ float Ml[DMF_Q][PJ];
-    __shared__ int32_t Rl[2][DMF_Q];
+    constexpr int PD = 68, PJ = 16 * JT + 16, TB = SHORT ? DMF_TB : 1, DP = SHORT ? SHORT : DMF_P;
+    extern __shared__ __align__(16) float dml[];
+    float(*Dl)[PD] = reinterpret_cast<float(*)[PD]>(dml);                 // [TB * DP]
+    float(*Ml)[PJ] = reinterpret_cast<float(*)[PJ]>(dml + TB * DP * PD);  // [TB * DMF_Q]
+    int32_t* Rl = reinterpret_cast<int32_t*>(dml + TB * (DP * PD + DMF_Q * PJ));  // offsets of rows of M: twice eight tiles, or the chunk's
+    const int q_total = at.q_total;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, ln = lane & 15, kg = lane >> 4;
     if ((int)blockIdx.x >= n_df) {  // dM and dc of one tile a wave (no barrier: the waves are on their own)
         const int tile = dm_t * xcd_remap(blockIdx.x - n_df, gridDim.x - n_df) + wave;
         if (wave >= dm_t || tile >= n_tiles) return;
         const int q0 = tile * DMF_Q, q4 = q0 + 4 * ln;
+        int32_t mo, co;  // of row q0 + lane
+        at.offsets(F, q0 + lane < q_total ? q0 + lane : q_total - 1, mo, co);
         float4_t acc[4][JT];
         float dc[4] = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
@@ -739,8 +803,9 @@ __global__ __launch_bounds__(64 * DMF_W) void k_hyper_dM_df(const float* __restr
 #pragma unroll
             for (int mt = 0; mt < 4; ++mt) {
                 const int q = q0 + 16 * kg + 4 * e + mt;
+                const int32_t to = __shfl(mo, 16 * kg + 4 * e + mt, 64);
                 if (q < q_total) {
-                    float* mr = dhp + mrow[q];
+                    float* mr = dhp + to;
 #pragma unroll
                     for (int jt = 0; jt < JT; ++jt)
                         if (16 * jt + ln < F) mr[16 * jt + ln] = acc[mt][jt][e];
@@ -754,73 +819,124 @@ __global__ __launch_bounds__(64 * DMF_W) void k_hyper_dM_df(const float* __restr
             dc[mt] += __shfl_xor(dc[mt], 32, 64);
             if (kg == mt) mine = dc[mt];
         }
-        if (q4 + kg < q_total) dhp[crow[q4 + kg]] = mine;
+        const int32_t to = __shfl(co, 4 * ln + kg, 64);
+        if (q4 + kg < q_total) dhp[to] = mine;
         return;
     }
     // df partials of preferences p0 .. p0 + 15 (this wave's)
     const int id = xcd_remap(blockIdx.x, n_df), chunk = id / n_p, pb = id % n_p * DMF_P, p0 = pb + 16 * wave;
     const int t_lo = chunk * tpw, t_hi = (t_lo + tpw < n_tiles) ? (t_lo + tpw) : n_tiles;
     constexpr int MPT = DMF_Q * 16 * JT / (64 * DMF_W);
-    float nxt[DMF_P / DMF_W], mnx[MPT];
-    auto row_of = [&](int tile) {  // (threads 0 .. 63) offset of a row of M
-        const int q = tile * DMF_Q + (int)threadIdx.x;
-        return tile < t_hi && threadIdx.x < DMF_Q && q < q_total ? mrow[q] : 0;
-    };
-    auto fetch = [&](int tile) {
-        const int q = tile * DMF_Q + lane;
-#pragma unroll
-        for (int i = 0; i < DMF_P / DMF_W; ++i) {
-            const int pp = pb + wave + DMF_W * i;
-            nxt[i] = (pp < P && q < q_total) ? grad_row(dfac, dvec, pp, q, fac_len, vec_len) : 0.f;
-        }
-#pragma unroll
-        for (int i = 0; i < MPT; ++i) {
-            const int idx = threadIdx.x + 64 * DMF_W * i, qq = idx / (16 * JT), j = idx % (16 * JT);
-            mnx[i] = (tile * DMF_Q + qq < q_total && j < F) ? hp[Rl[tile & 1][qq] + j] : 0.f;
-        }
-    };
     float4_t accF[JT];
 #pragma unroll
     for (int jt = 0; jt < JT; ++jt) accF[jt] = float4_t{0.f, 0.f, 0.f, 0.f};
     float4_t sumF[FINE ? JT : 1];  // FINE: the sum of the tiles before this one
-    if constexpr (FINE) {
+    if constexpr (SHORT > 0) {
+        float g[TB][DP / DMF_W], m[TB][MPT];
 #pragma unroll
-        for (int jt = 0; jt < JT; ++jt) sumF[jt] = accF[jt];
-    }
-    if (threadIdx.x < DMF_Q) Rl[t_lo & 1][threadIdx.x] = row_of(t_lo);
-    int32_t rnext = row_of(t_lo + 1);
-    __syncthreads();
-    fetch(t_lo);
-    for (int tile = t_lo; tile < t_hi; ++tile) {
-        __syncthreads();  // the previous tile's readers are done
+        for (int t = 0; t < TB; ++t)
 #pragma unroll
-        for (int i = 0; i < DMF_P / DMF_W; ++i) Dl[wave + DMF_W * i][lane] = nxt[i];
-#pragma unroll
-        for (int i = 0; i < MPT; ++i) {
-            const int idx = threadIdx.x + 64 * DMF_W * i;
-            Ml[idx / (16 * JT)][idx % (16 * JT)] = mnx[i];
+            for (int i = 0; i < DP / DMF_W; ++i) {
+                const int pp = wave + DMF_W * i, q = (t_lo + t) * DMF_Q + lane;
+                g[t][i] = grad_row(dfac, dvec, pp < P ? pp : P - 1, q < q_total ? q : q_total - 1, fac_len, vec_len);
+            }
+        if (threadIdx.x < TB * DMF_Q) {
+            const int q = t_lo * DMF_Q + (int)threadIdx.x;
+            int32_t mo, co;
+            at.offsets(F, q < q_total ? q : q_total - 1, mo, co);
+            Rl[threadIdx.x] = mo;
         }
-        if (threadIdx.x < DMF_Q) Rl[(tile + 1) & 1][threadIdx.x] = rnext;
         __syncthreads();
-        if (tile + 1 < t_hi) {
-            fetch(tile + 1);
-            rnext = row_of(tile + 2);
-        }
-        if (p0 < P) {
+#pragma unroll
+        for (int t = 0; t < TB; ++t)
+#pragma unroll
+            for (int i = 0; i < MPT; ++i) {
+                const int idx = threadIdx.x + 64 * DMF_W * i, qq = idx / (16 * JT), j = idx % (16 * JT);
+                m[t][i] = hp[Rl[t * DMF_Q + qq] + (j < F ? j : 0)];
+            }
+#pragma unroll
+        for (int t = 0; t < TB; ++t)
+#pragma unroll
+            for (int i = 0; i < DP / DMF_W; ++i) {
+                const int pp = wave + DMF_W * i;
+                Dl[t * DP + pp][lane] = pp < P && (t_lo + t) * DMF_Q + lane < q_total ? g[t][i] : 0.f;
+            }
+#pragma unroll
+        for (int t = 0; t < TB; ++t)
+#pragma unroll
+            for (int i = 0; i < MPT; ++i) {
+                const int idx = threadIdx.x + 64 * DMF_W * i, qq = idx / (16 * JT), j = idx % (16 * JT);
+                Ml[t * DMF_Q + qq][j] = (t_lo + t) * DMF_Q + qq < q_total && j < F ? m[t][i] : 0.f;
+            }
+        __syncthreads();
+        if (p0 >= P) return;
+        for (int t = 0; t < t_hi - t_lo; ++t)
 #pragma unroll
             for (int kk = 0; kk < DMF_Q / 4; ++kk) {
-                const float a = Dl[16 * wave + ln][4 * kk + kg];
+                const float a = Dl[t * DP + 16 * wave + ln][4 * kk + kg];
 #pragma unroll
                 for (int jt = 0; jt < JT; ++jt)
-                    accF[jt] = __builtin_amdgcn_mfma_f32_16x16x4f32(a, Ml[4 * kk + kg][16 * jt + ln], accF[jt], 0, 0, 0);
+                    accF[jt] = __builtin_amdgcn_mfma_f32_16x16x4f32(a, Ml[t * DMF_Q + 4 * kk + kg][16 * jt + ln], accF[jt], 0, 0, 0);
             }
-        }
+    } else {
+        float nxt[DMF_P / DMF_W], mnx[MPT];
+        static_assert(64 * DMF_W == 8 * DMF_Q, "a thread a row of eight tiles");
+        auto fill_rows = [&](int eight) {  // the offsets of the rows of M of the chunk's `eight`-th eight tiles
+            const int q = (t_lo + 8 * eight) * DMF_Q + (int)threadIdx.x;
+            int32_t mo, co;
+            at.offsets(F, q < q_total ? q : q_total - 1, mo, co);
+            Rl[(eight & 1) * 8 * DMF_Q + threadIdx.x] = mo;
+        };
+        auto fetch = [&](int tile) {
+            const int q = tile * DMF_Q + lane;
+#pragma unroll
+            for (int i = 0; i < DMF_P / DMF_W; ++i) {
+                const int pp = pb + wave + DMF_W * i;
+                nxt[i] = (pp < P && q < q_total) ? grad_row(dfac, dvec, pp, q, fac_len, vec_len) : 0.f;
+            }
+#pragma unroll
+            for (int i = 0; i < MPT; ++i) {
+                const int idx = threadIdx.x + 64 * DMF_W * i, qq = idx / (16 * JT), j = idx % (16 * JT);
+                mnx[i] = (tile * DMF_Q + qq < q_total && j < F) ? hp[Rl[((tile - t_lo) & 15) * DMF_Q + qq] + j] : 0.f;
+            }
+        };
         if constexpr (FINE) {
 #pragma unroll
-            for (int jt = 0; jt < JT; ++jt) {
+            for (int jt = 0; jt < JT; ++jt) sumF[jt] = accF[jt];
+        }
+        fill_rows(0);
+        __syncthreads();
+        fetch(t_lo);
+        for (int tile = t_lo; tile < t_hi; ++tile) {
+            __syncthreads();  // the previous tile's readers are done
 #pragma unroll
-                for (int e = 0; e < 4; ++e) sumF[jt][e] += accF[jt][e];
-                accF[jt] = float4_t{0.f, 0.f, 0.f, 0.f};
+            for (int i = 0; i < DMF_P / DMF_W; ++i) Dl[wave + DMF_W * i][lane] = nxt[i];
+#pragma unroll
+            for (int i = 0; i < MPT; ++i) {
+                const int idx = threadIdx.x + 64 * DMF_W * i;
+                Ml[idx / (16 * JT)][idx % (16 * JT)] = mnx[i];
+            }
+            if (((tile - t_lo) & 7) == 6) fill_rows(((tile - t_lo) >> 3) + 1);  // (before the tile behind the next asks for them)
+            __syncthreads();
+            if (tile + 1 < t_hi) {
+                fetch(tile + 1);
+            }
+            if (p0 < P) {
+#pragma unroll
+                for (int kk = 0; kk < DMF_Q / 4; ++kk) {
+                    const float a = Dl[16 * wave + ln][4 * kk + kg];
+#pragma unroll
+                    for (int jt = 0; jt < JT; ++jt)
+                        accF[jt] = __builtin_amdgcn_mfma_f32_16x16x4f32(a, Ml[4 * kk + kg][16 * jt + ln], accF[jt], 0, 0, 0);
+                }
+            }
+            if constexpr (FINE) {
+#pragma unroll
+                for (int jt = 0; jt < JT; ++jt) {
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) sumF[jt][e] += accF[jt][e];
+                    accF[jt] = float4_t{0.f, 0.f, 0.f, 0.f};
+                }
             }
         }
     }
@@ -1012,6 +1128,17 @@ static int dm_tiles(int n_tiles) {
     return t < DMF_W ? t : DMF_W;
 }
 
+// more LDS than the default, allowed once per device (a bit each) and kernel
+static void allow_lds(const void* kernel, int bytes, int slot) {
+    static std::atomic<uint64_t> allowed[4];
+    int dev = 0;
+    (void)hipGetDevice(&dev);
+    const uint64_t bit = (uint64_t)1 << (dev & 63);
+    if (allowed[slot].load(std::memory_order_relaxed) & bit) return;
+    (void)hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
+    allowed[slot].fetch_or(bit, std::memory_order_relaxed);
+}
+
 void launch_hypernet_bwd(const morlax_ctx* c, int net, const float* hparams, const float* w,
                          const float* dtheta_mat, const float* dtheta_vec, float* dhparams, void* ws,
                          bool kept, hipStream_t s) {
@@ -1031,42 +1158,51 @@ void launch_hypernet_bwd(const morlax_ctx* c, int net, const float* hparams, con
         // recompute f and the factors; the theta_vec rows of the affine map land in a scratch nobody reads
         if (!kept) run_trunk_and_affine(c, net, hparams, w, L, L.vecs, s);
     }
-    const BaseWork bw = {affine ? 0 : (int)((nd.mat_len / 4 + 255) / 256), (at.q_total + 255) / 256, dhparams, L.mrow, L.crow, F};
-    const int n_base = bw.n_dw0 + bw.n_rows;
+    const int n_hidden = nd.n_layers - 1;
+    auto elems = [&](int l) { return nd.layer[l].d_out * nd.layer[l].d_in; };
+    BaseWork bw = {dhparams, nd.mat_len, layer_items(elems(0), n_hidden > 1 ? elems(1) : 0), 0};
+    const LayerRule lr = layer_rule(nd);
+    const AffineRows ar = affine_rows(at, F);
+    const int n_base = affine ? 0 : (int)((nd.mat_len / 4 + 255) / 256);  // (strictly affine form: W0 is a constant of the rows)
     if (r > 0) {
-        DabWork wk;
-        wk.n = 0;
-        int merged = 0;  // elements of the largest dA that is added up from column runs
+        int merged = 0, n_runs = 0;  // elements of the largest dA that is added up from column runs; column runs of all layers
+        auto runs = [&](int l) { return (nd.layer[l].d_in + DAB_COLS - 1) / DAB_COLS; };
         for (int l = 0; l < nd.n_layers; ++l) {
-            const int n_cs = (nd.layer[l].d_in + DAB_COLS - 1) / DAB_COLS;
-            if (n_cs > 1 && nd.layer[l].d_out * r > merged) merged = nd.layer[l].d_out * r;
-            for (int cs = 0; cs < n_cs; ++cs) {
-                wk.layer[wk.n] = (int16_t)l;
-                wk.cs[wk.n] = (int16_t)cs;
-                ++wk.n;
-            }
+            if (runs(l) > 1 && nd.layer[l].d_out * r > merged) merged = nd.layer[l].d_out * r;
+            n_runs += runs(l);
         }
-        const int nb = wk.n * P + n_base;
-        if (r <= 16) k_hyper_dAB<1><<<nb, 256, 0, s>>>(nd, wk, at, bw, dtheta_mat, L.fac, L.dfac, L.da_part, r, P);
-        else k_hyper_dAB<2><<<nb, 256, 0, s>>>(nd, wk, at, bw, dtheta_mat, L.fac, L.dfac, L.da_part, r, P);
+        const int nb = n_runs * P + n_base;
+        bw.share = (((uint64_t)n_base << 32) + nb - 1) / nb;
+        auto dab = [&](auto kernel) {
+            kernel<<<nb, 256, 0, s>>>(lr, layer_items(runs(0), n_hidden > 1 ? runs(1) : 0), row_div(P), bw, dtheta_mat, L.fac, L.dfac,
+                                      L.da_part, r, P, nd.fac_len);
+        };
+        if (r <= 16) dab(k_hyper_dAB<1>);
+        else dab(k_hyper_dAB<2>);
         if (merged > 0)
             k_hyper_dA_merge<<<dim3((merged + 1023) / 1024, P, nd.n_layers), 256, 0, s>>>(nd, L.da_part, L.dfac, r, P);
     }
-    if (r <= 0) k_hyper_base<<<n_base, 256, 0, s>>>(nd, at, bw, dtheta_mat, P);
+    if (r == 0) k_hyper_base<<<n_base, 256, 0, s>>>(lr, bw, dtheta_mat, P);
     const int n_tiles = (at.q_total + DMF_Q - 1) / DMF_Q, tpw = df_chunk_tiles(at.q_total);
     const int n_chunk = (n_tiles + tpw - 1) / tpw;
     const int n_p = (P + DMF_P - 1) / DMF_P, n_df = n_chunk * n_p, dm_t = dm_tiles(n_tiles), n_dm = (n_tiles + dm_t - 1) / dm_t;
-    auto dM_df = [&](auto kernel) {
-        kernel<<<n_df + n_dm, 64 * DMF_W, 0, s>>>(hparams, L.mrow, L.crow, L.f, dlead, dtheta_vec, dhparams, L.df_part, P, F,
-                                                  nd.fac_len, nd.vec_len, at.q_total, n_tiles, tpw, n_p, n_df, dm_t);
+    auto dM_df = [&](auto jt, auto fine, auto brief) {
+        constexpr int JT = decltype(jt)::value;
+        constexpr int SHORT = decltype(brief)::value;
+        constexpr int TB = SHORT ? DMF_TB : 1, bytes = 4 * (TB * ((SHORT ? SHORT : DMF_P) * 68 + DMF_Q * (16 * JT + 16)) + (SHORT ? TB : 16) * DMF_Q);
+        auto kernel = k_hyper_dM_df<JT, decltype(fine)::value, SHORT>;
+        if (bytes > 64 * 1024) allow_lds(reinterpret_cast<const void*>(kernel), bytes, (JT == 2 ? 0 : 1) + (SHORT == 32 ? 0 : 2));
+        kernel<<<n_df + n_dm, 64 * DMF_W, bytes, s>>>(hparams, ar, L.f, dlead, dtheta_vec, dhparams, L.df_part, P, F, nd.fac_len,
+                                                      nd.vec_len, n_tiles, tpw, n_p, n_df, dm_t);
     };
-    if (n_p == 1) {
-        if (F <= 32) dM_df(k_hyper_dM_df<2, false>);
-        else dM_df(k_hyper_dM_df<4, false>);
-    } else {
-        if (F <= 32) dM_df(k_hyper_dM_df<2, true>);
-        else dM_df(k_hyper_dM_df<4, true>);
-    }
+    auto pick = [&](auto fine, auto brief) {
+        if (F <= 32) dM_df(std::integral_constant<int, 2>{}, fine, brief);
+        else dM_df(std::integral_constant<int, 4>{}, fine, brief);
+    };
+    if (n_p > 1) pick(std::true_type{}, std::integral_constant<int, 0>{});
+    else if (P <= 32 && tpw == DMF_TB) pick(std::false_type{}, std::integral_constant<int, 32>{});
+    else if (P <= 64 && tpw == DMF_TB) pick(std::false_type{}, std::integral_constant<int, 64>{});
+    else pick(std::false_type{}, std::integral_constant<int, 0>{});
     const int lds = (7 * P * F + P * K) * 4;  // (with the kernel's 16 KB at most 64)
     if (trunk_bwd_inside(P, F, n_chunk) && lds <= 48 * 1024) {
         k_hyper_trunk_bwd<<<1, 1024, lds, s>>>(hparams, L.df_part, n_chunk, L.f, L.h1, w, dhparams, P, K, F, nd.hp_wh1, nd.hp_bh1,
