@@ -2318,14 +2318,19 @@ __global__ __launch_bounds__(256, sizeof(T) == 2 ? 4 : 2) void k_head_bwd(HeadDz
                                                  int64_t mat_len, int64_t mat_off,
                                                  const typename GradT<T>::type* __restrict__ G, T* __restrict__ dZ,
                                                  float* __restrict__ pw, float* __restrict__ pb, float* __restrict__ part,
-                                                 int W, int Mp) {
+                                                 int W, int Mp, int n_front, int per_rest, RowDiv by_dw, RowDiv by_rest) {
     constexpr size_t kLds = sizeof(HeadBwdLds<T>) > sizeof(HeadBwdLdsDz) ? sizeof(HeadBwdLds<T>) : sizeof(HeadBwdLdsDz);
     __shared__ __align__(16) unsigned char lds[kLds];
     constexpr int VE = Elems<T>::VE;
-    const int p = blockIdx.y, ncol = (W + 127) / 128, M = hz.M;
+    const int ncol = (W + 127) / 128, M = hz.M;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const bool dw_role = (int)blockIdx.x < ncol * HB_SPLIT;
-    const int item = dw_role ? blockIdx.x : blockIdx.x - ncol * HB_SPLIT;
+    // n_front dW workgroups ahead of everything else, or (0) every preference's ahead of its dZ ones (rule: the launch)
+    const bool front = (int)blockIdx.x < n_front;
+    const int id = front ? blockIdx.x : blockIdx.x - n_front;
+    const int p = (int)(front ? by_dw : by_rest).quotient((uint32_t)id);
+    int item = id - p * (front ? ncol * HB_SPLIT : per_rest);
+    const bool dw_role = front || (n_front == 0 && item < ncol * HB_SPLIT);
+    if (!dw_role && n_front == 0) item -= ncol * HB_SPLIT;
     const int i0 = item % ncol * 128;
     if (!dw_role) {
         HeadBwdLdsDz& L = *reinterpret_cast<HeadBwdLdsDz*>(lds);
@@ -3209,9 +3214,15 @@ static void policy_bwd_t(const morlax_ctx* c, int net, const T* theta_mat, const
         hz.dout = dout; hz.saved_out = saved_out; hz.out_dim = nd.out_dim; hz.M = M; hz.rm = rm;
         hz.tanh_cols = (net == MORLAX_ACTOR && c->d.mean_tanh) ? c->d.act_dim : 0;
         const int ncol = (W + 127) / 128;
-        k_head_bwd<T><<<dim3(ncol * (HB_SPLIT + n64), P), 256, 0, s>>>(hz, Hbuf(L - 1), theta_mat, nd.mat_len, Lh.mat_off,
-                                                                     Gbuf(L - 1), dZbuf(L - 1), part + B.pw, part + B.pb,
-                                                                     part + B.colsum[L - 1], W, Mp);
+        // Up to one dW workgroup a CU, they start first: each walks a quarter of a preference's rows, and those of the last
+        // preferences were at it long after the others had ended.  us a backward pass of one hidden layer, among the others and
+        // first: 32 preferences x 8192 rows of 256 138 and 122, fp32, 16 x 8192 of 256 156 and 124, 8 x 3337 of 512 71 and 58; with
+        // more of them there is too little else to run beside them (64 x 4096 of 512 234 and 238, 128 x 2048 229 and 239).
+        const int n_dw = ncol * HB_SPLIT * P, n_front = n_dw <= resident_slots() / 2 ? n_dw : 0;
+        const int per_rest = ncol * (n_front ? n64 : HB_SPLIT + n64);
+        k_head_bwd<T><<<ncol * (HB_SPLIT + n64) * P, 256, 0, s>>>(hz, Hbuf(L - 1), theta_mat, nd.mat_len, Lh.mat_off, Gbuf(L - 1),
+                                                                dZbuf(L - 1), part + B.pw, part + B.pb, part + B.colsum[L - 1], W, Mp,
+                                                                n_front, per_rest, row_div(ncol * HB_SPLIT), row_div(per_rest));
     }
     for (int l = L - 1; l >= 0; --l) {
         const LayerDev& Ld = nd.layer[l];
