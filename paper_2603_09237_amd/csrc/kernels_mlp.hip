@@ -1483,7 +1483,8 @@ __global__ __launch_bounds__(2 * TN, 2) void k_gemm_pers(GemmArgs<bf16_t, KA, KB
 // on four tiles, 36 on nine small ones; 32 x 32: 16 and 4).  A wave owns one block; the contraction (whole 32-index steps)
 // runs in the same order, so the sums keep their bits.  A step is sixteen contraction indices, six products' worth of work, so
 // the operands of the next F32S_AHEAD steps are on their way in registers (one step ahead: 3.6 us more a launch for 10
-// preferences x 1850 rows x 160 x 160).
+// preferences x 1850 rows x 160 x 160), and the next step's are split beside this one's products (in front of them: the backward pass
+// of those 78.4 us, 75.0 so; 16 x 6000 rows of 3 x 64 139 and 128).
 #define F32S_AHEAD 4
 template <class Epi>
 __global__ __launch_bounds__(256) void k_gemm_f32_small(GemmArgs<float, SRC_KSTRIDED, SRC_KSTRIDED, Epi, true, GEMM_NCH> g) {
@@ -1511,16 +1512,27 @@ __global__ __launch_bounds__(256) void k_gemm_f32_small(GemmArgs<float, SRC_KSTR
             rb[slot][e] = B[(k0 + e) * g.b.ld];
         }
     };
-    auto store = [&](int slot, int buf) {
-        put_chunk<float, GEMM_NCH>(lds[buf][0], lane, wave, __builtin_bit_cast(uint4, make_float4(ra[slot][0], ra[slot][1], ra[slot][2], ra[slot][3])));
-        put_chunk<float, GEMM_NCH>(lds[buf][1], lane, wave, __builtin_bit_cast(uint4, make_float4(rb[slot][0], rb[slot][1], rb[slot][2], rb[slot][3])));
+    auto split = [&](int slot, uint2 (&pa)[3], uint2 (&pb)[3]) __attribute__((always_inline)) {
+        split3(__builtin_bit_cast(uint4, make_float4(ra[slot][0], ra[slot][1], ra[slot][2], ra[slot][3])), pa);
+        split3(__builtin_bit_cast(uint4, make_float4(rb[slot][0], rb[slot][1], rb[slot][2], rb[slot][3])), pb);
+    };
+    auto store = [&](const uint2 (&pa)[3], const uint2 (&pb)[3], int buf) __attribute__((always_inline)) {
+#pragma unroll
+        for (int q = 0; q < 3; ++q) {
+            *reinterpret_cast<uint2*>(lds[buf][0] + lane * PITCH + q * (GEMM_NCH * 8) + wave * 8) = pa[q];
+            *reinterpret_cast<uint2*>(lds[buf][1] + lane * PITCH + q * (GEMM_NCH * 8) + wave * 8) = pb[q];
+        }
     };
     float16_t acc[1][1], low;
 #pragma unroll
     for (int e = 0; e < 16; ++e) acc[0][0][e] = low[e] = 0.f;
 #pragma unroll
     for (int u = 0; u < F32S_AHEAD; ++u) load(u, u);
-    store(0, 0);
+    {
+        uint2 pa[3], pb[3];
+        split(0, pa, pb);
+        store(pa, pb, 0);
+    }
     load(0, F32S_AHEAD);
     __syncthreads();
     for (int k0 = 0; k0 < nk; k0 += F32S_AHEAD) {
@@ -1528,8 +1540,6 @@ __global__ __launch_bounds__(256) void k_gemm_f32_small(GemmArgs<float, SRC_KSTR
         for (int u = 0; u < F32S_AHEAD; ++u) {
             const int kt = k0 + u, cur = u & 1, nxt = (u + 1) % F32S_AHEAD;
             if (kt >= nk) break;
-            store(nxt, cur ^ 1);  // (its readers passed the barrier of the step before)
-            load(nxt, kt + 1 + F32S_AHEAD);
             const unsigned char* ta = lds[cur][0] + (wm + lr) * PITCH + lg * 16;
             const unsigned char* tb = lds[cur][1] + (wn + lr) * PITCH + lg * 16;
             uint4 fa[3], fb[3];
@@ -1538,8 +1548,20 @@ __global__ __launch_bounds__(256) void k_gemm_f32_small(GemmArgs<float, SRC_KSTR
                 fa[q] = *reinterpret_cast<const uint4*>(ta + q * 32);
                 fb[q] = *reinterpret_cast<const uint4*>(tb + q * 32);
             }
+            // the next step's operands are split beside this one's reads and products and written behind them
+            uint2 pa[3], pb[3];
+            split(nxt, pa, pb);
 #pragma unroll
             for (int t = 0; t < 6; ++t) split_mma(t, fa, fb, acc[0][0], low);
+            store(pa, pb, cur ^ 1);  // (its readers passed the barrier of the step before)
+            load(nxt, kt + 1 + F32S_AHEAD);
+            __builtin_amdgcn_sched_group_barrier(0x100, 6, 0);  // LDS reads
+            __builtin_amdgcn_sched_group_barrier(0x002, 24, 0);
+#pragma unroll
+            for (int t = 0; t < 6; ++t) {
+                __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);  // a product
+                __builtin_amdgcn_sched_group_barrier(0x002, 10, 0);
+            }
             __syncthreads();
         }
     }
@@ -1557,7 +1579,8 @@ __global__ __launch_bounds__(256) void k_gemm_f32_small(GemmArgs<float, SRC_KSTR
 // dW of few preferences on 128 x 128 tiles leaves CUs without a workgroup, and its contraction may only be split where the
 // grouping of its sums says so.  Smaller tiles keep every sum as it is.  A wave owns 32 x 32 outputs; a step of 32
 // contraction indices is two products, so what bounds a workgroup is the latency of its operands: eight stages of 8 KB,
-// seven of them on their way.
+// six of them on their way, two multiplied behind one barrier (one by one: 14.4 us a launch for 24 preferences x 1250 rows x 256 x
+// 256, 13.7 so; the operands come out of the L2s at some 14 TB/s).
 #define SG_NST 8
 #define SG_STAGE 8192
 template <class Epi>
@@ -1586,26 +1609,35 @@ __global__ __launch_bounds__(256) void k_gemm_small(GemmArgs<bf16_t, SRC_KSTRIDE
         A.issue(kt, tile);
         B.issue(kt, tile + SG_STAGE / 2);
     };
-    for (int st = 0; st < SG_NST - 1 && st < nk; ++st) issue(st);
-    for (int kt = 0; kt < nk; ++kt) {
-        // two loads a stage and wave; the oldest stage is the one multiplied next
-        const int ahead = nk - 1 - kt;
-        if (ahead >= SG_NST - 2) wait_vm<2 * (SG_NST - 2)>();
-        else if (ahead >= 3) wait_vm<6>();
-        else if (ahead == 2) wait_vm<4>();
-        else if (ahead == 1) wait_vm<2>();
+    for (int st = 0; st < SG_NST - 2 && st < nk; ++st) issue(st);
+    // two steps behind one barrier (their four products are one chain; a step by itself is barrier, LDS reads and two products one
+    // after the other, 360 cycles of which the products are 64); nk odd: the last one alone
+    for (int kt = 0; kt < nk; kt += 2) {
+        // two loads a stage and wave; the two oldest stages are the ones multiplied next
+        const int behind = nk - 2 - kt;
+        if (behind >= SG_NST - 4) wait_vm<2 * (SG_NST - 4)>();
+        else if (behind == 3) wait_vm<6>();
+        else if (behind == 2) wait_vm<4>();
+        else if (behind == 1) wait_vm<2>();
         else wait_vm<0>();
-        __syncthreads();  // stage kt has landed for every wave, and everyone is done with stage kt - 1
-        if (kt + SG_NST - 1 < nk) issue(kt + SG_NST - 1);
-        const unsigned char* ta = dlds + (kt % SG_NST) * SG_STAGE;
-        uint4 fa[2], fb[2];
+        __syncthreads();  // stages kt and kt + 1 have landed for every wave, and everyone is done with the two before
 #pragma unroll
-        for (int ks = 0; ks < 2; ++ks) {
-            fa[ks] = A.frag(ta, 0, ks);
-            fb[ks] = B.frag(ta + SG_STAGE / 2, 0, ks);
+        for (int u = 0; u < 2; ++u)
+            if (kt + SG_NST - 2 + u < nk) issue(kt + SG_NST - 2 + u);
+        const unsigned char* ta = dlds + (kt % SG_NST) * SG_STAGE;
+        const bool two = kt + 1 < nk;  // (kt is even and SG_NST too: the other stage follows in LDS)
+        uint4 fa[4], fb[4];
+#pragma unroll
+        for (int ks = 0; ks < 4; ++ks) {
+            fa[ks] = A.frag(ta + (ks >> 1) * SG_STAGE, 0, ks & 1);
+            fb[ks] = B.frag(ta + (ks >> 1) * SG_STAGE + SG_STAGE / 2, 0, ks & 1);
         }
 #pragma unroll
         for (int ks = 0; ks < 2; ++ks) Mma32<bf16_t>::run(fa[ks], fb[ks], acc[0][0]);
+        if (two) {
+#pragma unroll
+            for (int ks = 2; ks < 4; ++ks) Mma32<bf16_t>::run(fa[ks], fb[ks], acc[0][0]);
+        }
     }
     epilogue_f32(epi, acc, nullptr, p, tm, g.tiles_m, r0 + wm, c0 + wn, g.crows, g.ccols);
 }
