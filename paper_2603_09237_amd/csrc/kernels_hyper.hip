@@ -12,6 +12,8 @@
 #define DAB_COLS 128  // columns of dW one block of the fused dA/dB kernel walks
 #define DAB_NCT (DAB_COLS / 64)
 
+typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
+
 struct HyperWs {
     float *h1, *f, *fac, *dfac, *df_part, *df, *dz2, *dz1, *vecs, *da_part;
     int n_chunk, n_cs;
@@ -572,8 +574,15 @@ __global__ __launch_bounds__(256) void k_hyper_dAB(LayerRule lr, LayerItems runs
     // The tiles are walked row block by row block; the next tile of dW is fetched into registers while the
     // current one is multiplied out of LDS.
     const int nrb = (L.d_out + 63) / 64, ntile = nrb * nct;
-    auto fetch = [&](int tile, float4 (&regs)[4]) {
-        const int o0 = (tile / nct) * 64, i0 = c_lo + (tile % nct) * 64;
+    static_assert(DAB_NCT == 2, "one or two tiles a row block");
+    auto fetch = [&](int tile, u32x4_t (&regs)[4]) __attribute__((always_inline)) {
+        const int o0 = (nct == 2 ? tile >> 1 : tile) * 64, i0 = c_lo + (nct == 2 ? tile & 1 : 0) * 64;
+        if (vec && i0 + 64 <= c_hi && o0 + 64 <= L.d_out) {  // a whole tile: nothing in the way of requesting it at once
+            const float* src = dW + (int64_t)(o0 + (int)threadIdx.x / 16) * L.d_in + i0 + threadIdx.x % 16 * 4;
+#pragma unroll
+            for (int q = 0; q < 4; ++q) regs[q] = *reinterpret_cast<const u32x4_t*>(src + (int64_t)(16 * q) * L.d_in);
+            return;
+        }
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
             const int idx = threadIdx.x + 256 * q, row = idx / 16, c4 = (idx % 16) * 4;
@@ -589,7 +598,7 @@ __global__ __launch_bounds__(256) void k_hyper_dAB(LayerRule lr, LayerItems runs
                     if (i0 + c4 + 3 < c_hi) v.w = src[3];
                 }
             }
-            regs[q] = v;
+            regs[q] = __builtin_bit_cast(u32x4_t, v);
         }
     };
     // a row block's rows of A(p), requested one row block ahead
@@ -599,16 +608,25 @@ __global__ __launch_bounds__(256) void k_hyper_dAB(LayerRule lr, LayerItems runs
 #pragma unroll
         for (int q = 0; q < APT; ++q) {
             const int idx = threadIdx.x + 256 * q, row = idx / (16 * RT), k = idx % (16 * RT);
-            anx[q] = (rb * 64 + row < L.d_out && k < r) ? Ap[(int64_t)(rb * 64 + row) * r + k] : 0.f;
+            const int o = rb * 64 + row < L.d_out ? rb * 64 + row : L.d_out - 1;
+            anx[q] = Ap[(int64_t)o * r + (k < r ? k : 0)];
         }
     };
-    float4 nxt[4];
+    u32x4_t nxt[4];
     fetch(0, nxt);
     fetch_a(0);
-    // the block's columns of B(p): the same for every row block
-    for (int idx = threadIdx.x; idx < DAB_NCT * 16 * RT * 64; idx += 256) {
-        const int ct = idx / (16 * RT * 64), k = (idx / 64) % (16 * RT), cc = idx % 64, i = c_lo + ct * 64 + cc;
-        sB[ct][k][cc] = (k < r && i < c_hi) ? Bp[(int64_t)k * L.d_in + i] : 0.f;
+    {  // the block's columns of B(p), the same for every row block: requested together (one by one they were eight round trips)
+        constexpr int BPT = DAB_NCT * 16 * RT * 64 / 256;
+        float b[BPT];
+        auto each = [&](auto body) __attribute__((always_inline)) {
+#pragma unroll
+            for (int q = 0; q < BPT; ++q) {
+                const int idx = threadIdx.x + 256 * q, ct = idx / (16 * RT * 64), k = (idx / 64) % (16 * RT), cc = idx % 64;
+                body(b[q], ct, k, cc, c_lo + ct * 64 + cc);
+            }
+        };
+        each([&](float& v, int, int k, int, int i) { v = Bp[(int64_t)(k < r ? k : 0) * L.d_in + (i < c_hi ? i : c_hi - 1)]; });
+        each([&](float& v, int ct, int k, int cc, int i) { sB[ct][k][cc] = k < r && i < c_hi ? v : 0.f; });
     }
     for (int rb = 0; rb < nrb; ++rb) {
         const int o0 = rb * 64;
@@ -616,7 +634,7 @@ __global__ __launch_bounds__(256) void k_hyper_dAB(LayerRule lr, LayerItems runs
 #pragma unroll
         for (int q = 0; q < APT; ++q) {
             const int idx = threadIdx.x + 256 * q;
-            sA[idx / (16 * RT)][idx % (16 * RT)] = anx[q];
+            sA[idx / (16 * RT)][idx % (16 * RT)] = o0 + idx / (16 * RT) < L.d_out && idx % (16 * RT) < r ? anx[q] : 0.f;
         }
         if (rb + 1 < nrb) fetch_a(rb + 1);
         float4_t accA[RT];
@@ -629,7 +647,7 @@ __global__ __launch_bounds__(256) void k_hyper_dAB(LayerRule lr, LayerItems runs
 #pragma unroll
                 for (int q = 0; q < 4; ++q) {
                     const int idx = threadIdx.x + 256 * q;
-                    *reinterpret_cast<float4*>(&sW[idx / 16][(idx % 16) * 4]) = nxt[q];
+                    *reinterpret_cast<u32x4_t*>(&sW[idx / 16][(idx % 16) * 4]) = nxt[q];
                 }
                 if (rb * nct + ct + 1 < ntile) fetch(rb * nct + ct + 1, nxt);
                 __syncthreads();
