@@ -67,6 +67,19 @@ int64_t hyper_ws_bytes(const morlax_ctx* c) {
 
 // ------------------------------------------------------------------------------------------------
 // Trunk f(w): h1 = tanh(Wh1 w + bh1), f = tanh(Wh2 h1 + bh2).
+// n values from memory by NT threads, N of a thread requested together (a loop that waits for each before the next is a round trip
+// to memory a turn)
+template <int N, int NT, class Put>
+__device__ inline void take(const float* __restrict__ src, int n, Put put) {
+    for (int e0 = threadIdx.x; e0 < n; e0 += N * NT) {
+        float v[N];
+#pragma unroll
+        for (int u = 0; u < N; ++u) v[u] = src[e0 + u * NT < n ? e0 + u * NT : n - 1];
+#pragma unroll
+        for (int u = 0; u < N; ++u)
+            if (e0 + u * NT < n) put(e0 + u * NT, v[u]);
+    }
+}
 struct Trunk {
     const float* w;  // [P][K]
     float *h1, *f;   // [P][F]
@@ -74,12 +87,23 @@ struct Trunk {
     int64_t o_wh1, o_bh1, o_wh2, o_bh2;
     __device__ inline float hidden(const float* __restrict__ hp, int p, int j) const {
         float a = hp[o_bh1 + j];
-        for (int k = 0; k < K; ++k) a += hp[o_wh1 + (int64_t)j * K + k] * w[p * K + k];
+        for (int k0 = 0; k0 < K; k0 += 8) {
+            float u[8], v[8];
+#pragma unroll
+            for (int q = 0; q < 8; ++q) {
+                const int k = k0 + q < K ? k0 + q : K - 1;
+                u[q] = hp[o_wh1 + (int64_t)j * K + k];
+                v[q] = w[p * K + k];
+            }
+#pragma unroll
+            for (int q = 0; q < 8; ++q)
+                if (k0 + q < K) a += u[q] * v[q];
+        }
         return tanhf(a);
     }
     // a workgroup's own copy of the features of all preferences in LDS: sw [F][F + 1], sh and sf [P][F]
     __device__ inline void features(const float* __restrict__ hp, float* sw, float* sh, float* sf, int P, int F, bool keep) const {
-        for (int e = threadIdx.x; e < F * F; e += blockDim.x) sw[e / F * (F + 1) + e % F] = hp[o_wh2 + e];
+        take<4, 256>(hp + o_wh2, F * F, [&](int e, float v) { sw[e / F * (F + 1) + e % F] = v; });
         for (int i = threadIdx.x; i < P * F; i += blockDim.x) {
             const float a = hidden(hp, i / F, i % F);
             sh[i] = a;
@@ -97,21 +121,32 @@ struct Trunk {
         __syncthreads();
     }
 };
-// One block per preference.
+// One block per preference; a thread's row of Wh2 is on its way while h1 is made.
 __global__ __launch_bounds__(64) void k_hyper_trunk(Trunk t, const float* __restrict__ hp, int F) {
     __shared__ float sh[MORLAX_MAX_F];
     const int p = blockIdx.x, j = threadIdx.x;
+    constexpr int B = 32;
+    const float* row = hp + t.o_wh2 + (int64_t)(j < F ? j : 0) * F;
+    float v[B];
+    auto get = [&](int i0) __attribute__((always_inline)) {
+#pragma unroll
+        for (int i = 0; i < B; ++i) v[i] = row[i0 + i < F ? i0 + i : F - 1];
+    };
+    get(0);
+    float a2 = hp[t.o_bh2 + (j < F ? j : 0)];
     if (j < F) {
         const float a = t.hidden(hp, p, j);
         sh[j] = a;
         t.h1[p * F + j] = a;
     }
     __syncthreads();
-    if (j < F) {
-        float a = hp[t.o_bh2 + j];
-        for (int i = 0; i < F; ++i) a += hp[t.o_wh2 + (int64_t)j * F + i] * sh[i];
-        t.f[p * F + j] = tanhf(a);
+    for (int i0 = 0; i0 < F; i0 += B) {
+        if (i0 > 0) get(i0);
+#pragma unroll
+        for (int i = 0; i < B; ++i)
+            if (i0 + i < F) a2 += v[i] * sh[i0 + i];
     }
+    if (j < F) t.f[p * F + j] = tanhf(a2);
 }
 
 // Kernel arguments lie in host memory: the first use of each of their cache lines takes a workgroup about half a microsecond,
@@ -983,7 +1018,7 @@ __global__ __launch_bounds__(256) void k_hyper_trunk_bwd_a(const float* __restri
     const int PF = P * F, per = (64 / F) * F;
     const int i = blockIdx.x * per + o;
     const bool live = o < per && i < PF;
-    for (int e = threadIdx.x; e < F * F; e += 256) wh2[e] = hp[o_wh2 + e];
+    take<4, 256>(hp + o_wh2, F * F, [&](int e, float v) { wh2[e] = v; });
     float a = 0.f;
     if (live) {
         int c = g;

@@ -2343,7 +2343,7 @@ struct HeadBwdLds {
     T sh[R][HP];
 };
 struct HeadBwdLdsDz {
-    float sdz[64][MORLAX_MAX_OUT], sdu[64][MORLAX_MAX_OUT + 1], red[16][128];
+    float sdz[64][MORLAX_MAX_OUT], sdu[64][MORLAX_MAX_OUT + 1], red[16][128], sw[MORLAX_MAX_OUT][128];
 };
 template <typename T>
 __global__ __launch_bounds__(256, sizeof(T) == 2 ? 4 : 2) void k_head_bwd(HeadDz hz, const T* __restrict__ Hin, const T* __restrict__ theta_mat,
@@ -2377,16 +2377,31 @@ __global__ __launch_bounds__(256, sizeof(T) == 2 ? 4 : 2) void k_head_bwd(HeadDz
             gq[a].lo = src[0];
             if (sizeof(T) == 4) gq[a].hi = src[1];
         }
+        // (W_L through LDS: read where it was needed it was a round trip to memory for every output, one behind the other; us a
+        // backward pass of one hidden layer, so and here: 32 preferences x 8192 rows of 256 122 and 118, 24 x 1250 25.5 and 24.8)
+        const int mm = threadIdx.x / 4, q = threadIdx.x % 4, m = m0 + mm;
+        HeadDz::Raw raw;
+        hz.request(p, m < M ? m : M - 1, q, raw);
+        const int wj = threadIdx.x / 16;  // the thread's row of W_L, columns ti .. ti + 7
+        Pack8 wq;
         {
-            const int mm = threadIdx.x / 4, q = threadIdx.x % 4, m = m0 + mm;
-            HeadDz::Raw r;
-            hz.request(p, m < M ? m : M - 1, q, r);
+            const uint4* src = reinterpret_cast<const uint4*>(theta_mat + (int64_t)p * mat_len + mat_off + (int64_t)(wj < hz.out_dim ? wj : 0) * W + (live ? ti : 0));
+            wq.lo = src[0];
+            if (sizeof(T) == 4) wq.hi = src[1];
+        }
 #pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                const float d = hz.value(r, q, e, m < M);
-                L.sdu[mm][4 * q + e] = d;
-                L.sdz[mm][4 * q + e] = to_f(cvt<T>(d));  // GEMM input rounding
-            }
+        for (int e = 0; e < 4; ++e) {
+            const float d = hz.value(raw, q, e, m < M);
+            L.sdu[mm][4 * q + e] = d;
+            L.sdz[mm][4 * q + e] = to_f(cvt<T>(d));  // GEMM input rounding
+        }
+        {
+            float wv[8];
+            const uint32_t w[8] = {wq.lo.x, wq.lo.y, wq.lo.z, wq.lo.w, wq.hi.x, wq.hi.y, wq.hi.z, wq.hi.w};
+#pragma unroll
+            for (int b = 0; b < 8; ++b)
+                wv[b] = __uint_as_float(sizeof(T) == 4 ? w[b] : (b & 1) ? w[b >> 1] & 0xffff0000u : w[b >> 1] << 16);
+            store8(&L.sw[wj][threadIdx.x % 16 * 8], wv);
         }
         __syncthreads();
         float acc[4][8];
@@ -2394,11 +2409,9 @@ __global__ __launch_bounds__(256, sizeof(T) == 2 ? 4 : 2) void k_head_bwd(HeadDz
         for (int a = 0; a < 4; ++a)
 #pragma unroll
             for (int b = 0; b < 8; ++b) acc[a][b] = 0.f;
-        const T* wl = theta_mat + (int64_t)p * mat_len + mat_off;
-        for (int j = 0; j < hz.out_dim && live; ++j) {
+        for (int j = 0; j < hz.out_dim; ++j) {
             float wv[8];
-#pragma unroll
-            for (int b = 0; b < 8; ++b) wv[b] = to_f(wl[(int64_t)j * W + ti + b]);
+            get8(&L.sw[j][threadIdx.x % 16 * 8], wv);
 #pragma unroll
             for (int a = 0; a < 4; ++a) {
                 const float d = L.sdz[tr + a][j];
