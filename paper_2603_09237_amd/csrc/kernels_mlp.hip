@@ -2778,6 +2778,10 @@ __global__ __launch_bounds__(256) void k_first_bwd_dw(const float* __restrict__ 
 //   split dW   the ranges of a layer whose contraction was split, in order, four elements a thread
 //   first dW   the ranges' partials [i][o] of the narrow first layer, in order
 // Fixed associations throughout: results repeat bit for bit.
+// Bound by latency where the partials are few and by memory where they are many, so a thread requests up to 32 terms of its sum
+// together, those behind the last one the last one once more, and walks the first layer's partials along their rows.  us a launch, in
+// loops of two to four requests, and so: 16 preferences x 8192 rows of 3 x 256, fp32, 8 ranges 32.8 and 22.0; 32 of them, bf16, 4 ranges
+// 26.2 and 22.5; 64 x 4096 of 4 x 512 16.1 and 14.5; 24 x 1250 of 3 x 256 4.8 and 4.4; few rows of 2 x 32 3.4 and 4.0 (the step the same).
 struct BwdFinalArgs {
     const float *part, *dlogsig;
     float *dmat, *dvec;
@@ -2788,6 +2792,28 @@ struct BwdFinalArgs {
     int64_t mat_off[MORLAX_MAX_LAYERS], vec_off[MORLAX_MAX_LAYERS], n[MORLAX_MAX_LAYERS], logsig_off;  // (index L: output layer)
     int32_t b_head, b_split[MORLAX_MAX_LAYERS], b_first;  // first block of each kind
 };
+// N of the terms at(0) .. at(n - 1) from q on, requested together
+template <int N, typename V, typename At>
+__device__ inline void get_terms(V (&v)[N], int q, int n, const At& at) {
+#pragma unroll
+    for (int u = 0; u < N; ++u) v[u] = at(q + u < n ? q + u : n - 1);
+}
+// add(at(lo)), .. add(at(hi - 1)) in order, so many requested together as there are: FEW or MANY
+template <int N, typename V, typename At, typename Add>
+__device__ inline void each_term(int lo, int hi, const At& at, const Add& add) {
+    for (int q = lo; q < hi; q += N) {
+        V v[N];
+        get_terms(v, q, hi, at);
+#pragma unroll
+        for (int u = 0; u < N; ++u)
+            if (q + u < hi) add(v[u]);
+    }
+}
+template <int FEW, int MANY, typename V, typename At, typename Add>
+__device__ inline void in_order(int lo, int hi, int n, const At& at, const Add& add) {
+    if (n <= FEW) each_term<FEW, V>(lo, hi, at, add);
+    else each_term<MANY, V>(lo, hi, at, add);
+}
 __global__ __launch_bounds__(256) void k_bwd_final(BwdFinalArgs a) {
     __shared__ float sg[8][32];
     const int p = blockIdx.y, b = blockIdx.x, W = a.W;
@@ -2795,14 +2821,14 @@ __global__ __launch_bounds__(256) void k_bwd_final(BwdFinalArgs a) {
     float* dvec = a.dvec + (int64_t)p * a.vec_len;
     if (b < a.b_head) {
         const int cw = (W + 31) / 32, l = b / cw, np = a.n_part[l];
-        const float* part = a.part + a.colsum[l] + (int64_t)p * np * W;
-        const int c = threadIdx.x & 31, g = threadIdx.x >> 5, i = (b % cw) * 32 + c;
+        const int c = threadIdx.x & 31, g = threadIdx.x >> 5, i = (b - l * cw) * 32 + c;
+        const float* part = a.part + a.colsum[l] + (int64_t)p * np * W + (i < W ? i : W - 1);
         const int per = (np + 7) / 8, q_lo = g * per, q_hi = (q_lo + per < np) ? q_lo + per : np;
         float t = 0.f;
-        if (i < W) {
-#pragma unroll 4
-            for (int q = q_lo; q < q_hi; ++q) t += part[(int64_t)q * W + i];
-        }
+        auto at = [&](int q) { return part[(int64_t)q * W]; };
+        auto add = [&](float v) { t += v; };
+        if (per == 1) each_term<1, float>(q_lo, q_hi, at, add);
+        else in_order<4, 8, float>(q_lo, q_hi, per, at, add);
         sg[g][c] = t;
         __syncthreads();
         if (g == 0 && i < W) {
@@ -2824,10 +2850,20 @@ __global__ __launch_bounds__(256) void k_bwd_final(BwdFinalArgs a) {
         }
         if (idx < a.out_dim) {
             const float* pb = a.part + a.pb + (int64_t)p * a.n_pb * MORLAX_MAX_OUT + idx;
-            auto at = [&](int m) { return m < a.n_pb ? pb[(int64_t)m * MORLAX_MAX_OUT] : 0.f; };
             float v = 0.f;
-#pragma unroll 2
-            for (int m = 0; m < a.n_pb; m += 4) v += (at(m) + at(m + 1)) + (at(m + 2) + at(m + 3));
+            auto add = [&](auto some) __attribute__((always_inline)) {
+                constexpr int N = decltype(some)::value;  // sums of 64 rows requested together
+                for (int m = 0; m < a.n_pb; m += N) {
+                    float t[N];
+                    get_terms(t, m, a.n_pb, [&](int q) { return pb[(int64_t)q * MORLAX_MAX_OUT]; });
+                    auto at = [&](int u) { return m + u < a.n_pb ? t[u] : 0.f; };
+#pragma unroll
+                    for (int u = 0; u < N; u += 4)
+                        if (m + u < a.n_pb) v += (at(u) + at(u + 1)) + (at(u + 2) + at(u + 3));
+                }
+            };
+            if (a.n_pb <= 4) add(std::integral_constant<int, 4>{});
+            else add(std::integral_constant<int, 32>{});
             dvec[a.vec_off[a.L] + idx] = v;
         }
         if (idx < a.A) dvec[a.logsig_off + idx] = a.dlogsig ? a.dlogsig[p * a.A + idx] : 0.f;
@@ -2835,28 +2871,33 @@ __global__ __launch_bounds__(256) void k_bwd_final(BwdFinalArgs a) {
     }
     if (b < a.b_first) {
         int l = 0;
-        while (l + 1 < a.L && b >= a.b_split[l + 1]) ++l;
+#pragma unroll
+        for (int k = 1; k < MORLAX_MAX_LAYERS; ++k) l = k < a.L && b >= a.b_split[k] ? k : l;
         const int64_t n = a.n[l], i4 = ((int64_t)(b - a.b_split[l]) * 256 + threadIdx.x) * 4;
         if (i4 >= n) return;
         const int S = a.S[l];
         const float* src = a.part + a.split[l] + (int64_t)p * S * n + i4;
-        float4 v = *reinterpret_cast<const float4*>(src);
-#pragma unroll 3
-        for (int c = 1; c < S; ++c) {
-            const float4 u = *reinterpret_cast<const float4*>(src + c * n);
-            v.x += u.x; v.y += u.y; v.z += u.z; v.w += u.w;
-        }
+        float v[4];
+        auto at = [&](int c) { return *reinterpret_cast<const u32x4_t*>(src + c * n); };
+        auto add = [&](const u32x4_t& u) {
+#pragma unroll
+            for (int e = 0; e < 4; ++e) v[e] += __uint_as_float(u[e]);
+        };
+        const u32x4_t first = at(0);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) v[e] = __uint_as_float(first[e]);
+        in_order<3, 7, u32x4_t>(1, S, S - 1, at, add);
         // W is a multiple of 16, so every matrix starts on a 16-byte boundary of the row
-        *reinterpret_cast<float4*>(dmat + a.mat_off[l] + i4) = v;
+        *reinterpret_cast<float4*>(dmat + a.mat_off[l] + i4) = make_float4(v[0], v[1], v[2], v[3]);
         return;
     }
-    const int idx = (b - a.b_first) * 256 + threadIdx.x;
+    const int idx = (b - a.b_first) * 256 + threadIdx.x;  // along the partials' rows: they are read first_ns times, written once
     if (idx >= W * a.O) return;
-    const int o = idx / a.O, i = idx % a.O;
+    const int i = idx / W, o = idx - i * W;
+    const float* src = a.part + a.first + ((int64_t)p * a.first_ns * a.OP + i) * W + o;
     float v = 0.f;
-#pragma unroll 4
-    for (int c = 0; c < a.first_ns; ++c) v += a.part[a.first + (((int64_t)p * a.first_ns + c) * a.OP + i) * W + o];
-    dmat[a.mat_off[0] + idx] = v;
+    in_order<4, 16, float>(0, a.first_ns, a.first_ns, [&](int q) { return src[(int64_t)q * a.OP * W]; }, [&](float t) { v += t; });
+    dmat[a.mat_off[0] + (int64_t)o * a.O + i] = v;
 }
 
 // Rows of the fp32 observation tensor picked by the row map, rounded to the GEMM input type, as compact

@@ -31,6 +31,11 @@ CASES += [case(512, 128, 40, 3, 2, 2, 2, wdtype=1), case(2048, 64, 40, 3, 2, 3, 
 # bf16 first layers on small tiles whose last range is the shorter one (padded rows 2112 + 2016 and 2112 + 2048)
 CASES += [case(4115, 80, 33, 3, 2, 2, 2, wdtype=1), case(4160, 144, 70, 3, 2, 1, 2, wdtype=1)]
 
+# terms requested together at the end of the backward pass: 32 sums of 64 rows of the output layer's bias (31, 32, 33 and 65 of them), 8
+# row blocks of an eighth of a layer's bias sums, 16 ranges of the first layer's dW (16, 17 and more), 2, 4, 8 and 16 ranges of a split one
+CASES += [case(M, 64, O, 3, 2, 2, 2, wdtype=b) for b in (0, 1) for M, O in ((1984, 11), (2048, 16), (2049, 17), (4097, 3))]
+CASES += [case(M, 128, 40, 3, 2, 2, 2, wdtype=0) for M in (129, 257, 512, 1024, 1030)]
+
 
 @pytest.mark.parametrize("cfg", CASES, ids=lambda c: c.name)
 def test_backward_at_the_edges_of_its_partial_sums(cfg, torch, binding):  # noqa: F811
