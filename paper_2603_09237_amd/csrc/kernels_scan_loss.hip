@@ -500,8 +500,12 @@ __device__ inline void lds_to_cells(const CellRuns& g, float* __restrict__ X, in
 }
 
 // NT threads work on groups of NT cells, moved run by run (RUNS) or piece by piece (rule: loss_by_runs)
+// Eight waves a SIMD, 64 registers.  From 13 action components on a group's cells are at least 14 KB of LDS, which leaves room for
+// eleven blocks, 5.5 waves a SIMD: asked for 64 registers the pieces spilled two of them for nothing (us a call, with 64 and
+// with as many as six waves leave: 13 components, 24 preferences x 1250 cells in runs of 50 18.6 and 18.1; 16 of them, 64 x 4000 in
+// runs of 16 44.4 and 43.1, 128 x 65 536 in runs of 512 936 and 904).
 template <int A_MAX, int NT, bool V4, bool RUNS>
-__global__ __launch_bounds__(NT, 8) void k_ppo_loss_grad(
+__global__ __launch_bounds__(NT, A_MAX > 12 ? 6 : 8) void k_ppo_loss_grad(
     RowSel rs, const float* __restrict__ mu, const float* __restrict__ logsig, int ls_stride,
     const float* __restrict__ act, const float* __restrict__ logp_old, const float* __restrict__ adv_s,
     const float* __restrict__ v, const float* __restrict__ vtarg, const double* __restrict__ adv_part, int n_adv,
@@ -765,8 +769,10 @@ void launch_ppo_loss_grad(const morlax_ctx* c, const RowSel& rs, const float* mu
             rs, mu, logsig, logsig_stride, act, logp_old, adv_s, v, vtarg, L.adv_part, pl.n_adv, clip_eps, norm_adv,
             cnt, dmu, dv, L.stat_part, L.dls_part, N, c->n_g, A, K, pl.G, sig, row_div(mus), row_div(A), row_div(K));
     };
-    // (code and registers of as few action components as the call has, in steps of four: with sixteen for all of them 64
-    // registers were not enough)
+    // Code and registers of as few action components as the call has, in steps of four: with sixteen for all of them 64 registers
+    // are not enough for the pieces, and what is skipped costs the runs time (128 x 65 536 cells in runs of 512, us a call with the
+    // code for sixteen and so: 2 components 191 and 170, 6 258 and 244, 10 328 and 320; 128 x 8192 in runs of 256, 2 components 35.7
+    // and 32.8).
     auto pick = [&](auto v4, auto runs) {
         if (A <= 4) launch(v4, std::integral_constant<int, 4>{}, runs);
         else if (A <= 8) launch(v4, std::integral_constant<int, 8>{}, runs);
