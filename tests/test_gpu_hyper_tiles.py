@@ -1,0 +1,18 @@
+"""dA and dB where a row of weights is no multiple of four values, or the last rows and columns do not fill a tile: the values a
+tile is short of are requested at its edge and zeroed.  Against the oracle with the bounds of the parity tests."""
+import pytest
+
+import test_gpu_parity as parity
+from paper_2603_09237_amd.configs import scaled
+from test_gpu_parity import RAGGED, _float32_default, binding, torch  # noqa: F401  (fixtures)
+
+pytestmark = pytest.mark.gpu
+
+CASES = [scaled(RAGGED, name=f"r{r}-O{O}-W{W}-A{A}", rank=r, obs_dim=O, width=W, act_dim=A, P=3, N=6, n_hidden=2)
+         for r, O, W, A in ((4, 1, 16, 1), (1, 2, 48, 3), (8, 3, 64, 2), (16, 63, 80, 5), (17, 65, 64, 4), (5, 127, 144, 3), (32, 129, 32, 16),
+                            (8, 131, 208, 7), (3, 190, 128, 1))]
+
+
+@pytest.mark.parametrize("cfg", CASES, ids=lambda c: c.name)
+def test_factor_gradients_at_the_edges_of_tiles(cfg, torch, binding):  # noqa: F811
+    parity.test_hypernet_bwd_matches_oracle(cfg, torch, binding)
