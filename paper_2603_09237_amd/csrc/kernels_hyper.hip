@@ -25,6 +25,15 @@ static int df_chunk_tiles(int64_t q_total) {
     return t < 4 ? 4 : (int)t;
 }
 
+static int cu_count() {
+    static int n = 0;
+    if (n == 0) {
+        int dev = 0, cus = 0;
+        n = hipGetDevice(&dev) == hipSuccess && hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess && cus > 0 ? cus : 256;
+    }
+    return n;
+}
+
 static HyperWs hyper_ws_layout(const morlax_ctx* c, void* ws, int64_t* total) {
     const int64_t P = c->d.P, F = c->d.hyper_width;
     const bool affine = c->d.rank < 0;  // no factor vector: the leading stacked rows are theta_mat itself
@@ -552,11 +561,14 @@ __device__ inline void dbase_block(const LayerRule& lr, const LayerItems& elems,
     float* d = dhp + lr.at(l).hp_w0 + at;
     d[0] = a.x; d[1] = a.y; d[2] = a.z; d[3] = a.w;
 }
-struct BaseWork {  // blocks of 256 threads that add up dW0: by themselves or, where there are factors, among those of k_hyper_dAB
+struct BaseWork {  // blocks of 256 threads that add up dW0: by themselves or, where there are factors, beside those of k_hyper_dAB
     float* dhp;
     int64_t mat_len;
     LayerItems elems;  // elements of theta_mat
-    uint64_t share;    // among others: base blocks a block, 2^32 times and rounded up (so all of them end up in front of the end)
+    int32_t n, n_dab;  // base blocks, blocks of dA / dB
+    // 0: base blocks behind all others.  Else among them, row by row of eight: base rows a row, 2^32 times and rounded up (so all of
+    // them end up in front of the end).
+    uint64_t share;
 };
 __global__ __launch_bounds__(256) void k_hyper_base(LayerRule lr, BaseWork bw, const float* __restrict__ dmat, int P) {
     dbase_block(lr, bw.elems, bw.mat_len, dmat, bw.dhp, P, blockIdx.x);
@@ -567,9 +579,18 @@ __global__ __launch_bounds__(256) void k_hyper_base(LayerRule lr, BaseWork bw, c
 // A block owns (p, layer, a run of <= DAB_COLS columns).  It walks the 64 x 64 tiles of dW row block by row
 // block: wave w multiplies rows 16 w .. of the tile by B^T (dA, finished after the columns of a row block)
 // and A^T by columns 16 w .. of the tile (dB, accumulated over all row blocks in registers).
-// dW0, which reads the same matrices, runs in blocks spread evenly among these: it is bound by memory, dA / dB by its
-// products (128 preferences of 4 x 512, rank 16: 87 us behind 133 as launches of their own, together 182; 24 of 3 x 256: 5.6
-// + 18 and 22.4).  Both go through the layers in order, all preferences of one before the next: what either reads first the
+// dW0, which reads the same matrices, runs in the same launch: it is bound by memory, dA / dB by its products (128 preferences of
+// 4 x 512, rank 16: 87 us behind 133 as launches of their own, together 182; 24 of 3 x 256: 5.6 + 18 and 22.4).  While the blocks of
+// dA / dB are about as many as the chip holds, four a CU and an eighth of that (the first to go, those of the first layer, are
+// short), they come first and dW0 runs beside them; from some 80 preferences on up to 3.5 a CU, because a block of dW0 adds its
+// preferences eight at a time, one batch behind the other, and is no longer the shorter one.  More of them are spread evenly among
+// its blocks, in rows of eight consecutive blocks of one kind, one to a die.  (Block by block every eighth was dA / dB for 9
+// preferences of 3 x 768, all of them on one die.)
+// us a call of hypernet_bwd, spread block by block, in rows of eight, and with dA / dB first: those 9 101, 72, 63; 4 x 512, 16
+// preferences (272 blocks) 62, 72, 54, 48 (816) 101, 107, 88, 64 (1088) 117, 116, 109, 80 (1360) 138, 135, 139, 128 (2176) 196, 194,
+// 247; 3 x 1024, 44 (1100) 191, 193, 185, 50 (1250) 210, 214, 233; 3 x 384 with 97 observations, 90 (900) 86, 87, 85, 110 (1100) 96, 97,
+// 100; 3 x 256, 128 (896) 62, 62, 62, 160 (1120) 87, 85, 89; rank 32, 4 x 512, 50 (850) 146, 150, 133.
+// Both go through the layers in order, all preferences of one before the next: what either reads first the
 // other finds in the memory-side cache (128 matrices of 512 x 512 are 134 of its 256 MB).  Preference by preference 183 us for
 // the 128, layer by layer 165; 22.5 and 19 for the 24, 25 and 22 for 32 of 3 x 256, rank 8.  (A wave on sixteen rows by itself,
 // operands four columns a lane, no barrier: 181 and 19.7.)
@@ -582,12 +603,19 @@ __global__ __launch_bounds__(256) void k_hyper_dAB(LayerRule lr, LayerItems runs
     __shared__ __align__(16) float sW[64][68];
     __shared__ float sA[64][AP];
     __shared__ float sB[DAB_NCT][16 * RT][68];
-    const int before = (int)(bw.share * blockIdx.x >> 32);  // base blocks in front of this one
-    if ((int)(bw.share * (blockIdx.x + 1) >> 32) != before) {
-        dbase_block(lr, bw.elems, bw.mat_len, dmat, bw.dhp, P, before);
+    int dab = blockIdx.x, base = dab - bw.n_dab;  // number among the blocks of its kind; base < 0: none of the other kind
+    if (bw.share) {
+        const int row = blockIdx.x >> 3, before = (int)(bw.share * row >> 32);  // base rows in front of this one
+        const bool is_base = (int)(bw.share * (row + 1) >> 32) != before;
+        base = is_base ? before * 8 + (blockIdx.x & 7) : -1;
+        dab = (row - before) * 8 + (blockIdx.x & 7);
+        if (is_base ? base >= bw.n : dab >= bw.n_dab) return;
+    }
+    if (base >= 0) {
+        dbase_block(lr, bw.elems, bw.mat_len, dmat, bw.dhp, P, base);
         return;
     }
-    const int dab = blockIdx.x - before, item = (int)by_p.quotient((uint32_t)dab), p = dab - item * P;
+    const int item = (int)by_p.quotient((uint32_t)dab), p = dab - item * P;
     int cs;
     const LayerPlace L = lr.at(runs.layer(lr, item, cs));
     const int c_lo = cs * DAB_COLS;
@@ -1215,7 +1243,7 @@ void launch_hypernet_bwd(const morlax_ctx* c, int net, const float* hparams, con
     }
     const int n_hidden = nd.n_layers - 1;
     auto elems = [&](int l) { return nd.layer[l].d_out * nd.layer[l].d_in; };
-    BaseWork bw = {dhparams, nd.mat_len, layer_items(elems(0), n_hidden > 1 ? elems(1) : 0), 0};
+    BaseWork bw = {dhparams, nd.mat_len, layer_items(elems(0), n_hidden > 1 ? elems(1) : 0), 0, 0, 0};
     const LayerRule lr = layer_rule(nd);
     const AffineRows ar = affine_rows(at, F);
     const int n_base = affine ? 0 : (int)((nd.mat_len / 4 + 255) / 256);  // (strictly affine form: W0 is a constant of the rows)
@@ -1226,8 +1254,14 @@ void launch_hypernet_bwd(const morlax_ctx* c, int net, const float* hparams, con
             if (runs(l) > 1 && nd.layer[l].d_out * r > merged) merged = nd.layer[l].d_out * r;
             n_runs += runs(l);
         }
-        const int nb = n_runs * P + n_base;
-        bw.share = (((uint64_t)n_base << 32) + nb - 1) / nb;
+        bw.n = n_base;
+        bw.n_dab = n_runs * P;
+        int nb = bw.n_dab + n_base;
+        if (bw.n_dab > (P <= 80 ? 9 : 7) * cu_count() / 2) {
+            const int rows = (n_base + 7) / 8, all = rows + (bw.n_dab + 7) / 8;
+            bw.share = (((uint64_t)rows << 32) + all - 1) / all;
+            nb = 8 * all;
+        }
         auto dab = [&](auto kernel) {
             kernel<<<nb, 256, 0, s>>>(lr, layer_items(runs(0), n_hidden > 1 ? runs(1) : 0), row_div(P), bw, dtheta_mat, L.fac, L.dfac,
                                       L.da_part, r, P, nd.fac_len);

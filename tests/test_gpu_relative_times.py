@@ -51,3 +51,10 @@ def test_gradient_of_odd_rows_takes_little_more_than_of_even_ones(torch, binding
     """hypernet_bwd with 190 observations against 192, whose rows are whole four-value pieces: a quarter for the pieces and the clock."""
     odd, even = (hyper(torch, binding, case(13, 2, 512, o, rank=16))[1] for o in (190, 192))
     assert ratio(torch, odd, even) < 1.25
+
+
+def test_gradient_takes_no_longer_for_another_number_of_base_blocks(torch, binding):  # noqa: F811
+    """hypernet_bwd of 9 preferences of 3 x 768 with 57 observations against 60: the less work, so the shorter call (a tenth is left for
+    the clock).  Spread block by block, every eighth block of the former was one of dA / dB: all of them on one die."""
+    fewer, more = (hyper(torch, binding, case(9, 3, 768, o, rank=16))[1] for o in (57, 60))
+    assert ratio(torch, fewer, more) < 1.1
