@@ -816,7 +816,7 @@ __device__ inline float grad_row(const float* __restrict__ dfac, const float* __
 // us a call of hypernet_bwd, with row offsets in memory besides, and so: 4 preferences of 2 x 32 18.8 and 15.2, 24 of 3 x 256 40.7 and
 // 35.6, 64 46.2 and 43.4, 32 of 4 x 512, rank 16 97 and 78; strictly affine, 10 of 2 x 160 22.3 and 19.5.
 template <int JT, bool FINE, int SHORT>
-__global__ __launch_bounds__(64 * DMF_W) void k_hyper_dM_df(const float* __restrict__ hp, AffineRows at, const float* __restrict__ f,
+__global__ __launch_bounds__(64 * DMF_W, JT == 2 ? 4 : 2) void k_hyper_dM_df(const float* __restrict__ hp, AffineRows at, const float* __restrict__ f,
                                                     const float* __restrict__ dfac, const float* __restrict__ dvec,
                                                     float* __restrict__ dhp, float* __restrict__ part, int P, int F,
                                                     int64_t fac_len, int64_t vec_len, int n_tiles, int tpw,
@@ -825,15 +825,17 @@ __global__ __launch_bounds__(64 * DMF_W) void k_hyper_dM_df(const float* __restr
     extern __shared__ __align__(16) float dml[];
     float(*Dl)[PD] = reinterpret_cast<float(*)[PD]>(dml);                 // [TB * DP]
     float(*Ml)[PJ] = reinterpret_cast<float(*)[PJ]>(dml + TB * DP * PD);  // [TB * DMF_Q]
-    int32_t* Rl = reinterpret_cast<int32_t*>(dml + TB * (DP * PD + DMF_Q * PJ));  // offsets of rows of M: twice eight tiles, or the chunk's
+    int32_t* Rl = reinterpret_cast<int32_t*>(dml + TB * (DP * PD + DMF_Q * PJ));  // offsets of rows of M: twice eight tiles and the table of segments, or the chunk's
     const int q_total = at.q_total;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, ln = lane & 15, kg = lane >> 4;
     if ((int)blockIdx.x >= n_df) {  // dM and dc of one tile a wave (no barrier: the waves are on their own)
         const int tile = dm_t * xcd_remap(blockIdx.x - n_df, gridDim.x - n_df) + wave;
         if (wave >= dm_t || tile >= n_tiles) return;
         const int q0 = tile * DMF_Q, q4 = q0 + 4 * ln;
-        int32_t mo, co;  // of row q0 + lane
-        at.offsets(F, q0 + lane < q_total ? q0 + lane : q_total - 1, mo, co);
+        int sg = 0;  // segment of row q0 + lane; its offsets are not needed before the results are there
+#pragma unroll
+        for (int s = 1; s < MORLAX_MAX_SEG; ++s) sg = q0 + lane >= at.q0[s] ? s : sg;
+        const int32_t mo = at.m[sg] + (q0 + lane) * F, co = at.c[sg] + q0 + lane;
         float4_t acc[4][JT];
         float dc[4] = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
@@ -964,11 +966,16 @@ __global__ __launch_bounds__(64 * DMF_W) void k_hyper_dM_df(const float* __restr
     } else {
         float nxt[DMF_P / DMF_W], mnx[MPT];
         static_assert(64 * DMF_W == 8 * DMF_Q, "a thread a row of eight tiles");
-        auto fill_rows = [&](int eight) {  // the offsets of the rows of M of the chunk's `eight`-th eight tiles
-            const int q = (t_lo + 8 * eight) * DMF_Q + (int)threadIdx.x;
-            int32_t mo, co;
-            at.offsets(F, q < q_total ? q : q_total - 1, mo, co);
-            Rl[(eight & 1) * 8 * DMF_Q + threadIdx.x] = mo;
+        // the offsets of the rows of M of the chunk's `eight`-th eight tiles, from a copy of the table in LDS.  (From the arguments 84
+        // scalars lived through the loop, spilled into vector registers: beyond 128 preferences past 128 of them, where a CU holds one
+        // workgroup instead of two.  139 preferences of a strictly affine 4 x 512 network 451 us a launch, 343 here.)
+        int32_t* tab = Rl + 16 * DMF_Q;
+        auto fill_rows = [&](int eight) {
+            const int q0 = (t_lo + 8 * eight) * DMF_Q + (int)threadIdx.x, q = q0 < q_total ? q0 : q_total - 1;
+            int s = 0;  // the last segment that starts at or before q
+#pragma unroll
+            for (int step = 16; step > 0; step >>= 1) s = q >= tab[s + step] ? s + step : s;
+            Rl[(eight & 1) * 8 * DMF_Q + threadIdx.x] = tab[32 + s] + q * F;
         };
         auto fetch = [&](int tile) {
             const int q = tile * DMF_Q + lane;
@@ -987,6 +994,13 @@ __global__ __launch_bounds__(64 * DMF_W) void k_hyper_dM_df(const float* __restr
 #pragma unroll
             for (int jt = 0; jt < JT; ++jt) sumF[jt] = accF[jt];
         }
+        static_assert(MORLAX_MAX_SEG <= 32, "five halvings");
+        if (threadIdx.x < 32) {
+            const int s = threadIdx.x < MORLAX_MAX_SEG ? threadIdx.x : 0;
+            tab[threadIdx.x] = threadIdx.x < MORLAX_MAX_SEG ? at.q0[s] : INT32_MAX;
+            tab[32 + threadIdx.x] = at.m[s];
+        }
+        __syncthreads();
         fill_rows(0);
         __syncthreads();
         fetch(t_lo);
@@ -1278,7 +1292,7 @@ void launch_hypernet_bwd(const morlax_ctx* c, int net, const float* hparams, con
     auto dM_df = [&](auto jt, auto fine, auto brief) {
         constexpr int JT = decltype(jt)::value;
         constexpr int SHORT = decltype(brief)::value;
-        constexpr int TB = SHORT ? DMF_TB : 1, bytes = 4 * (TB * ((SHORT ? SHORT : DMF_P) * 68 + DMF_Q * (16 * JT + 16)) + (SHORT ? TB : 16) * DMF_Q);
+        constexpr int TB = SHORT ? DMF_TB : 1, bytes = 4 * (TB * ((SHORT ? SHORT : DMF_P) * 68 + DMF_Q * (16 * JT + 16)) + (SHORT ? TB * DMF_Q : 16 * DMF_Q + 64));
         auto kernel = k_hyper_dM_df<JT, decltype(fine)::value, SHORT>;
         if (bytes > 64 * 1024) allow_lds(reinterpret_cast<const void*>(kernel), bytes, (JT == 2 ? 0 : 1) + (SHORT == 32 ? 0 : 2));
         kernel<<<n_df + n_dm, 64 * DMF_W, bytes, s>>>(hparams, ar, L.f, dlead, dtheta_vec, dhparams, L.df_part, P, F, nd.fac_len,

@@ -56,6 +56,18 @@ def of(built, pattern):
     return hit
 
 
-@pytest.mark.parametrize("pattern", [r"k_ppo_loss_grad"])
+@pytest.mark.parametrize("pattern", [r"k_ppo_loss_grad", r"k_hyper_dM_df"])
 def test_no_scratch_memory(pattern, built):
     assert {n: k[".private_segment_fixed_size"] for n, k in of(built, pattern).items() if k[".private_segment_fixed_size"]} == {}
+
+
+# pattern, registers: workgroups of eight waves, two of them to a CU
+@pytest.mark.parametrize("pattern, registers", [(r"k_hyper_dM_dfILi2E", 128)])
+def test_registers_leave_room_for_the_workgroups_of_a_cu(pattern, registers, built):
+    assert {n: k[".vgpr_count"] for n, k in of(built, pattern).items() if k[".vgpr_count"] > registers} == {}
+
+
+@pytest.mark.parametrize("pattern", [r"k_hyper_dM_df"])
+def test_scalars_stay_scalar(pattern, built):
+    """No table of kernel arguments is kept in the lanes of vector registers."""
+    assert {n: k[".sgpr_spill_count"] for n, k in of(built, pattern).items() if k[".sgpr_spill_count"]} == {}
