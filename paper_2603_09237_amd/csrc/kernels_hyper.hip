@@ -566,8 +566,8 @@ struct BaseWork {  // blocks of 256 threads that add up dW0: by themselves or, w
     int64_t mat_len;
     LayerItems elems;  // elements of theta_mat
     int32_t n, n_dab;  // base blocks, blocks of dA / dB
-    // 0: base blocks behind all others.  Else among them, row by row of eight: base rows a row, 2^32 times and rounded down, those in
-    // front of a row rounded up (so the first row is one of them and the last is not).
+    // 0: base blocks behind all others.  Else in rows of eight: base rows a row until there are no more, 2^32 times and rounded down,
+    // those in front of a row rounded up (so the first row is one of them, and 2^32 puts all of them first).
     uint64_t share;
 };
 __global__ __launch_bounds__(256) void k_hyper_base(LayerRule lr, BaseWork bw, const float* __restrict__ dmat, int P) {
@@ -583,14 +583,14 @@ __global__ __launch_bounds__(256) void k_hyper_base(LayerRule lr, BaseWork bw, c
 // 4 x 512, rank 16: 87 us behind 133 as launches of their own, together 182; 24 of 3 x 256: 5.6 + 18 and 22.4).  While the blocks of
 // dA / dB are about as many as the chip holds, four a CU and an eighth of that (the first to go, those of the first layer, are
 // short), they come first and dW0 runs beside them; from some 80 preferences on up to 3.5 a CU, because a block of dW0 adds its
-// preferences eight at a time, one batch behind the other, and is no longer the shorter one.  More of them are spread evenly among
-// its blocks, in rows of eight consecutive blocks of one kind, one to a die, a row of dW0 first (where there are few of them, one
-// at the end is what the launch waits for: 400 preferences of 3 x 64 89 and 86 us).  (Block by block every eighth was dA / dB for 9
-// preferences of 3 x 768, all of them on one die.)
+// preferences eight at a time, one batch behind the other, and is no longer the shorter one.  With more blocks of dA / dB than that
+// dW0's are spread evenly among them, in rows of eight consecutive blocks of one kind, one to a die, or come first where there is no
+// more than one a CU.  (Block by block every eighth was dA / dB for 9 preferences of 3 x 768, all of them on one die.)
 // us a call of hypernet_bwd, spread block by block, in rows of eight, and with dA / dB first: those 9 101, 72, 63; 4 x 512, 16
 // preferences (272 blocks) 62, 72, 54, 48 (816) 101, 107, 88, 64 (1088) 117, 116, 109, 80 (1360) 138, 135, 139, 128 (2176) 196, 194,
 // 247; 3 x 1024, 44 (1100) 191, 193, 185, 50 (1250) 210, 214, 233; 3 x 384 with 97 observations, 90 (900) 86, 87, 85, 110 (1100) 96, 97,
-// 100; 3 x 256, 128 (896) 62, 62, 62, 160 (1120) 87, 85, 89; rank 32, 4 x 512, 50 (850) 146, 150, 133.
+// 100; 3 x 256, 128 (896) 62, 62, 62, 160 (1120) 87, 85, 89; rank 32, 4 x 512, 50 (850) 146, 150, 133.  In rows, evenly and dW0 first:
+// 3 x 256, 146 preferences (144 blocks of dW0) 79, 76, 400 195, 174; 500 of 3 x 128 (48) 134, 126; 3 x 384, 146 (336) 125, 133, 200 160, 163.
 // Both go through the layers in order, all preferences of one before the next: what either reads first the
 // other finds in the memory-side cache (128 matrices of 512 x 512 are 134 of its 256 MB).  Preference by preference 183 us for
 // the 128, layer by layer 165; 22.5 and 19 for the 24, 25 and 22 for 32 of 3 x 256, rank 8.  (A wave on sixteen rows by itself,
@@ -606,8 +606,10 @@ __global__ __launch_bounds__(256) void k_hyper_dAB(LayerRule lr, LayerItems runs
     __shared__ float sB[DAB_NCT][16 * RT][68];
     int dab = blockIdx.x, base = dab - bw.n_dab;  // number among the blocks of its kind; base < 0: none of the other kind
     if (bw.share) {
-        const int row = blockIdx.x >> 3, before = (int)((bw.share * row + 0xffffffffu) >> 32);  // base rows in front of this one
-        const bool is_base = (int)((bw.share * (row + 1) + 0xffffffffu) >> 32) != before;
+        const int row = blockIdx.x >> 3, rows = (bw.n + 7) >> 3;
+        auto in_front = [&](int r) { return min((int)((bw.share * r + 0xffffffffu) >> 32), rows); };
+        const int before = in_front(row);  // base rows in front of this one
+        const bool is_base = in_front(row + 1) != before;
         base = is_base ? before * 8 + (blockIdx.x & 7) : -1;
         dab = (row - before) * 8 + (blockIdx.x & 7);
         if (is_base ? base >= bw.n : dab >= bw.n_dab) return;
@@ -1274,7 +1276,7 @@ void launch_hypernet_bwd(const morlax_ctx* c, int net, const float* hparams, con
         int nb = bw.n_dab + n_base;
         if (bw.n_dab > (P <= 80 ? 9 : 7) * cu_count() / 2) {
             const int rows = (n_base + 7) / 8, all = rows + (bw.n_dab + 7) / 8;
-            bw.share = ((uint64_t)rows << 32) / all;
+            bw.share = n_base <= cu_count() ? (uint64_t)1 << 32 : ((uint64_t)rows << 32) / all;
             nb = 8 * all;
         }
         auto dab = [&](auto kernel) {

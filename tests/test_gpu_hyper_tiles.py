@@ -1,4 +1,4 @@
-"""dA and dB of as many blocks as the chip holds, of which those of dW0 come last, and of more, which stand among them in rows of eight;
+"""dA and dB of as many blocks as the chip holds, in front of those of dW0, and of more, behind or among them in rows of eight;
 dA and dB where a row of weights is no multiple of four values, or the last rows and columns do not fill a tile: the values a
 tile is short of are requested at its edge and zeroed.  Against the oracle with the bounds of the parity tests."""
 import pytest
@@ -19,9 +19,10 @@ def test_factor_gradients_at_the_edges_of_tiles(cfg, torch, binding):  # noqa: F
     parity.test_hypernet_bwd_matches_oracle(cfg, torch, binding)
 
 
-# blocks of dA / dB (four column runs and more to a preference): 892, 896, 900 of many preferences, 1152 and 1168 of few; dW0 in 1, 7, 8, 9 blocks and more
+# blocks of dA / dB (four column runs and more to a preference): 892, 896, 900 of many preferences, 1152 and 1168 of few; dW0 in few
+# blocks and in 9, 44, 256, 258, 555
 SHARE_CASES = [scaled(RAGGED, name=f"P{P}-L{L}-W{W}-O{O}", rank=2, obs_dim=O, width=W, P=P, N=2 * P, n_hidden=L, hyper_width=4)
-               for P, L, W, O in ((223, 3, 16, 5), (224, 3, 16, 5), (225, 3, 48, 24), (290, 3, 48, 76), (173, 3, 144, 17), (72, 3, 528, 17), (73, 3, 528, 17))]
+               for P, L, W, O in ((223, 3, 16, 5), (224, 3, 16, 5), (225, 3, 48, 24), (290, 3, 48, 76), (173, 3, 144, 17), (72, 3, 528, 17), (73, 3, 528, 17), (130, 2, 400, 250), (130, 2, 400, 256))]
 
 
 @pytest.mark.parametrize("cfg", SHARE_CASES, ids=lambda c: c.name)
