@@ -815,9 +815,8 @@ __device__ inline float grad_row(const float* __restrict__ dfac, const float* __
 #define DMF_P (16 * DMF_W)  // preferences of a df workgroup
 #define DMF_TB 4            // tiles of a short chunk
 // SHORT (up to so many preferences, 32 or 64, in chunks of four tiles; 0: any): a df workgroup requests all of its chunk together
-// instead of tile by tile, each behind the one before; the products are the same, in the same order.
-// us a call of hypernet_bwd, with row offsets in memory besides, and so: 4 preferences of 2 x 32 18.8 and 15.2, 24 of 3 x 256 40.7 and
-// 35.6, 64 46.2 and 43.4, 32 of 4 x 512, rank 16 97 and 78; strictly affine, 10 of 2 x 160 22.3 and 19.5.
+// instead of tile by tile, each behind the one before (rule and both sides' times: dm_df_brief); the products are the same, in the
+// same order.
 template <int JT, bool FINE, int SHORT>
 __global__ __launch_bounds__(64 * DMF_W, JT == 2 ? 4 : 2) void k_hyper_dM_df(const float* __restrict__ hp, AffineRows at, const float* __restrict__ f,
                                                     const float* __restrict__ dfac, const float* __restrict__ dvec,
@@ -1228,15 +1227,14 @@ static int dm_tiles(int n_tiles) {
     return t < DMF_W ? t : DMF_W;
 }
 
-// more LDS than the default, allowed once per device (a bit each) and kernel
-static void allow_lds(const void* kernel, int bytes, int slot) {
-    static std::atomic<uint64_t> allowed[4];
-    int dev = 0;
-    (void)hipGetDevice(&dev);
-    const uint64_t bit = (uint64_t)1 << (dev & 63);
-    if (allowed[slot].load(std::memory_order_relaxed) & bit) return;
-    (void)hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
-    allowed[slot].fetch_or(bit, std::memory_order_relaxed);
+// Whether df workgroups request their chunk together.  Its 85 to 153 KB of LDS leave one workgroup a CU, the dM ones of the launch,
+// which use none of it, included.  With up to 32 features the general form has room for two, so the whole chunk is for launches
+// that are one round of one a CU; beyond, the registers hold the general form to one as well.  us a call of hypernet_bwd, tile by
+// tile and chunk by chunk, 32 features: 24 preferences of 3 x 256 (159 workgroups) 35.8 and 32.5, 64 (206) 44.2 and 42.8, 64 of 2 x 160,
+// strictly affine (238) 20.9 and 19.9, 48 of 3 x 384 (274) 56.8 and 59.0, 64 (317) 72.2 and 74.2, 32 of 3 x 512 (317) 62.0 and 63.0,
+// 64 of 4 x 512 (402) 105.7 and 107.9; 64 features: 24 of 3 x 256 41.9 and 37.2, 8 of 4 x 512 66.2 and 60.5, 64 121.0 and 119.9.
+static bool dm_df_brief(int F, int tiles_per_chunk, int workgroups) {
+    return tiles_per_chunk == DMF_TB && (F > 32 || workgroups <= cu_count());
 }
 
 void launch_hypernet_bwd(const morlax_ctx* c, int net, const float* hparams, const float* w,
@@ -1297,7 +1295,16 @@ void launch_hypernet_bwd(const morlax_ctx* c, int net, const float* hparams, con
         constexpr int SHORT = decltype(brief)::value;
         constexpr int TB = SHORT ? DMF_TB : 1, bytes = 4 * (TB * ((SHORT ? SHORT : DMF_P) * 68 + DMF_Q * (16 * JT + 16)) + (SHORT ? TB * DMF_Q : 16 * DMF_Q + 64));
         auto kernel = k_hyper_dM_df<JT, decltype(fine)::value, SHORT>;
-        if (bytes > 64 * 1024) allow_lds(reinterpret_cast<const void*>(kernel), bytes, (JT == 2 ? 0 : 1) + (SHORT == 32 ? 0 : 2));
+        if (bytes > 64 * 1024) {
+            static std::atomic<uint64_t> allowed{0};  // devices on which the kernel may take more LDS than the default (a bit each)
+            int dev = 0;
+            (void)hipGetDevice(&dev);
+            const uint64_t bit = (uint64_t)1 << (dev & 63);
+            if (!(allowed.load(std::memory_order_relaxed) & bit)) {
+                (void)hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
+                allowed.fetch_or(bit, std::memory_order_relaxed);
+            }
+        }
         kernel<<<n_df + n_dm, 64 * DMF_W, bytes, s>>>(hparams, ar, L.f, dlead, dtheta_vec, dhparams, L.df_part, P, F, nd.fac_len,
                                                       nd.vec_len, n_tiles, tpw, n_p, n_df, dm_t);
     };
@@ -1305,9 +1312,10 @@ void launch_hypernet_bwd(const morlax_ctx* c, int net, const float* hparams, con
         if (F <= 32) dM_df(std::integral_constant<int, 2>{}, fine, brief);
         else dM_df(std::integral_constant<int, 4>{}, fine, brief);
     };
+    const bool brief = P <= 64 && dm_df_brief(F, tpw, n_df + n_dm);
     if (n_p > 1) pick(std::true_type{}, std::integral_constant<int, 0>{});
-    else if (P <= 32 && tpw == DMF_TB) pick(std::false_type{}, std::integral_constant<int, 32>{});
-    else if (P <= 64 && tpw == DMF_TB) pick(std::false_type{}, std::integral_constant<int, 64>{});
+    else if (brief && P <= 32) pick(std::false_type{}, std::integral_constant<int, 32>{});
+    else if (brief) pick(std::false_type{}, std::integral_constant<int, 64>{});
     else pick(std::false_type{}, std::integral_constant<int, 0>{});
     const int lds = (7 * P * F + P * K) * 4;  // (with the kernel's 16 KB at most 64)
     if (trunk_bwd_inside(P, F, n_chunk) && lds <= 48 * 1024) {

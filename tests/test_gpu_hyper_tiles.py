@@ -1,6 +1,8 @@
-"""dA and dB of as many blocks as the chip holds, in front of those of dW0, and of more, behind or among them in rows of eight;
-dA and dB where a row of weights is no multiple of four values, or the last rows and columns do not fill a tile: the values a
-tile is short of are requested at its edge and zeroed.  Against the oracle with the bounds of the parity tests."""
+"""Gradients of a low-rank hypernetwork at the lines of what its two large launches do.  dA and dB of as many blocks as the chip
+holds, in front of those of dW0, and of more, behind or among them in rows of eight.  dA and dB where a row of weights is no
+multiple of four values, or the last rows and columns do not fill a tile: the values a tile is short of are requested at its edge
+and zeroed.  Chunks of stacked rows on both sides of the rule for their requests.  Against the oracle with the bounds of the
+parity tests."""
 import pytest
 
 import test_gpu_parity as parity
@@ -27,4 +29,15 @@ SHARE_CASES = [scaled(RAGGED, name=f"P{P}-L{L}-W{W}-O{O}", rank=2, obs_dim=O, wi
 
 @pytest.mark.parametrize("cfg", SHARE_CASES, ids=lambda c: c.name)
 def test_blocks_of_both_kinds_are_all_there(cfg, torch, binding):  # noqa: F811
+    parity.test_hypernet_bwd_matches_oracle(cfg, torch, binding)
+
+
+# chunks of rows that a workgroup requests as a whole or tile by tile: 256 and 258 workgroups of 32 features, and of 33, more of them
+BRIEF_CASES = [scaled(RAGGED, name=f"P{P}-F{F}-O{O}-W{W}", rank=-1, obs_dim=O, width=W, P=P, N=2 * P, n_hidden=2, hyper_width=F)
+               for P, F, O, W in ((3, 32, 61, 160), (3, 32, 63, 160), (3, 33, 63, 160), (33, 32, 61, 160), (33, 32, 63, 160), (33, 40, 63, 160),
+                                  (64, 32, 45, 256), (64, 40, 45, 256))]
+
+
+@pytest.mark.parametrize("cfg", BRIEF_CASES, ids=lambda c: c.name)
+def test_chunks_as_a_whole_and_tile_by_tile(cfg, torch, binding):  # noqa: F811
     parity.test_hypernet_bwd_matches_oracle(cfg, torch, binding)
