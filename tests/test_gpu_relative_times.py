@@ -58,3 +58,10 @@ def test_gradient_takes_no_longer_for_another_number_of_base_blocks(torch, bindi
     the clock).  Spread block by block, every eighth block of the former was one of dA / dB: all of them on one die."""
     fewer, more = (hyper(torch, binding, case(9, 3, 768, o, rank=16))[1] for o in (57, 60))
     assert ratio(torch, fewer, more) < 1.1
+
+
+def test_features_beyond_32_cost_little_more_than_32(torch, binding):  # noqa: F811
+    """hypernet_fwd of 40 preferences of 2 x 64 with 40 features against 32: a fourth more of M to read and to multiply by, an eighth of
+    the call at most (the launches and the trunk are its larger part)."""
+    more, fewer = (hyper(torch, binding, case(40, 2, 64, 45, rank=4, hyper_width=F, wdtype=0))[0] for F in (40, 32))
+    assert ratio(torch, more, fewer, turns=25) < 1.125
