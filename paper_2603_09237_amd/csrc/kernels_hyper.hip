@@ -386,8 +386,12 @@ static void launch_trunk_affine(const AffineTable& table, const Trunk& tk, const
 // 256, here 8.3, 12.9 and 9.8 for 32; 91.6 for 128 of 4 x 512, the same here: 48 for the stores alone, W0 (twice the
 // results' bytes, from the caches) and the factors on top.  (W0 shared by two preferences in registers: 101; a
 // preference's tiles on one die: 120.)
+// Four waves a SIMD, three for ranks beyond 16, asked for by name: with all rows of a tile requested at once the compiler takes 136
+// and 172 registers, one wave less, if it is let.  us a call of hypernet_fwd, let and so: bf16, 128 preferences of 4 x 512, rank 16
+// 97.8 and 87.4, 12 89.6 and 80.3, 17 153 and 129, 32 177 and 154; 100 of 2 x 160, rank 16 22.6 and 20.8; fp32, 64 of 3 x 256, rank 24
+// 43.9 and 41.3, 16 33.4 and 32.8.
 template <typename T, int KS>
-__global__ __launch_bounds__(256) void k_hyper_materialize(LayerRule lr, LayerItems tiles, RowDiv by_ti0, RowDiv by_ti, const float* __restrict__ hp,
+__global__ __launch_bounds__(256, KS == 8 ? 3 : 4) void k_hyper_materialize(LayerRule lr, LayerItems tiles, RowDiv by_ti0, RowDiv by_ti, const float* __restrict__ hp,
                                                           const float* __restrict__ fac, T* __restrict__ theta_mat, int r,
                                                           int64_t fac_len, int64_t mat_len) {
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, ln = lane & 15, kg = lane >> 4;

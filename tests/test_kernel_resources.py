@@ -56,13 +56,14 @@ def of(built, pattern):
     return hit
 
 
-@pytest.mark.parametrize("pattern", [r"k_ppo_loss_grad", r"k_hyper_dM_df"])
+@pytest.mark.parametrize("pattern", [r"k_ppo_loss_grad", r"k_hyper_dM_df", r"k_hyper_materialize"])
 def test_no_scratch_memory(pattern, built):
     assert {n: k[".private_segment_fixed_size"] for n, k in of(built, pattern).items() if k[".private_segment_fixed_size"]} == {}
 
 
-# pattern, registers: workgroups of eight waves, two of them to a CU
-@pytest.mark.parametrize("pattern, registers", [(r"k_hyper_dM_dfILi2E", 128)])
+# pattern, registers: workgroups of eight waves, two of them to a CU; of four waves, four and three of them
+@pytest.mark.parametrize("pattern, registers", [(r"k_hyper_dM_dfILi2E", 128), (r"k_hyper_materializeI(f|DF16b)Li[024]E", 128),
+                                                (r"k_hyper_materializeI(f|DF16b)Li8E", 168)])
 def test_registers_leave_room_for_the_workgroups_of_a_cu(pattern, registers, built):
     assert {n: k[".vgpr_count"] for n, k in of(built, pattern).items() if k[".vgpr_count"] > registers} == {}
 
