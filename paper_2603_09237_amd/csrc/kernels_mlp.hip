@@ -2815,7 +2815,7 @@ __device__ inline void in_order(int lo, int hi, int n, const At& at, const Add& 
     else each_term<MANY, V>(lo, hi, at, add);
 }
 __global__ __launch_bounds__(256) void k_bwd_final(BwdFinalArgs a) {
-    __shared__ float sg[8][32];
+    __shared__ float sg[8][33];
     const int p = blockIdx.y, b = blockIdx.x, W = a.W;
     float* dmat = a.dmat + (int64_t)p * a.mat_len;
     float* dvec = a.dvec + (int64_t)p * a.vec_len;
@@ -2891,13 +2891,18 @@ __global__ __launch_bounds__(256) void k_bwd_final(BwdFinalArgs a) {
         *reinterpret_cast<float4*>(dmat + a.mat_off[l] + i4) = make_float4(v[0], v[1], v[2], v[3]);
         return;
     }
-    const int idx = (b - a.b_first) * 256 + threadIdx.x;  // along the partials' rows: they are read first_ns times, written once
-    if (idx >= W * a.O) return;
-    const int i = idx / W, o = idx - i * W;
-    const float* src = a.part + a.first + ((int64_t)p * a.first_ns * a.OP + i) * W + o;
-    float v = 0.f;
-    in_order<4, 16, float>(0, a.first_ns, a.first_ns, [&](int q) { return src[(int64_t)q * a.OP * W]; }, [&](float t) { v += t; });
-    dmat[a.mat_off[0] + (int64_t)o * a.O + i] = v;
+    // eight inputs x 32 features, read along the partials' rows and turned in LDS: every access is a run of 32 bytes or more
+    const int cw = (W + 31) / 32, it = (b - a.b_first) / cw, o0 = (b - a.b_first - it * cw) * 32, i0 = it * 8;
+    {
+        const int c = threadIdx.x & 31, g = threadIdx.x >> 5, o = o0 + c < W ? o0 + c : W - 1, i = i0 + g < a.O ? i0 + g : a.O - 1;
+        const float* src = a.part + a.first + ((int64_t)p * a.first_ns * a.OP + i) * W + o;
+        float v = 0.f;
+        in_order<4, 16, float>(0, a.first_ns, a.first_ns, [&](int q) { return src[(int64_t)q * a.OP * W]; }, [&](float t) { v += t; });
+        sg[g][c] = v;
+    }
+    __syncthreads();
+    const int o = o0 + (threadIdx.x >> 3), i = i0 + (threadIdx.x & 7);
+    if (o < W && i < a.O) dmat[a.mat_off[0] + (int64_t)o * a.O + i] = sg[threadIdx.x & 7][threadIdx.x >> 3];
 }
 
 // Rows of the fp32 observation tensor picked by the row map, rounded to the GEMM input type, as compact
@@ -3361,7 +3366,7 @@ static void policy_bwd_t(const morlax_ctx* c, int net, const T* theta_mat, const
         if (fin.S[l] > 1) b += (int)((fin.n[l] / 4 + 255) / 256);
     }
     fin.b_first = b;
-    if (fin.first_ns > 0) b += (W * O + 255) / 256;
+    if (fin.first_ns > 0) b += (W + 31) / 32 * ((O + 7) / 8);
     k_bwd_final<<<dim3(b, P), 256, 0, s>>>(fin);
 }
 
