@@ -1816,15 +1816,17 @@ __global__ __launch_bounds__(WD, 2) void k_mlp_fused_fwd(FusedFwdArgs a) {
                         if (c < np) put_piece(v, id >> sh, c);
                     }
                 }
-            } else {  // rows shorter than a piece, element by element
+            } else {  // rows shorter than a piece, element by element; the zeros behind them by all threads
                 for (int r = threadIdx.x; r < FF_ROWS; r += WD) {
                     const float* row = obs_row(r);
-                    for (int c = 0; c < np; ++c) {
-                        float v[8];
+                    float v[8];
 #pragma unroll
-                        for (int e = 0; e < 8; ++e) v[e] = 8 * c + e < O ? row[8 * c + e < O ? 8 * c + e : O - 1] : 0.f;
-                        put_piece(v, r, c);
-                    }
+                    for (int e = 0; e < 8; ++e) v[e] = e < O ? row[e < O ? e : O - 1] : 0.f;
+                    put_piece(v, r, 0);
+                }
+                for (int id = opaque((int)threadIdx.x) + FF_ROWS; id < FF_ROWS * np; id += WD) {
+                    const float zero[8] = {};
+                    put_piece(zero, id % FF_ROWS, id / FF_ROWS);
                 }
             }
         }

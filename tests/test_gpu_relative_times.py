@@ -65,3 +65,15 @@ def test_features_beyond_32_cost_little_more_than_32(torch, binding):  # noqa: F
     the call at most (the launches and the trunk are its larger part)."""
     more, fewer = (hyper(torch, binding, case(40, 2, 64, 45, rank=4, hyper_width=F, wdtype=0))[0] for F in (40, 32))
     assert ratio(torch, more, fewer, turns=25) < 1.125
+
+
+def test_rows_shorter_than_a_piece_take_no_longer_than_a_piece(torch, binding):  # noqa: F811
+    """Acting with 7 observations against 8, 106 preferences x 870 rows of 1 x 512: an input less (a thirtieth is left for the clock)."""
+    def act(O):
+        cfg = case(106, 1, 512, O, N=106 * 87, T=10, rank=4)
+        ctx, z = binding.Context.from_config(cfg), lambda *s: torch.zeros(*s, device="cuda")
+        tm, tv = z(cfg.P, ctx.theta_mat_len(0)).to(torch.bfloat16), z(cfg.P, ctx.theta_vec_len(0))
+        x, out, rows = z(cfg.T + 1, cfg.N, O), z(cfg.T + 1, cfg.N, cfg.act_dim), (0, cfg.T, 0, cfg.n_g)
+        ws = torch.empty(ctx.workspace_bytes(rows), dtype=torch.uint8, device="cuda")
+        return lambda: ctx.policy_fwd(0, tm, tv, x, rows, out, ws=ws)
+    assert ratio(torch, act(7), act(8), turns=25) < 1.033
