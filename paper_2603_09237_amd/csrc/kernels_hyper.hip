@@ -631,28 +631,32 @@ __global__ __launch_bounds__(256) void k_hyper_dAB(LayerRule lr, LayerItems runs
         typedef u32x4_t word_t __attribute__((aligned(4)));
         const int o0 = (nct == 2 ? tile >> 1 : tile) * 64, i0 = c_lo + (nct == 2 ? tile & 1 : 0) * 64;
         const int row = o0 + (int)threadIdx.x / 16, i = i0 + (int)threadIdx.x % 16 * 4;
+        // (a matrix stays far below 2^32 bytes: one base, an offset of 32 bits a lane; 64-bit addresses were 0.1 to 0.4 us a call more)
+        const char* base = reinterpret_cast<const char*>(dW);
         if (vec || i0 + 64 <= c_hi) {  // four values of a row are all in the tile or all beyond it
+            const uint32_t col = (uint32_t)(i < c_hi ? i : c_hi - 4);
 #pragma unroll
             for (int q = 0; q < 4; ++q)
-                regs[q] = *reinterpret_cast<const word_t*>(dW + (int64_t)(row + 16 * q < L.d_out ? row + 16 * q : L.d_out - 1) * L.d_in + (i < c_hi ? i : c_hi - 4));
+                regs[q] = *reinterpret_cast<const word_t*>(base + ((uint32_t)(row + 16 * q < L.d_out ? row + 16 * q : L.d_out - 1) * (uint32_t)L.d_in + col) * 4u);
             return;
         }
+        uint32_t col[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) col[e] = (uint32_t)(i + e < c_hi ? i + e : c_hi - 1);
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
-            const float* src = dW + (int64_t)(row + 16 * q < L.d_out ? row + 16 * q : L.d_out - 1) * L.d_in;
+            const uint32_t at = (uint32_t)(row + 16 * q < L.d_out ? row + 16 * q : L.d_out - 1) * (uint32_t)L.d_in;
 #pragma unroll
-            for (int e = 0; e < 4; ++e) regs[q][e] = __float_as_uint(src[i + e < c_hi ? i + e : c_hi - 1]);
+            for (int e = 0; e < 4; ++e) regs[q][e] = *reinterpret_cast<const uint32_t*>(base + (at + col[e]) * 4u);
         }
     };
     auto put = [&](int o0, int i0, const u32x4_t (&regs)[4]) __attribute__((always_inline)) {
         const int row = threadIdx.x / 16, c4 = threadIdx.x % 16 * 4;
-        const bool whole = o0 + 64 <= L.d_out && i0 + 64 <= c_hi;
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
             u32x4_t v = regs[q];
-            if (!whole)
 #pragma unroll
-                for (int e = 0; e < 4; ++e) v[e] = o0 + row + 16 * q < L.d_out && i0 + c4 + e < c_hi ? v[e] : 0u;
+            for (int e = 0; e < 4; ++e) v[e] = o0 + row + 16 * q < L.d_out && i0 + c4 + e < c_hi ? v[e] : 0u;
             *reinterpret_cast<u32x4_t*>(&sW[row + 16 * q][c4]) = v;
         }
     };
@@ -817,10 +821,16 @@ __global__ __launch_bounds__(64 * DMF_W, JT == 2 ? 4 : 2) void k_hyper_dM_df(con
         const int tile = dm_t * xcd_remap(blockIdx.x - n_df, gridDim.x - n_df) + wave;
         if (wave >= dm_t || tile >= n_tiles) return;
         const int q0 = tile * DMF_Q, q4 = q0 + 4 * ln;
-        int sg = 0;  // segment of row q0 + lane; its offsets are not needed before the results are there
+        int32_t mo, co;  // of row q0 + lane
+        if constexpr (SHORT > 0) {
+            at.offsets(F, q0 + lane < q_total ? q0 + lane : q_total - 1, mo, co);
+        } else {  // looked up by their segment: not needed before the results are there
+            int sg = 0;
 #pragma unroll
-        for (int s = 1; s < MORLAX_MAX_SEG; ++s) sg = q0 + lane >= at.q0[s] ? s : sg;
-        const int32_t mo = at.m[sg] + (q0 + lane) * F, co = at.c[sg] + q0 + lane;
+            for (int s = 1; s < MORLAX_MAX_SEG; ++s) sg = q0 + lane >= at.q0[s] ? s : sg;
+            mo = at.m[sg] + (q0 + lane) * F;
+            co = at.c[sg] + q0 + lane;
+        }
         float4_t acc[4][JT];
         float dc[4] = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll

@@ -68,7 +68,7 @@ def test_registers_leave_room_for_the_workgroups_of_a_cu(pattern, registers, bui
     assert {n: k[".vgpr_count"] for n, k in of(built, pattern).items() if k[".vgpr_count"] > registers} == {}
 
 
-@pytest.mark.parametrize("pattern", [r"k_hyper_dM_df"])
+@pytest.mark.parametrize("pattern", [r"k_hyper_dM_dfILi\dELb\dELi0E"])
 def test_scalars_stay_scalar(pattern, built):
-    """No table of kernel arguments is kept in the lanes of vector registers."""
+    """No table of kernel arguments is kept in the lanes of vector registers through a loop."""
     assert {n: k[".sgpr_spill_count"] for n, k in of(built, pattern).items() if k[".sgpr_spill_count"]} == {}
