@@ -2356,6 +2356,7 @@ __global__ __launch_bounds__(256, sizeof(T) == 2 ? 4 : 2) void k_head_bwd(HeadDz
     constexpr size_t kLds = sizeof(HeadBwdLds<T>) > sizeof(HeadBwdLdsDz) ? sizeof(HeadBwdLds<T>) : sizeof(HeadBwdLdsDz);
     __shared__ __align__(16) unsigned char lds[kLds];
     constexpr int VE = Elems<T>::VE;
+    asm volatile("" ::"s"(hz.dout), "s"(theta_mat), "s"(n_front));  // (a value of each line of the arguments, as in k_bwd_final)
     const int ncol = (W + 127) / 128, M = hz.M;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     // n_front dW workgroups ahead of everything else, or (0) every preference's ahead of its dZ ones (rule: the launch)
@@ -2781,9 +2782,11 @@ __global__ __launch_bounds__(256) void k_first_bwd_dw(const float* __restrict__ 
 //   first dW   the ranges' partials [i][o] of the narrow first layer, in order
 // Fixed associations throughout: results repeat bit for bit.
 // Bound by latency where the partials are few and by memory where they are many, so a thread requests up to 32 terms of its sum
-// together, those behind the last one the last one once more, and walks the first layer's partials along their rows.  us a launch, in
-// loops of two to four requests, and so: 16 preferences x 8192 rows of 3 x 256, fp32, 8 ranges 32.8 and 22.0; 32 of them, bf16, 4 ranges
-// 26.2 and 22.5; 64 x 4096 of 4 x 512 16.1 and 14.5; 24 x 1250 of 3 x 256 4.8 and 4.4; few rows of 2 x 32 3.4 and 4.0 (the step the same).
+// together, those behind the last one the last one once more, and the narrow first layer's partials are read along their rows and
+// turned in LDS; where they are few the reads of its arguments, some ten lines of host memory, are the larger part, and are on their
+// way together too.  us a launch, in loops of two to four requests, and so: 16 preferences x 8192 rows of 3 x 256, fp32, 8 ranges 32.8 and
+// 20.4; 32 of them, bf16, 4 ranges 26.2 and 22.2; 64 x 4096 of 4 x 512 16.1 and 15.0; 24 x 1250 of 3 x 256 4.1 and 3.7; 4 x 256 of 2 x 32
+// 3.7 and 3.0; 112 x 84 of 4 x 160 4.2 and 5.2.
 struct BwdFinalArgs {
     const float *part, *dlogsig;
     float *dmat, *dvec;
@@ -2818,6 +2821,10 @@ __device__ inline void in_order(int lo, int hi, int n, const At& at, const Add& 
 }
 __global__ __launch_bounds__(256) void k_bwd_final(BwdFinalArgs a) {
     __shared__ float sg[8][33];
+    // a value of each 64-byte line of the arguments (host memory, half a microsecond the first time a workgroup reads a line), all on
+    // their way together
+    asm volatile("" ::"s"(a.W), "s"(a.n_part[0]), "s"(a.n_pb), "s"((int)a.colsum[MORLAX_MAX_LAYERS - 1]), "s"((int)a.first),
+                 "s"((int)a.mat_off[0]), "s"((int)a.vec_off[0]), "s"((int)a.n[0]), "s"(a.b_head), "s"(a.b_first));
     const int p = blockIdx.y, b = blockIdx.x, W = a.W;
     float* dmat = a.dmat + (int64_t)p * a.mat_len;
     float* dvec = a.dvec + (int64_t)p * a.vec_len;
