@@ -129,12 +129,15 @@ def _nbytes(t):
 
 
 def _stream():
-    """The current stream of the current device as a hipStream_t.  Asked for by its handle: making the stream object takes the
-    host 3 us, a third of a call of one launch, which bounds the smallest steps (7.7 and 4.9 us a call of `vec_gae`)."""
+    """The current stream of the current device as a hipStream_t.  Asked for by its handle where this torch has a function for that:
+    making the stream object takes the host 3 us, a third of a call of one launch, which bounds the smallest steps (7.7 and 4.9 us a
+    call of `vec_gae`)."""
     import torch
-    if not torch.cuda.is_initialized():
+    handle = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+    device = getattr(torch._C, "_cuda_getDevice", None)
+    if handle is None or device is None or not torch.cuda.is_initialized():
         return torch.cuda.current_stream().cuda_stream
-    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+    return handle(device())
 
 
 def _rows(rows):
