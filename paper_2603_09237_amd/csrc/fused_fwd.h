@@ -14,8 +14,9 @@
 // requests three 512 x 512 matrices, one workgroup of eight waves a CU and 16 KB a wave in flight, takes 46 us that way (16
 // bytes per clock and CU) and 19 us with eight lanes to a line, while the caches serve the weights (32 workgroups on 16
 // networks; 256 on 8: 47 and 20 us).  With every CU on weights of its own the way from memory bounds both: 59 and 63 us; the
-// largest policies are there (a step of 128 preferences x 128 rows of 4 x 512: 56.7 us a network, 3.7 TB/s; 62.6 before the ring
-// was filled ahead of the first layer).  (Copying the matrices into fragment order first, as the kernel for tall selections does, is a launch of 87
+// largest policies are there (128 preferences x 128 rows of 4 x 512, both networks in turn, whose 422 MB of weights come from
+// memory: 56.7 us a network, 3.7 TB/s, 62.7 before the ring was filled ahead of the first layer; one network again and again, most
+// of its 211 MB out of the memory-side cache: 48 to 49, 4.4 TB/s, and 53 to 55).  (Copying the matrices into fragment order first, as the kernel for tall selections does, is a launch of 87
 // us at that size.)
 //
 // bf16 products are 32x32x16 in the contraction order of the kernels that serve taller selections of the same network
@@ -136,7 +137,7 @@ __global__ __launch_bounds__(64 * NW, sizeof(T) == 4 ? 3 : 2) void k_mlp_fwd(Fwd
     constexpr int D = fwd_depth(ES, NW, RT);
     // The ring is filled with the tile's other first requests, where tall saving tiles do not wait for each other's stores: ahead
     // of the first layer and behind it, 20 preferences x 850 rows of 3 x 256, saving, 29.6 and 27.3 us, 128 x 128 of 4 x 512
-    // 79.8 and 78.6 (acting, ahead: 51.6 -> 46.1)
+    // 79.8 and 78.6 (acting, one network again and again, ahead: 51.6 -> 46.1)
     constexpr bool EARLY = !SAVE || RT <= 2;
     static_assert(S1 % D == 0, "the ring of requests wraps at layer ends");
     extern __shared__ __align__(16) unsigned char dlds[];
@@ -239,8 +240,8 @@ __global__ __launch_bounds__(64 * NW, sizeof(T) == 4 ? 3 : 2) void k_mlp_fwd(Fwd
 
     // What the tile starts from is requested together, what is needed first ahead of the rest: observations, biases (a register
     // load later on would stand behind the ring's requests), W_0, the ring.  us, as a loop of pieces with two divisions each,
-    // the biases layer by layer behind it, and so: acting, 128 preferences x 128 rows of 4 x 512 51.4 and 45.6, 32 x 256 of 3 x 256
-    // 14.2 and 13.6, 64 x 6000 of 3 x 64 with 120 observations 126 and 78; saving, 38 x 850 of 3 x 256 47.8 and 43.9.
+    // the biases layer by layer behind it, and so, one network again and again: acting, 128 preferences x 128 rows of 4 x 512 51.4 and
+    // 45.6 (both networks in turn 62.7 and 56.7 each), 32 x 256 of 3 x 256 14.2 and 13.6, 64 x 6000 of 3 x 64 with 120 observations 126 and 78; saving, 38 x 850 of 3 x 256 47.8 and 43.9.
     {
         constexpr int NT = 64 * NW, NB = 4;  // layers whose biases come along
         constexpr int G = 4 * RT >= 4 * NW ? 4 : (4 * RT + NW - 1) / NW;  // pieces a thread requests together: 128 observations in bf16, 64 in fp32
